@@ -9,8 +9,11 @@ The stages are the slices of the networks that this repository is configured for
 that a mini-batch can be compared between two correct implementations: every ReLU and max-pool takes a decision on a
 bf16 value, two orders of summation disagree about a few of those decisions, and each one that flips moves the
 gradients upstream of it.  Over the ten bottlenecks of the full residual stage that is 47 % of the input gradient
-(2-norm), over the six convolutions of the deep VGG stage 10 %, over one bottleneck or three convolutions about 1 %,
+(2-norm), over the six convolutions of the deep VGG stage 10 %, over one bottleneck or three convolutions 1 to 2 %,
 so the residual stage appears as its single bottlenecks and the deep stage as its two halves, at their full sizes.
+For the same reason the weights are what a bf16 checkpoint holds (masters on bf16 values: an update of LR does not push
+them over a rounding boundary in one implementation and not in the other), and weights and upstream gradients are
+uniform (no single flipped gate outweighs the rest of an element's sum).
 """
 import math
 
@@ -19,16 +22,18 @@ import torch
 from paper_2012_12544_amd import binding as B
 from stage_inputs import configs as C
 
-LR = 1e-3
+LR = 2e-5
 
 
 # ---------------------------------------------------------------------------------------------- the stages
 def _identity_bottleneck(channels, mid, hw, micro_batch, n_micro):
-    """One bottleneck whose shortcut is its input: the second block of a residual group, as a stage of its own."""
+    """One bottleneck whose shortcut is its input: the second block of a residual group, as a stage of its own.  The
+    layers below are frozen, so nothing is handed back: behind an identity shortcut a flipped output gate would be the
+    whole of a dx element."""
     two = C.resnet50_stage(cin=channels, mid3=mid, hw=2 * hw, n3=2, n4=0, micro_batch=micro_batch, n_micro=n_micro)
     first = 1 + [L["kind"] for L in two["layers"]].index(C.ADD)
     layers = [dict(L, src0=max(L["src0"] - first, -1), src1=max(L["src1"] - first, -1)) for L in two["layers"][first:]]
-    return dict(two, layers=layers, in_c=4 * mid, in_h=hw, in_w=hw)
+    return dict(two, layers=layers, in_c=4 * mid, in_h=hw, in_w=hw, need_input_grad=0)
 
 
 def _stage(case):
@@ -134,26 +139,29 @@ def _side_streams():
     return _side
 
 
+def _uniform(shape, bound, g):
+    return (torch.rand(shape, device="cuda", generator=g) * 2 - 1) * bound
+
+
 def _parameters(stage, g):
-    """(w, b) per layer, on the GPU: the repository's recipe (Kaiming / Xavier, gamma 1, biases and beta 0)."""
+    """(w, b) per layer, on the GPU: Kaiming- / Xavier-uniform, gamma 1, biases and beta 0."""
     out = []
     for L in stage["layers"]:
         w = b = None
         if L["kind"] == C.CONV2D:
-            std = math.sqrt(2.0 / (L["cin"] * L["kh"] * L["kw"]))
-            w = torch.randn(L["cout"], L["cin"], L["kh"], L["kw"], device="cuda", generator=g) * std
+            w = _uniform((L["cout"], L["cin"], L["kh"], L["kw"]), math.sqrt(6.0 / (L["cin"] * L["kh"] * L["kw"])), g)
             if L["has_bias"]:
                 b = torch.zeros(L["cout"], device="cuda")
         elif L["kind"] == C.LINEAR:
-            bound = math.sqrt(6.0 / (L["cin"] + L["cout"]))
-            w = (torch.rand(L["cout"], L["cin"], device="cuda", generator=g) * 2 - 1) * bound
+            w = _uniform((L["cout"], L["cin"]), math.sqrt(6.0 / (L["cin"] + L["cout"])), g)
             b = torch.zeros(L["cout"], device="cuda")
         elif L["kind"] == C.LSTM:
-            bound = 1.0 / math.sqrt(L["cout"])
-            w = (torch.rand(4 * L["cout"], L["cin"] + L["cout"], device="cuda", generator=g) * 2 - 1) * bound
+            w = _uniform((4 * L["cout"], L["cin"] + L["cout"]), 1.0 / math.sqrt(L["cout"]), g)
             b = torch.zeros(4 * L["cout"], device="cuda")
         elif L["kind"] == C.BATCHNORM2D:
             w, b = torch.ones(L["cout"], device="cuda"), torch.zeros(L["cout"], device="cuda")
+        if w is not None and stage["dtype"] == C.BF16:
+            w = w.bfloat16().float()
         out.append((w, b))
     return out
 
@@ -186,18 +194,17 @@ class _Program:
         shapes = C.infer_shapes(stage)
         oc, oh, ow = shapes[-1]
 
-        def normal(c, h, w, scale=1.0):
-            shape = (mb, h, w, c) if nhwc else (mb, c, h, w)
-            return (torch.randn(shape, device="cuda", generator=g) * scale).to(dtype)
+        def io(c, h, w):
+            return (mb, h, w, c) if nhwc else (mb, c, h, w)
 
         # N(0,1) activations; upstream gradients with the size a mean over samples and positions gives them
-        self.x = [normal(stage["in_c"], stage["in_h"], stage["in_w"]) for _ in range(self.M)]
+        self.x = [torch.randn(io(stage["in_c"], stage["in_h"], stage["in_w"]), device="cuda", generator=g).to(dtype) for _ in range(self.M)]
         self.loss = _ends_in_loss(stage)
         if self.loss:
             self.g = [torch.randint(0, oc, (mb,), device="cuda", generator=g, dtype=torch.int32) for _ in range(self.M)]
         else:
-            self.g = [normal(oc, oh, ow, 1.0 / (mb * self.M * oh * ow)) for _ in range(self.M)]
-        out_shape = (mb, oh, ow, oc) if nhwc else (mb, oc, oh, ow)
+            self.g = [_uniform(io(oc, oh, ow), math.sqrt(3.0) / (mb * self.M * oh * ow), g).to(dtype) for _ in range(self.M)]
+        out_shape = io(oc, oh, ow)
         self.y = torch.zeros((self.M,) + out_shape, device="cuda", dtype=torch.float32 if self.loss else dtype)
         self.dx = torch.zeros((self.M,) + tuple(self.x[0].shape), device="cuda", dtype=dtype) if stage["need_input_grad"] else None
 
@@ -279,14 +286,15 @@ def work(case):
 
 def tolerance(case):
     """Measured by running each stage a second time with the channels of every tensor permuted (the same sums in another
-    order): relative 2-norm of the difference of y / dx / accumulated gradients, the worst of them about
+    order), over the listed cases and drawn ones, first and second mini-batch: the relative 2-norm of the difference, the
+    worst of y, dx and the accumulated gradients, was
 
-        tiny 3e-7;  vgg_stage1 5e-3;  vgg_block 1e-2;  classifier 1.5e-3;  projection, identity 5e-3;  stem 3.5e-3;
-        tail 1.1e-2;  lstm 1.1e-3
+        tiny 3e-7;  vgg_stage1 6.5e-3;  vgg_block 2.1e-2;  classifier 3.8e-3;  projection 5e-3 (2.6e-2 at the smallest sizes);
+        identity 1.3e-2;  stem 7e-3 (1.4e-2);  tail 1.6e-2;  lstm 1.2e-3
 
-    with single elements of dx, behind a flipped decision, off by 0.4 to 0.7 of their size (of the root mean square
-    where that is larger)."""
+    and single elements of dx behind a flipped decision were off by up to 0.7 of their size (of the root mean square
+    where that is larger); 0.17 in the classifier, 0.02 in the LSTM."""
     if case["kind"] == "tiny":
         return {"rel": 1e-5, "max": 1e-3}
-    rel = {"vgg_stage1": 0.02, "classifier": 0.006, "projection": 0.02, "identity": 0.02, "stem": 0.014, "lstm": 0.0045}
-    return {"rel": rel.get(case["kind"], 0.03), "max": 0.1 if case["kind"] in ("classifier", "lstm") else 0.99}
+    rel = {"vgg_stage1": 0.026, "classifier": 0.015, "lstm": 0.005}
+    return {"rel": rel.get(case["kind"], 0.03), "max": {"classifier": 0.7, "lstm": 0.1}.get(case["kind"], 0.99)}
