@@ -135,6 +135,15 @@ hipError_t lstm_cell_fwd(int dt, const void *P, const float *gh, int S, float *g
 hipError_t lstm_cell_bwd(int dt, const void *dy, const float *r, int S, const float *gates, const float *cells,
                          float *dcn, void *D, int N, int T, int H, int t, hipStream_t s);
 
+// ---- the whole recurrence of an LSTM layer in one launch per direction, bf16 (kernels_lstm.hip); arguments as above,
+// w_hh [4H][H] and wt_h [H][4H] are the recurrent matrix and its transpose in the storage type
+bool lstm_seq_supported(int N, int H);
+size_t lstm_seq_workspace(int N, int H);
+hipError_t lstm_seq_fwd(const void *P, const void *w_hh, float *gates, float *cells, void *h, void *hs, int N, int T, int H,
+                        void *workspace, hipStream_t s);
+hipError_t lstm_seq_bwd(const void *dy, const void *wt_h, const float *gates, const float *cells, void *D, int N, int T, int H,
+                        void *workspace, hipStream_t s);
+
 size_t bn_workspace(int rows, int C);
 // stats: [2][C] floats (mean, invstd)
 // pre_chunks > 0: the workspace already holds [2][pre_chunks][C] partial sums of x and x^2 (left there by

@@ -432,7 +432,9 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
         HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, s));
     else
         HIPCHK(conv_gather_direct(st->dt, x, L.w_work, L.bias, P, 0, none, gx, s));
-    for (int t = 0; t < T; ++t) {
+    const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, H);
+    if (one_launch) HIPCHK(lstm_seq_fwd(P, w_hh, gates, cells, h, hs, N, T, H, st->work, s));
+    for (int t = 0; t < T && !one_launch; ++t) {
         int S = 0;
         if (t > 0) {                                   // W_h h_{t-1}: row t of the delayed copy
             int rc = step_product(st, hs, w_hh, step_geom(N, T, H, G, t), &S);
@@ -461,7 +463,9 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     const char *wt_x = (const char *)L.w_t, *wt_h = wt_x + (size_t)G * In * es;
     const bool mf = st->dt == DT_BF16;
     bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
-    for (int t = T - 1; t >= 0; --t) {
+    const bool one_launch = mf && lstm_seq_supported(N, H);
+    if (one_launch) HIPCHK(lstm_seq_bwd(dy, wt_h, gates, cells, D, N, T, H, st->work, s));
+    for (int t = T - 1; t >= 0 && !one_launch; --t) {
         int S = 0;
         if (t + 1 < T) {                               // W_h^T D_{t+1}
             int rc = step_product(st, D, wt_h, step_geom(N, T, G, H, t + 1), &S);
@@ -1202,6 +1206,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 v = conv_gather_mfma_workspace(rows_geom(N, T, G, In)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, H, G, 1)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, G, H, 1)); w = v > w ? v : w;
+                v = lstm_seq_workspace(N, H); w = v > w ? v : w;
                 v = conv_wgrad_mfma_workspace(cx); w = v > w ? v : w;
                 v = conv_wgrad_mfma_workspace(ch); w = v > w ? v : w;
             } else {

@@ -1,0 +1,31 @@
+"""The sizes at which a kernel with a narrow domain can go wrong: edges of its tiles, remainders, the ends of its range."""
+import numpy as np
+import pytest
+
+from gpu_harness import compare_minibatch, gpu_minibatch
+from stage_inputs import configs as C
+from test_gpu_stage import single
+
+pytestmark = pytest.mark.gpu
+
+
+# ------------------------------------------------------------------------------ LSTM recurrence in one launch
+@pytest.mark.parametrize("cin,hidden,T,mb", [
+    (16, 128, 1, 1),         # no recurrent product, one block column of the smallest matrix
+    (24, 128, 2, 17),        # a second group of sequences with one member
+    (128, 384, 5, 16),       # four pieces of K for each half of the rows, not eight for all
+    (64, 640, 3, 3),
+    (128, 1024, 4, 33),      # the widest matrix, a ragged third group
+])
+@pytest.mark.parametrize("need_dx", [1, 0])
+def test_lstm_sequence_kernels(cin, hidden, T, mb, need_dx):
+    st = single(lambda b: b.lstm(cin, hidden, src=-1), cin, (T, 1), C.BF16, micro_batch=mb, need_input_grad=need_dx)
+    compare_minibatch(st, verbose="lstm %d->%d T=%d N=%d" % (cin, hidden, T, mb))
+
+
+def test_lstm_sequence_kernels_twice_are_bit_identical():
+    """Blocks hand their slices to each other inside the launch: a missing wait would show as a difference."""
+    st = C.gnmt_lstm_stage(hidden=256, seq=30, n_layers=2, micro_batch=40, n_micro=3)
+    a, b = gpu_minibatch(st), gpu_minibatch(st)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
