@@ -42,7 +42,12 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // choosing WHICH chunk a lane fetches, since WHERE it lands is fixed by the lane id.
 // STAGES tiles form a ring; tile kt+STAGES-1 is requested right after the barrier that retires
 // tile kt-1, so STAGES-1 K-tiles of latency are covered while the MFMAs run.
-template <int BP, int BC, int WP, int WC, int BK, int STAGES, bool S1, bool TAPS_INNER>
+// PHASED (gradient of a strided convolution, s_in > 1): an output pixel only meets the taps whose offset is congruent to
+// its own position modulo the stride, so the output is taken apart into the s_in^2 grids of pixels with equal remainders;
+// on each the product is an ordinary stride-1 one with the taps of that class (for 3x3 / 2: 4, 2, 2 and 1 of the 9).
+// blockIdx.z is the class, the one with most taps first.  Without it three quarters of the multiply-adds meet a zero:
+// 3x3 / 2, 512 channels, 14x14 from 7x7, 32 samples: 104 -> 30 us; 128 channels, 56x56 from 28x28: 84 -> 44 us.
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, bool S1, bool TAPS_INNER, bool PHASED = false>
 __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
@@ -69,6 +74,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     uint16_t *sO = reinterpret_cast<uint16_t *>(smem);                 // [BP][SROW] (epilogue, reuses the ring)
     constexpr size_t RING_BYTES = (size_t)STAGES * STAGE_ELEMS * 2, EPI_BYTES = (size_t)BP * SROW * 2;
     float *sBias = reinterpret_cast<float *>(smem + (RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES));   // [BC]
+    int *sPix = reinterpret_cast<int *>(sBias + BC);                  // PHASED: [BP] output pixel of a tile row, npix past the end
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -84,7 +90,22 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     const int pix0 = tile_p * BP;                    // pixel counts fit 31 bits (checked by the launcher)
     const int npix = g.N * g.Ho * g.Wo;
     const int K = g.R * g.S * g.Ci;
-    const int KT = TAPS_INNER ? (g.Ci / BK) * g.R * g.S : (K + BK - 1) / BK;
+    // the class of a PHASED block: output pixels (s_in i + pa, s_in j + pb) and the taps (r0 + s_in i, q0 + s_in j)
+    const int sd = PHASED ? g.s_in : 1;
+    int pa = 0, pb = 0, r0 = 0, q0 = 0, Rn = g.R, Sn = g.S, Hp = g.Ho, Wp = g.Wo;
+    if (PHASED) {
+        const int zc = (int)blockIdx.z;
+        pa = (zc / sd + g.pad_h) % sd;               // class 0: the pixels that tap (0, 0) reaches
+        pb = (zc % sd + g.pad_w) % sd;
+        r0 = (g.pad_h % sd - pa + sd) % sd;
+        q0 = (g.pad_w % sd - pb + sd) % sd;
+        Rn = r0 < g.R ? (g.R - r0 + sd - 1) / sd : 0;
+        Sn = q0 < g.S ? (g.S - q0 + sd - 1) / sd : 0;
+        Hp = (g.Ho - pa + sd - 1) / sd;
+        Wp = (g.Wo - pb + sd - 1) / sd;
+    }
+    const int rows = g.N * Hp * Wp;                  // output pixels of the class
+    const int KT = TAPS_INNER ? (g.Ci / BK) * Rn * Sn : (K + BK - 1) / BK;
     constexpr unsigned OOB = 0x80000000u;
 
     __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(in), 0, (int)in_bytes, 0x00020000);
@@ -103,19 +124,19 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     for (int i = 0; i < XL; ++i) {
         int p = pix0 + (i * NW + wave) * RPW + lrow;
         tapmask[i] = 0;
-        if (p < npix) {
-            int ow = p % g.Wo;
-            int t = p / g.Wo;
-            int oh = t % g.Ho;
-            int n = t / g.Ho;
-            hb[i] = oh * g.s_out - g.pad_h;
-            wb[i] = ow * g.s_out - g.pad_w;
+        if (p < rows) {
+            int ow = p % Wp;
+            int t = p / Wp;
+            int oh = t % Hp;
+            int n = t / Hp;
+            hb[i] = PHASED ? oh + (pa + r0 - g.pad_h) / sd : oh * g.s_out - g.pad_h;      // exact division
+            wb[i] = PHASED ? ow + (pb + q0 - g.pad_w) / sd : ow * g.s_out - g.pad_w;
             xoff[i] = (unsigned)n * (unsigned)(g.Hi * g.Wi * g.Ci) * 2u;
             if (FAST) {
-                for (int r = 0; r < g.R; ++r)
-                    for (int q = 0; q < g.S; ++q)
+                for (int r = 0; r < Rn; ++r)
+                    for (int q = 0; q < Sn; ++q)
                         if ((unsigned)(hb[i] + r) < (unsigned)g.Hi && (unsigned)(wb[i] + q) < (unsigned)g.Wi)
-                            tapmask[i] |= 1u << (r * g.S + q);
+                            tapmask[i] |= 1u << (r * Sn + q);
                 xoff[i] += (unsigned)((hb[i] * g.Wi + wb[i]) * g.Ci + 8 * lc) * 2u;     // may wrap; the tap offset undoes it
             }
         } else {
@@ -141,10 +162,10 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     int kr = kk / (g.S * g.Ci), ks = (kk / g.Ci) % g.S, kc = kk % g.Ci;
     int cb = 0;                                        // FAST: first channel of the tile (wave-uniform)
     if (TAPS_INNER) {
-        const int tap = kt0 % (g.R * g.S);
+        const int tap = PHASED ? 0 : kt0 % (g.R * g.S);            // PHASED launches do not split K
         kr = tap / g.S;
         ks = tap % g.S;
-        cb = (kt0 / (g.R * g.S)) * BK;
+        cb = PHASED ? (KT ? 0 : g.Ci) : (kt0 / (g.R * g.S)) * BK;  // a class without taps reads nothing
         kc = cb + 8 * lc;                              // channel offset; tap = (kr, ks)
     }
 
@@ -152,8 +173,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
             const bool kin = cb < g.Ci;
-            const int tap = kr * g.S + ks;
-            const unsigned bit = kin ? 1u << tap : 0u;
+            const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
+            const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
             const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + cb) * 2u;
             const unsigned wo = kin ? (unsigned)(tap * g.Ci + cb) * 2u : OOB;
 #pragma unroll
@@ -218,9 +239,9 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // scalar code does not split the block in which the MFMAs and the address arithmetic interleave.
     auto advance_tile = [&]() {
         if (FAST) {
-            if (++ks == g.S) {
+            if (++ks == Sn) {
                 ks = 0;
-                if (++kr == g.R) {
+                if (++kr == Rn) {
                     kr = 0;
                     cb += BK;
                 }
@@ -262,6 +283,14 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
 
     // the block's bias slice goes to LDS now; it is read after the barriers of the main loop
     if (tid < BC) sBias[tid] = (bias && co0 + tid < g.Co) ? bias[co0 + tid] : 0.0f;
+    if (PHASED) {
+        for (int i = tid; i < BP; i += NT) {
+            const int p = pix0 + i;
+            sPix[i] = p < rows ? ((p / (Hp * Wp)) * g.Ho + p / Wp % Hp * sd + pa) * g.Wo + p % Wp * sd + pb : npix;
+        }
+    }
+    const int tile_z = PHASED ? (int)blockIdx.z * ((int)gridDim.x / tiles_c) + tile_p : tile_p;      // of the statistics
+    const int tiles_all = ((int)gridDim.x / tiles_c) * (PHASED ? (int)gridDim.z : 1);
 
     // Software pipeline.  The ring holds STAGES tiles in flight or in use; every iteration requests
     // exactly XL+WL loads per wave (tiles past the end fetch zeros nobody multiplies), so "at most
@@ -358,7 +387,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
 #pragma unroll
         for (int it = 0; it < GPRE; ++it) {
             const int u = tid + it * NT;
-            const int p = pix0 + u / (BC / 8), co = co0 + (u % (BC / 8)) * 8;
+            const int p = PHASED ? sPix[u / (BC / 8)] : pix0 + u / (BC / 8), co = co0 + (u % (BC / 8)) * 8;
             gpre[it] = (p < npix && co < g.Co) ? *reinterpret_cast<const chunk16 *>(gate + (size_t)p * g.Co + co) : zero16;
         }
     }
@@ -370,16 +399,15 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         for (int cc = tid; cc < BC; cc += NT) {
             const int co = co0 + cc;
             if (co < g.Co) {
-                const int rows = npix - pix0 < BP ? npix - pix0 : BP;
+                const int here = rows - pix0 < BP ? rows - pix0 : BP;
                 float s1 = 0.0f, s2 = 0.0f;
-                for (int r = 0; r < rows; ++r) {
+                for (int r = 0; r < here; ++r) {
                     const float v = __uint_as_float((uint32_t)sO[r * SROW + cc] << 16);
                     s1 += v;
                     s2 += v * v;
                 }
-                const int tiles_p = (int)gridDim.x / tiles_c;
-                stat_part[(size_t)tile_p * g.Co + co] = s1;
-                stat_part[((size_t)tiles_p + tile_p) * g.Co + co] = s2;
+                stat_part[(size_t)tile_z * g.Co + co] = s1;
+                stat_part[((size_t)tiles_all + tile_z) * g.Co + co] = s2;
             }
         }
     }
@@ -403,7 +431,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     for (int it = 0; it < UNITS; ++it) {
         const int u = tid + it * NT;
         const int prow = u / CH8, c8i = u % CH8;
-        const int p = pix0 + prow;
+        const int p = PHASED ? sPix[prow] : pix0 + prow;
         const int co = co0 + c8i * 8;
         if (p < npix && co < g.Co) {
             chunk8 lo = *reinterpret_cast<const chunk8 *>(sO + prow * SROW + c8i * 8);
@@ -453,9 +481,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
                     t1 += red[(k * 2 + 0) * BC + cc];
                     t2 += red[(k * 2 + 1) * BC + cc];
                 }
-                const int tiles_p = (int)gridDim.x / tiles_c;
-                stat_part[(size_t)tile_p * g.Co + co] = t1;
-                stat_part[((size_t)tiles_p + tile_p) * g.Co + co] = t2;
+                stat_part[(size_t)tile_z * g.Co + co] = t1;
+                stat_part[((size_t)tiles_all + tile_z) * g.Co + co] = t2;
             }
         }
     }
@@ -493,7 +520,16 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 
 struct GatherPlan {
     int bp, bc, splits, kt_per_split;
+    int classes;             // 1, or s_in^2: a PHASED launch
+    long long class_pix;     // output pixels of the largest class
 };
+
+// The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask.  A 1x1 filter has nothing to take
+// apart (one class with its tap, the others empty).
+bool gather_phased(const GatherConv &g)
+{
+    return g.s_in > 1 && g.s_out == 1 && g.Ci % 32 == 0 && g.R * g.S > 1 && g.R * g.S <= 32 && g.pad_h >= 0 && g.pad_w >= 0;
+}
 
 // Tile shape and split-K factor.  K is split only when there are very few output tiles (the linear
 // layers: one pixel tile).
@@ -501,10 +537,12 @@ GatherPlan gather_plan(const GatherConv &g)
 {
     GatherPlan p;
     const long long npix = (long long)g.N * g.Ho * g.Wo;
-    p.bp = npix <= 64 ? 64 : 256;
+    p.classes = gather_phased(g) ? g.s_in * g.s_in : 1;
+    p.class_pix = p.classes == 1 ? npix : (long long)g.N * ((g.Ho + g.s_in - 1) / g.s_in) * ((g.Wo + g.s_in - 1) / g.s_in);
+    p.bp = p.class_pix <= 64 ? 64 : 256;
     p.bc = g.Co <= 64 ? 64 : 128;
     if (p.bp == 64) p.bc = 128;
-    auto tiles_of = [&](int bp) { return ((npix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
+    auto tiles_of = [&](int bp) { return p.classes * ((p.class_pix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
     // 256-pixel tiles that cannot even fill 400 of the 512 block slots (14x14 layers, the 1x1 convs of
     // the bottleneck blocks): halve the pixel tile rather than split K, whose fp32 partials cost more
     // than the smaller tile loses (measured on 512-channel 14x14 layers: 73 us against 100 us)
@@ -515,7 +553,7 @@ GatherPlan gather_plan(const GatherConv &g)
     // small products (the bottleneck blocks of ResNet: under ~8 GMAC) are bound by the latency of a block's
     // load - multiply - store chain, not by throughput: many 64-pixel blocks and no split of K were the
     // fastest choice on every such shape measured (e.g. 1x1 1024->256 at 14x14: 11.5 us against 22.2)
-    if (p.bc == 128 && npix > 64 && (double)npix * g.Co * g.R * g.S * g.Ci < 8e9) p.bp = 64;
+    if (p.bc == 128 && npix > 64 && (double)npix * g.Co * g.R * g.S * g.Ci < 8e9 * p.classes) p.bp = 64;
     // plenty of 256-pixel tiles and whole 256-channel tiles: one 8-wave block per CU owns 256 x 256, which
     // halves the L2 -> LDS traffic of two independent 256 x 128 blocks (3 % on the 512-channel 28x28 layers)
     if (!few && p.bp == 256 && p.bc == 128 && g.Co % 256 == 0) p.bc = 256;
@@ -526,7 +564,7 @@ GatherPlan gather_plan(const GatherConv &g)
     long long most = KT / 16;                       // at least 16 K-tiles per split
     if (want > most) want = most;
     if (want > 32) want = 32;
-    if (want < 1) want = 1;
+    if (want < 1 || p.classes > 1) want = 1;
     p.kt_per_split = (int)((KT + want - 1) / want);
     p.splits = (KT + p.kt_per_split - 1) / p.kt_per_split;
     return p;
@@ -540,18 +578,21 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     constexpr int NT = WP * WC * 64;
     constexpr size_t main_bytes = (size_t)STAGES * (BP + BC) * BK * 2;
     constexpr size_t epi_bytes = (size_t)BP * (BC + 4) * 2;
-    constexpr size_t smem = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float);
-    static_assert(smem <= (NT >= 512 ? 160 : 80) * 1024, "two blocks of 4 waves (one of 8) must fit the 160 KB LDS of a CU");
+    constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float);
+    const bool phased = plan.classes > 1;
+    constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
+    const size_t smem = phased ? smem_phased : smem_flat;
+    static_assert(smem_phased <= (NT >= 512 ? 160 : 80) * 1024, "two blocks of 4 waves (one of 8) must fit the 160 KB LDS of a CU");
     const long long npix = (long long)g.N * g.Ho * g.Wo;
-    const int tiles_p = (int)((npix + BP - 1) / BP), tiles_c = (g.Co + BC - 1) / BC;
+    const int tiles_p = (int)((plan.class_pix + BP - 1) / BP), tiles_c = (g.Co + BC - 1) / BC;
     const int is_grad = (epi.gate != nullptr || epi.accum) ? 1 : 0;
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
-    dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits);
-#define GATHER_LAUNCH(S1_, TI_)                                                                                   \
+    dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
+#define GATHER_LAUNCH(S1_, TI_, PH_)                                                                                   \
     do {                                                                                                          \
-        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, S1_, TI_>;                                           \
+        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, S1_, TI_, PH_>;                                      \
         static bool attr_set = false;                                                                             \
         if (!attr_set && smem > 64 * 1024) {                                                                      \
             hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
@@ -564,12 +605,14 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
                            (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
-    if (g.s_in == 1) {
-        if (taps_inner) GATHER_LAUNCH(true, true);
-        else GATHER_LAUNCH(true, false);
+    if (phased) {
+        GATHER_LAUNCH(true, true, true);
+    } else if (g.s_in == 1) {
+        if (taps_inner) GATHER_LAUNCH(true, true, false);
+        else GATHER_LAUNCH(true, false, false);
     } else {
-        if (taps_inner) GATHER_LAUNCH(false, true);
-        else GATHER_LAUNCH(false, false);
+        if (taps_inner) GATHER_LAUNCH(false, true, false);
+        else GATHER_LAUNCH(false, false, false);
     }
 #undef GATHER_LAUNCH
     if (part && !raw) {
@@ -935,7 +978,7 @@ int conv_gather_mfma_stat_chunks(const GatherConv &g)
     if (!conv_gather_mfma_supported(g) || conv3x3_halo_supported(g) || conv3x3_c8_supported(g)) return 0;
     const GatherPlan p = gather_plan(g);
     if (p.splits != 1) return 0;
-    return (int)(((long long)g.N * g.Ho * g.Wo + p.bp - 1) / p.bp);
+    return (int)(p.classes * ((p.class_pix + p.bp - 1) / p.bp));
 }
 
 hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, void *out, int relu,

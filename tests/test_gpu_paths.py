@@ -29,3 +29,18 @@ def test_lstm_sequence_kernels_twice_are_bit_identical():
     a, b = gpu_minibatch(st), gpu_minibatch(st)
     for k in a:
         assert np.array_equal(a[k], b[k]), k
+
+
+# ------------------------------------------------------------------------------ input gradient of a strided convolution
+@pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
+    (3, 2, 1, 64, 32, (21, 19), 3),      # classes of unequal size, one K-tile a tap
+    (3, 2, 1, 72, 64, (8, 7), 2),        # a ragged channel tile
+    (3, 2, 1, 136, 96, (2, 3), 1),       # smaller than a tile in every class
+    (3, 2, 0, 256, 32, (17, 16), 5),     # no padding: class 0 sits on the even pixels
+    (5, 3, 2, 64, 32, (16, 14), 2),      # nine classes of 1, 2 and 4 taps
+    (2, 3, 0, 64, 64, (13, 14), 2),      # stride beyond the filter: classes without taps
+    (3, 2, 1, 128, 128, (56, 56), 3),    # many tiles
+])
+def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="strided conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
