@@ -75,6 +75,15 @@ __device__ __forceinline__ uint32_t grad_epilogue_pair(uint32_t v, uint32_t old,
     return packed;
 }
 
+// XCD-aware block order: hardware deals consecutive block ids round-robin to the 8 XCDs
+// (each with its own L2).  Re-number so that every XCD walks one contiguous range of tiles
+// and the blocks that share an input tile run on the same L2.
+__device__ __forceinline__ int xcd_remap(int id, int nb)
+{
+    const int x = id & 7, q = nb >> 3, rem = nb & 7;
+    return x * q + (x < rem ? x : rem) + (id >> 3);
+}
+
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll

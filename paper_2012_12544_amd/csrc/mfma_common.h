@@ -1,5 +1,5 @@
-// Pieces shared by the MFMA kernels (gfx950): operand fragment types, the vmcnt-only wait, the
-// XCD-aware block order and the transposing-read fragment loader of the weight-gradient kernels.
+// Pieces shared by the MFMA kernels (gfx950): operand fragment types, the vmcnt-only wait
+// and the transposing-read fragment loader of the weight-gradient kernels.
 #pragma once
 #include "dev_common.h"
 
@@ -44,15 +44,6 @@ struct lds_addr_of {
 };
 
 __device__ __forceinline__ bf16x8_t as_frag(chunk16 c) { return __builtin_bit_cast(bf16x8_t, c); }
-
-// XCD-aware block order: hardware deals consecutive block ids round-robin to the 8 XCDs
-// (each with its own L2).  Re-number so that every XCD walks one contiguous range of tiles
-// and the blocks that share an input tile run on the same L2.
-__device__ __forceinline__ int xcd_remap(int id, int nb)
-{
-    const int x = id & 7, q = nb >> 3, rem = nb & 7;
-    return x * q + (x < rem ? x : rem) + (id >> 3);
-}
 
 // acc + the 8 bf16 values of an MFMA operand fragment (v_dot2c_f32_bf16 against a pair of ones)
 __device__ __forceinline__ float frag_sum(bf16x8_t f, float acc)
