@@ -66,7 +66,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     constexpr int SROW = BC + 4;             // staging row (elements): 8-byte aligned, odd multiple of 8 bytes
     constexpr int STAGE_ELEMS = (BP + BC) * BK;
     static_assert(XL >= 1 && WL >= 1 && BP % (RPW * NW) == 0 && BC % (RPW * NW) == 0, "tile/thread mismatch");
-    static_assert(BK == 32, "swizzle below assumes 4 chunks per row");
+    // BK = 64: a whole K-tile of fragments in registers while the next one is read (see the loop)
+    static_assert(BK == 32 || (BK == 64 && S1 && TAPS_INNER && (NW & 1) == 0), "lane-to-slot maps below");
 
     extern __shared__ __align__(16) unsigned char smem[];
     const lds_addr_of lds_of(smem);
@@ -80,8 +81,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wp = wave % WP, wc = wave / WP;
     // slot (row, c') a lane fills inside one wave-wide load, and the chunk column it must fetch
-    const int lrow = lane >> 2;
-    const int lc = (lane & 3) ^ ((lane >> 4) & 3);       // = c' ^ swz(row); the same for every load
+    const int lrow = lane / CPR;
+    const int lc = (lane % CPR) ^ swz<BK>(wave * RPW + lrow);       // = c' ^ swz(row); the same for every load
 
     // split-K: blockIdx.y owns K-tiles [kt0, kt1) and leaves fp32 partial sums in part[split][pixel][co]
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
@@ -299,7 +300,6 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // they are needed, and the barrier that publishes tile kt+1 sits between the two MFMA groups of
     // tile kt.  By then every wave holds all of tile kt in registers, so its slot is refilled at once.
     // sched_barrier pins that order: left alone the scheduler sinks the reads next to their MFMAs.
-    static_assert(KSUB == 2, "pipeline below is written for two sub-steps per tile");
     constexpr int NLOAD = XL + WL;
 #pragma unroll
     for (int st = 0; st < STAGES; ++st) {
@@ -309,25 +309,55 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     WAIT_VMCNT((STAGES - 1) * NLOAD);
     WAIT_LGKMCNT(0);       // no scalar load may be pending at loop entry, or every LDS wait in the loop becomes a full drain
     __builtin_amdgcn_s_barrier();
-    bf16x8_t fa0[TC], fb0[TP], fa1[TC], fb1[TP];
-    load_frags(0, 0, fa0, fb0);
-    int rd = 0;
-    for (int kt = kt0; kt < kt1; ++kt) {
-        const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-        load_frags(rd, 1, fa1, fb1);
-        __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
-        mfma_all(fa0, fb0);
-        __builtin_amdgcn_sched_barrier(0);
-        WAIT_LGKMCNT(0);                              // this wave has read all of tile kt
-        WAIT_VMCNT((STAGES - 2) * NLOAD);             // its share of tile kt+1 has landed
-        __builtin_amdgcn_s_barrier();
-        load_frags(nx, 0, fa0, fb0);
-        __builtin_amdgcn_sched_barrier(0);
-        issue_tile(rd);                               // tile kt+STAGES into the slot just retired; its address
-        mfma_all(fa1, fb1);                           // arithmetic is free to mix with these MFMAs
-        __builtin_amdgcn_sched_barrier(0);
-        advance_tile();
-        rd = nx;
+    if constexpr (BK == 64) {
+        // Few MFMAs per wave and sub-step (two for a 64 x 32 wave tile) cannot cover the LDS latency of the next
+        // sub-step's reads, and a launch of about one block per compute unit has nobody else to cover it: the tile is
+        // read one whole K-tile ahead instead, so one barrier and one wait, both behind eight MFMAs, serve 64 channels.
+        bf16x8_t fa[2][KSUB][TC], fb[2][KSUB][TP];
+#pragma unroll
+        for (int j = 0; j < KSUB; ++j) load_frags(0, j, fa[0][j], fb[0][j]);
+        int rd = 0;
+        for (int kt = kt0; kt < kt1; kt += 2) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {             // two tiles a trip: which half holds what is known when compiling
+                if (kt + h >= kt1) break;
+                const int nx = rd + 1 == STAGES ? 0 : rd + 1;
+                WAIT_LGKMCNT(0);                      // this wave holds all of tile kt + h
+                WAIT_VMCNT((STAGES - 2) * NLOAD);     // its share of the next one has landed
+                __builtin_amdgcn_s_barrier();
+#pragma unroll
+                for (int j = 0; j < KSUB; ++j) load_frags(nx, j, fa[h ^ 1][j], fb[h ^ 1][j]);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_tile(rd);
+#pragma unroll
+                for (int j = 0; j < KSUB; ++j) mfma_all(fa[h][j], fb[h][j]);
+                __builtin_amdgcn_sched_barrier(0);
+                advance_tile();
+                rd = nx;
+            }
+        }
+    } else {
+        static_assert(BK == 64 || KSUB == 2, "pipeline below is written for two sub-steps per tile");
+        bf16x8_t fa0[TC], fb0[TP], fa1[TC], fb1[TP];
+        load_frags(0, 0, fa0, fb0);
+        int rd = 0;
+        for (int kt = kt0; kt < kt1; ++kt) {
+            const int nx = rd + 1 == STAGES ? 0 : rd + 1;
+            load_frags(rd, 1, fa1, fb1);
+            __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
+            mfma_all(fa0, fb0);
+            __builtin_amdgcn_sched_barrier(0);
+            WAIT_LGKMCNT(0);                              // this wave has read all of tile kt
+            WAIT_VMCNT((STAGES - 2) * NLOAD);             // its share of tile kt+1 has landed
+            __builtin_amdgcn_s_barrier();
+            load_frags(nx, 0, fa0, fb0);
+            __builtin_amdgcn_sched_barrier(0);
+            issue_tile(rd);                               // tile kt+STAGES into the slot just retired; its address
+            mfma_all(fa1, fb1);                           // arithmetic is free to mix with these MFMAs
+            __builtin_amdgcn_sched_barrier(0);
+            advance_tile();
+            rd = nx;
+        }
     }
     WAIT_VMCNT(0);
     __syncthreads();
@@ -519,7 +549,7 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 }
 
 struct GatherPlan {
-    int bp, bc, splits, kt_per_split;
+    int bp, bc, bk, splits, kt_per_split;
     int classes;             // 1, or s_in^2: a PHASED launch
     long long class_pix;     // output pixels of the largest class
 };
@@ -558,10 +588,16 @@ GatherPlan gather_plan(const GatherConv &g)
     // halves the L2 -> LDS traffic of two independent 256 x 128 blocks (3 % on the 512-channel 28x28 layers)
     if (!few && p.bp == 256 && p.bc == 128 && g.Co % 256 == 0) p.bc = 256;
     const long long tiles = tiles_of(p.bp);
-    const int BK = 32;
+    // K-tiles of 64 channels, read a whole tile ahead, for 64-pixel tiles that come to at most two blocks per compute
+    // unit (that kernel's LDS and registers allow no more): 3x3 256->256 and 1x1 1024->256 at 14x14, 32 samples, 196
+    // blocks, together 21.8 -> 18.1 us a launch; VGG-16's first linear layer 54.5 -> 48 us forward, 63.8 -> 52 gradient.
+    // With more blocks than that the four smaller ones that fit a unit hide the latencies better (1x1 512->256 at 56x56,
+    // 3136 blocks: 53 us against 81).  Does not depend on `beside`: K is summed in another order.
+    p.bk = p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
+    const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
     long long want = tiles >= 128 ? 1 : (512 + tiles - 1) / tiles;
-    long long most = KT / 16;                       // at least 16 K-tiles per split
+    long long most = KT * BK / 512;                 // at least 512 of K per split
     if (want > most) want = most;
     if (want > 32) want = 32;
     if (want < 1 || p.classes > 1) want = 1;
@@ -605,7 +641,10 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
                            (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
-    if (phased) {
+    if constexpr (BK == 64) {
+        if (phased) GATHER_LAUNCH(true, true, true);
+        else GATHER_LAUNCH(true, true, false);
+    } else if (phased) {
         GATHER_LAUNCH(true, true, true);
     } else if (g.s_in == 1) {
         if (taps_inner) GATHER_LAUNCH(true, true, false);
@@ -993,6 +1032,7 @@ hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, v
     if (conv3x3_halo_supported(g)) return conv3x3_halo_mfma(in, wt, bias, out, relu, epi, g, s);
     if (!epi.gate && !epi.accum && conv3x3_c8_supported(g)) return conv3x3_c8_mfma(in, wt, bias, out, relu, g, s);
     const GatherPlan p = gather_plan(g);
+    if (p.bk == 64) return launch_gather<64, 128, 1, 4, 64, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
     if (p.bp == 64) return launch_gather<64, 128, 1, 4, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
     if (p.bc == 64) return launch_gather<256, 64, 4, 1, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
     if (p.bc == 256) return launch_gather<256, 256, 2, 4, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
@@ -1013,6 +1053,7 @@ hipError_t conv_gather_mfma_raw(const void *in, const void *wt, const GatherConv
     *splits = p.splits;
     if ((long long)g.N * g.Ho * g.Wo == 0) return hipSuccess;
     const GradEpi none{nullptr, 0};
+    if (p.bk == 64) return launch_gather<64, 128, 1, 4, 64, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
     if (p.bp == 64) return launch_gather<64, 128, 1, 4, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
     if (p.bc == 64) return launch_gather<256, 64, 4, 1, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
     if (p.bc == 256) return launch_gather<256, 256, 2, 4, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);

@@ -44,3 +44,15 @@ def test_lstm_sequence_kernels_twice_are_bit_identical():
 def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
     compare_minibatch(st, verbose="strided conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
+
+
+# ------------------------------------------------------------------------------ 64-channel K-tiles of the 64-pixel gather tile
+@pytest.mark.parametrize("k,cin,cout,hw,mb", [
+    (1, 64, 136, (9, 11), 2),        # one K-tile (an odd count: the second half of the trip is skipped), ragged tiles
+    (3, 192, 64, (7, 7), 3),         # 27 K-tiles; the gradient has 9 of them
+    (1, 2048, 128, (5, 5), 2),       # few tiles: K split over blocks, every split ending inside the tensor
+    (3, 128, 256, (14, 14), 5),      # 36 or 18 K-tiles, whole channel tiles
+])
+def test_conv_wide_k_tiles(k, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="wide K tiles k%d %d->%d %s" % (k, cin, cout, hw))
