@@ -56,3 +56,15 @@ def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
 def test_conv_wide_k_tiles(k, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
     compare_minibatch(st, verbose="wide K tiles k%d %d->%d %s" % (k, cin, cout, hw))
+
+
+# ------------------------------------------------------------------------------ direct convolution (fp32 stages)
+@pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
+    (3, 1, 1, 20, 12, (9, 11), 3),       # a last trip of one vector of channels
+    (3, 2, 2, 4, 8, (8, 7), 2),          # fewer channels than a trip, two columns of padding
+    (1, 3, 0, 36, 5, (10, 10), 2),       # gradient operand with an odd channel count: one channel at a time
+    (5, 3, 1, 16, 16, (7, 19), 1),       # columns at the right edge that no output reads
+])
+def test_direct_conv(k, stride, pad, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.FP32, micro_batch=mb)
+    compare_minibatch(st, verbose="direct conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
