@@ -13,13 +13,19 @@ struct bf16_t {
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float(((uint32_t)x.v) << 16); }
 
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
+// Two floats to bf16 in one 32-bit word, rounded to nearest even (v_cvt_pk_bf16_f32; agrees with the rounding written out
+// in integer arithmetic on all 2^32 inputs, NaNs and denormals among them).  Written out, the rounding was eight
+// instructions and a branch per value, about as many issue slots as the MFMAs of a short product (per mini-batch: VGG stage 1 9.52 -> 9.00 ms, conv4 block
+// 1.56 -> 1.49, ResNet stem 5.51 -> 5.26).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x0040u);   // quiet NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+
+__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return (uint16_t)pack_bf16(f, f); }
 
 template <class T> __device__ __forceinline__ T from_f32(float f);
 template <> __device__ __forceinline__ float from_f32<float>(float f) { return f; }

@@ -267,8 +267,8 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
                     v3 = fmaxf(v3, 0.0f);
                 }
                 chunk8 c8;
-                c8[0] = (uint32_t)f32_to_bf16_bits(v0) | ((uint32_t)f32_to_bf16_bits(v1) << 16);
-                c8[1] = (uint32_t)f32_to_bf16_bits(v2) | ((uint32_t)f32_to_bf16_bits(v3) << 16);
+                c8[0] = pack_bf16(v0, v1);
+                c8[1] = pack_bf16(v2, v3);
                 *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
             }
         }
@@ -473,8 +473,8 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
                     v3 = fmaxf(v3, 0.0f);
                 }
                 chunk8 c8;
-                c8[0] = (uint32_t)f32_to_bf16_bits(v0) | ((uint32_t)f32_to_bf16_bits(v1) << 16);
-                c8[1] = (uint32_t)f32_to_bf16_bits(v2) | ((uint32_t)f32_to_bf16_bits(v3) << 16);
+                c8[0] = pack_bf16(v0, v1);
+                c8[1] = pack_bf16(v2, v3);
                 *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
             }
         }

@@ -403,8 +403,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
                     v3 = fmaxf(v3, 0.0f);
                 }
                 chunk8 c8;
-                c8[0] = (uint32_t)f32_to_bf16_bits(v0) | ((uint32_t)f32_to_bf16_bits(v1) << 16);
-                c8[1] = (uint32_t)f32_to_bf16_bits(v2) | ((uint32_t)f32_to_bf16_bits(v3) << 16);
+                c8[0] = pack_bf16(v0, v1);
+                c8[1] = pack_bf16(v2, v3);
                 *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
             }
         }
