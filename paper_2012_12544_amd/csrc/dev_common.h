@@ -15,8 +15,8 @@ __device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float(((uin
 
 // Two floats to bf16 in one 32-bit word, rounded to nearest even (v_cvt_pk_bf16_f32; agrees with the rounding written out
 // in integer arithmetic on all 2^32 inputs, NaNs and denormals among them).  Written out, the rounding was eight
-// instructions and a branch per value, about as many issue slots as the MFMAs of a short product (per mini-batch: VGG stage 1 9.52 -> 9.00 ms, conv4 block
-// 1.56 -> 1.49, ResNet stem 5.51 -> 5.26).
+// instructions and a branch per value, about as many issue slots as the MFMAs of a short product (per mini-batch: VGG
+// stage 1 9.52 -> 9.00 ms, conv4 block 1.56 -> 1.49, ResNet stem 5.51 -> 5.26).
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

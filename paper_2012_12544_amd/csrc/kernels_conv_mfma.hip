@@ -73,7 +73,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     const lds_addr_of lds_of(smem);
     uint16_t *ring = reinterpret_cast<uint16_t *>(smem);               // [STAGES][ W tile | X tile ]
     uint16_t *sO = reinterpret_cast<uint16_t *>(smem);                 // [BP][SROW] (epilogue, reuses the ring)
-    constexpr size_t RING_BYTES = (size_t)STAGES * STAGE_ELEMS * 2, EPI_BYTES = (size_t)BP * SROW * 2;
+    constexpr size_t RING_BYTES = (size_t)STAGES * STAGE_ELEMS * 2, TILE_BYTES = (size_t)BP * SROW * 2, EPI_BYTES = TILE_BYTES + NT * 8;
     float *sBias = reinterpret_cast<float *>(smem + (RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES));   // [BC]
     int *sPix = reinterpret_cast<int *>(sBias + BC);                  // PHASED: [BP] output pixel of a tile row, npix past the end
 
@@ -409,47 +409,36 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             }
         }
     }
-    // gradient epilogue: the ReLU-gate rows of the thread's first units are requested now, so that they travel
-    // while the staging tile is being completed instead of after the barrier
-    constexpr int GUNITS = BP * (BC / 8) / NT, GPRE = GUNITS < 8 ? GUNITS : 8;
-    chunk16 gpre[GPRE];
-    if (is_grad && gate) {
-#pragma unroll
-        for (int it = 0; it < GPRE; ++it) {
-            const int u = tid + it * NT;
-            const int p = PHASED ? sPix[u / (BC / 8)] : pix0 + u / (BC / 8), co = co0 + (u % (BC / 8)) * 8;
-            gpre[it] = (p < npix && co < g.Co) ? *reinterpret_cast<const chunk16 *>(gate + (size_t)p * g.Co + co) : zero16;
-        }
-    }
-    __syncthreads();
-    // Per-channel sum and sum of squares of the STORED (rounded) values of this pixel tile, for a batch-norm
-    // that follows: stat_part[q][pixel tile][channel], q = 0 sum, 1 squares - the layout the final pass of the
-    // column reductions reads.  One thread per channel walks down the staged tile.
-    if (stat_part && !bn_x) {
-        for (int cc = tid; cc < BC; cc += NT) {
-            const int co = co0 + cc;
-            if (co < g.Co) {
-                const int here = rows - pix0 < BP ? rows - pix0 : BP;
-                float s1 = 0.0f, s2 = 0.0f;
-                for (int r = 0; r < here; ++r) {
-                    const float v = __uint_as_float((uint32_t)sO[r * SROW + cc] << 16);
-                    s1 += v;
-                    s2 += v * v;
-                }
-                stat_part[(size_t)tile_z * g.Co + co] = s1;
-                stat_part[((size_t)tiles_all + tile_z) * g.Co + co] = s2;
-            }
-        }
-    }
+    // The tile leaves in 16-byte units, UNITS per thread.  What a gradient unit needs besides its own value (gate row,
+    // stored gradient, batch-norm input) is requested for a whole batch of units before the first of them is used or
+    // stored - the first batch now, while the staging tile is being completed.  Requested unit by unit, behind the store
+    // of the one before (which may alias), each cost a memory latency: 1x1 128->256 at 56x56, 32 samples, with the stored
+    // gradient added, 53 -> 48 us; 3x3 / 2 gradient of 128 channels at 56x56 with the batch-norm sums, 44 -> 42 us.
     constexpr int CH8 = BC / 8;                 // 16-byte units per pixel row
     constexpr int UNITS = BP * CH8 / NT;        // per thread
-    static_assert(NT % CH8 == 0, "a thread keeps one channel group through the loop below");
-    // bn_x: the gradient written here is the output gradient of a batch-norm whose input is bn_x and whose
-    // (mean, 1/std) are bn_stats: the per-channel sums of dy and dy*xhat over this pixel tile are taken on
-    // the way out (what the first pass of the batch-norm's backward would compute from HBM)
+    constexpr int BATCH = UNITS < 8 ? UNITS : 8;
+    static_assert(NT % CH8 == 0 && UNITS % BATCH == 0, "a thread keeps one channel group; whole batches");
+    const int c8i = tid % CH8, rg = tid / CH8, co = co0 + c8i * 8;
+    auto pixel_of = [&](int it) { const int prow = rg + it * (NT / CH8); return PHASED ? sPix[prow] : pix0 + prow; };
+    chunk16 gpre[BATCH] = {}, opre[BATCH] = {}, xpre[BATCH] = {};
+    auto fetch = [&](chunk16(&to)[BATCH], const bf16_t *from, int it0) {
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int p = pixel_of(it0 + j);
+            to[j] = p < npix && co < g.Co ? *reinterpret_cast<const chunk16 *>(from + (size_t)p * g.Co + co) : zero16;
+        }
+    };
+    auto request = [&](int it0) {
+        if (gate) fetch(gpre, gate, it0);
+        if (accum) fetch(opre, old_from ? old_from : out, it0);
+        if (bn_x) fetch(xpre, bn_x, it0);
+    };
+    if (is_grad) request(0);
+    // Per-channel sums over this pixel tile for a batch-norm, stat_part[q][pixel tile][channel], the layout the final pass
+    // of the column reductions reads.  For one whose output gradient this is (bn_x its input, bn_stats its mean and
+    // 1/std): of dy and dy*xhat, taken on the way out.
     float bs1[8], bs2[8], bmu[8], binv[8];
     if (bn_x) {
-        const int co = co0 + (tid % CH8) * 8;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             bs1[j] = bs2[j] = 0.0f;
@@ -457,64 +446,81 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             binv[j] = co + j < g.Co ? bn_stats[g.Co + co + j] : 0.0f;
         }
     }
+    __syncthreads();
+    // For one that follows: of the STORED (rounded) values and their squares, what its first pass would compute.  All
+    // threads walk down the staged tile, NT / BC of them per channel (one per channel left three of four waves of a
+    // 256 x 64 tile waiting for 256 rows: 1x1 and 3x3 64->64 at 56x56 and their like, 23.4 -> 22 us a launch).
+    float2 *sums = reinterpret_cast<float2 *>(smem + TILE_BYTES);        // [NT / BC][BC]
+    constexpr int GROUPS = NT / BC, GROWS = BP / GROUPS;
+    if (stat_part && !bn_x) {
+        const int cc = tid % BC, r0 = tid / BC * GROWS;
+        const int here = rows - pix0 < BP ? rows - pix0 : BP, r1 = r0 + GROWS < here ? r0 + GROWS : here;
+        float2 t = make_float2(0.0f, 0.0f);
+#pragma unroll 8
+        for (int r = r0; r < r1; ++r) {
+            const float v = __uint_as_float((uint32_t)sO[r * SROW + cc] << 16);
+            t.x += v;
+            t.y += v * v;
+        }
+        sums[tid] = t;
+    }
 #pragma unroll
-    for (int it = 0; it < UNITS; ++it) {
-        const int u = tid + it * NT;
-        const int prow = u / CH8, c8i = u % CH8;
-        const int p = PHASED ? sPix[prow] : pix0 + prow;
-        const int co = co0 + c8i * 8;
-        if (p < npix && co < g.Co) {
-            chunk8 lo = *reinterpret_cast<const chunk8 *>(sO + prow * SROW + c8i * 8);
-            chunk8 hi = *reinterpret_cast<const chunk8 *>(sO + prow * SROW + c8i * 8 + 4);
-            chunk16 v = {lo[0], lo[1], hi[0], hi[1]};
-            bf16_t *dst = out + (size_t)p * g.Co + co;
-            if (is_grad) {
-                chunk16 old = zero16, gt = zero16, r;
-                if (accum) old = *reinterpret_cast<const chunk16 *>(old_from ? old_from + (size_t)p * g.Co + co : dst);
-                if (gate) gt = it < GPRE ? gpre[it < GPRE ? it : 0] : *reinterpret_cast<const chunk16 *>(gate + (size_t)p * g.Co + co);
+    for (int it0 = 0; it0 < UNITS; it0 += BATCH) {
+        if (it0 && is_grad) request(it0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] = grad_epilogue_pair(v[j], old[j], gt[j], accum != 0, gate != nullptr);
-                *reinterpret_cast<chunk16 *>(dst) = r;
+        for (int j0 = 0; j0 < BATCH; ++j0) {
+            const int p = pixel_of(it0 + j0);
+            if (p < npix && co < g.Co) {
+                const uint16_t *src = sO + (rg + (it0 + j0) * (NT / CH8)) * SROW + c8i * 8;
+                const chunk8 lo = *reinterpret_cast<const chunk8 *>(src), hi = *reinterpret_cast<const chunk8 *>(src + 4);
+                chunk16 r = {lo[0], lo[1], hi[0], hi[1]};
+                if (is_grad) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) r[j] = grad_epilogue_pair(r[j], opre[j0][j], gpre[j0][j], accum != 0, gate != nullptr);
+                }
+                *reinterpret_cast<chunk16 *>(out + (size_t)p * g.Co + co) = r;
                 if (bn_x) {
-                    const chunk16 xv = *reinterpret_cast<const chunk16 *>(bn_x + (size_t)p * g.Co + co);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
                         const float gj = __uint_as_float((j & 1) ? (r[j >> 1] & 0xFFFF0000u) : (r[j >> 1] << 16));
-                        const float xj = __uint_as_float((j & 1) ? (xv[j >> 1] & 0xFFFF0000u) : (xv[j >> 1] << 16));
+                        const float xj = __uint_as_float((j & 1) ? (xpre[j0][j >> 1] & 0xFFFF0000u) : (xpre[j0][j >> 1] << 16));
                         bs1[j] += gj;
                         bs2[j] += gj * ((xj - bmu[j]) * binv[j]);
                     }
                 }
-            } else {
-                *reinterpret_cast<chunk16 *>(dst) = v;
             }
         }
     }
+    if (!stat_part) return;
+    float *red = reinterpret_cast<float *>(smem);                          // [RG][2][BC]; the staging tile is free now
+    constexpr int RG = NT / CH8;                                           // threads that share a channel group
+    static_assert((size_t)RG * BC * 2 * sizeof(float) <= TILE_BYTES && NT % BC == 0 && BP % GROUPS == 0, "sums fit their places");
+    __syncthreads();
     if (bn_x) {
-        // combine the NT / CH8 threads that share a channel group through LDS (the staging tile is free now)
-        constexpr int RG = NT / CH8;
-        static_assert((size_t)RG * BC * 2 * sizeof(float) <= EPI_BYTES, "reduction buffer fits the staging tile");
-        float *red = reinterpret_cast<float *>(smem);                      // [RG][2][BC]
-        __syncthreads();
-        const int rg = tid / CH8, c8i = tid % CH8;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             red[(rg * 2 + 0) * BC + c8i * 8 + j] = bs1[j];
             red[(rg * 2 + 1) * BC + c8i * 8 + j] = bs2[j];
         }
         __syncthreads();
-        for (int cc = tid; cc < BC; cc += NT) {
-            const int co = co0 + cc;
-            if (co < g.Co) {
-                float t1 = 0.0f, t2 = 0.0f;
-                for (int k = 0; k < RG; ++k) {
-                    t1 += red[(k * 2 + 0) * BC + cc];
-                    t2 += red[(k * 2 + 1) * BC + cc];
-                }
-                stat_part[(size_t)tile_z * g.Co + co] = t1;
-                stat_part[((size_t)tiles_all + tile_z) * g.Co + co] = t2;
+    }
+    if (tid < BC && co0 + tid < g.Co) {
+        float2 t = make_float2(0.0f, 0.0f);
+        if (bn_x) {
+#pragma unroll 8
+            for (int k = 0; k < RG; ++k) {
+                t.x += red[(k * 2 + 0) * BC + tid];
+                t.y += red[(k * 2 + 1) * BC + tid];
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < GROUPS; ++k) {
+                t.x += sums[k * BC + tid].x;
+                t.y += sums[k * BC + tid].y;
             }
         }
+        stat_part[(size_t)tile_z * g.Co + co0 + tid] = t.x;
+        stat_part[((size_t)tiles_all + tile_z) * g.Co + co0 + tid] = t.y;
     }
 }
 
@@ -613,7 +619,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
 {
     constexpr int NT = WP * WC * 64;
     constexpr size_t main_bytes = (size_t)STAGES * (BP + BC) * BK * 2;
-    constexpr size_t epi_bytes = (size_t)BP * (BC + 4) * 2;
+    constexpr size_t epi_bytes = (size_t)BP * (BC + 4) * 2 + NT * 8;      // staging tile, per-thread sums
     constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float);
     const bool phased = plan.classes > 1;
     constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
