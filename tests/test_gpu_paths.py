@@ -68,3 +68,17 @@ def test_conv_wide_k_tiles(k, cin, cout, hw, mb):
 def test_direct_conv(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.FP32, micro_batch=mb)
     compare_minibatch(st, verbose="direct conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
+
+
+# ------------------------------------------------------------------------------ weight gradient: steps of 32 pixels through small images
+@pytest.mark.parametrize("k,stride,cin,cout,hw,mb", [
+    (3, 1, 64, 72, (2, 3), 23),          # 32 pixels are five images and two pixels
+    (3, 1, 16, 64, (1, 5), 17),          # ... six rows, each an image
+    (3, 2, 64, 64, (9, 13), 5),          # the columns wrap in a step, with a stride
+    (3, 1, 64, 128, (40, 1), 3),         # rows of one pixel
+    (1, 1, 136, 64, (5, 7), 9),          # 1x1: a plain list of rows, ragged tiles
+    (1, 2, 64, 64, (5, 4), 9),           # 1x1 with a stride keeps its image
+])
+def test_wgrad_small_images(k, stride, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="wgrad k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
