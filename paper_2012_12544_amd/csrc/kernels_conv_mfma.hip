@@ -589,7 +589,10 @@ GatherPlan gather_plan(const GatherConv &g)
     // small products (the bottleneck blocks of ResNet: under ~8 GMAC) are bound by the latency of a block's
     // load - multiply - store chain, not by throughput: many 64-pixel blocks and no split of K were the
     // fastest choice on every such shape measured (e.g. 1x1 1024->256 at 14x14: 11.5 us against 22.2)
-    if (p.bc == 128 && npix > 64 && (double)npix * g.Co * g.R * g.S * g.Ci < 8e9 * p.classes) p.bp = 64;
+    // So are products up to twice that whose 64-pixel tiles fit two blocks per unit (the LSTM's input gradient, 3200 x 1024
+    // x 4096: 400 blocks, 59 -> 43 us); where they do not (its input projection, 1600 blocks), the larger tile stays.
+    const double macs = (double)npix * g.Co * g.R * g.S * g.Ci / p.classes;
+    if (p.bc == 128 && npix > 64 && (macs < 8e9 || (macs < 16e9 && tiles_of(64) <= 512))) p.bp = 64;
     // plenty of 256-pixel tiles and whole 256-channel tiles: one 8-wave block per CU owns 256 x 256, which
     // halves the L2 -> LDS traffic of two independent 256 x 128 blocks (3 % on the 512-channel 28x28 layers)
     if (!few && p.bp == 256 && p.bc == 128 && g.Co % 256 == 0) p.bc = 256;
