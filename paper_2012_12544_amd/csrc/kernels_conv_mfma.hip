@@ -557,14 +557,16 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 struct GatherPlan {
     int bp, bc, bk, splits, kt_per_split;
     int classes;             // 1, or s_in^2: a PHASED launch
+    int busy;                // classes that have taps
     long long class_pix;     // output pixels of the largest class
 };
 
-// The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask.  A 1x1 filter has nothing to take
-// apart (one class with its tap, the others empty).
+// The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask.  Of a 1x1 filter's classes one has
+// the tap and the others only their epilogue (a projection shortcut's gradient, 56x56 of 256 channels, 32 samples: 27 us,
+// as a dense product into the workspace and a pass that spread it 16 + 23).
 bool gather_phased(const GatherConv &g)
 {
-    return g.s_in > 1 && g.s_out == 1 && g.Ci % 32 == 0 && g.R * g.S > 1 && g.R * g.S <= 32 && g.pad_h >= 0 && g.pad_w >= 0;
+    return g.s_in > 1 && g.s_out == 1 && g.Ci % 32 == 0 && g.R * g.S <= 32 && g.pad_h >= 0 && g.pad_w >= 0;
 }
 
 // Tile shape and split-K factor.  K is split only when there are very few output tiles (the linear
@@ -574,11 +576,12 @@ GatherPlan gather_plan(const GatherConv &g)
     GatherPlan p;
     const long long npix = (long long)g.N * g.Ho * g.Wo;
     p.classes = gather_phased(g) ? g.s_in * g.s_in : 1;
+    p.busy = p.classes == 1 ? 1 : (g.R < g.s_in ? g.R : g.s_in) * (g.S < g.s_in ? g.S : g.s_in);
     p.class_pix = p.classes == 1 ? npix : (long long)g.N * ((g.Ho + g.s_in - 1) / g.s_in) * ((g.Wo + g.s_in - 1) / g.s_in);
     p.bp = p.class_pix <= 64 ? 64 : 256;
     p.bc = g.Co <= 64 ? 64 : 128;
     if (p.bp == 64) p.bc = 128;
-    auto tiles_of = [&](int bp) { return p.classes * ((p.class_pix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
+    auto tiles_of = [&](int bp) { return p.busy * ((p.class_pix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
     // 256-pixel tiles that cannot even fill 400 of the 512 block slots (14x14 layers, the 1x1 convs of
     // the bottleneck blocks): halve the pixel tile rather than split K, whose fp32 partials cost more
     // than the smaller tile loses (measured on 512-channel 14x14 layers: 73 us against 100 us)

@@ -86,10 +86,6 @@ struct Layer {
     // input-gradient kernel leaves the per-tile sums of dy and dy*xhat for that batch-norm's backward
     int bnb_chunks = 0;
     bool bwd_sums_given = false;
-    // 1x1 conv with a stride: its input gradient is non-zero only at multiples of the stride, so the product
-    // with the filter is taken at the output's resolution into the workspace (at up_off) and spread from there
-    bool strided_1x1 = false;
-    size_t up_off = 0;
     int fuse_add = -1;     // batch-norm: the residual ADD (layer index) whose sum this layer's normalisation pass stores
     // LSTM: per in-flight micro-batch the slot keeps the gates and cell states (float), the delayed
     // copy of h that the recurrent products read, the buffer shared by the input projection
@@ -700,7 +696,7 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
         }
         if (a_grad) {
             GatherConv dg = dgrad_geom(st, L);
-            dg.beside = st->stream_b && !c.profiling && !L.bnb_chunks && !L.strided_1x1;
+            dg.beside = st->stream_b && !c.profiling && !L.bnb_chunks;
             GradEpi e = epi_for(st, L.a, c);
             if (c.pending[A.root]) {                      // the residual ADD's share, added here instead of copied there
                 e.accum_from = c.pending[A.root];
@@ -709,14 +705,7 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             void *dx = grad_ptr(st, L.a, c);
             const bool mf = use_mfma_gather(st, dg);
             const bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
-            if (mf && L.strided_1x1) {
-                GatherConv dense = dg;                       // dy as the image, one output pixel per dy pixel
-                dense.Ho = dg.Hi; dense.Wo = dg.Wi; dense.s_in = 1;
-                GradEpi none{nullptr, 0};
-                void *tmp = st->work + L.up_off;
-                HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, tmp, 0, none, dense, st->work, s));
-                HIPCHK(upsample_grad(dt, tmp, dx, e, dg.N, dg.Ho, dg.Wo, dg.Hi, dg.Wi, dg.Co, L.d.stride, s));
-            } else if (mf && L.bnb_chunks && !c.profiling && (e.gate || e.accum)) {
+            if (mf && L.bnb_chunks && !c.profiling && (e.gate || e.accum)) {
                 const Layer &B = st->layers[li - 1];
                 HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, dx, 0, e, dg, st->work, s, (float *)st->work,
                                         st->tptr(B.a, c.mbid), (const float *)(st->slot(c.mbid) + B.aux_off)));
@@ -1250,19 +1239,6 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 }
             }
         }
-        if (L.d.kind == BAPIPE_CONV2D && st->dt == DT_BF16 && L.d.kh == 1 && L.d.kw == 1 && L.d.stride > 1 && L.d.pad == 0 &&
-            st->tensors[st->tensors[L.a].root].need_grad) {
-            const GatherConv dg = dgrad_geom(st, L);
-            GatherConv dense = dg;
-            dense.Ho = dg.Hi; dense.Wo = dg.Wi; dense.s_in = 1;
-            if (use_mfma_gather(st, dg) && use_mfma_gather(st, dense)) {
-                L.strided_1x1 = true;
-                L.bnb_chunks = 0;
-                L.up_off = align_up(conv_gather_mfma_workspace(dense));
-                const size_t w = L.up_off + align_up((size_t)dense.N * dense.Ho * dense.Wo * dense.Co * es);
-                work = w > work ? w : work;
-            }
-        }
         if (L.d.kind == BAPIPE_CONV2D || L.d.kind == BAPIPE_LINEAR) {
             ConvShape cs = conv_shape(st, L);
             if (L.d.kind == BAPIPE_LINEAR && n_micro > 1 && use_mfma_wgrad(st, cs)) {
@@ -1298,7 +1274,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         const Layer &Lc = st->layers[ic], &La = st->layers[ia];
         if (ic >= ia || Lc.d.kind != BAPIPE_CONV2D || La.d.kind != BAPIPE_ADD || Lc.a != t || (La.a != t && La.b != t)) continue;
         const GatherConv dg = dgrad_geom(st, Lc);
-        if (!use_mfma_gather(st, dg) || conv3x3_halo_supported(dg) || Lc.strided_1x1 || Lc.bnb_chunks) continue;
+        if (!use_mfma_gather(st, dg) || conv3x3_halo_supported(dg) || Lc.bnb_chunks) continue;
         T.fanout_conv = ic;
     }
     st->slot_bytes = align_up(slot);

@@ -40,6 +40,8 @@ def test_lstm_sequence_kernels_twice_are_bit_identical():
     (5, 3, 2, 64, 32, (16, 14), 2),      # nine classes of 1, 2 and 4 taps
     (2, 3, 0, 64, 64, (13, 14), 2),      # stride beyond the filter: classes without taps
     (3, 2, 1, 128, 128, (56, 56), 3),    # many tiles
+    (1, 2, 0, 72, 64, (15, 15), 2),      # 1x1: one class with a tap, three with their epilogue only
+    (1, 3, 0, 136, 32, (7, 8), 2),
 ])
 def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
