@@ -161,8 +161,12 @@ hipError_t xent_bwd(int dt, const float *p, const int32_t *labels, float scale, 
                     int rows, int K, hipStream_t s);
 
 // ---- parameters
-// w <- w - lr*g ; g <- 0 ; work <- storage(w)   (work may be NULL for float vectors)
-hipError_t sgd_step(int dt, float *w, float *g, float lr, void *work, size_t n, hipStream_t s);
+// w <- w - lr*g ; g <- 0
+hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s);
+// the same for a weight matrix [K][R][S][C] with its working copy and transposed copy (see recast and
+// make_dgrad_filter), and for its bias b / db [K] (may be NULL)
+hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
+                      float *db, hipStream_t s);
 hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s);
 // wt[c][R-1-r][S-1-s][k] = work(w[k][r][s][c])   (dgrad filter)
 hipError_t make_dgrad_filter(int dt, const float *w, void *wt, int K, int R, int S, int C, hipStream_t s);

@@ -988,15 +988,73 @@ __global__ void k_xent_loss(const float *__restrict__ p, const int32_t *__restri
 }
 
 // ------------------------------------------------------------------ parameters
-template <class T, bool HAS_WORK>
-__global__ void k_sgd(float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work, size_t n)
+__global__ void k_sgd(float *__restrict__ w, float *__restrict__ g, float lr, size_t n)
 {
     size_t i = (size_t)blockIdx.x * TPB + threadIdx.x;
     if (i >= n) return;
-    float v = w[i] - lr * g[i];
-    w[i] = v;
+    w[i] -= lr * g[i];
     g[i] = 0.0f;
-    if (HAS_WORK) work[i] = from_f32<T>(v);
+}
+
+// The whole update of a weight matrix [K][R*S][C]: w -= lr g, g = 0, the working copy, the transposed (flipped) copy of
+// the input gradient (see k_dgrad_filter) and the bias, in one pass on 64 x 64 tiles of one tap through LDS; V channels a
+// thread and access.  HBM-bound for the big linear layers: as an update and a transposing pass that read the masters
+// again VGG-16's first linear layer took 310 + 193 us, 400 us here; for a convolution layer it is one launch of a few
+// microseconds instead of three.
+template <class T, int V>
+__global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work,
+                                                    T *__restrict__ wt, int K, int R, int S, int C, float *__restrict__ b,
+                                                    float *__restrict__ db)
+{
+    constexpr int LANES = 64 / V, ROWS = TPB / LANES, TRIPS = 64 / ROWS;
+    __shared__ float tile[64][65];
+    const int c0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
+    const int tap = blockIdx.z, RS = R * S, tap_t = RS - 1 - tap;
+    const int tx = threadIdx.x % LANES, ty = threadIdx.x / LANES;
+    vec_t<float, V> wv[TRIPS], gv[TRIPS];
+#pragma unroll
+    for (int i = 0; i < TRIPS; ++i) {
+        const int k = k0 + ty + ROWS * i, c = c0 + V * tx;
+        if (k < K && c < C) {
+            const size_t at = ((size_t)k * RS + tap) * C + c;
+            wv[i] = *reinterpret_cast<const vec_t<float, V> *>(w + at);
+            gv[i] = *reinterpret_cast<const vec_t<float, V> *>(g + at);
+        }
+    }
+    const vec_t<float, V> zero = {};
+#pragma unroll
+    for (int i = 0; i < TRIPS; ++i) {
+        const int k = k0 + ty + ROWS * i, c = c0 + V * tx;
+        if (k < K && c < C) {
+            const size_t at = ((size_t)k * RS + tap) * C + c;
+            vec_t<T, V> o;
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                wv[i].e[j] -= lr * gv[i].e[j];
+                o.e[j] = from_f32<T>(wv[i].e[j]);
+                tile[ty + ROWS * i][V * tx + j] = wv[i].e[j];
+            }
+            *reinterpret_cast<vec_t<float, V> *>(w + at) = wv[i];
+            *reinterpret_cast<vec_t<float, V> *>(g + at) = zero;
+            *reinterpret_cast<vec_t<T, V> *>(work + at) = o;
+        }
+    }
+    if (b && blockIdx.x == 0 && tap == 0 && threadIdx.x < 64 && k0 + (int)threadIdx.x < K) {
+        const int k = k0 + threadIdx.x;
+        b[k] -= lr * db[k];
+        db[k] = 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TRIPS; ++i) {
+        const int c = c0 + ty + ROWS * i, k = k0 + V * tx;
+        if (c < C && k < K) {
+            vec_t<T, V> o;
+#pragma unroll
+            for (int j = 0; j < V; ++j) o.e[j] = from_f32<T>(tile[V * tx + j][ty + ROWS * i]);
+            *reinterpret_cast<vec_t<T, V> *>(wt + ((size_t)c * RS + tap_t) * K + k) = o;
+        }
+    }
 }
 
 template <class T> __global__ void k_recast(const float *__restrict__ w, T *__restrict__ work, size_t n)
@@ -1469,16 +1527,27 @@ hipError_t xent_bwd(int dt, const float *p, const int32_t *labels, float scale, 
     return hipGetLastError();
 }
 
-hipError_t sgd_step(int dt, float *w, float *g, float lr, void *work, size_t n, hipStream_t s)
+hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    if (!work) {
-        hipLaunchKernelGGL((k_sgd<float, false>), dim3(blocks_for(n)), dim3(TPB), 0, s, w, g, lr, (float *)nullptr, n);
-    } else {
-        DISPATCH_T(dt, {
-            hipLaunchKernelGGL((k_sgd<T, true>), dim3(blocks_for(n)), dim3(TPB), 0, s, w, g, lr, (T *)work, n);
-        });
-    }
+    hipLaunchKernelGGL(k_sgd, dim3(blocks_for(n)), dim3(TPB), 0, s, w, g, lr, n);
+    return hipGetLastError();
+}
+
+hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
+                      float *db, hipStream_t s)
+{
+    if ((size_t)K * R * S * C == 0) return hipSuccess;
+    const dim3 grid((unsigned)((C + 63) / 64), (unsigned)((K + 63) / 64), (unsigned)(R * S));
+    const size_t es = dt_size(dt);
+    // four values per access where rows of both copies and their starts allow it
+    const bool vec = C % 4 == 0 && K % 4 == 0 && aligned16(w) && aligned16(g) && (uintptr_t)work % (4 * es) == 0 && (uintptr_t)wt % (4 * es) == 0;
+    DISPATCH_T(dt, {
+        if (vec)
+            hipLaunchKernelGGL((k_sgd_matrix<T, 4>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db);
+        else
+            hipLaunchKernelGGL((k_sgd_matrix<T, 1>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db);
+    });
     return hipGetLastError();
 }
 

@@ -372,6 +372,26 @@ hipError_t refresh_transposed(bapipe_stage *st, Layer &L)
     return make_dgrad_filter(st->dt, L.w, L.w_t, L.d.cout, R, S, L.cin_p, st->stream);
 }
 
+// weights, bias and working copies of one layer after a mini-batch
+hipError_t update_layer(bapipe_stage *st, Layer &L, float lr)
+{
+    float *b = L.b_elems ? L.bias : nullptr;
+    if (!has_matrix(L.d.kind)) {
+        const hipError_t e = sgd_step(L.w, L.dw, lr, L.w_elems, st->stream);
+        return e != hipSuccess || !b ? e : sgd_step(b, L.db, lr, L.b_elems, st->stream);
+    }
+    if (L.d.kind == BAPIPE_LSTM) {       // the input block [4H][In], then the recurrent block [4H][H]
+        const int In = L.d.cin, H = L.d.cout, G = 4 * H;
+        const size_t at = (size_t)G * In, es = dt_size(st->dt);
+        const hipError_t e = sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, G, 1, 1, In, b, L.db, st->stream);
+        if (e != hipSuccess) return e;
+        return sgd_matrix(st->dt, L.w + at, L.dw + at, lr, (char *)L.w_work + at * es, (char *)L.w_t + at * es, G, 1, 1, H,
+                          nullptr, nullptr, st->stream);
+    }
+    const int R = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kh, S = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kw;
+    return sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, L.d.cout, R, S, L.cin_p, b, L.db, st->stream);
+}
+
 hipError_t refresh_work(bapipe_stage *st, Layer &L)
 {
     if (!has_matrix(L.d.kind)) return hipSuccess;
@@ -1531,10 +1551,7 @@ int bapipe_stage_step(bapipe_stage_t *st, float lr)
     }
     for (auto &L : st->layers) {
         if (!L.w_elems) continue;
-        const bool mat = L.d.kind != BAPIPE_BATCHNORM2D;
-        HIPCHK(sgd_step(st->dt, L.w, L.dw, lr, mat ? L.w_work : nullptr, L.w_elems, st->stream));
-        if (L.b_elems) HIPCHK(sgd_step(st->dt, L.bias, L.db, lr, nullptr, L.b_elems, st->stream));
-        if (mat) HIPCHK(refresh_transposed(st, L));
+        HIPCHK(update_layer(st, L, lr));
     }
     st->n_fwd = st->n_bwd = 0;
     st->flushed = 0;

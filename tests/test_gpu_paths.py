@@ -2,8 +2,11 @@
 import numpy as np
 import pytest
 
-from gpu_harness import compare_minibatch, gpu_minibatch
+from gpu_harness import GpuStage, compare_minibatch, gpu_minibatch, stage_io
+from oracle.stage import one_f_one_b_order
+from paper_2012_12544_amd import binding as B
 from stage_inputs import configs as C
+from stage_inputs import gen
 from test_gpu_stage import single
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +87,40 @@ def test_direct_conv(k, stride, pad, cin, cout, hw, mb):
 def test_wgrad_small_images(k, stride, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
     compare_minibatch(st, verbose="wgrad k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
+
+
+# ------------------------------------------------------------------------------ weight update: ragged tiles, both access widths, both copies
+def _mini_batch(gpu, stage, xs, gs):
+    out = []
+    for t, m in one_f_one_b_order(stage["n_micro"], B.bapipe_stage_stash_bytes(gpu.h)[1]):
+        out.append(gpu.forward(m, xs[m]) if t == "F" else gpu.backward(m, gs[m]))
+    return out
+
+
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("kind,cin,cout", [("conv", 72, 136), ("conv", 3, 20), ("conv", 7, 5), ("linear", 136, 72),
+                                           ("linear", 24, 8), ("lstm", 24, 40), ("lstm", 128, 128)])
+def test_update_leaves_the_copies_that_setting_the_weights_makes(dtype, kind, cin, cout):
+    """The mini-batch after an update runs on the copies that the update wrote; the same weights set from the host are
+    copied by other kernels.  Outputs and input gradients (working and transposed copies) agree bit for bit."""
+    b = C._Builder()
+    if kind == "conv":
+        b.conv(cin, cout, 3, relu=1, src=-1)
+        b.conv(cout, cin, 3, relu=0)
+    elif kind == "linear":
+        b.linear(cin, cout, relu=1, src=-1)
+        b.linear(cout, cin, relu=0)
+    else:
+        b.lstm(cin, cout, src=-1)
+    hw = {"conv": (6, 5), "linear": (1, 1), "lstm": (4, 1)}[kind]
+    st = C._stage("update", b.layers, dtype, (cin,) + hw, 3, 2, 1, 2, 1, C.BASE_SEED + 78, "lstm" if kind == "lstm" else "kaiming")
+    xs, gs = stage_io(st)
+    one = GpuStage(st, gen.all_params(st, perturb=True))
+    _mini_batch(one, st, xs, gs)
+    B.bapipe_stage_step(one.h, 0.05)
+    other = GpuStage(st, [one.get_params(i) if w is not None else (None, None)
+                          for i, (w, _) in enumerate(gen.all_params(st, perturb=True))])
+    for u, v in zip(_mini_batch(one, st, xs, gs), _mini_batch(other, st, xs, gs)):
+        assert np.array_equal(u, v)
+    one.close()
+    other.close()
