@@ -5,14 +5,14 @@
 // nearly all of it launch gaps and one block's load - multiply - store chain.  Here the matrix never moves: a block of
 // eight waves keeps the rows of 32 hidden units in registers for the whole sequence (128 registers a lane at hidden
 // 1024), and a step is the exchange of one small vector.  Hidden 1024, 50 steps, 64 sequences, one direction: 650 us
-// before, 240 us (forward) and 217 us (backward) here; of a backward step of 4.4 us 1.9 us are the 16 MB that all
+// before, 203 us (forward) and 211 us (backward) here; of a backward step of 4.4 us 1.9 us are the 16 MB that all
 // blocks together read of the step before, 1.2 us the hand-over, 0.6 us the cell.
 //
 // Split.  16 sequences (the N of the MFMA) form a group, H/32 blocks work on a group, each owns 32 units: their four
 // gates in forward (M = 128 rows, K = H in eight pieces, a piece a wave), their rows of W_h^T in backward (M = 32,
 // K = 4H, half a gate a wave).  The waves' partial sums meet in LDS; thread i then owns one (sequence, unit) for all
 // steps, so the cell state and the cell-gradient carry stay in its register.  Blocks of 16 units (twice the blocks, each
-// reading the whole vector) made a backward step 6.1 us; in forward they are faster alone (213 us) and slower where a
+// reading the whole vector) made a backward step 6.1 us; in forward they were faster alone (213 against 240 us) and slower where a
 // backward pass runs on another stream, because both launches then want all compute units (11.5 against 10.5 ms for a
 // mini-batch of two layers).
 //
