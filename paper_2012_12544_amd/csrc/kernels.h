@@ -133,13 +133,16 @@ hipError_t lstm_cell_bwd(int dt, const void *dy, const float *r, int S, const fl
                          float *dcn, void *D, int N, int T, int H, int t, hipStream_t s);
 
 // ---- the whole recurrence of an LSTM layer in one launch per direction, bf16 (kernels_lstm.hip); arguments as above,
-// w_hh [4H][H] and wt_h [H][4H] are the recurrent matrix and its transpose in the storage type
-bool lstm_seq_supported(int N, int H);
+// w_hh [4H][H] and wt_h [H][4H] are the recurrent matrix and its transpose in the storage type.  A block that has polled for
+// another one's step wait_polls times gives up, and its group of sequences is computed by one block alone: the results are
+// the same bit for bit, whatever the limit.
+constexpr unsigned kLstmWaitPolls = 1u << 16;      // of 0.13 to 0.21 us
+bool lstm_seq_supported(int N, int H, int compute_units);
 size_t lstm_seq_workspace(int N, int H);
 hipError_t lstm_seq_fwd(const void *P, const void *w_hh, float *gates, float *cells, void *h, void *hs, int N, int T, int H,
-                        void *workspace, hipStream_t s);
-hipError_t lstm_seq_bwd(const void *dy, const void *wt_h, const float *gates, const float *cells, void *D, int N, int T, int H,
-                        void *workspace, hipStream_t s);
+                        void *workspace, hipStream_t s, unsigned wait_polls = kLstmWaitPolls);
+hipError_t lstm_seq_bwd(const void *dy, const void *wt_h, const float *gates, const float *cells, float *dcn, void *D, int N, int T, int H,
+                        void *workspace, hipStream_t s, unsigned wait_polls = kLstmWaitPolls);
 
 size_t bn_workspace(int rows, int C);
 // stats: [2][C] floats (mean, invstd)

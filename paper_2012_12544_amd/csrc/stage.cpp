@@ -103,6 +103,7 @@ struct bapipe_stage {
     bapipe_stage_opts_t opts;
     int dt = DT_F32;
     int mb = 0, M = 0, depth = 0;
+    int compute_units = 0;       // of the device (or partition) the stage was created on
     float loss_scale = 0.f;
     hipStream_t stream = nullptr;
     // with a backward stream (bapipe_stage_set_streams) the backward passes run beside the forward passes of
@@ -448,7 +449,7 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
         HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, s));
     else
         HIPCHK(conv_gather_direct(st->dt, x, L.w_work, L.bias, P, 0, none, gx, s));
-    const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, H);
+    const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, H, st->compute_units);
     if (one_launch) HIPCHK(lstm_seq_fwd(P, w_hh, gates, cells, h, hs, N, T, H, st->work, s));
     for (int t = 0; t < T && !one_launch; ++t) {
         int S = 0;
@@ -479,8 +480,8 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     const char *wt_x = (const char *)L.w_t, *wt_h = wt_x + (size_t)G * In * es;
     const bool mf = st->dt == DT_BF16;
     bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
-    const bool one_launch = mf && lstm_seq_supported(N, H);
-    if (one_launch) HIPCHK(lstm_seq_bwd(dy, wt_h, gates, cells, D, N, T, H, st->work, s));
+    const bool one_launch = mf && lstm_seq_supported(N, H, st->compute_units);
+    if (one_launch) HIPCHK(lstm_seq_bwd(dy, wt_h, gates, cells, dcn, D, N, T, H, st->work, s));
     for (int t = T - 1; t >= 0 && !one_launch; --t) {
         int S = 0;
         if (t + 1 < T) {                               // W_h^T D_{t+1}
@@ -950,6 +951,14 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     st->depth = live < n_micro ? live : n_micro;
     st->loss_scale = opts->loss_scale > 0.f ? opts->loss_scale : 1.0f / ((float)micro_batch * (float)n_micro);
     st->loss_valid.assign(n_micro, 0);
+    {
+        int dev = 0;                                             // without a device the allocations below report it
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&st->compute_units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+            (void)hipGetLastError();
+            st->compute_units = 0;
+        }
+    }
     const size_t es = dt_size(st->dt);
 
     // ---- shape inference
@@ -1215,7 +1224,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 v = conv_gather_mfma_workspace(rows_geom(N, T, G, In)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, H, G, 1)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, G, H, 1)); w = v > w ? v : w;
-                v = lstm_seq_workspace(N, H); w = v > w ? v : w;
+                if (lstm_seq_supported(N, H, st->compute_units)) { v = lstm_seq_workspace(N, H); w = v > w ? v : w; }
                 v = conv_wgrad_mfma_workspace(cx); w = v > w ? v : w;
                 v = conv_wgrad_mfma_workspace(ch); w = v > w ? v : w;
             } else {
@@ -1524,8 +1533,9 @@ int bapipe_stage_backward_static(bapipe_stage_t *st, int mb_id, const void *dy_d
                         st->work_bytes, (size_t)BAPIPE_STATIC_SCRATCH_BYTES);
     char *ws = nullptr;
     HIPCHK(static_scratch(&ws));
-    // every kernel of the backward pass writes its partial results before a later kernel of the same pass reads
-    // them (no atomics, nothing accumulates in the workspace), so what the previous call left there needs no clearing
+    // every kernel of the backward pass writes its partial results before a later kernel of the same pass reads them, and
+    // the tickets and flags of an LSTM recurrence are cleared by a kernel in front of it, so what the previous call left
+    // there does not matter
     char *own_f = st->work_f, *own_b = st->work_b;
     hipStream_t own_w = st->stream_w;
     st->work = st->work_f = ws;

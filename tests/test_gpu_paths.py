@@ -1,6 +1,9 @@
 """The sizes at which a kernel with a narrow domain can go wrong: edges of its tiles, remainders, the ends of its range."""
+import ctypes as ct
+
 import numpy as np
 import pytest
+import torch
 
 from gpu_harness import GpuStage, compare_minibatch, gpu_minibatch, stage_io
 from oracle.stage import one_f_one_b_order
@@ -32,6 +35,45 @@ def test_lstm_sequence_kernels_twice_are_bit_identical():
     a, b = gpu_minibatch(st), gpu_minibatch(st)
     for k in a:
         assert np.array_equal(a[k], b[k]), k
+
+
+def _lstm_seq(direction, signature):
+    f = getattr(B.load(), "_ZN6bapipe12lstm_seq_%sE%s" % (direction, signature))
+    f.restype = ct.c_int
+    return f
+
+
+def _lstm_layer(n, t, h, polls):
+    """Both directions of one layer's recurrence on seeded operands: every tensor they write, as integers."""
+    g = torch.Generator("cuda")
+    g.manual_seed(n + t + h)
+    bf16 = dict(device="cuda", dtype=torch.bfloat16)
+    rand = lambda *shape: (torch.rand(shape, device="cuda", generator=g) * 2 - 1).bfloat16()
+    p, dy, w = rand(n, t, 4 * h), rand(n, t, h), rand(4 * h, h) / h ** 0.5
+    wt = w.t().contiguous()
+    gates, cells = torch.empty(n, t, 4 * h, device="cuda"), torch.empty(n, t, h, device="cuda")
+    y, ys, d = torch.empty(n, t, h, **bf16), torch.empty(n, t, h, **bf16), torch.empty(n, t, 4 * h, **bf16)
+    carry = torch.empty(n, h, device="cuda")
+    size = getattr(B.load(), "_ZN6bapipe18lstm_seq_workspaceEii")
+    size.restype, size.argtypes = ct.c_size_t, [ct.c_int] * 2
+    work = torch.empty(size(n, h), device="cuda", dtype=torch.uint8)
+    ptr = lambda x: ct.c_void_p(x.data_ptr())
+    stream = ct.c_void_p(torch.cuda.current_stream().cuda_stream)
+    dims = (ct.c_int(n), ct.c_int(t), ct.c_int(h), ptr(work), stream, ct.c_uint(polls))
+    assert _lstm_seq("fwd", "PKvS1_PfS2_PvS3_iiiS3_P12ihipStream_tj")(ptr(p), ptr(w), ptr(gates), ptr(cells), ptr(y), ptr(ys), *dims) == 0
+    assert _lstm_seq("bwd", "PKvS1_PKfS3_PfPviiiS5_P12ihipStream_tj")(ptr(dy), ptr(wt), ptr(gates), ptr(cells), ptr(carry), ptr(d), *dims) == 0
+    torch.cuda.synchronize()
+    return [x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32).clone() for x in (gates, cells, y, ys, d)]
+
+
+@pytest.mark.parametrize("h,t,n", [(128, 2, 3), (256, 7, 33), (640, 3, 16), (1024, 5, 40)])
+def test_lstm_sequence_kernels_finish_without_their_neighbours(h, t, n):
+    """A block that does not wait, or hardly, leaves its group of sequences to one block that computes it alone: the
+    same bits, whichever step the group was left at."""
+    want = _lstm_layer(n, t, h, 1 << 16)
+    for polls in (0, 1, 8, 64):
+        for a, b in zip(_lstm_layer(n, t, h, polls), want):
+            assert torch.equal(a, b), polls
 
 
 # ------------------------------------------------------------------------------ input gradient of a strided convolution
