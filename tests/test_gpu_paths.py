@@ -93,6 +93,50 @@ def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
     compare_minibatch(st, verbose="strided conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
 
 
+@pytest.mark.parametrize("k,stride,cin,mid,cout,hw,mb", [
+    (1, 2, 72, 72, 64, (15, 13), 3),     # ragged tiles in every class, three of them with gate and sum only
+    (3, 2, 64, 136, 96, (9, 10), 2),
+    (1, 3, 64, 64, 32, (7, 8), 2),
+])
+def test_strided_conv_gradient_behind_a_gate_and_a_sum(k, stride, cin, mid, cout, hw, mb):
+    """The strided layer's input is a ReLU output that a second layer reads too: its gradient is added to and gated, also
+    at the pixels that no tap reaches."""
+    def build(b):
+        t = b.conv(cin, mid, 3, relu=1, src=-1)
+        s = b.conv(mid, cout, k, stride=stride, pad=k // 2, src=t)
+        u = b.conv(mid, cout, 3, stride=stride, pad=1, src=t)
+        b.addl(s, u, relu=0)
+    st = single(build, cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="strided conv k%d s%d %d->%d %s, gate and sum" % (k, stride, mid, cout, hw))
+
+
+def test_strided_conv_gradient_takes_a_residual_share():
+    """A tensor read by a strided 1x1 layer and by an ADD: the ADD's share comes in with the strided gradient."""
+    def build(b):
+        t = b.conv(64, 72, 3, relu=1, src=-1)
+        s = b.conv(72, 64, 1, stride=2, pad=0, src=t)
+        u = b.conv(64, 72, 3, src=-1)
+        a = b.addl(t, u, relu=1)
+        v = b.conv(72, 64, 3, stride=2, pad=1, src=a)
+        b.addl(s, v, relu=0)
+    compare_minibatch(single(build, 64, (11, 14), C.BF16), verbose="strided 1x1 and residual share")
+
+
+@pytest.mark.parametrize("k,cin,c,cout,hw,mb,relu", [
+    (1, 64, 72, 64, (25, 23), 4, 1),     # sums of dy and dy*xhat per class tile, ragged channel tile
+    (1, 64, 128, 32, (48, 45), 2, 1),
+    (3, 64, 64, 64, (29, 27), 3, 1),
+])
+def test_strided_conv_gradient_with_batch_norm_sums(k, cin, c, cout, hw, mb, relu):
+    def build(b):
+        b.conv(cin, c, 1, pad=0, bias=0, src=-1)
+        b.bn(c, relu=relu)
+        b.conv(c, cout, k, stride=2, pad=k // 2)
+    st = single(build, cin, hw, C.BF16, micro_batch=mb)
+    assert mb * hw[0] * hw[1] > 2048             # below that the batch-norm reads its input itself
+    compare_minibatch(st, verbose="batch-norm and strided conv k%d %d->%d %s" % (k, c, cout, hw))
+
+
 # ------------------------------------------------------------------------------ 64-channel K-tiles of the 64-pixel gather tile
 @pytest.mark.parametrize("k,cin,cout,hw,mb", [
     (1, 64, 136, (9, 11), 2),        # one K-tile (an odd count: the second half of the trip is skipped), ragged tiles

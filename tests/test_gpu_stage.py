@@ -493,6 +493,7 @@ def test_loss_of_the_previous_mini_batch_is_not_served_again():
     ("resnet50_stage", C.resnet50_stage(cin=64, mid3=32, mid4=64, hw=24, n3=2, n4=2, micro_batch=4, n_micro=2)),
     ("classifier", C.vgg16_classifier(c=32, hw=3, hidden=136, classes=29, micro_batch=6, n_micro=3)),
     ("lstm", C.gnmt_lstm_stage(hidden=64, seq=9, n_layers=2, micro_batch=5, n_micro=2)),
+    ("lstm, one launch per direction", C.gnmt_lstm_stage(hidden=384, seq=9, n_layers=2, micro_batch=20, n_micro=2)),
     ("tiny fp32", C.tiny_stage()),
 ])
 def test_same_mini_batch_twice_is_bit_identical(name, stage):
@@ -512,6 +513,8 @@ OVERLAP_STAGES = [
     ("resnet50_stage", lambda: C.resnet50_stage(cin=64, mid3=32, mid4=64, hw=24, n3=2, n4=2, micro_batch=4, n_micro=5)),  # depth 3
     ("classifier", lambda: C.vgg16_classifier(c=32, hw=3, hidden=136, classes=29, micro_batch=6, n_micro=3)),       # depth 1
     ("tiny fp32", lambda: C.tiny_stage()),
+    # recurrences of both directions at once, each in one launch whose blocks wait for each other                  depth 3
+    ("lstm, one launch per direction", lambda: C.gnmt_lstm_stage(hidden=256, seq=9, n_layers=2, micro_batch=20, n_micro=4)),
 ]
 
 

@@ -16,12 +16,14 @@ pytestmark = pytest.mark.gpu
 
 STAGES = [
     # bottleneck blocks at 24x24: split weight-gradient partials, batch-norm statistics and backward sums handed
-    # over through the workspace (above 2048 rows), the dense product of the strided 1x1 input gradient
+    # over through the workspace (above 2048 rows)
     ("resnet blocks 24x24", lambda: C.resnet50_stage(cin=64, mid3=32, mid4=64, hw=24, n3=2, n4=2, micro_batch=4, n_micro=3)),
     # the same layers on a quarter of the pixels and fewer samples
     ("resnet blocks 12x12", lambda: C.resnet50_stage(cin=64, mid3=32, mid4=64, hw=12, n3=2, n4=2, micro_batch=3, n_micro=2)),
     ("vgg stage 1, 32x32", lambda: C.vgg16_stage1(c1=64, c2=128, hw=32, micro_batch=2, n_micro=3)),
     ("classifier", lambda: C.vgg16_classifier(c=16, hw=3, hidden=72, classes=13, micro_batch=5, n_micro=3)),
+    # tickets, flags and slices of the recurrences in the workspace, after whatever the stages above left there
+    ("lstm", lambda: C.gnmt_lstm_stage(hidden=256, seq=7, n_layers=2, micro_batch=20, n_micro=2)),
     ("tiny fp32", lambda: C.tiny_stage(c=8, hw=12, micro_batch=2, n_micro=2)),
 ]
 
