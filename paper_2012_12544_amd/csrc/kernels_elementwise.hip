@@ -265,22 +265,32 @@ __global__ void k_avgpool_fwd(const T *__restrict__ x, T *__restrict__ y, PoolWi
 #pragma unroll
     for (int j = 0; j < V; ++j) acc[j] = 0.0f;
     // few threads, each with a long chain of loads (a 7x7 window of 2048 channels and 32 samples is 8192 threads): eight
-    // positions are requested at a time, 18 -> 12 us there
-    constexpr int AHEAD = 8;
-    const int positions = g.kh * g.kw;
-    for (int i0 = 0; i0 < positions; i0 += AHEAD) {
-        vec_t<T, V> a[AHEAD];
+    // positions are requested at a time, then four, then one: 10.9 us there one by one, 8.9 in batches of eight that were
+    // filled up with the last position, 4.6 so (fp32: 8.5, 8.5, 3.9).  Filling up cost where windows are small (2x2, 64
+    // channels, 16 images of 112x112: 6.3, 6.7, 4.8 us).
+    const vec_t<T, V> *at = xv + (((size_t)n * g.H + p * g.kh) * g.W + q * g.kw) * g.CV + cv;
+    int left = g.kh * g.kw, column = 0;
+    auto take = [&](auto count) {
+        constexpr int B = decltype(count)::value;
+        vec_t<T, V> a[B];
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const int k = i0 + u < positions ? i0 + u : positions - 1;
-            a[u] = xv[(((size_t)n * g.H + p * g.kh + k / g.kw) * g.W + q * g.kw + k % g.kw) * g.CV + cv];
+        for (int u = 0; u < B; ++u) {
+            a[u] = *at;
+            at += g.CV;
+            if (++column == g.kw) {
+                column = 0;
+                at += (size_t)(g.W - g.kw) * g.CV;
+            }
         }
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u)
-            if (i0 + u < positions)
+        for (int u = 0; u < B; ++u)
 #pragma unroll
-                for (int j = 0; j < V; ++j) acc[j] += to_f32(a[u].e[j]);
-    }
+            for (int j = 0; j < V; ++j) acc[j] += to_f32(a[u].e[j]);
+        left -= B;
+    };
+    while (left >= 8) take(std::integral_constant<int, 8>());
+    if (left >= 4) take(std::integral_constant<int, 4>());
+    while (left > 0) take(std::integral_constant<int, 1>());
     const float cnt = (float)(g.kh * g.kw);
     vec_t<T, V> r;
 #pragma unroll

@@ -161,6 +161,14 @@ def test_direct_conv(k, stride, pad, cin, cout, hw, mb):
     compare_minibatch(st, verbose="direct conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
 
 
+# ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("k,c,hw", [(1, 8, (3, 4)), (2, 24, (7, 4)), (3, 5, (10, 9)), (5, 16, (5, 11)), (6, 8, (13, 6))])
+def test_avgpool_windows(dtype, k, c, hw):
+    st = single(lambda b: b.avgpool(k, src=-1), c, hw, dtype)
+    compare_minibatch(st, verbose="avgpool %d of %s" % (k, hw))
+
+
 # ------------------------------------------------------------------------------ weight gradient: steps of 32 pixels through small images
 @pytest.mark.parametrize("k,stride,cin,cout,hw,mb", [
     (3, 1, 64, 72, (2, 3), 23),          # 32 pixels are five images and two pixels
