@@ -155,10 +155,23 @@ def test_conv_wide_k_tiles(k, cin, cout, hw, mb):
     (3, 2, 2, 4, 8, (8, 7), 2),          # fewer channels than a trip, two columns of padding
     (1, 3, 0, 36, 5, (10, 10), 2),       # gradient operand with an odd channel count: one channel at a time
     (5, 3, 1, 16, 16, (7, 19), 1),       # columns at the right edge that no output reads
+    (3, 2, 1, 7, 6, (9, 8), 2),          # three and two channels left of a group, two classes of taps a side
+    (5, 3, 2, 9, 13, (16, 14), 2),       # one channel left
+    (2, 5, 1, 20, 28, (13, 12), 2),      # stride beyond the filter: pixels that no tap reaches
+    (4, 2, 3, 24, 8, (7, 6), 3),         # padding: taps before the first row
 ])
 def test_direct_conv(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.FP32, micro_batch=mb)
     compare_minibatch(st, verbose="direct conv k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
+
+
+@pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
+    (3, 2, 1, 9, 22, (9, 8), 2),
+    (5, 3, 2, 30, 13, (16, 14), 2),
+])
+def test_direct_conv_bf16(k, stride, pad, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="direct conv bf16 k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
 
 
 # ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
