@@ -95,9 +95,9 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     const int sd = PHASED ? g.s_in : 1;
     int pa = 0, pb = 0, r0 = 0, q0 = 0, Rn = g.R, Sn = g.S, Hp = g.Ho, Wp = g.Wo;
     if (PHASED) {
-        const int zc = (int)blockIdx.z;
-        pa = (zc / sd + g.pad_h) % sd;               // class 0: the pixels that tap (0, 0) reaches
-        pb = (zc % sd + g.pad_w) % sd;
+        const int zc = (int)blockIdx.z, ch = sd < g.Ho ? sd : g.Ho, cw = sd < g.Wo ? sd : g.Wo;      // remainders that occur
+        pa = (zc / cw + g.pad_h) % ch;               // class 0 (stride up to the image): the pixels that tap (0, 0) reaches
+        pb = (zc % cw + g.pad_w) % cw;
         r0 = (g.pad_h % sd - pa + sd) % sd;
         q0 = (g.pad_w % sd - pb + sd) % sd;
         Rn = r0 < g.R ? (g.R - r0 + sd - 1) / sd : 0;
@@ -556,17 +556,26 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 
 struct GatherPlan {
     int bp, bc, bk, splits, kt_per_split;
-    int classes;             // 1, or s_in^2: a PHASED launch
+    int classes;             // 1, or the classes of a PHASED launch
     int busy;                // classes that have taps
     long long class_pix;     // output pixels of the largest class
 };
 
+// output pixels of the largest class
+long long class_pixels(const GatherConv &g) { return (long long)g.N * ((g.Ho + g.s_in - 1) / g.s_in) * ((g.Wo + g.s_in - 1) / g.s_in); }
+
 // The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask.  Of a 1x1 filter's classes one has
 // the tap and the others only their epilogue (a projection shortcut's gradient, 56x56 of 256 channels, 32 samples: 27 us,
 // as a dense product into the workspace and a pass that spread it 16 + 23).
-bool gather_phased(const GatherConv &g)
+// A class is a step of the grid's z axis (65536 at most): s_in^2 of them, fewer where the image is smaller than the stride.
+// More of them than the chip holds blocks have to fill a quarter of a tile each, or their epilogues take longer than the
+// products with zeros (backward of 1x1 / 100, 64 channels, one 100x100 image: 67 us as 10000 classes, 13 without; 1x1 / 20:
+// 9.0 us as 400 classes, 13.4 without).
+int gather_classes(const GatherConv &g)
 {
-    return g.s_in > 1 && g.s_out == 1 && g.Ci % 32 == 0 && g.R * g.S <= 32 && g.pad_h >= 0 && g.pad_w >= 0;
+    if (g.s_in == 1 || g.s_out != 1 || g.Ci % 32 != 0 || g.R * g.S > 32 || g.pad_h < 0 || g.pad_w < 0) return 1;
+    const long long n = (long long)(g.s_in < g.Ho ? g.s_in : g.Ho) * (g.s_in < g.Wo ? g.s_in : g.Wo);
+    return n <= 1024 || (n <= 65535 && class_pixels(g) >= 16) ? (int)n : 1;
 }
 
 // Tile shape and split-K factor.  K is split only when there are very few output tiles (the linear
@@ -575,9 +584,10 @@ GatherPlan gather_plan(const GatherConv &g)
 {
     GatherPlan p;
     const long long npix = (long long)g.N * g.Ho * g.Wo;
-    p.classes = gather_phased(g) ? g.s_in * g.s_in : 1;
-    p.busy = p.classes == 1 ? 1 : (g.R < g.s_in ? g.R : g.s_in) * (g.S < g.s_in ? g.S : g.s_in);
-    p.class_pix = p.classes == 1 ? npix : (long long)g.N * ((g.Ho + g.s_in - 1) / g.s_in) * ((g.Wo + g.s_in - 1) / g.s_in);
+    p.classes = gather_classes(g);
+    p.busy = (g.R < g.s_in ? g.R : g.s_in) * (g.S < g.s_in ? g.S : g.s_in);
+    if (p.busy > p.classes) p.busy = p.classes;
+    p.class_pix = p.classes == 1 ? npix : class_pixels(g);
     p.bp = p.class_pix <= 64 ? 64 : 256;
     p.bc = g.Co <= 64 ? 64 : 128;
     if (p.bp == 64) p.bc = 128;

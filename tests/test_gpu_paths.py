@@ -87,6 +87,11 @@ def test_lstm_sequence_kernels_finish_without_their_neighbours(h, t, n):
     (3, 2, 1, 128, 128, (56, 56), 3),    # many tiles
     (1, 2, 0, 72, 64, (15, 15), 2),      # 1x1: one class with a tap, three with their epilogue only
     (1, 3, 0, 136, 32, (7, 8), 2),
+    (2, 5, 1, 64, 32, (3, 4), 2),        # stride beyond the image: fewer classes than stride^2
+    (3, 300, 1, 16, 32, (7, 9), 2),
+    (1, 300, 0, 8, 32, (301, 301), 1),   # more classes than a grid axis holds
+    (1, 40, 0, 16, 32, (41, 83), 2),     # 1600 classes of 12 pixels: taken together
+    (3, 40, 1, 16, 32, (41, 83), 3),     # ... of 18: apart
 ])
 def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
