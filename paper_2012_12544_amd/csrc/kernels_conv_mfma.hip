@@ -46,7 +46,8 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // its own position modulo the stride, so the output is taken apart into the s_in^2 grids of pixels with equal remainders;
 // on each the product is an ordinary stride-1 one with the taps of that class (for 3x3 / 2: 4, 2, 2 and 1 of the 9).
 // blockIdx.z is the class, the one with most taps first.  Without it three quarters of the multiply-adds meet a zero:
-// 3x3 / 2, 512 channels, 14x14 from 7x7, 32 samples: 104 -> 30 us; 128 channels, 56x56 from 28x28: 84 -> 44 us.
+// 3x3 / 2, 512 channels, 14x14 from 7x7, 32 samples: 104 -> 30 us; 128 channels, 56x56 from 28x28: 84 -> 44 us.  With the
+// taps not innermost only for 1x1 filters, whose K is the channels of the one tap either way.
 template <int BP, int BC, int WP, int WC, int BK, int STAGES, bool S1, bool TAPS_INNER, bool PHASED = false>
 __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
@@ -106,18 +107,19 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         Wp = (g.Wo - pb + sd - 1) / sd;
     }
     const int rows = g.N * Hp * Wp;                  // output pixels of the class
-    const int KT = TAPS_INNER ? (g.Ci / BK) * Rn * Sn : (K + BK - 1) / BK;
+    const int KT = TAPS_INNER ? (g.Ci / BK) * Rn * Sn : (Rn * Sn * g.Ci + BK - 1) / BK;
     constexpr unsigned OOB = 0x80000000u;
 
     __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(in), 0, (int)in_bytes, 0x00020000);
     __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wt), 0, (int)wt_bytes, 0x00020000);
 
     // ---- per-lane gather state: the pixel rows this lane fetches (row = (i*NW + wave)*RPW + lrow)
-    // FAST (stride 1, taps innermost, at most 32 taps): everything that depends on the lane is
+    // FAST (taps innermost, at most 32 of them; stride 1): everything that depends on the lane is
     // computed once - the byte offset of the lane's chunk at tap (0,0) and a bit mask of the taps
     // that fall inside the image - so that a K-tile costs one scalar offset, one mask test and one
     // add per load.
-    constexpr bool FAST = S1 && TAPS_INNER;
+    constexpr bool FAST = TAPS_INNER;
+    static_assert(!TAPS_INNER || S1, "a strided operand takes its taps in the flattened order");
     int hb[XL], wb[XL];
     unsigned xoff[XL];                       // generic: byte offset of pixel (n, 0, 0), channel 0; FAST: see above
     unsigned tapmask[XL];
@@ -161,13 +163,13 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     const int kt1 = part ? (kt0 + kt_per_split < KT ? kt0 + kt_per_split : KT) : KT;
     int kk = kt0 * BK + 8 * lc;                        // flattened k of this lane's chunk (generic order)
     int kr = kk / (g.S * g.Ci), ks = (kk / g.Ci) % g.S, kc = kk % g.Ci;
+    if (PHASED && KT == 0) kr = g.R;                   // a class without taps reads nothing
     int cb = 0;                                        // FAST: first channel of the tile (wave-uniform)
     if (TAPS_INNER) {
         const int tap = PHASED ? 0 : kt0 % (g.R * g.S);            // PHASED launches do not split K
         kr = tap / g.S;
         ks = tap % g.S;
         cb = PHASED ? (KT ? 0 : g.Ci) : (kt0 / (g.R * g.S)) * BK;  // a class without taps reads nothing
-        kc = cb + 8 * lc;                              // channel offset; tap = (kr, ks)
     }
 
     auto issue_tile = [&](int stage) {
@@ -191,8 +193,8 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             }
             return;                                   // the caller advances (kr, ks, cb) after its MFMAs
         }
-        const bool kin = TAPS_INNER ? (kc < g.Ci) : (kr < g.R);
-        const unsigned koff = (unsigned)(TAPS_INNER ? (kr * g.S + ks) * g.Ci + kc : kk) * 2u;
+        const bool kin = kr < g.R;
+        const unsigned koff = (unsigned)kk * 2u;
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
             int hn = hb[i] + kr, wn = wb[i] + ks;
@@ -216,23 +218,13 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             dma16(wrsrc, lds_of(sw + (i * NW + wave) * RPW * BK), vo);
         }
         // advance to the next K-tile
-        if (TAPS_INNER) {
+        kk += BK;
+        kc += BK;
+        while (kc >= g.Ci) {
+            kc -= g.Ci;
             if (++ks == g.S) {
                 ks = 0;
-                if (++kr == g.R) {
-                    kr = 0;
-                    kc += BK;
-                }
-            }
-        } else {
-            kk += BK;
-            kc += BK;
-            while (kc >= g.Ci) {
-                kc -= g.Ci;
-                if (++ks == g.S) {
-                    ks = 0;
-                    ++kr;
-                }
+                ++kr;
             }
         }
     };
@@ -564,16 +556,17 @@ struct GatherPlan {
 // output pixels of the largest class
 long long class_pixels(const GatherConv &g) { return (long long)g.N * ((g.Ho + g.s_in - 1) / g.s_in) * ((g.Wo + g.s_in - 1) / g.s_in); }
 
-// The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask.  Of a 1x1 filter's classes one has
-// the tap and the others only their epilogue (a projection shortcut's gradient, 56x56 of 256 channels, 32 samples: 27 us,
-// as a dense product into the workspace and a pass that spread it 16 + 23).
+// The taps-innermost order of K needs whole K-tiles of channels and a 32-bit tap mask; for a 1x1 filter there is one tap and
+// any K will do.  Of its classes one has the tap and the others only their epilogue (a projection shortcut's gradient, 56x56
+// of 256 channels, 32 samples: 27 us, as a dense product into the workspace and a pass that spread it 16 + 23).
 // A class is a step of the grid's z axis (65536 at most): s_in^2 of them, fewer where the image is smaller than the stride.
 // More of them than the chip holds blocks have to fill a quarter of a tile each, or their epilogues take longer than the
 // products with zeros (backward of 1x1 / 100, 64 channels, one 100x100 image: 67 us as 10000 classes, 13 without; 1x1 / 20:
 // 9.0 us as 400 classes, 13.4 without).
 int gather_classes(const GatherConv &g)
 {
-    if (g.s_in == 1 || g.s_out != 1 || g.Ci % 32 != 0 || g.R * g.S > 32 || g.pad_h < 0 || g.pad_w < 0) return 1;
+    if (g.s_in == 1 || g.s_out != 1 || g.pad_h < 0 || g.pad_w < 0) return 1;
+    if (!(g.R == 1 && g.S == 1) && (g.Ci % 32 != 0 || g.R * g.S > 32)) return 1;
     const long long n = (long long)(g.s_in < g.Ho ? g.s_in : g.Ho) * (g.s_in < g.Wo ? g.s_in : g.Wo);
     return n <= 1024 || (n <= 65535 && class_pixels(g) >= 16) ? (int)n : 1;
 }
@@ -667,13 +660,13 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         if (phased) GATHER_LAUNCH(true, true, true);
         else GATHER_LAUNCH(true, true, false);
     } else if (phased) {
-        GATHER_LAUNCH(true, true, true);
+        if (taps_inner) GATHER_LAUNCH(true, true, true);
+        else GATHER_LAUNCH(true, false, true);
     } else if (g.s_in == 1) {
         if (taps_inner) GATHER_LAUNCH(true, true, false);
         else GATHER_LAUNCH(true, false, false);
     } else {
-        if (taps_inner) GATHER_LAUNCH(false, true, false);
-        else GATHER_LAUNCH(false, false, false);
+        GATHER_LAUNCH(false, false, false);
     }
 #undef GATHER_LAUNCH
     if (part && !raw) {

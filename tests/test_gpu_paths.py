@@ -87,6 +87,9 @@ def test_lstm_sequence_kernels_finish_without_their_neighbours(h, t, n):
     (3, 2, 1, 128, 128, (56, 56), 3),    # many tiles
     (1, 2, 0, 72, 64, (15, 15), 2),      # 1x1: one class with a tap, three with their epilogue only
     (1, 3, 0, 136, 32, (7, 8), 2),
+    (1, 2, 0, 64, 40, (15, 14), 3),      # 1x1 with a ragged K-tile of channels: 32 + 8
+    (1, 2, 0, 136, 8, (9, 9), 2),        # ... of 8 alone
+    (1, 3, 0, 256, 520, (20, 22), 5),    # ... 16 whole ones and 8, many tiles
     (2, 5, 1, 64, 32, (3, 4), 2),        # stride beyond the image: fewer classes than stride^2
     (3, 300, 1, 16, 32, (7, 9), 2),
     (1, 300, 0, 8, 32, (301, 301), 1),   # more classes than a grid axis holds
@@ -102,6 +105,7 @@ def test_strided_conv_gradient(k, stride, pad, cin, cout, hw, mb):
     (1, 2, 72, 72, 64, (15, 13), 3),     # ragged tiles in every class, three of them with gate and sum only
     (3, 2, 64, 136, 96, (9, 10), 2),
     (1, 3, 64, 64, 32, (7, 8), 2),
+    (1, 2, 64, 72, 40, (15, 13), 3),     # a ragged K-tile of channels
 ])
 def test_strided_conv_gradient_behind_a_gate_and_a_sum(k, stride, cin, mid, cout, hw, mb):
     """The strided layer's input is a ReLU output that a second layer reads too: its gradient is added to and gated, also
@@ -131,6 +135,7 @@ def test_strided_conv_gradient_takes_a_residual_share():
     (1, 64, 72, 64, (25, 23), 4, 1),     # sums of dy and dy*xhat per class tile, ragged channel tile
     (1, 64, 128, 32, (48, 45), 2, 1),
     (3, 64, 64, 64, (29, 27), 3, 1),
+    (1, 64, 72, 24, (25, 23), 4, 1),
 ])
 def test_strided_conv_gradient_with_batch_norm_sums(k, cin, c, cout, hw, mb, relu):
     def build(b):
