@@ -139,34 +139,41 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
     part[(size_t)blockIdx.y * total + i] = acc;
 }
 
-// dw[i] += sum_chunk part[chunk][i].  A block owns 16 elements; 16 lanes per element walk the chunks, and their sums are
-// added in lane order: a fixed order (bit-reproducible), and chains of chunks / 16 loads instead of chunks (128 chunks of
-// 2304 elements: 30 -> 2.7 us).
-constexpr int RED_EL = 16, RED_LANES = TPB / RED_EL;
-__global__ void k_wgrad_reduce(const float *__restrict__ part, float *dw, size_t total, int chunks)
+// dw[i] += sum_chunk part[chunk][i].  LANES threads per element walk the chunks, eight loads requested at once, and their
+// sums are added in lane order: a fixed order (bit-reproducible), and chains of chunks / LANES loads (128 chunks of 2304
+// elements: 30 us with one lane, 2.7 with 16).  Up to 16 chunks, of which there are that few where the elements alone fill
+// the chip, one lane takes them all, for lanes without a chunk are not free (backward pass of a 4096 -> 4096 linear layer,
+// one chunk, 3674 -> 3224 us).
+constexpr int RED_LANES = 16;
+template <int LANES> __global__ void k_wgrad_reduce(const float *__restrict__ part, float *dw, size_t total, int chunks)
 {
-    __shared__ float red[RED_LANES][RED_EL];
-    const int el = threadIdx.x % RED_EL, ln = threadIdx.x / RED_EL;
-    const size_t i = (size_t)blockIdx.x * RED_EL + el;
+    constexpr int EL = TPB / LANES;
+    const int el = threadIdx.x % EL, ln = threadIdx.x / EL;
+    const size_t i = (size_t)blockIdx.x * EL + el;
     float acc = 0.0f;
     if (i < total)
-        for (int k = ln; k < chunks; k += 8 * RED_LANES) {
+        for (int k = ln; k < chunks; k += 8 * LANES) {
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int kk = k + u * RED_LANES;
+                const int kk = k + u * LANES;
                 v[u] = kk < chunks ? part[(size_t)kk * total + i] : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc += v[u];
         }
-    red[ln][el] = acc;
-    __syncthreads();
-    if (ln == 0 && i < total) {
-        float t = 0.0f;
+    if constexpr (LANES == 1) {
+        if (i < total) dw[i] += acc;
+    } else {
+        __shared__ float red[LANES][EL];
+        red[ln][el] = acc;
+        __syncthreads();
+        if (ln == 0 && i < total) {
+            float t = 0.0f;
 #pragma unroll
-        for (int l = 0; l < RED_LANES; ++l) t += red[l][el];
-        dw[i] += t;
+            for (int l = 0; l < LANES; ++l) t += red[l][el];
+            dw[i] += t;
+        }
     }
 }
 
@@ -222,7 +229,12 @@ hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, v
     else
         hipLaunchKernelGGL((k_conv_wgrad_partial<bf16_t>), dim3(nb, chunks), dim3(TPB), 0, s,
                            (const bf16_t *)x, (const bf16_t *)dy, part, c, rpc);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((total + RED_EL - 1) / RED_EL)), dim3(TPB), 0, s, part, dw, total, chunks);
+    if (chunks <= RED_LANES) {
+        hipLaunchKernelGGL(k_wgrad_reduce<1>, dim3(nb), dim3(TPB), 0, s, part, dw, total, chunks);
+    } else {                                                       // a million elements at most
+        constexpr int EL = TPB / RED_LANES;
+        hipLaunchKernelGGL(k_wgrad_reduce<RED_LANES>, dim3((unsigned)((total + EL - 1) / EL)), dim3(TPB), 0, s, part, dw, total, chunks);
+    }
     return hipGetLastError();
 }
 

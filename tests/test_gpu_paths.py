@@ -184,6 +184,26 @@ def test_direct_conv_bf16(k, stride, pad, cin, cout, hw, mb):
     compare_minibatch(st, verbose="direct conv bf16 k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
 
 
+@pytest.mark.parametrize("cin,cout,mb", [
+    (16384, 16384, 1),      # 2^28 weights: more threads than a grid holds if several share one of them
+])
+def test_gradients_of_the_largest_linear_layers(cin, cout, mb):
+    """One or two samples: the sums are single products, and sums of two floats, which have one rounding."""
+    st = single(lambda b: b.linear(cin, cout, src=-1), cin, (1, 1), C.FP32, micro_batch=mb, n_micro=1, need_input_grad=0)
+    g = GpuStage(st, [(None, None)])
+    rng = np.random.default_rng(cin)
+    x = rng.standard_normal((mb, cin, 1, 1), dtype=np.float32)
+    dy = rng.standard_normal((mb, cout, 1, 1), dtype=np.float32)
+    g.forward(0, x)
+    g.backward(0, dy)
+    dw, db = B.bapipe_stage_get_grads(g.h, 0, (cout, cin), (cout,))
+    g.close()
+    dy = dy.reshape(mb, cout)
+    assert np.array_equal(db, dy.sum(axis=0, dtype=np.float64).astype(np.float32))
+    for k in range(0, cout, 997):              # terms below 16: two roundings of 2^-21 at most
+        assert np.allclose(dw[k], dy[:, k].astype(np.float64) @ x.reshape(mb, cin), rtol=0, atol=2.0 ** -20)
+
+
 # ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("k,c,hw", [(1, 8, (3, 4)), (2, 24, (7, 4)), (3, 5, (10, 9)), (5, 16, (5, 11)), (6, 8, (13, 6))])
