@@ -425,30 +425,33 @@ __global__ void k_colsum_partial(const T *__restrict__ a, int rows, int C, ColPl
     col_partial_body<T, V, 1>(f, rows, p, part, C);
 }
 
-// Final pass over the per-chunk partials: a block of 16 waves owns 4 channels, 256 lanes per channel walk the chunks,
-// eight of them requested at once, and the lanes are combined by wave butterflies and then wave by wave through LDS: a
-// fixed order, so the result does not depend on scheduling.  Returns true in the lane that holds the totals.  These
-// launches are a chain of latencies (a megabyte or so of partials, no arithmetic): the trips per lane and the length of
-// the last serial sum are what they take.  64 lanes per channel and a serial sum over all of them took 15.6 us for 1568
-// chunks of 256 channels and 11 us for 128 channels, against 7.4 and 6.0 now.  Neighbouring groups of four
-// channels share cache lines of the partials, so they are numbered to run on one XCD.
-constexpr int FIN_CH = 4, FIN_TPB = 1024, FIN_LANES = FIN_TPB / FIN_CH, FIN_AHEAD = 8;
-template <int NQ>
+// Final pass over the per-chunk partials: a block owns 4 channels, its lanes (256 per channel, 64 where there are no more
+// chunks) walk the chunks, eight of them requested at once, and are combined by wave butterflies and then wave by wave
+// through LDS: a fixed order, so the result does not depend on scheduling.  Returns true in the lane that holds the totals.
+// These launches are a chain of latencies (a megabyte or so of partials, no arithmetic): the trips per lane and the length
+// of the last serial sum are what they take.  64 lanes per channel and a serial sum over all of them took 15.6 us for 1568
+// chunks of 256 channels and 11 us for 128 channels, against 7.4 and 6.0 now.  Wide tensors have few chunks and many blocks,
+// and waves without a chunk cost them (batch-norm of 2560 rows of 16384 floats, all passes: forward 91.7 us with 256 lanes
+// per channel, 81.3 with 64; backward 171 and 158).  Neighbouring groups of four channels share cache lines of the partials,
+// so they are numbered to run on one XCD.
+constexpr int FIN_CH = 4, FIN_AHEAD = 8;
+template <int NQ, int NT>
 __device__ __forceinline__ bool col_final_sums(const float *__restrict__ part, int chunks, int C, int &c,
                                                double (&tot)[NQ])
 {
-    __shared__ double red[FIN_TPB / 64][NQ][FIN_CH];
+    constexpr int LANES = NT / FIN_CH, WAVES = NT / 64;
+    __shared__ double red[WAVES][NQ][FIN_CH];
     const int cc = threadIdx.x % FIN_CH, cl = threadIdx.x / FIN_CH;
     c = xcd_remap(blockIdx.x, gridDim.x) * FIN_CH + cc;
     double s[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) s[q] = 0.0;
     if (c < C)
-        for (int k = cl; k < chunks; k += FIN_AHEAD * FIN_LANES) {
+        for (int k = cl; k < chunks; k += FIN_AHEAD * LANES) {
             float v[FIN_AHEAD][NQ];
 #pragma unroll
             for (int u = 0; u < FIN_AHEAD; ++u) {
-                const int kk = k + u * FIN_LANES;
+                const int kk = k + u * LANES;
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) v[u][q] = kk < chunks ? part[((size_t)q * chunks + kk) * C + c] : 0.0f;
             }
@@ -469,19 +472,28 @@ __device__ __forceinline__ bool col_final_sums(const float *__restrict__ part, i
     for (int q = 0; q < NQ; ++q) {
         double t = 0.0;
 #pragma unroll
-        for (int k = 0; k < FIN_TPB / 64; ++k) t += red[k][q][cc];
+        for (int k = 0; k < WAVES; ++k) t += red[k][q][cc];
         tot[q] = t;
     }
     return true;
 }
 
+#define LAUNCH_FINAL(kernel, chunks, C, s, ...)                                                              \
+    do {                                                                                                     \
+        if ((chunks) > 64)                                                                                   \
+            hipLaunchKernelGGL((kernel<1024>), dim3(final_blocks(C)), dim3(1024), 0, s, __VA_ARGS__);        \
+        else                                                                                                 \
+            hipLaunchKernelGGL((kernel<256>), dim3(final_blocks(C)), dim3(256), 0, s, __VA_ARGS__);          \
+    } while (0)
+
 inline unsigned final_blocks(int C) { return (unsigned)((C + FIN_CH - 1) / FIN_CH); }
 
-__global__ __launch_bounds__(FIN_TPB) void k_colsum_final(const float *__restrict__ part, int chunks, int C, float *out)
+template <int NT>
+__global__ __launch_bounds__(NT) void k_colsum_final(const float *__restrict__ part, int chunks, int C, float *out)
 {
     int c;
     double t[1];
-    if (col_final_sums<1>(part, chunks, C, c, t)) out[c] += (float)t[0];
+    if (col_final_sums<1, NT>(part, chunks, C, c, t)) out[c] += (float)t[0];
 }
 
 // ------------------------------------------------------------------ batch-norm
@@ -501,12 +513,13 @@ __global__ void k_bn_stat_partial(const T *__restrict__ x, int rows, int C, ColP
     col_partial_body<T, V, 2>(f, rows, p, part, C);
 }
 
-__global__ __launch_bounds__(FIN_TPB) void k_bn_stat_final(const float *__restrict__ part, int chunks, int C, int rows, float eps,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bn_stat_final(const float *__restrict__ part, int chunks, int C, int rows, float eps,
                                 float *stats)
 {
     int c;
     double t[2];
-    if (!col_final_sums<2>(part, chunks, C, c, t)) return;
+    if (!col_final_sums<2, NT>(part, chunks, C, c, t)) return;
     double m = (double)rows, mu = t[0] / m, var = t[1] / m - mu * mu;
     if (var < 0.0) var = 0.0;
     stats[c] = (float)mu;
@@ -600,12 +613,13 @@ __global__ void k_bn_bwd_partial(const T *__restrict__ x, const T *__restrict__ 
 }
 
 // sums[c] = (sum dy, sum dy*xhat) of this micro-batch; dbeta/dgamma accumulate over micro-batches
-__global__ __launch_bounds__(FIN_TPB) void k_bn_bwd_final(const float *__restrict__ part, int chunks, int C, float *sums,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bn_bwd_final(const float *__restrict__ part, int chunks, int C, float *sums,
                                float *dgamma, float *dbeta)
 {
     int c;
     double t[2];
-    if (!col_final_sums<2>(part, chunks, C, c, t)) return;
+    if (!col_final_sums<2, NT>(part, chunks, C, c, t)) return;
     sums[c] = (float)t[0];
     sums[C + c] = (float)t[1];
     dbeta[c] += (float)t[0];
@@ -1396,7 +1410,7 @@ hipError_t colsum_accumulate(int dt, const void *a, int rows, int C, float *out,
         ColPlan p = col_plan(rows, C, V);
         hipLaunchKernelGGL((k_colsum_partial<T, V>), dim3(p.gx, p.chunks), dim3(TPB), 0, s, (const T *)a, rows,
                            C, p, part);
-        hipLaunchKernelGGL(k_colsum_final, dim3(final_blocks(C)), dim3(FIN_TPB), 0, s, part, p.chunks, C, out);
+        LAUNCH_FINAL(k_colsum_final, p.chunks, C, s, part, p.chunks, C, out);
     });
     return hipGetLastError();
 }
@@ -1426,7 +1440,7 @@ hipError_t bn_fwd(int dt, const void *x, const float *gamma, const float *beta, 
     int Vsel = col_vec(dt, C, x, y, res);
     float *part = (float *)workspace;
     if (pre_chunks > 0) {                 // statistics partials came with x: final pass and normalisation only
-        hipLaunchKernelGGL(k_bn_stat_final, dim3(final_blocks(C)), dim3(FIN_TPB), 0, s, part, pre_chunks, C, rows, eps, stats);
+        LAUNCH_FINAL(k_bn_stat_final, pre_chunks, C, s, part, pre_chunks, C, rows, eps, stats);
         DISPATCH_TV(dt, Vsel > 1, {
             ColPlan p = col_plan(rows, C, V);
             const int rpb = p.RY * BN_ROWS_PER_THREAD;
@@ -1444,7 +1458,7 @@ hipError_t bn_fwd(int dt, const void *x, const float *gamma, const float *beta, 
         ColPlan p = col_plan(rows, C, V);
         hipLaunchKernelGGL((k_bn_stat_partial<T, V>), dim3(p.gx, p.chunks), dim3(TPB), 0, s, (const T *)x,
                            rows, C, p, part);
-        hipLaunchKernelGGL(k_bn_stat_final, dim3(final_blocks(C)), dim3(FIN_TPB), 0, s, part, p.chunks, C, rows,
+        LAUNCH_FINAL(k_bn_stat_final, p.chunks, C, s, part, p.chunks, C, rows,
                            eps, stats);
         const int rpb = p.RY * BN_ROWS_PER_THREAD;
         hipLaunchKernelGGL((k_bn_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s, (const T *)x,
@@ -1463,7 +1477,7 @@ hipError_t bn_bwd(int dt, const void *x, const void *dy, const float *gamma, con
     float *part = (float *)workspace;
     if (pre_chunks > 0) {                 // the sums over dy came with dy: final pass and the dx pass only
         float *sums = part + (size_t)2 * pre_chunks * C;
-        hipLaunchKernelGGL(k_bn_bwd_final, dim3(final_blocks(C)), dim3(FIN_TPB), 0, s, part, pre_chunks, C, sums, dgamma, dbeta);
+        LAUNCH_FINAL(k_bn_bwd_final, pre_chunks, C, s, part, pre_chunks, C, sums, dgamma, dbeta);
         if (dx) {
             DISPATCH_TV(dt, Vsel > 1, {
                 ColPlan p = col_plan(rows, C, V);
@@ -1485,7 +1499,7 @@ hipError_t bn_bwd(int dt, const void *x, const void *dy, const float *gamma, con
         float *sums = part + (size_t)2 * p.chunks * C;
         hipLaunchKernelGGL((k_bn_bwd_partial<T, V>), dim3(p.gx, p.chunks), dim3(TPB), 0, s, (const T *)x,
                            (const T *)dy, stats, rows, C, p, part);
-        hipLaunchKernelGGL(k_bn_bwd_final, dim3(final_blocks(C)), dim3(FIN_TPB), 0, s, part, p.chunks, C, sums,
+        LAUNCH_FINAL(k_bn_bwd_final, p.chunks, C, s, part, p.chunks, C, sums,
                            dgamma, dbeta);
         if (dx) {
             const int rpb = p.RY * BN_ROWS_PER_THREAD;

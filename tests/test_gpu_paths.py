@@ -186,6 +186,7 @@ def test_direct_conv_bf16(k, stride, pad, cin, cout, hw, mb):
 
 @pytest.mark.parametrize("cin,cout,mb", [
     (16384, 16384, 1),      # 2^28 weights: more threads than a grid holds if several share one of them
+    (1, 1 << 24, 2),        # 2^24 bias gradients: the same for the column sums
 ])
 def test_gradients_of_the_largest_linear_layers(cin, cout, mb):
     """One or two samples: the sums are single products, and sums of two floats, which have one rounding."""
