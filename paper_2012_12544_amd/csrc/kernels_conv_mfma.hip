@@ -595,10 +595,15 @@ GatherPlan gather_plan(const GatherConv &g)
     // small products (the bottleneck blocks of ResNet: under ~8 GMAC) are bound by the latency of a block's
     // load - multiply - store chain, not by throughput: many 64-pixel blocks and no split of K were the
     // fastest choice on every such shape measured (e.g. 1x1 1024->256 at 14x14: 11.5 us against 22.2)
-    // So are products up to twice that whose 64-pixel tiles fit two blocks per unit (the LSTM's input gradient, 3200 x 1024
-    // x 4096: 400 blocks, 59 -> 43 us); where they do not (its input projection, 1600 blocks), the larger tile stays.
+    // So are products up to twice that whose 64-pixel tiles fit two blocks per unit (3x3 512->512 at 14x14, 32 samples:
+    // 47.6 -> 36.8 us; the LSTM's input gradient, 3200 x 1024 x 4096: 59 -> 43), if they do not fetch much more that way.  A
+    // 3x3 filter re-reads the tile's pixels, and filters up to 12 MB stay in the L2s; of larger 1x1 filters every row of
+    // tiles streams its own copy (4096->4096, 900 rows, two blocks per unit: 46.0 us against 63.6; 25088->4096, 128 rows, K
+    // split over half as many tiles: 54 against 73), so there it takes one block per unit and no split (6144->3072, 600
+    // rows: 58.6 -> 46.9; 4096->4096, 512 rows: 43.6 -> 39.9).
     const double macs = (double)npix * g.Co * g.R * g.S * g.Ci / p.classes;
-    if (p.bc == 128 && npix > 64 && (macs < 8e9 || (macs < 16e9 && tiles_of(64) <= 512))) p.bp = 64;
+    const bool cheap = g.R * g.S > 1 || (double)g.Co * g.Ci * 2 <= 12e6 || (tiles_of(64) > 128 && tiles_of(64) <= 256);
+    if (p.bc == 128 && npix > 64 && (macs < 8e9 || (macs < 16e9 && tiles_of(64) <= 512 && cheap))) p.bp = 64;
     // plenty of 256-pixel tiles and whole 256-channel tiles: one 8-wave block per CU owns 256 x 256, which
     // halves the L2 -> LDS traffic of two independent 256 x 128 blocks (3 % on the 512-channel 28x28 layers)
     if (!few && p.bp == 256 && p.bc == 128 && g.Co % 256 == 0) p.bc = 256;

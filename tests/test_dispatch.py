@@ -25,3 +25,31 @@ def test_one_launch_recurrence_takes_the_hidden_sizes_it_has_kernels_for():
     assert _lstm_seq_supported(1, 128, 256) and _lstm_seq_supported(512, 1024, 256)
     for n, hidden in ((64, 64), (64, 192), (64, 1152), (528, 1024), (0, 128)):
         assert not _lstm_seq_supported(n, hidden, 256)
+
+
+class _GatherConv(ct.Structure):
+    _fields_ = [(f, ct.c_int) for f in "N Hi Wi Ci Ho Wo Co R S s_out s_in pad_h pad_w beside".split()]
+
+
+def _pixel_tiles(rows, cin, cout, k=1, hw=1):
+    """(pixel tiles of the product where K is not split, bytes of partial sums where it is)"""
+    lib, g = B.load(), _GatherConv(rows, hw, hw, cin, hw, hw, cout, k, k, 1, 1, k // 2, k // 2, 0)
+    chunks = getattr(lib, "_ZN6bapipe28conv_gather_mfma_stat_chunksERKNS_10GatherConvE")
+    work = getattr(lib, "_ZN6bapipe26conv_gather_mfma_workspaceERKNS_10GatherConvE")
+    work.restype = ct.c_size_t
+    return chunks(ct.byref(g)), work(ct.byref(g))
+
+
+@pytest.mark.parametrize("rows,cin,cout,k,hw,tile", [
+    (900, 4096, 4096, 1, 1, 128),     # two blocks of 64 rows per unit would stream 34 MB of weights each
+    (600, 6144, 3072, 1, 1, 64),      # one block of 64 rows per unit
+    (512, 4096, 4096, 1, 1, 64),
+    (3200, 4096, 1024, 1, 1, 64),     # weights that stay in the L2s
+    (32, 512, 512, 3, 14, 64),        # a 3x3 filter reads the tile's pixels again
+])
+def test_pixel_tile_of_products_of_8_to_16_gmac(rows, cin, cout, k, hw, tile):
+    assert _pixel_tiles(rows, cin, cout, k, hw) == ((rows * hw * hw + tile - 1) // tile, 0)
+
+
+def test_large_weights_are_not_streamed_by_more_rows_of_tiles_than_before():
+    assert _pixel_tiles(128, 25088, 4096) == (0, 16 * 128 * 4096 * 4)
