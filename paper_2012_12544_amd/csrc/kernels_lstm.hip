@@ -469,12 +469,19 @@ size_t ctl_bytes(int N) { return (size_t)(1 + groups_of(N)) * kCtlWords * sizeof
 
 // Up to hidden 1024 a block's rows fit its registers.  Past a thousand blocks (four rounds of the chip) the two launches
 // per step are no longer mostly gaps: a mini-batch of 2 x 512 sequences of 20 steps at hidden 1024 (1024 blocks) takes
-// 6.7 ms against 7.5 with them, of 2 x 256 3.7 against 4.9.
+// 6.7 ms against 7.5 with them, of 2 x 256 3.7 against 4.9.  Every round of the chip (three blocks to a unit at hidden 128,
+// two up to 384, then one) loads the matrix again, which a short sequence does not pay back: at hidden 1024, forward +
+// backward of a layer, one launch against two per step: 512 sequences (four rounds) of 2 steps 76 + 139 us against 42 + 112,
+// of 6 164 + 244 against 141 + 257; 256 (two rounds) of 2 48 + 86 against 32 + 77, of 4 66 against 73 forward.
+// A single step has no product at all (16 sequences: 20 + 40 us against 12 + 32).
 // The blocks wait for each other: a group has to find its blocks' slots beside up to seven more such launches (forward and
 // backward passes of up to four stages), at one block per compute unit; a GPU partition of few units takes two launches a step.
-bool lstm_seq_supported(int N, int H, int compute_units)
+bool lstm_seq_supported(int N, int T, int H, int compute_units)
 {
-    return N > 0 && H % 128 == 0 && H <= 1024 && (long long)groups_of(N) * (H / kUnits) <= 1024 && 8 * (H / kUnits - 1) < compute_units;
+    if (N < 1 || T < 2 || H % 128 != 0 || H > 1024 || 8 * (H / kUnits - 1) >= compute_units) return false;
+    const long long blocks = (long long)groups_of(N) * (H / kUnits);
+    const int per_unit = H <= 128 ? 3 : H <= 384 ? 2 : 1;
+    return blocks <= 1024 && 2 * blocks <= 256ll * per_unit * T;
 }
 
 // ticket line and flags, then two copies of every group's slices (backward's, the wider ones), then those of the blocks that

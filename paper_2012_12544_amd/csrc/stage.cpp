@@ -449,7 +449,7 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
         HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, s));
     else
         HIPCHK(conv_gather_direct(st->dt, x, L.w_work, L.bias, P, 0, none, gx, s));
-    const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, H, st->compute_units);
+    const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, T, H, st->compute_units);
     if (one_launch) HIPCHK(lstm_seq_fwd(P, w_hh, gates, cells, h, hs, N, T, H, st->work, s));
     for (int t = 0; t < T && !one_launch; ++t) {
         int S = 0;
@@ -480,7 +480,7 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     const char *wt_x = (const char *)L.w_t, *wt_h = wt_x + (size_t)G * In * es;
     const bool mf = st->dt == DT_BF16;
     bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
-    const bool one_launch = mf && lstm_seq_supported(N, H, st->compute_units);
+    const bool one_launch = mf && lstm_seq_supported(N, T, H, st->compute_units);
     if (one_launch) HIPCHK(lstm_seq_bwd(dy, wt_h, gates, cells, dcn, D, N, T, H, st->work, s));
     for (int t = T - 1; t >= 0 && !one_launch; --t) {
         int S = 0;
@@ -1224,7 +1224,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 v = conv_gather_mfma_workspace(rows_geom(N, T, G, In)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, H, G, 1)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, G, H, 1)); w = v > w ? v : w;
-                if (lstm_seq_supported(N, H, st->compute_units)) { v = lstm_seq_workspace(N, H); w = v > w ? v : w; }
+                if (lstm_seq_supported(N, T, H, st->compute_units)) { v = lstm_seq_workspace(N, H); w = v > w ? v : w; }
                 v = conv_wgrad_mfma_workspace(cx); w = v > w ? v : w;
                 v = conv_wgrad_mfma_workspace(ch); w = v > w ? v : w;
             } else {

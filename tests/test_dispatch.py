@@ -6,10 +6,10 @@ import pytest
 from paper_2012_12544_amd import binding as B
 
 
-def _lstm_seq_supported(n, hidden, compute_units):
-    f = getattr(B.load(), "_ZN6bapipe18lstm_seq_supportedEiii")
-    f.restype, f.argtypes = ct.c_bool, [ct.c_int] * 3
-    return f(n, hidden, compute_units)
+def _lstm_seq_supported(n, hidden, compute_units, steps=50):
+    f = getattr(B.load(), "_ZN6bapipe18lstm_seq_supportedEiiii")
+    f.restype, f.argtypes = ct.c_bool, [ct.c_int] * 4
+    return f(n, steps, hidden, compute_units)
 
 
 @pytest.mark.parametrize("hidden", [128, 256, 512, 640, 1024])
@@ -25,6 +25,16 @@ def test_one_launch_recurrence_takes_the_hidden_sizes_it_has_kernels_for():
     assert _lstm_seq_supported(1, 128, 256) and _lstm_seq_supported(512, 1024, 256)
     for n, hidden in ((64, 64), (64, 192), (64, 1152), (528, 1024), (0, 128)):
         assert not _lstm_seq_supported(n, hidden, 256)
+
+
+@pytest.mark.parametrize("n,hidden,least", [
+    (1, 128, 2), (64, 256, 2), (64, 1024, 2),       # a single step has no recurrent product
+    (256, 1024, 4), (512, 1024, 8),                 # two and four rounds of the chip, each of which loads the matrix
+    (1024, 512, 8), (2048, 256, 4), (4096, 128, 3),
+])
+def test_one_launch_recurrence_needs_two_steps_a_round(n, hidden, least):
+    assert not _lstm_seq_supported(n, hidden, 256, least - 1)
+    assert _lstm_seq_supported(n, hidden, 256, least)
 
 
 class _GatherConv(ct.Structure):
