@@ -459,9 +459,11 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
         }
         HIPCHK(lstm_cell_fwd(st->dt, P, (const float *)st->work, S, gates, cells, h, hs, N, T, H, t, s));
     }
-    // x and W_x once, W_h once per step, P written and read, h written
+    // x and W_x once, W_h once or, in two launches per step, each step; P written and read, h and its delayed copy written;
+    // gates and cells written (float)
     st->tap_end(tp, 2.0 * N * T * (double)G * (L.d.cin + H),
-                dt_size(st->dt) * ((double)N * T * (In + 2.0 * G + H) + (double)G * In + (double)(T - 1) * G * H));
+                dt_size(st->dt) * ((double)N * T * (In + 2.0 * G + 2.0 * H) + (double)G * In + (one_launch ? 1.0 : T - 1.0) * G * H) +
+                    4.0 * N * T * (G + H));
     return BAPIPE_OK;
 }
 
@@ -499,8 +501,9 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
             HIPCHK(conv_gather_direct(st->dt, D, wt_x, nullptr, dx, 0, e, gd, s));
         flop += 2.0 * N * T * (double)G * L.d.cin;
     }
-    st->tap_end(tp, flop, dt_size(st->dt) * ((double)N * T * (H + 2.0 * G + (dx ? In : 0)) + (double)G * In +
-                                             (double)(T - 1) * G * H));
+    // dy, gates and cells read, D written; W_h as in forward; for dx D and W_x read, dx written (and read where it is added to)
+    st->tap_end(tp, flop, dt_size(st->dt) * ((double)N * T * (H + G) + (one_launch ? 1.0 : T - 1.0) * G * H) + 4.0 * N * T * (G + H) +
+                              (dx ? dt_size(st->dt) * ((double)N * T * (G + In * (1.0 + (e.accum ? 1.0 : 0.0) + (e.gate ? 1.0 : 0.0))) + (double)G * In) : 0.0));
     // dW_x += D^T x (the bias gradient rides along), dW_h += D^T (delayed h)
     ConvShape cx{N, T, 1, In, T, 1, G, 1, 1, 1, 0}, ch{N, T, 1, H, T, 1, G, 1, 1, 1, 0};
     float *dw_h = L.dw + (size_t)G * In;

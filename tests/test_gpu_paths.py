@@ -76,6 +76,23 @@ def test_lstm_sequence_kernels_finish_without_their_neighbours(h, t, n):
             assert torch.equal(a, b), polls
 
 
+@pytest.mark.parametrize("hidden,reads", [(128, 1), (64, 5)])       # the recurrent matrix: kept for the launch, read each step
+def test_lstm_traffic_is_what_the_layer_moves(hidden, reads):
+    cin, t, n, g = 24, 6, 5, 4 * hidden
+    st = single(lambda b: b.lstm(cin, hidden, src=-1), cin, (t, 1), C.BF16, micro_batch=n, n_micro=1)
+    gpu = GpuStage(st, gen.all_params(st))
+    xs, gs = stage_io(st)
+    B.bapipe_stage_kernel_timing(gpu.h, 0)
+    gpu.forward(0, xs[0])
+    fwd = B.bapipe_stage_kernel_timing_read(gpu.h)
+    gpu.backward(0, gs[0])
+    bwd = B.bapipe_stage_kernel_timing_read(gpu.h)
+    gpu.close()
+    floats = 4 * n * t * (g + hidden)                             # gates and cells
+    assert fwd["bytes"] == 2 * (n * t * (cin + 2 * g + 2 * hidden) + g * cin + reads * g * hidden) + floats
+    assert bwd["bytes"] == 2 * (n * t * (hidden + 2 * g + cin) + g * cin + reads * g * hidden) + floats
+
+
 # ------------------------------------------------------------------------------ input gradient of a strided convolution
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 2, 1, 64, 32, (21, 19), 3),      # classes of unequal size, one K-tile a tap
