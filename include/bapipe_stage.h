@@ -181,7 +181,7 @@ int bapipe_stage_set_streams(bapipe_stage_t *st, void *hip_stream_backward, void
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): same arguments,
  * same schedule rules, same results bit for bit, but the kernels' workspace (split-K partial
  * sums of the weight-gradient and linear-layer GEMMs, column-reduction partials of batch-norm and
- * bias gradients, the dense product of a strided 1x1 input gradient) is a statically allocated
+ * bias gradients, what the blocks of an LSTM recurrence hand to each other) is a statically allocated
  * device array of BAPIPE_STATIC_SCRATCH_BYTES inside the library instead of the workspace the
  * handle obtained from its allocator.  The call allocates and frees nothing on the device.  Every
  * GPU the library runs on holds one copy of the array until the process ends, and all handles on

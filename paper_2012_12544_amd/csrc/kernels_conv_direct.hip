@@ -19,7 +19,7 @@ __device__ __forceinline__ int first_tap(int x, int m)
 
 // What bounds it at the sizes of an fp32 stage (tens of thousands of outputs) is the latency of a thread's loads: V
 // channels come in one load, and four such loads of each operand are requested before the first product (16 channels,
-// 3x3, 32x32 images of four: 24 us with one channel at a time, 7.5 us so).  A tap outside the image reads the nearest pixel
+// 3x3, 32x32 images of four: 24 us with one channel at a time, 5.7 us so).  A tap outside the image reads the nearest pixel
 // inside and its sum is not taken, so that no branch stands between the loads of one tap and the next.  In the gradient of
 // a strided convolution a pixel only walks the taps that meet an output; walking all and dropping the rest took the backward
 // pass of 66 channels, 3x3 / 2, eight 56x56 images from 896 us (taps tested and skipped, one channel at a time) to 1770;

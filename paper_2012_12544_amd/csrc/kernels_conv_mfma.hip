@@ -43,11 +43,12 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // STAGES tiles form a ring; tile kt+STAGES-1 is requested right after the barrier that retires
 // tile kt-1, so STAGES-1 K-tiles of latency are covered while the MFMAs run.
 // PHASED (gradient of a strided convolution, s_in > 1): an output pixel only meets the taps whose offset is congruent to
-// its own position modulo the stride, so the output is taken apart into the s_in^2 grids of pixels with equal remainders;
+// its own position modulo the stride, so the output is taken apart into the grids of pixels with equal remainders;
 // on each the product is an ordinary stride-1 one with the taps of that class (for 3x3 / 2: 4, 2, 2 and 1 of the 9).
 // blockIdx.z is the class, the one with most taps first.  Without it three quarters of the multiply-adds meet a zero:
-// 3x3 / 2, 512 channels, 14x14 from 7x7, 32 samples: 104 -> 30 us; 128 channels, 56x56 from 28x28: 84 -> 44 us.  With the
-// taps not innermost only for 1x1 filters, whose K is the channels of the one tap either way.
+// 3x3 / 2 with the gate and batch-norm sums of a bottleneck, 32 samples, 512 channels, 14x14 from 7x7: 104 -> 24 us; 128
+// channels, 56x56 from 28x28: 84 -> 41 us.  With the taps not innermost only for 1x1 filters, whose K is the channels of the
+// one tap either way.
 template <int BP, int BC, int WP, int WC, int BK, int STAGES, bool S1, bool TAPS_INNER, bool PHASED = false>
 __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,

@@ -5,8 +5,9 @@
 // nearly all of it launch gaps and one block's load - multiply - store chain.  Here the matrix never moves: a block of
 // eight waves keeps the rows of 32 hidden units in registers for the whole sequence (128 registers a lane at hidden
 // 1024), and a step is the exchange of one small vector.  Hidden 1024, 50 steps, 64 sequences, one direction: 650 us
-// before, 203 us (forward) and 211 us (backward) here; of a backward step of 4.4 us 1.9 us are the 16 MB that all
-// blocks together read of the step before, 1.2 us the hand-over, 0.6 us the cell.
+// before, 207 us (forward) and 184 us (backward) here.  Of a backward step of 4.4 us, before all its loads were requested
+// first (3.7 now), 1.9 us were the 16 MB that all blocks together read of the step before, 1.2 us the hand-over, 0.6 us the
+// cell.
 //
 // Split.  16 sequences (the N of the MFMA) form a group, H/32 blocks work on a group, each owns 32 units: their four
 // gates in forward (M = 128 rows, K = H in eight pieces, a piece a wave), their rows of W_h^T in backward (M = 32,

@@ -497,7 +497,7 @@ def test_loss_of_the_previous_mini_batch_is_not_served_again():
     ("tiny fp32", C.tiny_stage()),
 ])
 def test_same_mini_batch_twice_is_bit_identical(name, stage):
-    """Every reduction runs in a fixed order (split partials added by a second kernel, no atomics), so two
+    """Every reduction runs in a fixed order (split partials added by a second kernel, no atomic sums), so two
     runs of the same mini-batch on fresh handles agree bit for bit; a race would show up here."""
     from gpu_harness import gpu_minibatch
     a, b = gpu_minibatch(stage), gpu_minibatch(stage)
