@@ -40,14 +40,17 @@ __global__ void k_conv_gather(const T *__restrict__ in, const T *__restrict__ wt
     int n = (int)(t / g.Ho);
     float acc = bias ? bias[ko] : 0.0f;
     const int hn = oh * g.s_out - g.pad_h, wn = ow * g.s_out - g.pad_w;
-    const int r0 = first_tap(hn, g.s_in), s0 = first_tap(wn, g.s_in);
-    const int ih0 = (hn + r0) / g.s_in, iw0 = (wn + s0) / g.s_in;        // exact
+    // unsigned, for a tap index plus a stride may pass the range of int
+    const unsigned r0 = first_tap(hn, g.s_in), s0 = first_tap(wn, g.s_in), step = g.s_in;
+    const int ih0 = (int)(hn + r0) / g.s_in, iw0 = (int)(wn + s0) / g.s_in;        // exact
     constexpr int STEP = 4 * V;
-    for (int r = r0, ih = ih0; r < g.R; r += g.s_in, ++ih) {
+    int ih = ih0;
+    for (unsigned r = r0; r < (unsigned)g.R; r += step, ++ih) {
         const bool hok = (unsigned)ih < (unsigned)g.Hi;
         const T *row = in + ((size_t)n * g.Hi + (hok ? ih : 0)) * g.Wi * g.Ci;
         const T *wp = wt + (((size_t)ko * g.R + r) * g.S + s0) * g.Ci;
-        for (int s = s0, iw = iw0; s < g.S; s += g.s_in, ++iw, wp += g.s_in * g.Ci) {
+        int iw = iw0;
+        for (unsigned s = s0; s < (unsigned)g.S; s += step, ++iw, wp += (size_t)step * g.Ci) {
             const bool ok = hok && (unsigned)iw < (unsigned)g.Wi;
             const T *ip = row + (size_t)(ok ? iw : 0) * g.Ci;
             float sum = acc;
@@ -121,8 +124,9 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
         // output columns whose input column lies in the image; eight of them are requested at once (16 channels, 32x32:
         // 15 -> 8.4 us a launch)
         const int off = s - c.pad;
-        const int q0 = off < 0 ? (-off + c.stride - 1) / c.stride : 0;
-        const int qe = c.W - off > 0 ? (c.W - off + c.stride - 1) / c.stride : 0, q1 = qe < c.Q ? qe : c.Q;
+        const unsigned stride = c.stride;                // a distance plus a stride may pass the range of int
+        const int q0 = off < 0 ? (int)((-off + stride - 1) / stride) : 0;
+        const int qe = c.W - off > 0 ? (int)((c.W - off + stride - 1) / stride) : 0, q1 = qe < c.Q ? qe : c.Q;
         for (int q = q0; q < q1; q += 8) {
             float a[8], b[8];
 #pragma unroll

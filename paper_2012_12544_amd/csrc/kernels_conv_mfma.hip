@@ -566,7 +566,7 @@ long long class_pixels(const GatherConv &g) { return (long long)g.N * ((g.Ho + g
 // 9.0 us as 400 classes, 13.4 without).
 int gather_classes(const GatherConv &g)
 {
-    if (g.s_in == 1 || g.s_out != 1 || g.pad_h < 0 || g.pad_w < 0) return 1;
+    if (g.s_in == 1 || g.s_in > 65535 || g.s_out != 1 || g.pad_h < 0 || g.pad_w < 0) return 1;
     if (!(g.R == 1 && g.S == 1) && (g.Ci % 32 != 0 || g.R * g.S > 32)) return 1;
     const long long n = (long long)(g.s_in < g.Ho ? g.s_in : g.Ho) * (g.s_in < g.Wo ? g.s_in : g.Wo);
     return n <= 1024 || (n <= 65535 && class_pixels(g) >= 16) ? (int)n : 1;

@@ -164,6 +164,13 @@ def test_strided_conv_gradient_with_batch_norm_sums(k, cin, c, cout, hw, mb, rel
     compare_minibatch(st, verbose="batch-norm and strided conv k%d %d->%d %s" % (k, c, cout, hw))
 
 
+@pytest.mark.parametrize("dtype,cin,cout", [(C.FP32, 8, 12), (C.BF16, 9, 7), (C.BF16, 16, 32)])
+@pytest.mark.parametrize("k,stride,pad", [(3, 2 ** 31 - 1, 1), (3, 2 ** 31 - 3, 2), (1, 2 ** 31 - 1, 0), (3, 70000, 0)])
+def test_strides_of_one_output(dtype, cin, cout, k, stride, pad):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, (5, 6), dtype)
+    compare_minibatch(st, verbose="conv k%d s%d p%d" % (k, stride, pad))
+
+
 # ------------------------------------------------------------------------------ 64-channel K-tiles of the 64-pixel gather tile
 @pytest.mark.parametrize("k,cin,cout,hw,mb", [
     (1, 64, 136, (9, 11), 2),        # one K-tile (an odd count: the second half of the trip is skipped), ragged tiles
