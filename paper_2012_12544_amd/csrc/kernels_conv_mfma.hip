@@ -691,8 +691,17 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
 // of BCI columns covers one tap (or part of it) when C >= BCI and several taps when C is small.
 // grid: x = (ko tile, n tile) ; y = split over pixel chunks.  Same HBM -> LDS ring as the gather
 // kernel: STAGES tiles of 32 pixels, requests issued STAGES-1 tiles ahead, hand-placed vmcnt waits.
-template <int BKO, int BCI, int WKO, int WCI, int STAGES>
-__global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *__restrict__ x,
+// KG > 1: the block is KG groups of waves, each with a ring and a full set of sums of its own, that take the steps in turn;
+// their sums meet in LDS at the end.  A lone block's chain of steps is KG times shorter that way, and nothing is written and
+// read again for it, as the partial sums of KG times as many splits would be.
+// LDS bytes of a block: the rings, or what KG groups park at the end
+template <int BKO, int BCI, int STAGES, int KG>
+constexpr size_t kWgradLds = KG > 1 && (size_t)KG * (BKO * (BCI + 4) + BKO) * 4 > (size_t)KG * STAGES * 32 * (BKO + BCI) * 2
+                                 ? (size_t)KG * (BKO * (BCI + 4) + BKO) * 4
+                                 : (size_t)KG * STAGES * 32 * (BKO + BCI) * 2;
+
+template <int BKO, int BCI, int WKO, int WCI, int STAGES, int KG = 1>
+__global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(const bf16_t *__restrict__ x,
                                                                   const bf16_t *__restrict__ dy,
                                                                   float *part, float *bpart, size_t split_stride,
                                                                   ConvShape c, int tiles_n, int pix_per_split,
@@ -700,7 +709,8 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
                                                                   unsigned dy_bytes)
 {
     constexpr int BKP = 32;
-    constexpr int NW = WKO * WCI;
+    constexpr int NW = WKO * WCI;                        // waves of a group
+    constexpr int STEP = KG * BKP;                       // pixels from one tile of a group to its next
     constexpr int CPA = BKO / 8, CPB = BCI / 8;          // 16-byte chunks per tile row
     constexpr int AL = (BKP * CPA / 64) / NW, BL = (BKP * CPB / 64) / NW;   // wave-wide loads per wave and tile
     constexpr int WT_KO = BKO / WKO, WT_CI = BCI / WCI;
@@ -711,11 +721,12 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
 
     extern __shared__ __align__(16) unsigned char smem[];
     const lds_addr_of lds_of(smem);
-    uint16_t *ring = reinterpret_cast<uint16_t *>(smem);         // [STAGES][ A tile | B tile ]
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_id % NW, kg = wave_id / NW;            // place inside the group, group
     const int wk = wave % WKO, wi = wave / WKO;
+    uint16_t *ring = reinterpret_cast<uint16_t *>(smem) + kg * STAGES * STAGE_ELEMS;      // the group's [STAGES][ A tile | B tile ]
     // The tiles of one pixel split read the same dy and x rows: number the blocks so that a split's tiles run on
     // one XCD (one L2) - consecutive block ids go round the eight XCDs, so each XCD gets a contiguous range of
     // (split, tile) positions.  With a single split (or few blocks) this is the identity up to a permutation.
@@ -727,7 +738,8 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
     const int npix = c.N * c.P * c.Q;
     const int p_begin = by * pix_per_split;
     const int p_end = p_begin + pix_per_split < npix ? p_begin + pix_per_split : npix;
-    const int KT = (p_end - p_begin + BKP - 1) / BKP;
+    const int KT = (p_end - p_begin + KG * BKP - 1) / (KG * BKP);      // tiles of a group, which takes every KG-th
+    const int p_first = p_begin + kg * BKP;
 
     __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(x), 0, (int)x_bytes, 0x00020000);
     __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(dy), 0, (int)dy_bytes, 0x00020000);
@@ -743,8 +755,8 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
         const int row = slot / CPA, cs = slot % CPA;
         const int ch = ((((cs >> 1) ^ wg_swz<BKO>(row)) << 1) | (cs & 1));
         const bool kin = ko0 + ch * 8 < c.K;
-        ap[i] = kin ? p_begin + row : (1 << 30);
-        aoff[i] = ((unsigned)(p_begin + row) * (unsigned)c.K + (unsigned)(ko0 + ch * 8)) * 2u;
+        ap[i] = kin ? p_first + row : (1 << 30);
+        aoff[i] = ((unsigned)(p_first + row) * (unsigned)c.K + (unsigned)(ko0 + ch * 8)) * 2u;
     }
     // ---- B (x) loads: filter position of the lane's chunk column (fixed) and its pixel (advancing):
     // bp = output pixel index, (ph, pw) = stride * (output row, column), boff = byte offset of the
@@ -758,8 +770,8 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
     const unsigned colstep = (unsigned)(c.stride * c.C) * 2u;
     const unsigned rowstep = (unsigned)(c.stride * (c.W - c.Q) * c.C) * 2u;                 // extra, on top of Q columns
     const unsigned imgstep = (unsigned)((c.H - c.P * c.stride) * c.W * c.C) * 2u;           // extra, on top of P rows
-    const int rows_on = BKP / c.Q, cols_on = BKP % c.Q;
-    const unsigned tilestep = (unsigned)BKP * colstep + (unsigned)rows_on * rowstep;
+    const int rows_on = STEP / c.Q, cols_on = STEP % c.Q;
+    const unsigned tilestep = (unsigned)STEP * colstep + (unsigned)rows_on * rowstep;
 #pragma unroll
     for (int i = 0; i < BL; ++i) {
         const int slot = (i * NW + wave) * 64 + lane;
@@ -769,7 +781,7 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
         const int tap = n / c.C, ci = n % c.C;
         br[i] = tap / c.S - c.pad;
         bs[i] = tap % c.S - c.pad;
-        const int p0 = p_begin + row;
+        const int p0 = p_first + row;
         bp[i] = n < Ntot ? p0 : (1 << 30);
         const int q = p0 % c.Q, t = p0 / c.Q;
         const int pr = t % c.P, img = t / c.P;
@@ -797,17 +809,17 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
     auto advance_tile = [&]() {
 #pragma unroll
         for (int i = 0; i < AL; ++i) {
-            ap[i] += BKP;
-            aoff[i] += (unsigned)(BKP * c.K) * 2u;
+            ap[i] += STEP;
+            aoff[i] += (unsigned)(STEP * c.K) * 2u;
         }
 #pragma unroll
         for (int i = 0; i < BL; ++i) {
-            bp[i] += BKP;
+            bp[i] += STEP;
             if (one_pixel) {                     // linear layers: every "pixel" is the next sample
-                boff[i] += BKP * sample_bytes;
+                boff[i] += STEP * sample_bytes;
                 continue;
             }
-            // 32 pixels on = rows_on whole rows and cols_on columns, plus a row where the columns wrap
+            // STEP pixels on = rows_on whole rows and cols_on columns, plus a row where the columns wrap
             pw[i] += cols_on * c.stride;
             ph[i] += rows_on * c.stride;
             boff[i] += tilestep;
@@ -816,7 +828,7 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
                 boff[i] += rowstep;
                 ph[i] += c.stride;
             }
-            while (ph[i] >= Ps) {                // at most once from 32 pixels an image
+            while (ph[i] >= Ps) {                // at most once from STEP pixels an image
                 ph[i] -= Ps;
                 boff[i] += imgstep;
             }
@@ -890,6 +902,59 @@ __global__ __launch_bounds__(WKO *WCI * 64, 2) void k_wgrad_mfma(const bf16_t *_
     }
     WAIT_VMCNT(0);
 
+    if constexpr (KG > 1) {
+        // Every group parks its sums in LDS ([row][column] floats over its own ring and the next ones), then all threads
+        // add the KG copies of a float4 in the groups' order and write it.
+        constexpr int PITCH = BCI + 4;
+        static_assert((size_t)KG * (BKO * PITCH + BKO) * 4 <= kWgradLds<BKO, BCI, STAGES, KG>, "the sums fit");
+        float *sums = reinterpret_cast<float *>(smem), *sbias = sums + KG * BKO * PITCH;
+        const int col = lane & 31, half = lane >> 5;
+        __syncthreads();                                      // every wave has left its ring
+#pragma unroll
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    sums[(kg * BKO + wk * WT_KO + a * 32 + 8 * (v >> 2) + 4 * half + (v & 3)) * PITCH + wi * WT_CI + b * 32 + col] = acc[a][b][v];
+        if (do_bias) {
+#pragma unroll
+            for (int a = 0; a < TA; ++a) {
+                const float t = bsum[a] + __shfl_xor(bsum[a], 32, 64);
+                if (half == 0) sbias[kg * BKO + wk * WT_KO + a * 32 + col] = t;
+            }
+        }
+        __syncthreads();
+        float *dst = part + (size_t)by * split_stride;
+        constexpr int NT = NW * KG * 64, F4 = BCI / 4, IT = BKO * F4 / NT;
+        static_assert(IT >= 1 && BKO * F4 % NT == 0, "whole rounds of the block");
+        float4 o[IT];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int at = it * NT + tid, ko = ko0 + at / F4, n = n0 + at % F4 * 4;
+            o[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (add_to_dst && ko < c.K && n < Ntot) o[it] = *reinterpret_cast<const float4 *>(dst + (size_t)ko * Ntot + n);
+        }
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int at = it * NT + tid, row = at / F4, c4 = at % F4 * 4, ko = ko0 + row, n = n0 + c4;
+            float4 t = *reinterpret_cast<const float4 *>(sums + row * PITCH + c4);
+#pragma unroll
+            for (int g = 1; g < KG; ++g) {
+                const float4 v = *reinterpret_cast<const float4 *>(sums + (g * BKO + row) * PITCH + c4);
+                t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+            }
+            if (ko < c.K && n < Ntot)
+                *reinterpret_cast<float4 *>(dst + (size_t)ko * Ntot + n) = make_float4(t.x + o[it].x, t.y + o[it].y, t.z + o[it].z, t.w + o[it].w);
+        }
+        if (bpart != nullptr && tn == 0 && tid < BKO && ko0 + tid < c.K) {
+            float *bdst = bpart + (size_t)by * split_stride + ko0 + tid, t = sbias[tid];
+#pragma unroll
+            for (int g = 1; g < KG; ++g) t += sbias[g * BKO + tid];
+            *bdst = add_to_dst ? *bdst + t : t;
+        }
+        return;
+    }
     // partial[split][ko][n]
     float *dst = part + (size_t)by * split_stride;
     const int col = lane & 31, half = lane >> 5;
@@ -975,23 +1040,60 @@ __global__ void k_splitk_reduce(const float *__restrict__ part, float *dw, float
 }
 
 struct WgradPlan {
-    int bko, bci, tiles_ko, tiles_n, splits, pix_per_split;
+    int bko, bci, kg, tiles_ko, tiles_n, splits, pix_per_split;
 };
 
 WgradPlan wgrad_plan(const ConvShape &c)
 {
     WgradPlan p;
     const int Ntot = c.R * c.S * c.C;
-    p.bko = c.K > 128 ? 256 : (c.K > 64 ? 128 : 64);
-    p.bci = Ntot > 64 ? 128 : 64;
-    if (p.bko == 256 && p.bci == 64) p.bko = 128;
-    // small products (under ~8 GMAC, the bottleneck blocks of ResNet) are latency-bound: more, smaller
-    // tiles measured 10-25 % faster than 256-wide ones on every such shape
-    if (p.bko == 256 && (double)c.N * c.P * c.Q * c.K * Ntot < 8e9) p.bko = 128;
+    const long long npix = (long long)c.N * c.P * c.Q;
+    auto tiles_of = [&](int bko, int bci) { return (long long)((c.K + bko - 1) / bko) * ((Ntot + bci - 1) / bci); };
+    // A product of up to 14 GMAC is bound by the chain of steps of one block, and by what it fetches per step, not by the
+    // matrix cores: 64-column tiles whose steps two groups of four waves take in turn.  64 x 64 up to 3 GMAC and for narrow
+    // layers, 128 x 64 above (with the reduction of the partial sums, us, KG = 1 before -> now: 256x1024 from 784 rows 15.0 ->
+    // 7.9, 256x2304 16.9 -> 8.8, from 6272 rows 30.5 -> 26.2; 2048x512 from 1568 22.4 -> 12.2; 64x576 from 40500 22.9 -> 17.4,
+    // from 320000 63 -> 58; 512x4608 from 3136 38.1 -> 35; 4096x1024 from 3200 56.6 -> 45.4; 512x2304 from 6272 37.6 -> 34.4).
+    // Larger products (256x2304 from 25088 rows: 53.7 against 54.1, from 100352 148 against 173), and those of more tiles
+    // than the chip holds at once (4096x4096 from 1024 rows: 53 against 74; 25088x4096 from 128: 171 against 210), where the
+    // operands and the sums themselves are what moves, take wider tiles.
+    const double macs = (double)npix * c.K * Ntot;
+    const bool narrow = c.K <= 64 || Ntot <= 64;
+    p.kg = 2;
+    p.bci = 64;
+    if (tiles_of(64, 64) <= 1024 && (c.K <= 64 || macs < 3e9)) {
+        p.bko = 64;
+    } else if (tiles_of(128, 64) <= 512 && (narrow || macs < 14e9)) {
+        p.bko = 128;
+    } else {
+        p.kg = 1;
+        p.bci = 128;
+        p.bko = c.K > 128 && macs >= 8e9 && npix > 128 ? 256 : 128;
+    }
     p.tiles_ko = (c.K + p.bko - 1) / p.bko;
     p.tiles_n = (Ntot + p.bci - 1) / p.bci;
-    long long npix = (long long)c.N * c.P * c.Q;
-    long long tiles = (long long)p.tiles_ko * p.tiles_n;
+    const long long tiles = (long long)p.tiles_ko * p.tiles_n;
+    if (p.kg == 2) {
+        // us, fitted to 60 shapes of 10 to 100 000 tile steps: a step of 64 pixels of a unit's only block and of one of several
+        // that share it; a second launch and the partial sums, written and read
+        double best = 1e30;
+        long long want = 1;
+        const double alone = p.bko == 64 ? 0.36 : 0.45, shared = p.bko == 64 ? 0.30 : 0.36;
+        for (long long sp = 1; sp <= 256; ++sp) {
+            if (sp > 1 && (npix < 64 * sp || tiles * sp > 2048 || (double)sp * c.K * (Ntot + 1) * 4 > 32e6)) break;
+            const long long per_unit = (tiles * sp + 255) / 256;
+            const double cost = (double)per_unit * (double)((npix + 64 * sp - 1) / (64 * sp)) * (per_unit == 1 ? alone : shared) +
+                                (sp > 1 ? 3.5 + (double)sp * c.K * Ntot * 2e-6 : 0.0);
+            if (cost < best) {
+                best = cost;
+                want = sp;
+            }
+        }
+        const long long pps = ((npix + want - 1) / want + 63) / 64 * 64;
+        p.pix_per_split = (int)pps;
+        p.splits = npix > 0 ? (int)((npix + pps - 1) / pps) : 1;
+        return p;
+    }
     // Split count: the chip holds 512 blocks at once (256 CUs x 2), and a launch whose block count is
     // just above a multiple of that leaves most CUs idle during the last blocks.  Take the split count
     // that minimises (time relative to perfectly filled rounds) + (relative cost of the partials: every
@@ -1122,31 +1224,29 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
     const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (db ? c.K : 0);
     float *part = direct ? dw : (float *)workspace;
     float *bpart = !db ? nullptr : (direct ? db : part + total_w);
-#define WG_LAUNCH(BKO_, BCI_, WKO_, WCI_)                                                                  \
+#define WG_LAUNCH(BKO_, BCI_, WKO_, WCI_, KG_)                                                             \
     do {                                                                                                   \
-        constexpr size_t smem = (size_t)3 * 32 * (BKO_ + BCI_) * 2;                                        \
-        auto kfn = k_wgrad_mfma<BKO_, BCI_, WKO_, WCI_, 3>;                                                \
+        constexpr size_t smem = kWgradLds<BKO_, BCI_, 3, KG_>;                                             \
+        auto kfn = k_wgrad_mfma<BKO_, BCI_, WKO_, WCI_, 3, KG_>;                                              \
         static bool attr_set = false;                                                                      \
         if (!attr_set && smem > 64 * 1024) {                                                               \
             hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
             if (e != hipSuccess) return e;                                                                 \
             attr_set = true;                                                                               \
         }                                                                                                  \
-        hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)dy, part, bpart, \
+        hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * KG_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)dy, part, bpart, \
                            total, c, p.tiles_n, p.pix_per_split, direct, x_bytes, dy_bytes);               \
     } while (0)
     const unsigned x_bytes = (unsigned)((size_t)c.N * c.H * c.W * c.C * 2);
     const unsigned dy_bytes = (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2);
-    if (p.bko == 256)
-        WG_LAUNCH(256, 128, 2, 2);
-    else if (p.bko == 128 && p.bci == 128)
-        WG_LAUNCH(128, 128, 2, 2);
-    else if (p.bko == 64 && p.bci == 128)
-        WG_LAUNCH(64, 128, 1, 4);
-    else if (p.bko == 128 && p.bci == 64)
-        WG_LAUNCH(128, 64, 4, 1);
+    if (p.kg == 2 && p.bko == 64)
+        WG_LAUNCH(64, 64, 2, 2, 2);
+    else if (p.kg == 2)
+        WG_LAUNCH(128, 64, 2, 2, 2);
+    else if (p.bko == 256)
+        WG_LAUNCH(256, 128, 2, 2, 1);
     else
-        WG_LAUNCH(64, 64, 2, 2);
+        WG_LAUNCH(128, 128, 2, 2, 1);
 #undef WG_LAUNCH
     if (!direct)
         hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, s, part,

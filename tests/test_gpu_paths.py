@@ -251,6 +251,20 @@ def test_wgrad_small_images(k, stride, cin, cout, hw, mb):
     compare_minibatch(st, verbose="wgrad k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
 
 
+@pytest.mark.parametrize("k,stride,cin,cout,hw,mb", [
+    (1, 1, 64, 64, (5, 6), 1),           # 30 pixels: the second group of waves has none
+    (3, 1, 72, 136, (7, 9), 1),          # 63 pixels: one short of a step of both groups; ragged tiles both ways
+    (3, 1, 8, 40, (13, 20), 1),          # 260 pixels: a step of four, over several splits
+    (3, 2, 128, 64, (31, 29), 5),        # splits that end inside an image
+    (1, 1, 256, 1024, (11, 9), 2),       # one split, added to the gradient
+    (3, 1, 520, 264, (30, 31), 3),       # 128-row tiles, the last of them ragged
+    (1, 1, 24, 2056, (40, 40), 20),      # ... of a layer narrower than a tile
+])
+def test_wgrad_groups_of_waves(k, stride, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="wgrad groups k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
+
+
 # ------------------------------------------------------------------------------ weight update: ragged tiles, both access widths, both copies
 def _mini_batch(gpu, stage, xs, gs):
     out = []
