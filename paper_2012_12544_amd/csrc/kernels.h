@@ -45,7 +45,8 @@ struct GradEpi {
 hipError_t conv_gather_direct(int dt, const void *in, const void *wt, const float *bias, void *out,
                               int relu, GradEpi epi, const GatherConv &g, hipStream_t s);
 size_t conv_wgrad_direct_workspace(const ConvShape &c);
-hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, void *workspace,
+// dw += dy^T x over all pixels; db (may be null) += column sums of dy, with a workspace that also holds colsum_workspace
+hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, float *db, void *workspace,
                              const ConvShape &c, hipStream_t s);
 
 // ---- bf16 MFMA implicit-GEMM convolution (kernels_conv_mfma.hip)

@@ -512,9 +512,8 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
         HIPCHK(conv_wgrad_mfma(x, D, L.dw, L.db, st->work, cx, s));
         HIPCHK(conv_wgrad_mfma(hs, D, dw_h, nullptr, st->work, ch, s));
     } else {
-        HIPCHK(conv_wgrad_direct(st->dt, x, D, L.dw, st->work, cx, s));
-        HIPCHK(conv_wgrad_direct(st->dt, hs, D, dw_h, st->work, ch, s));
-        if (L.db) HIPCHK(colsum_accumulate(st->dt, D, N * T, G, L.db, st->work, s));
+        HIPCHK(conv_wgrad_direct(st->dt, x, D, L.dw, L.db, st->work, cx, s));
+        HIPCHK(conv_wgrad_direct(st->dt, hs, D, dw_h, nullptr, st->work, ch, s));
     }
     st->tap_end(tp, 2.0 * N * T * (double)G * (L.d.cin + H),
                 dt_size(st->dt) * (double)N * T * (In + H + 2.0 * G) + 8.0 * L.w_elems);
@@ -684,13 +683,11 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
         const void *x = st->tptr(L.a, c.mbid);
         ConvShape cs = conv_shape(st, L);
         const double flop = conv_flop(fwd_geom(st, L), L.d.cin);
-        bool bias_done = false;
         if (L.deferred && !c.profiling) {
             // nothing to copy where the tensor already lives in the layer's buffer
             char *xk = L.def_x + (size_t)c.mbid * L.def_x_bytes, *gk = L.def_g + (size_t)c.mbid * L.def_g_bytes;
             if (x != xk) HIPCHK(hipMemcpyAsync(xk, x, L.def_x_bytes, hipMemcpyDeviceToDevice, s));
             if (g != gk) HIPCHK(hipMemcpyAsync(gk, g, L.def_g_bytes, hipMemcpyDeviceToDevice, s));
-            bias_done = true;                             // the column sums of dy ride along in the deferred GEMM
         } else {
             const bool mf = use_mfma_wgrad(st, cs);
             // a layer without an input gradient ends the pass's kernel chain: its weight gradient would only delay
@@ -706,17 +703,11 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
                 st->w_used = true;
             }
             const bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT, ws);
-            if (mf)
-                HIPCHK(conv_wgrad_mfma(x, g, L.dw, L.db, wwork, cs, ws));      // bias gradient rides along
+            if (mf)                                       // the bias gradient rides along in either, and in the deferred GEMM
+                HIPCHK(conv_wgrad_mfma(x, g, L.dw, L.db, wwork, cs, ws));
             else
-                HIPCHK(conv_wgrad_direct(dt, x, g, L.dw, st->work, cs, s));
+                HIPCHK(conv_wgrad_direct(dt, x, g, L.dw, L.db, st->work, cs, s));
             st->tap_end(tp, flop, (double)A.bytes() + O.bytes() + 8.0 * L.w_elems);   // x, dy read; fp32 dw read and written
-            bias_done = mf;
-        }
-        if (L.db && !bias_done) {
-            const bool tp = st->tap_begin(BAPIPE_KC_ELEMENTWISE);
-            HIPCHK(colsum_accumulate(dt, g, cs.N * cs.P * cs.Q, cs.K, L.db, st->work, s));
-            st->tap_end(tp, 0.0, (double)O.bytes());
         }
         if (a_grad) {
             GatherConv dg = dgrad_geom(st, L);
