@@ -49,15 +49,15 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // 3x3 / 2 with the gate and batch-norm sums of a bottleneck, 32 samples, 512 channels, 14x14 from 7x7: 104 -> 24 us; 128
 // channels, 56x56 from 28x28: 84 -> 41 us.  With the taps not innermost only for 1x1 filters, whose K is the channels of the
 // one tap either way.
-template <int BP, int BC, int WP, int WC, int BK, int STAGES, bool S1, bool TAPS_INNER, bool PHASED = false>
-__global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfma(
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false>
+__global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
     int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
     const bf16_t *old_from)
 {
-    constexpr int NT = WP * WC * 64, NW = WP * WC;
+    constexpr int NW = WP * WC, NT = NW * KG * 64;      // waves of a group, threads of the block
     constexpr int CPR = BK / 8;              // 16-byte chunks per tile row
     constexpr int RPW = 64 / CPR;            // tile rows one wave-wide load covers
     constexpr int XL = BP / (RPW * NW);      // loads per wave for the pixel tile
@@ -73,14 +73,18 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
 
     extern __shared__ __align__(16) unsigned char smem[];
     const lds_addr_of lds_of(smem);
-    uint16_t *ring = reinterpret_cast<uint16_t *>(smem);               // [STAGES][ W tile | X tile ]
-    uint16_t *sO = reinterpret_cast<uint16_t *>(smem);                 // [BP][SROW] (epilogue, reuses the ring)
-    constexpr size_t RING_BYTES = (size_t)STAGES * STAGE_ELEMS * 2, TILE_BYTES = (size_t)BP * SROW * 2, EPI_BYTES = TILE_BYTES + NT * 8;
+    // KG > 1: the groups' sums meet in front of the staging tile
+    constexpr int PITCH = BC + 4;
+    constexpr size_t PARK_BYTES = KG > 1 ? (size_t)KG * BP * PITCH * 4 : 0;
+    constexpr size_t RING_BYTES = (size_t)KG * STAGES * STAGE_ELEMS * 2, TILE_BYTES = (size_t)BP * SROW * 2, EPI_BYTES = PARK_BYTES + TILE_BYTES + NT * 8;
+    uint16_t *sO = reinterpret_cast<uint16_t *>(smem + PARK_BYTES);    // [BP][SROW] (epilogue, reuses the ring)
     float *sBias = reinterpret_cast<float *>(smem + (RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES));   // [BC]
     int *sPix = reinterpret_cast<int *>(sBias + BC);                  // PHASED: [BP] output pixel of a tile row, npix past the end
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_id % NW, kg = wave_id / NW;                 // place inside the group, group
+    uint16_t *ring = reinterpret_cast<uint16_t *>(smem) + kg * STAGES * STAGE_ELEMS;      // the group's [STAGES][ W tile | X tile ]
     const int wp = wave % WP, wc = wave / WP;
     // slot (row, c') a lane fills inside one wave-wide load, and the chunk column it must fetch
     const int lrow = lane / CPR;
@@ -162,21 +166,22 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // ci fastest, and a tile may straddle taps.  Both operands use the same order.
     const int kt0 = part ? blockIdx.y * kt_per_split : 0;
     const int kt1 = part ? (kt0 + kt_per_split < KT ? kt0 + kt_per_split : KT) : KT;
-    int kk = kt0 * BK + 8 * lc;                        // flattened k of this lane's chunk (generic order)
+    int ti = kt0 + kg;                                 // the group's next tile; it takes every KG-th
+    int kk = ti * BK + 8 * lc;                        // flattened k of this lane's chunk (generic order)
     int kr = kk / (g.S * g.Ci), ks = (kk / g.Ci) % g.S, kc = kk % g.Ci;
     if (PHASED && KT == 0) kr = g.R;                   // a class without taps reads nothing
     int cb = 0;                                        // FAST: first channel of the tile (wave-uniform)
     if (TAPS_INNER) {
-        const int tap = PHASED ? 0 : kt0 % (g.R * g.S);            // PHASED launches do not split K
-        kr = tap / g.S;
-        ks = tap % g.S;
-        cb = PHASED ? (KT ? 0 : g.Ci) : (kt0 / (g.R * g.S)) * BK;  // a class without taps reads nothing
+        const int taps = PHASED ? (KT ? Rn * Sn : 1) : g.R * g.S, tap = ti % taps;
+        kr = tap / (PHASED ? (KT ? Sn : 1) : g.S);
+        ks = tap % (PHASED ? (KT ? Sn : 1) : g.S);
+        cb = KT ? ti / taps * BK : g.Ci;               // a class without taps reads nothing
     }
 
     auto issue_tile = [&](int stage) {
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
-            const bool kin = cb < g.Ci;
+            const bool kin = KG > 1 ? ti < kt1 : cb < g.Ci;
             const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
             const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
             const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + cb) * 2u;
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             }
             return;                                   // the caller advances (kr, ks, cb) after its MFMAs
         }
-        const bool kin = kr < g.R;
+        const bool kin = kr < g.R && (KG == 1 || ti < kt1);
         const unsigned koff = (unsigned)kk * 2u;
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
@@ -219,8 +224,9 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
             dma16(wrsrc, lds_of(sw + (i * NW + wave) * RPW * BK), vo);
         }
         // advance to the next K-tile
-        kk += BK;
-        kc += BK;
+        ti += KG;
+        kk += KG * BK;
+        kc += KG * BK;
         while (kc >= g.Ci) {
             kc -= g.Ci;
             if (++ks == g.S) {
@@ -233,13 +239,20 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // scalar code does not split the block in which the MFMAs and the address arithmetic interleave.
     auto advance_tile = [&]() {
         if (FAST) {
-            if (++ks == Sn) {
-                ks = 0;
-                if (++kr == Rn) {
-                    kr = 0;
-                    cb += BK;
-                }
+            ti += KG;
+            if (KG > 1 && Rn * Sn == 1) {
+                cb += KG * BK;
+                return;
             }
+#pragma unroll
+            for (int j = 0; j < KG; ++j)
+                if (++ks == Sn) {
+                    ks = 0;
+                    if (++kr == Rn) {
+                        kr = 0;
+                        cb += BK;
+                    }
+                }
         }
     };
 
@@ -294,6 +307,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // tile kt.  By then every wave holds all of tile kt in registers, so its slot is refilled at once.
     // sched_barrier pins that order: left alone the scheduler sinks the reads next to their MFMAs.
     constexpr int NLOAD = XL + WL;
+    const int n_it = (kt1 - kt0 + KG - 1) / KG;
 #pragma unroll
     for (int st = 0; st < STAGES; ++st) {
         issue_tile(st);
@@ -310,12 +324,12 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
 #pragma unroll
         for (int j = 0; j < KSUB; ++j) load_frags(0, j, fa[0][j], fb[0][j]);
         int rd = 0;
-        for (int kt = kt0; kt < kt1; kt += 2) {
+        for (int it = 0; it < n_it; it += 2) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {             // two tiles a trip: which half holds what is known when compiling
-                if (kt + h >= kt1) break;
+                if (it + h >= n_it) break;
                 const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-                WAIT_LGKMCNT(0);                      // this wave holds all of tile kt + h
+                WAIT_LGKMCNT(0);                      // this wave holds all of tile it + h
                 WAIT_VMCNT((STAGES - 2) * NLOAD);     // its share of the next one has landed
                 __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -334,7 +348,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         bf16x8_t fa0[TC], fb0[TP], fa1[TC], fb1[TP];
         load_frags(0, 0, fa0, fb0);
         int rd = 0;
-        for (int kt = kt0; kt < kt1; ++kt) {
+        for (int it = 0; it < n_it; ++it) {
             const int nx = rd + 1 == STAGES ? 0 : rd + 1;
             load_frags(rd, 1, fa1, fb1);
             __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
@@ -355,7 +369,46 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     WAIT_VMCNT(0);
     __syncthreads();
 
-    if (part) {
+    // threads that move the finished tile in 16-byte units
+    constexpr int CH8 = BC / 8;                 // 16-byte units per pixel row
+    constexpr int ET = NT < BP * CH8 ? NT : BP * CH8;
+    if constexpr (KG > 1) {
+        // [group][pixel][channel] floats; every thread adds the groups' copies of a float4, in their order
+        float *park = reinterpret_cast<float *>(smem);
+#pragma unroll
+        for (int a = 0; a < TC; ++a)
+#pragma unroll
+            for (int b = 0; b < TP; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(park + (kg * BP + wp * WT_P + b * 32 + frow) * PITCH + wc * WT_C + a * 32 + 8 * q + 4 * fhalf) =
+                        make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
+        __syncthreads();
+        constexpr int F4 = BC / 4;
+        for (int i = tid; i < BP * F4; i += NT) {
+            const int prow = i / F4, col = i % F4 * 4;
+            float4 v = *reinterpret_cast<const float4 *>(park + prow * PITCH + col);
+#pragma unroll
+            for (int u = 1; u < KG; ++u) {
+                const float4 w = *reinterpret_cast<const float4 *>(park + (u * BP + prow) * PITCH + col);
+                v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+            }
+            if (part) {
+                const int p = pix0 + prow;
+                if (p < npix && co0 + col < g.Co)
+                    *reinterpret_cast<float4 *>(part + ((size_t)blockIdx.y * npix + p) * g.Co + co0 + col) = v;
+                continue;
+            }
+            const float4 bv = *reinterpret_cast<const float4 *>(sBias + col);
+            v.x += bv.x; v.y += bv.y; v.z += bv.z; v.w += bv.w;
+            if (relu) v = make_float4(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f), fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f));
+            chunk8 c8;
+            c8[0] = pack_bf16(v.x, v.y);
+            c8[1] = pack_bf16(v.z, v.w);
+            *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
+        }
+        if (part) return;
+    } else if (part) {
         // split-K: raw fp32 sums, 4 consecutive channels of one pixel per store; bias, ReLU and the
         // gradient epilogue are applied by the reduction kernel
         float *dst = part + (size_t)blockIdx.y * npix * g.Co;
@@ -379,7 +432,7 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // applied), one barrier, then the block streams the tile out as 16-byte coalesced rows
     const chunk16 zero16 = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int a = 0; a < TC; ++a) {
+    for (int a = 0; a < (KG == 1 ? TC : 0); ++a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int col = wc * WT_C + a * 32 + 8 * q + 4 * fhalf;      // channel inside the tile
@@ -407,17 +460,16 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // stored - the first batch now, while the staging tile is being completed.  Requested unit by unit, behind the store
     // of the one before (which may alias), each cost a memory latency: 1x1 128->256 at 56x56, 32 samples, with the stored
     // gradient added, 53 -> 48 us; 3x3 / 2 gradient of 128 channels at 56x56 with the batch-norm sums, 44 -> 42 us.
-    constexpr int CH8 = BC / 8;                 // 16-byte units per pixel row
-    constexpr int UNITS = BP * CH8 / NT;        // per thread
+    constexpr int UNITS = BP * CH8 / ET;        // per thread
     constexpr int BATCH = UNITS < 8 ? UNITS : 8;
-    static_assert(NT % CH8 == 0 && UNITS % BATCH == 0, "a thread keeps one channel group; whole batches");
+    static_assert(ET % CH8 == 0 && UNITS % BATCH == 0, "a thread keeps one channel group; whole batches");
     const int c8i = tid % CH8, rg = tid / CH8, co = co0 + c8i * 8;
-    auto pixel_of = [&](int it) { const int prow = rg + it * (NT / CH8); return PHASED ? sPix[prow] : pix0 + prow; };
+    auto pixel_of = [&](int it) { const int prow = rg + it * (ET / CH8); return PHASED ? sPix[prow] : pix0 + prow; };
     chunk16 gpre[BATCH] = {}, opre[BATCH] = {}, xpre[BATCH] = {};
     auto fetch = [&](chunk16(&to)[BATCH], const bf16_t *from, int it0) {
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
-            const int p = pixel_of(it0 + j);
+            const int p = tid < ET ? pixel_of(it0 + j) : npix;
             to[j] = p < npix && co < g.Co ? *reinterpret_cast<const chunk16 *>(from + (size_t)p * g.Co + co) : zero16;
         }
     };
@@ -443,9 +495,10 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
     // For one that follows: of the STORED (rounded) values and their squares, what its first pass would compute.  All
     // threads walk down the staged tile, NT / BC of them per channel (one per channel left three of four waves of a
     // 256 x 64 tile waiting for 256 rows: 1x1 and 3x3 64->64 at 56x56 and their like, 23.4 -> 22 us a launch).
-    float2 *sums = reinterpret_cast<float2 *>(smem + TILE_BYTES);        // [NT / BC][BC]
-    constexpr int GROUPS = NT / BC, GROWS = BP / GROUPS;
-    if (stat_part && !bn_x) {
+    float2 *sums = reinterpret_cast<float2 *>(smem + PARK_BYTES + TILE_BYTES);        // [GROUPS][BC]
+    constexpr int ST = NT / BC < BP ? NT : BP * BC;                     // threads that add them up
+    constexpr int GROUPS = ST / BC, GROWS = BP / GROUPS;
+    if (stat_part && !bn_x && tid < ST) {
         const int cc = tid % BC, r0 = tid / BC * GROWS;
         const int here = rows - pix0 < BP ? rows - pix0 : BP, r1 = r0 + GROWS < here ? r0 + GROWS : here;
         float2 t = make_float2(0.0f, 0.0f);
@@ -462,9 +515,9 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         if (it0 && is_grad) request(it0);
 #pragma unroll
         for (int j0 = 0; j0 < BATCH; ++j0) {
-            const int p = pixel_of(it0 + j0);
+            const int p = tid < ET ? pixel_of(it0 + j0) : npix;
             if (p < npix && co < g.Co) {
-                const uint16_t *src = sO + (rg + (it0 + j0) * (NT / CH8)) * SROW + c8i * 8;
+                const uint16_t *src = sO + (rg + (it0 + j0) * (ET / CH8)) * SROW + c8i * 8;
                 const chunk8 lo = *reinterpret_cast<const chunk8 *>(src), hi = *reinterpret_cast<const chunk8 *>(src + 4);
                 chunk16 r = {lo[0], lo[1], hi[0], hi[1]};
                 if (is_grad) {
@@ -485,15 +538,17 @@ __global__ __launch_bounds__(WP *WC * 64, WP *WC >= 8 ? 1 : 2) void k_gather_mfm
         }
     }
     if (!stat_part) return;
-    float *red = reinterpret_cast<float *>(smem);                          // [RG][2][BC]; the staging tile is free now
-    constexpr int RG = NT / CH8;                                           // threads that share a channel group
-    static_assert((size_t)RG * BC * 2 * sizeof(float) <= TILE_BYTES && NT % BC == 0 && BP % GROUPS == 0, "sums fit their places");
+    float *red = reinterpret_cast<float *>(smem);                          // [RG][2][BC]; what was parked and staged is free now
+    constexpr int RG = ET / CH8;                                           // threads that share a channel group
+    static_assert((size_t)RG * BC * 2 * sizeof(float) <= PARK_BYTES + TILE_BYTES && ST % BC == 0 && BP % GROUPS == 0, "sums fit their places");
     __syncthreads();
     if (bn_x) {
+        if (tid < ET) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            red[(rg * 2 + 0) * BC + c8i * 8 + j] = bs1[j];
-            red[(rg * 2 + 1) * BC + c8i * 8 + j] = bs2[j];
+            for (int j = 0; j < 8; ++j) {
+                red[(rg * 2 + 0) * BC + c8i * 8 + j] = bs1[j];
+                red[(rg * 2 + 1) * BC + c8i * 8 + j] = bs2[j];
+            }
         }
         __syncthreads();
     }
@@ -548,7 +603,7 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 }
 
 struct GatherPlan {
-    int bp, bc, bk, splits, kt_per_split;
+    int bp, bc, bk, kg, splits, kt_per_split;
     int classes;             // 1, or the classes of a PHASED launch
     int busy;                // classes that have taps
     long long class_pix;     // output pixels of the largest class
@@ -608,16 +663,40 @@ GatherPlan gather_plan(const GatherConv &g)
     // plenty of 256-pixel tiles and whole 256-channel tiles: one 8-wave block per CU owns 256 x 256, which
     // halves the L2 -> LDS traffic of two independent 256 x 128 blocks (3 % on the 512-channel 28x28 layers)
     if (!few && p.bp == 256 && p.bc == 128 && g.Co % 256 == 0) p.bc = 256;
+    // Few tiles: a block's chain of K-steps is what takes the time, and splitting K over blocks costs a second launch (and
+    // leaves no statistics for a batch-norm).  K is split over the wave groups of a block instead, on the smallest tiles that
+    // come to one block per unit (us, KG = 1 with its reduction before -> now: 32 x 32, 1024->256 from 784 pixels 10.7 -> 6.2,
+    // 3x3 256->256 12.9 -> 10.5, 4096->4096 for 8 rows 12.2 -> 9.2; 32 x 64, 2048->512 from 1000 14.6 -> 8.9; 64 x 64, 2048->512
+    // from 1568 18.9 -> 11.5, 3x3 512->512 27.9 -> 21.8).  More tiles than that hide each other's latencies better (64 x 64,
+    // 3x3 256->512 from 3136 pixels, 392 tiles: 25.5 against 17.9).  Not for a large filter, which every row of tiles would
+    // fetch again; one row of 64 takes it in as many splits as make a block per unit (25088->4096, 64 rows: 47.2 -> 38.5).
+    const long long K = (long long)g.R * g.S * g.Ci;
+    auto count = [&](int bp, int bc) { return ((npix + bp - 1) / bp) * ((g.Co + bc - 1) / bc); };
+    const bool large = 2.0 * g.Co * K > 40e6, k64 = g.Ci % 64 == 0 && g.R * g.S <= 32;
+    p.kg = 1;
+    if (g.s_in == 1 && large && npix > 32) {
+        if (npix <= 64 && k64 && count(64, 64) <= 128) p.kg = 2;
+    } else if (g.s_in == 1 && K >= 512 && count(32, 32) <= 256) {
+        p.kg = 8;
+        p.bp = p.bc = 32;
+    } else if (g.s_in == 1 && K >= 512 && count(32, 64) <= 256) {
+        p.kg = 4;
+        p.bp = 32;
+        p.bc = 64;
+    } else if (g.s_in == 1 && K >= 256 && count(64, 64) <= 256) {
+        p.kg = 2;
+    }
+    if (p.kg == 2) p.bp = p.bc = 64;
     const long long tiles = tiles_of(p.bp);
     // K-tiles of 64 channels, read a whole tile ahead, for 64-pixel tiles that come to at most two blocks per compute
     // unit (that kernel's LDS and registers allow no more): 3x3 256->256 and 1x1 1024->256 at 14x14, 32 samples, 196
     // blocks, together 21.8 -> 18.1 us a launch; VGG-16's first linear layer 54.5 -> 48 us forward, 63.8 -> 52 gradient.
     // With more blocks than that the four smaller ones that fit a unit hide the latencies better (1x1 512->256 at 56x56,
     // 3136 blocks: 53 us against 81).  Does not depend on `beside`: K is summed in another order.
-    p.bk = p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
+    p.bk = p.kg == 2 ? (k64 ? 64 : 32) : p.kg == 1 && p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
     const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
-    long long want = tiles >= 128 ? 1 : (512 + tiles - 1) / tiles;
+    long long want = p.kg > 1 ? (large ? 256 / tiles : 1) : tiles >= 128 ? 1 : (512 + tiles - 1) / tiles;
     long long most = KT * BK / 512;                 // at least 512 of K per split
     if (want > most) want = most;
     if (want > 32) want = 32;
@@ -627,14 +706,15 @@ GatherPlan gather_plan(const GatherConv &g)
     return p;
 }
 
-template <int BP, int BC, int WP, int WC, int BK, int STAGES>
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG = 1>
 hipError_t launch_gather(const void *in, const void *wt, const float *bias, void *out, int relu, GradEpi epi,
                          const GatherConv &g, const GatherPlan &plan, void *workspace, hipStream_t s, bool raw = false,
                          float *stat_part = nullptr, const void *bn_x = nullptr, const float *bn_stats = nullptr)
 {
-    constexpr int NT = WP * WC * 64;
-    constexpr size_t main_bytes = (size_t)STAGES * (BP + BC) * BK * 2;
-    constexpr size_t epi_bytes = (size_t)BP * (BC + 4) * 2 + NT * 8;      // staging tile, per-thread sums
+    constexpr int NT = WP * WC * KG * 64;
+    constexpr size_t main_bytes = (size_t)KG * STAGES * (BP + BC) * BK * 2;
+    // the groups' sums, staging tile, per-thread sums
+    constexpr size_t epi_bytes = (KG > 1 ? (size_t)KG * BP * (BC + 4) * 4 : 0) + (size_t)BP * (BC + 4) * 2 + NT * 8;
     constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float);
     const bool phased = plan.classes > 1;
     constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
@@ -649,7 +729,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
 #define GATHER_LAUNCH(S1_, TI_, PH_)                                                                                   \
     do {                                                                                                          \
-        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, S1_, TI_, PH_>;                                      \
+        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, KG, S1_, TI_, PH_>;                                      \
         static bool attr_set = false;                                                                             \
         if (!attr_set && smem > 64 * 1024) {                                                                      \
             hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
@@ -662,7 +742,10 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
                            (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
-    if constexpr (BK == 64) {
+    if constexpr (KG > 1) {                                         // stride-1 operands
+        if (taps_inner) GATHER_LAUNCH(true, true, false);
+        else if constexpr (BK == 32) GATHER_LAUNCH(true, false, false);
+    } else if constexpr (BK == 64) {
         if (phased) GATHER_LAUNCH(true, true, true);
         else GATHER_LAUNCH(true, true, false);
     } else if (phased) {
@@ -682,6 +765,24 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
                            is_grad, (const bf16_t *)epi.accum_from);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_plan(const void *in, const void *wt, const float *bias, void *out, int relu, GradEpi epi, const GatherConv &g,
+                       const GatherPlan &p, void *workspace, hipStream_t s, bool raw = false, float *stat_part = nullptr,
+                       const void *bn_x = nullptr, const float *bn_stats = nullptr)
+{
+#define TILE(...) return launch_gather<__VA_ARGS__>(in, wt, bias, out, relu, epi, g, p, workspace, s, raw, stat_part, bn_x, bn_stats)
+    if (p.kg == 8) TILE(32, 32, 1, 1, 32, 4, 8);
+    if (p.kg == 4) TILE(32, 64, 1, 2, 32, 4, 4);
+    if (p.kg == 2 && p.bk == 64) TILE(64, 64, 2, 2, 64, 3, 2);
+    if (p.kg == 2) TILE(64, 64, 2, 2, 32, 4, 2);
+    if (p.bk == 64) TILE(64, 128, 1, 4, 64, 3);
+    if (p.bp == 64) TILE(64, 128, 1, 4, 32, 3);
+    if (p.bc == 64) TILE(256, 64, 4, 1, 32, 3);
+    if (p.bc == 256) TILE(256, 256, 2, 4, 32, 3);
+    if (p.bp == 128) TILE(128, 128, 2, 2, 32, 3);
+    TILE(256, 128, 2, 2, 32, 3);
+#undef TILE
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1158,13 +1259,7 @@ hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, v
     if (epi.accum_from && (!epi.accum || conv3x3_halo_supported(g))) return hipErrorInvalidValue;   // gather kernel only
     if (conv3x3_halo_supported(g)) return conv3x3_halo_mfma(in, wt, bias, out, relu, epi, g, s);
     if (!epi.gate && !epi.accum && conv3x3_c8_supported(g)) return conv3x3_c8_mfma(in, wt, bias, out, relu, g, s);
-    const GatherPlan p = gather_plan(g);
-    if (p.bk == 64) return launch_gather<64, 128, 1, 4, 64, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
-    if (p.bp == 64) return launch_gather<64, 128, 1, 4, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
-    if (p.bc == 64) return launch_gather<256, 64, 4, 1, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
-    if (p.bc == 256) return launch_gather<256, 256, 2, 4, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
-    if (p.bp == 128) return launch_gather<128, 128, 2, 2, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
-    return launch_gather<256, 128, 2, 2, 32, 3>(in, wt, bias, out, relu, epi, g, p, workspace, s, false, stat_part, bn_x, bn_stats);
+    return launch_plan(in, wt, bias, out, relu, epi, g, gather_plan(g), workspace, s, false, stat_part, bn_x, bn_stats);
 }
 
 size_t conv_gather_mfma_raw_workspace(const GatherConv &g)
@@ -1180,12 +1275,7 @@ hipError_t conv_gather_mfma_raw(const void *in, const void *wt, const GatherConv
     *splits = p.splits;
     if ((long long)g.N * g.Ho * g.Wo == 0) return hipSuccess;
     const GradEpi none{nullptr, 0};
-    if (p.bk == 64) return launch_gather<64, 128, 1, 4, 64, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
-    if (p.bp == 64) return launch_gather<64, 128, 1, 4, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
-    if (p.bc == 64) return launch_gather<256, 64, 4, 1, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
-    if (p.bc == 256) return launch_gather<256, 256, 2, 4, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
-    if (p.bp == 128) return launch_gather<128, 128, 2, 2, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
-    return launch_gather<256, 128, 2, 2, 32, 3>(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
+    return launch_plan(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
 }
 
 bool conv_wgrad_mfma_supported(const ConvShape &c)

@@ -183,6 +183,52 @@ def test_conv_wide_k_tiles(k, cin, cout, hw, mb):
     compare_minibatch(st, verbose="wide K tiles k%d %d->%d %s" % (k, cin, cout, hw))
 
 
+# ------------------------------------------------------------------------------ gather tiles whose K is split over wave groups
+@pytest.mark.parametrize("k,cin,cout,hw,mb", [
+    (1, 512, 40, (5, 5), 2),         # 32 x 32: two K-tiles a group, ragged both ways
+    (3, 64, 72, (9, 8), 1),          # 18 K-tiles: two groups have one more than the rest
+    (1, 520, 64, (6, 5), 3),         # a ragged K-tile, flattened order of K
+    (3, 72, 24, (7, 7), 2),          # K-tiles that straddle taps
+    (1, 512, 520, (10, 10), 5),      # 32 x 64, ragged channel tile
+    (3, 96, 320, (20, 13), 6),
+    (1, 256, 1024, (14, 14), 4),     # 64 x 64, two groups
+    (1, 264, 1000, (14, 13), 4),     # ... of 32-channel K-tiles
+    (3, 128, 64, (45, 45), 3),
+])
+def test_conv_groups_of_waves(k, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="gather groups k%d %d->%d %s x %d" % (k, cin, cout, hw, mb))
+
+
+@pytest.mark.parametrize("cin,cout,mb", [
+    (4992, 4104, 40),      # a large matrix, one row of tiles: groups and splits
+    (4992, 4104, 32),      # ... few rows: groups alone
+    (4992, 4104, 65),      # ... more rows: splits alone
+    (1024, 1000, 1),
+])
+def test_linear_groups_of_waves(cin, cout, mb):
+    st = single(lambda b: b.linear(cin, cout, relu=1, src=-1), cin, (1, 1), C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="linear groups %d->%d x %d" % (cin, cout, mb))
+
+
+@pytest.mark.parametrize("cin,mid,hw,mb", [(512, 64, (7, 7), 3), (512, 72, (10, 9), 2)])
+def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
+    """Every epilogue on tiles of wave groups: statistics, sums of dy and dy*xhat behind a gate, a residual share.  Small
+    enough that no gate flips: of 1024/264 channels, 14x14, 8 samples, tiles without groups were off by up to 7.5e-2 of the
+    largest element and these by 7.7e-2, both beyond what an element-wise 2e-2 can tell from a mistake."""
+    def build(b):
+        t = b.conv(cin, cin, 1, pad=0, relu=1, src=-1)
+        b.conv(cin, mid, 1, pad=0, bias=0)
+        b.bn(mid, relu=1)
+        b.conv(mid, mid, 3, bias=0)
+        b.bn(mid, relu=1)
+        b.conv(mid, cin, 1, pad=0, bias=0)
+        u = b.bn(cin)
+        b.addl(u, t, relu=1)
+    st = single(build, cin, hw, C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="bottleneck %d/%d %s x %d" % (cin, mid, hw, mb))
+
+
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 1, 1, 20, 12, (9, 11), 3),       # a last trip of one vector of channels
