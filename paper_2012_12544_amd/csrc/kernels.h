@@ -146,6 +146,12 @@ hipError_t lstm_seq_bwd(const void *dy, const void *wt_h, const float *gates, co
                         void *workspace, hipStream_t s, unsigned wait_polls = kLstmWaitPolls);
 
 size_t bn_workspace(int rows, int C);
+// Up to so many chunks of partial sums the normalisation and gradient passes add them up themselves.  Two launches against one,
+// us: 1568 rows of 512 channels, 25 chunks, 6.9 / 4.0 forward and 7.1 / 4.4 backward; 6272 rows, 98 chunks, 256 channels 6.8 /
+// 6.8 and 512 7.1 / 11.3.
+constexpr int kBnSumChunks = 64;
+// whether a batch-norm is better off with the partial sums of a neighbouring kernel than in one launch that reads its input whole
+inline bool bn_takes_partials(int rows, int chunks) { return rows > 2048 || chunks <= kBnSumChunks; }
 // stats: [2][C] floats (mean, invstd)
 // pre_chunks > 0: the workspace already holds [2][pre_chunks][C] partial sums of x and x^2 (left there by
 // the kernel that produced x) and the first pass over x is skipped

@@ -680,6 +680,160 @@ __global__ void k_bn_bwd_apply(const T *__restrict__ x, const T *__restrict__ dy
     }
 }
 
+// ------------------------------------------------------------------ batch-norm passes that add the partial sums themselves
+// Where there are few chunks of partial sums a launch of its own to add them is mostly launch: a block of these passes owns
+// 64 channels of some rows, requests its rows, adds its channels' partials meanwhile (eight lanes a channel, in double, in the
+// same order in every block) and goes on.  The first row block of a slice leaves the statistics / the parameter gradients.
+constexpr int BI_NT = 512, BI_CH = 64, BI_LANES = BI_NT / BI_CH, BI_AHEAD = 8;
+struct slice_lds {
+    double red[BI_LANES][2][BI_CH], tot[2][BI_CH];
+    float a[BI_CH], b[BI_CH];
+};
+__device__ __forceinline__ void slice_sums(const float *__restrict__ part, int chunks, int C, int c0, slice_lds &l)
+{
+    const int ch = threadIdx.x % BI_CH, ln = threadIdx.x / BI_CH, c = c0 + ch < C ? c0 + ch : C - 1;
+    double s[2] = {0.0, 0.0};
+    for (int k = ln; k < chunks; k += BI_AHEAD * BI_LANES) {
+        float v[BI_AHEAD][2];
+#pragma unroll
+        for (int u = 0; u < BI_AHEAD; ++u) {
+            const int kk = k + u * BI_LANES;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) v[u][q] = kk < chunks ? part[((size_t)q * chunks + kk) * C + c] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < BI_AHEAD; ++u)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) s[q] += (double)v[u][q];
+    }
+    l.red[ln][0][ch] = s[0];
+    l.red[ln][1][ch] = s[1];
+    __syncthreads();
+    if (threadIdx.x < 2 * BI_CH) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < BI_LANES; ++k) t += l.red[k][threadIdx.x / BI_CH][ch];
+        l.tot[threadIdx.x / BI_CH][ch] = t;
+    }
+    __syncthreads();
+}
+
+template <class T, int V, int U>
+__global__ __launch_bounds__(BI_NT) void k_bn_apply_sums(const T *__restrict__ x, const float *__restrict__ gamma,
+                                                         const float *__restrict__ beta, const float *__restrict__ part, int chunks,
+                                                         float eps, float *__restrict__ stats, T *__restrict__ y, int relu, int rows,
+                                                         int C, const T *__restrict__ res, int relu_sum)
+{
+    constexpr int CGS = BI_CH / V, RY = BI_NT / CGS;
+    __shared__ slice_lds l;
+    const int cx = threadIdx.x % CGS, ry = threadIdx.x / CGS, CV = C / V, c0 = blockIdx.x * BI_CH, cg = c0 / V + cx;
+    const int r0 = blockIdx.y * (RY * U) + ry, cgl = cg < CV ? cg : CV - 1;
+    const vec_t<T, V> *xv = reinterpret_cast<const vec_t<T, V> *>(x), *bv = reinterpret_cast<const vec_t<T, V> *>(res);
+    vec_t<T, V> a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * RY < rows ? r0 + u * RY : rows - 1;
+        a[u] = xv[(size_t)r * CV + cgl];
+        if (res) b[u] = bv[(size_t)r * CV + cgl];
+    }
+    slice_sums(part, chunks, C, c0, l);
+    if (threadIdx.x < BI_CH) {
+        const int c = c0 + threadIdx.x;
+        const double m = (double)rows, mu = l.tot[0][threadIdx.x] / m;
+        double var = l.tot[1][threadIdx.x] / m - mu * mu;
+        if (var < 0.0) var = 0.0;
+        const float fm = (float)mu, fi = (float)(1.0 / sqrt(var + (double)eps));
+        l.a[threadIdx.x] = fm;
+        l.b[threadIdx.x] = fi;
+        if (blockIdx.y == 0 && c < C) {
+            stats[c] = fm;
+            stats[C + c] = fi;
+        }
+    }
+    __syncthreads();
+    if (cg >= CV) return;
+    float mu[V], inv[V], ga[V], be[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        mu[j] = l.a[cx * V + j];
+        inv[j] = l.b[cx * V + j];
+        ga[j] = gamma[cg * V + j];
+        be[j] = beta[cg * V + j];
+    }
+    vec_t<T, V> *yv = reinterpret_cast<vec_t<T, V> *>(y);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * RY;
+        if (r >= rows) break;
+        vec_t<T, V> o;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float xh = (to_f32(a[u].e[j]) - mu[j]) * inv[j];
+            float v = ga[j] * xh + be[j];
+            if (relu) v = fmaxf(v, 0.0f);
+            if (res) {                                   // residual ADD behind this layer, see k_bn_apply
+                v = round_to<T>(v) + to_f32(b[u].e[j]);
+                if (relu_sum) v = fmaxf(v, 0.0f);
+            }
+            o.e[j] = from_f32<T>(v);
+        }
+        yv[(size_t)r * CV + cg] = o;
+    }
+}
+
+template <class T, int V, int U>
+__global__ __launch_bounds__(BI_NT) void k_bn_bwd_apply_sums(const T *__restrict__ x, const T *__restrict__ dy,
+                                                             const float *__restrict__ gamma, const float *__restrict__ stats,
+                                                             const float *__restrict__ part, int chunks, T *dx,
+                                                             const T *__restrict__ gate, int accum, float *dgamma, float *dbeta,
+                                                             float inv_m, int rows, int C)
+{
+    constexpr int CGS = BI_CH / V, RY = BI_NT / CGS;
+    __shared__ slice_lds l;
+    const int cx = threadIdx.x % CGS, ry = threadIdx.x / CGS, CV = C / V, c0 = blockIdx.x * BI_CH, cg = c0 / V + cx;
+    const int r0 = blockIdx.y * (RY * U) + ry, cgl = cg < CV ? cg : CV - 1;
+    const vec_t<T, V> *xv = reinterpret_cast<const vec_t<T, V> *>(x), *gv = reinterpret_cast<const vec_t<T, V> *>(dy);
+    const vec_t<T, V> *tv = reinterpret_cast<const vec_t<T, V> *>(gate);
+    vec_t<T, V> *dv = reinterpret_cast<vec_t<T, V> *>(dx);
+    vec_t<T, V> a[U], g[U], old[U], gt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t i = (size_t)(r0 + u * RY < rows ? r0 + u * RY : rows - 1) * CV + cgl;
+        a[u] = xv[i];
+        g[u] = gv[i];
+        if (accum) old[u] = dv[i];
+        if (gate) gt[u] = tv[i];
+    }
+    slice_sums(part, chunks, C, c0, l);
+    if (blockIdx.y == 0 && threadIdx.x < BI_CH && c0 + threadIdx.x < C) {
+        dbeta[c0 + threadIdx.x] += (float)l.tot[0][threadIdx.x];
+        dgamma[c0 + threadIdx.x] += (float)l.tot[1][threadIdx.x];
+    }
+    if (cg >= CV) return;
+    float mu[V], inv[V], gi[V], m1[V], m2[V];          // mean, 1/std, gamma/std, sum(dy)/m, sum(dy*xhat)/m
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        mu[j] = stats[cg * V + j];
+        inv[j] = stats[C + cg * V + j];
+        gi[j] = gamma[cg * V + j] * inv[j];
+        m1[j] = (float)l.tot[0][cx * V + j] * inv_m;
+        m2[j] = (float)l.tot[1][cx * V + j] * inv_m;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * RY;
+        if (r >= rows) break;
+        vec_t<T, V> o;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float xh = (to_f32(a[u].e[j]) - mu[j]) * inv[j];
+            float v = gi[j] * (to_f32(g[u].e[j]) - m1[j] - xh * m2[j]);
+            o.e[j] = grad_out<T>(v, accum != 0, old[u].e[j], gate != nullptr, gt[u].e[j]);
+        }
+        dv[(size_t)r * CV + cg] = o;
+    }
+}
+
 // ------------------------------------------------------------------ batch-norm in one launch
 // For tensors of up to 2048 rows one block owns ONE group of V = 4 channels over ALL rows: every thread keeps its R rows in registers, the block
 // reduces the statistics (wave butterflies, then the 16 wave results added in double in wave
@@ -1431,6 +1585,41 @@ constexpr int OP_V = 4;
                        (const T_ *)dy, gamma, stats, (T_ *)dx, (const T_ *)epi.gate, epi.accum, dgamma, dbeta,    \
                        1.0f / (float)rows, rows, C)
 
+// rows per thread: four loads at a time where that leaves the chip full
+static dim3 sums_grid(int rows, int C, int V, int *u)
+{
+    const int per = BI_NT / (BI_CH / V), slices = (C + BI_CH - 1) / BI_CH;
+    auto blocks = [&](int uu) { return (long long)slices * ((rows + per * uu - 1) / (per * uu)); };
+    *u = blocks(4) >= 512 ? 4 : blocks(2) >= 512 ? 2 : 1;
+    return dim3((unsigned)slices, (unsigned)((rows + per * *u - 1) / (per * *u)));
+}
+
+// The statistics' final pass and the normalisation, over `chunks` partial sums at the front of the workspace
+static hipError_t bn_fwd_rest(int dt, const void *x, const float *gamma, const float *beta, float eps, void *y, float *stats,
+                              int relu, int rows, int C, const float *part, int chunks, int Vsel, hipStream_t s, const void *res,
+                              int relu_sum)
+{
+    if (Vsel > 1 && chunks <= kBnSumChunks) {
+        int u;
+        const dim3 grid = sums_grid(rows, C, Vsel, &u);
+#define BN_FWD_SUMS(T_, V_, U_)                                                                                          \
+    hipLaunchKernelGGL((k_bn_apply_sums<T_, V_, U_>), grid, dim3(BI_NT), 0, s, (const T_ *)x, gamma, beta, part, chunks, \
+                       eps, stats, (T_ *)y, relu, rows, C, (const T_ *)res, relu_sum)
+#define BN_U(LAUNCH, T_, V_) do { if (u == 4) LAUNCH(T_, V_, 4); else if (u == 2) LAUNCH(T_, V_, 2); else LAUNCH(T_, V_, 1); } while (0)
+        if (dt == DT_F32) BN_U(BN_FWD_SUMS, float, 4);
+        else BN_U(BN_FWD_SUMS, bf16_t, 8);
+        return hipGetLastError();
+    }
+    LAUNCH_FINAL(k_bn_stat_final, chunks, C, s, part, chunks, C, rows, eps, stats);
+    DISPATCH_TV(dt, Vsel > 1, {
+        ColPlan p = col_plan(rows, C, V);
+        const int rpb = p.RY * BN_ROWS_PER_THREAD;
+        hipLaunchKernelGGL((k_bn_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s, (const T *)x,
+                           gamma, beta, stats, (T *)y, relu, rows, C, p, (const T *)res, relu_sum);
+    });
+    return hipGetLastError();
+}
+
 hipError_t bn_fwd(int dt, const void *x, const float *gamma, const float *beta, float eps, void *y,
                   float *stats, int relu, int rows, int C, void *workspace, hipStream_t s, int pre_chunks,
                   const void *res, int relu_sum)
@@ -1439,31 +1628,48 @@ hipError_t bn_fwd(int dt, const void *x, const float *gamma, const float *beta, 
     if (res && relu) return hipErrorInvalidValue;          // the layer's own ReLU and a residual behind it exclude each other
     int Vsel = col_vec(dt, C, x, y, res);
     float *part = (float *)workspace;
-    if (pre_chunks > 0) {                 // statistics partials came with x: final pass and normalisation only
-        LAUNCH_FINAL(k_bn_stat_final, pre_chunks, C, s, part, pre_chunks, C, rows, eps, stats);
-        DISPATCH_TV(dt, Vsel > 1, {
-            ColPlan p = col_plan(rows, C, V);
-            const int rpb = p.RY * BN_ROWS_PER_THREAD;
-            hipLaunchKernelGGL((k_bn_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s, (const T *)x,
-                               gamma, beta, stats, (T *)y, relu, rows, C, p, (const T *)res, relu_sum);
-        });
-        return hipGetLastError();
-    }
+    if (pre_chunks > 0)                   // statistics partials came with x: final pass and normalisation only
+        return bn_fwd_rest(dt, x, gamma, beta, eps, y, stats, relu, rows, C, part, pre_chunks, Vsel, s, res, relu_sum);
     if (bn_onepass(Vsel, rows, C)) {
         if (dt == DT_F32) BN_FWD_OP(float, OP_R);
         else BN_FWD_OP(bf16_t, OP_R);
         return hipGetLastError();
     }
+    int chunks = 0;
     DISPATCH_TV(dt, Vsel > 1, {
         ColPlan p = col_plan(rows, C, V);
+        chunks = p.chunks;
         hipLaunchKernelGGL((k_bn_stat_partial<T, V>), dim3(p.gx, p.chunks), dim3(TPB), 0, s, (const T *)x,
                            rows, C, p, part);
-        LAUNCH_FINAL(k_bn_stat_final, p.chunks, C, s, part, p.chunks, C, rows,
-                           eps, stats);
-        const int rpb = p.RY * BN_ROWS_PER_THREAD;
-        hipLaunchKernelGGL((k_bn_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s, (const T *)x,
-                           gamma, beta, stats, (T *)y, relu, rows, C, p, (const T *)res, relu_sum);
     });
+    return bn_fwd_rest(dt, x, gamma, beta, eps, y, stats, relu, rows, C, part, chunks, Vsel, s, res, relu_sum);
+}
+
+// The sums' final pass (the parameter gradients) and, if anybody reads it, dx
+static hipError_t bn_bwd_rest(int dt, const void *x, const void *dy, const float *gamma, const float *stats, void *dx, float *dgamma,
+                              float *dbeta, GradEpi epi, int rows, int C, float *part, int chunks, int Vsel, hipStream_t s)
+{
+    if (dx && Vsel > 1 && chunks <= kBnSumChunks) {
+        int u;
+        const dim3 grid = sums_grid(rows, C, Vsel, &u);
+#define BN_BWD_SUMS(T_, V_, U_)                                                                                           \
+    hipLaunchKernelGGL((k_bn_bwd_apply_sums<T_, V_, U_>), grid, dim3(BI_NT), 0, s, (const T_ *)x, (const T_ *)dy, gamma, stats, \
+                       part, chunks, (T_ *)dx, (const T_ *)epi.gate, epi.accum, dgamma, dbeta, 1.0f / (float)rows, rows, C)
+        if (dt == DT_F32) BN_U(BN_BWD_SUMS, float, 4);
+        else BN_U(BN_BWD_SUMS, bf16_t, 8);
+        return hipGetLastError();
+    }
+    float *sums = part + (size_t)2 * chunks * C;
+    LAUNCH_FINAL(k_bn_bwd_final, chunks, C, s, part, chunks, C, sums, dgamma, dbeta);
+    if (dx) {
+        DISPATCH_TV(dt, Vsel > 1, {
+            ColPlan p = col_plan(rows, C, V);
+            const int rpb = p.RY * BN_ROWS_PER_THREAD;
+            hipLaunchKernelGGL((k_bn_bwd_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s,
+                               (const T *)x, (const T *)dy, gamma, stats, sums, (T *)dx, (const T *)epi.gate,
+                               epi.accum, 1.0f / (float)rows, rows, C, p);
+        });
+    }
     return hipGetLastError();
 }
 
@@ -1475,40 +1681,21 @@ hipError_t bn_bwd(int dt, const void *x, const void *dy, const float *gamma, con
     int Vsel = col_vec(dt, C, x, dy, dx);
     if (!aligned16(epi.gate)) Vsel = 1;
     float *part = (float *)workspace;
-    if (pre_chunks > 0) {                 // the sums over dy came with dy: final pass and the dx pass only
-        float *sums = part + (size_t)2 * pre_chunks * C;
-        LAUNCH_FINAL(k_bn_bwd_final, pre_chunks, C, s, part, pre_chunks, C, sums, dgamma, dbeta);
-        if (dx) {
-            DISPATCH_TV(dt, Vsel > 1, {
-                ColPlan p = col_plan(rows, C, V);
-                const int rpb = p.RY * BN_ROWS_PER_THREAD;
-                hipLaunchKernelGGL((k_bn_bwd_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s,
-                                   (const T *)x, (const T *)dy, gamma, stats, sums, (T *)dx, (const T *)epi.gate,
-                                   epi.accum, 1.0f / (float)rows, rows, C, p);
-            });
-        }
-        return hipGetLastError();
-    }
+    if (pre_chunks > 0)                   // the sums over dy came with dy: final pass and the dx pass only
+        return bn_bwd_rest(dt, x, dy, gamma, stats, dx, dgamma, dbeta, epi, rows, C, part, pre_chunks, Vsel, s);
     if (bn_onepass(Vsel, rows, C)) {
         if (dt == DT_F32) BN_BWD_OP(float, OP_R);
         else BN_BWD_OP(bf16_t, OP_R);
         return hipGetLastError();
     }
+    int chunks = 0;
     DISPATCH_TV(dt, Vsel > 1, {
         ColPlan p = col_plan(rows, C, V);
-        float *sums = part + (size_t)2 * p.chunks * C;
+        chunks = p.chunks;
         hipLaunchKernelGGL((k_bn_bwd_partial<T, V>), dim3(p.gx, p.chunks), dim3(TPB), 0, s, (const T *)x,
                            (const T *)dy, stats, rows, C, p, part);
-        LAUNCH_FINAL(k_bn_bwd_final, p.chunks, C, s, part, p.chunks, C, sums,
-                           dgamma, dbeta);
-        if (dx) {
-            const int rpb = p.RY * BN_ROWS_PER_THREAD;
-            hipLaunchKernelGGL((k_bn_bwd_apply<T, V>), dim3(p.gx, (rows + rpb - 1) / rpb), dim3(TPB), 0, s,
-                               (const T *)x, (const T *)dy, gamma, stats, sums, (T *)dx, (const T *)epi.gate,
-                               epi.accum, 1.0f / (float)rows, rows, C, p);
-        }
     });
-    return hipGetLastError();
+    return bn_bwd_rest(dt, x, dy, gamma, stats, dx, dgamma, dbeta, epi, rows, C, part, chunks, Vsel, s);
 }
 
 hipError_t lstm_cell_fwd(int dt, const void *P, const float *gh, int S, float *gates, float *cells, void *h,

@@ -1234,11 +1234,10 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             const Tensor &O = st->tensors[L.o];
             const GatherConv g = fwd_geom(st, L);
             const int rows = micro_batch * O.H * O.W;
-            // the one-launch batch-norm of tiny tensors reads x once anyway
             if (B.d.kind == BAPIPE_BATCHNORM2D && B.a == L.o && O.consumers.size() == 1 && !L.d.fuse_relu &&
-                rows > 2048 && use_mfma_gather(st, g)) {
+                use_mfma_gather(st, g)) {
                 const int chunks = conv_gather_mfma_stat_chunks(g);
-                if (chunks > 0) {
+                if (chunks > 0 && bn_takes_partials(rows, chunks)) {
                     L.stat_chunks = chunks;
                     B.stats_given = true;
                     const size_t w = (size_t)2 * chunks * O.C * sizeof(float) + 4 * (size_t)O.C * sizeof(float);
@@ -1252,9 +1251,9 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             const GatherConv dg = dgrad_geom(st, L);
             const int rows = micro_batch * X.H * X.W;
             if (B.d.kind == BAPIPE_BATCHNORM2D && X.root == L.a && X.consumers.size() == 1 && X.need_grad &&
-                st->tensors[st->tensors[B.a].root].need_grad && rows > 2048 && use_mfma_gather(st, dg)) {
+                st->tensors[st->tensors[B.a].root].need_grad && use_mfma_gather(st, dg)) {
                 const int chunks = conv_gather_mfma_stat_chunks(dg);
-                if (chunks > 0) {
+                if (chunks > 0 && bn_takes_partials(rows, chunks)) {
                     L.bnb_chunks = chunks;
                     B.bwd_sums_given = true;
                     const size_t w = (size_t)2 * chunks * X.C * sizeof(float) + 4 * (size_t)X.C * sizeof(float);

@@ -229,6 +229,25 @@ def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
     compare_minibatch(st, verbose="bottleneck %d/%d %s x %d" % (cin, mid, hw, mb))
 
 
+# ------------------------------------------------------------------------------ batch-norm passes that add the partial sums
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("c,hw,mb", [
+    (64, (29, 25), 3),       # one slice of 64 channels, a last row block of a few rows
+    (72, (29, 25), 3),       # a second slice of 8
+    (8, (33, 32), 2),        # less than a slice
+    (136, (50, 49), 5),      # several rows a thread
+    (12, (29, 25), 3),       # bf16: channels that no 16-byte access holds, two launches
+])
+def test_batch_norm_adds_partial_sums(dtype, c, hw, mb):
+    """More than 2048 rows and up to 64 chunks of partial sums, from passes of their own."""
+    def build(b):
+        u = b.bn(c, relu=1, src=-1)
+        v = b.bn(c)
+        b.addl(v, u, relu=1)
+    st = single(build, c, hw, dtype, micro_batch=mb)
+    compare_minibatch(st, verbose="batch-norm sums c%d %s x %d" % (c, hw, mb))
+
+
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 1, 1, 20, 12, (9, 11), 3),       # a last trip of one vector of channels
