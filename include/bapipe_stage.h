@@ -157,7 +157,7 @@ int bapipe_stage_backward(bapipe_stage_t *st, int mb_id, const void *dy_dev_or_l
  *  - Inside a backward pass a layer's weight gradient needs the layer's output gradient and its
  *    stashed input, nothing the remaining input-gradient kernels produce.  With
  *    hip_stream_wgrad the weight-gradient kernels of conv layers are enqueued on that stream,
- *    beside the input-gradient chain.
+ *    beside the input-gradient chain (short ones several at a time, or not at all).
  * Kernels of different streams share the compute units, so each fills what the others leave
  * idle while they ramp up, drain, or wait for memory.  Both streams are caller-owned, on the
  * stage's device, of default priority, and distinct from each other and from opts->hip_stream;

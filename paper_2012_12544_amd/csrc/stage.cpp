@@ -95,6 +95,21 @@ struct Layer {
     int pc = 0, ph = 0, pw = 0;
 };
 
+// a weight gradient that the backward pass has the operands of: the layer's input, its output gradient
+struct WgradLaunch {
+    const void *x, *dy;
+    const Layer *layer;
+    ConvShape shape;
+    double flop, bytes;
+};
+// Handing kernels to the weight-gradient stream takes an event and a wait, 11 us of the host, and as much again at the end of
+// the pass, where a launch takes 2.5: stages of short kernels were slower with that stream than without.  Weight gradients
+// wait for each other until that pays, about 20 us of them by the rates below (what is left at the end of a pass runs on the pass's own stream).
+// Mini-batches on three streams, us, each handed over by itself -> so: bottlenecks of 128 channels, 20x20, 16 samples 1450 -> 1075; of
+// 64, 23x23, 31 samples 1450 -> 1095; 10 samples of 16x16, projection, 720 -> 550; the ResNet stem of 8 images of 112x112
+// 2270 -> 1625; full-sized stages the same.
+constexpr double kForkUs = 10.5, kForkFlopPerUs = 6e8, kForkBytesPerUs = 2.5e6;
+
 }  // namespace
 
 struct bapipe_stage {
@@ -118,6 +133,8 @@ struct bapipe_stage {
     char *work_w = nullptr;
     hipEvent_t ev_g = nullptr, ev_w_end = nullptr;
     bool w_used = false;
+    std::vector<WgradLaunch> w_waiting;      // of the pass being enqueued, not handed over yet
+    double w_waiting_us = 0.0;
     char *work_f = nullptr, *work_b = nullptr;
     std::vector<hipEvent_t> ev_fwd, ev_bwd;
     // arenas
@@ -668,6 +685,28 @@ GradEpi epi_for(bapipe_stage *st, int t, BwdCtx &c, int pool_gate_t = -1)
     return e;
 }
 
+int run_wgrad(bapipe_stage *st, const WgradLaunch &w, bool mfma, hipStream_t s, char *work)
+{
+    const bool tp = st->tap_begin(mfma ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT, s);
+    if (mfma)
+        HIPCHK(conv_wgrad_mfma(w.x, w.dy, w.layer->dw, w.layer->db, work, w.shape, s));
+    else
+        HIPCHK(conv_wgrad_direct(st->dt, w.x, w.dy, w.layer->dw, w.layer->db, work, w.shape, s));
+    st->tap_end(tp, w.flop, w.bytes);
+    return BAPIPE_OK;
+}
+
+int run_waiting_wgrads(bapipe_stage *st, hipStream_t s, char *work)
+{
+    for (const WgradLaunch &w : st->w_waiting) {
+        const int rc = run_wgrad(st, w, true, s, work);
+        if (rc != BAPIPE_OK) return rc;
+    }
+    st->w_waiting.clear();
+    st->w_waiting_us = 0.0;
+    return BAPIPE_OK;
+}
+
 int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
 {
     Layer &L = st->layers[li];
@@ -690,24 +729,24 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             if (g != gk) HIPCHK(hipMemcpyAsync(gk, g, L.def_g_bytes, hipMemcpyDeviceToDevice, s));
         } else {
             const bool mf = use_mfma_wgrad(st, cs);
+            // the bias gradient rides along in either, and in the deferred GEMM; x, dy read, fp32 dw read and written
+            const WgradLaunch w{x, g, &L, cs, flop, (double)A.bytes() + O.bytes() + 8.0 * L.w_elems};
             // a layer without an input gradient ends the pass's kernel chain: its weight gradient would only delay
             // the end of the pass from the other stream
-            const bool side = mf && st->stream_w && !c.profiling && a_grad;
-            hipStream_t ws = s;
-            char *wwork = st->work;
-            if (side) {                                   // g is complete on the backward stream at this point
-                HIPCHK(hipEventRecord(st->ev_g, s));
-                HIPCHK(hipStreamWaitEvent(st->stream_w, st->ev_g, 0));
-                ws = st->stream_w;
-                wwork = st->work_w;
-                st->w_used = true;
+            if (mf && st->stream_w && !c.profiling && a_grad) {
+                st->w_waiting.push_back(w);
+                st->w_waiting_us += w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
+                if (st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
+                    HIPCHK(hipEventRecord(st->ev_g, s));
+                    HIPCHK(hipStreamWaitEvent(st->stream_w, st->ev_g, 0));
+                    st->w_used = true;
+                    const int rc = run_waiting_wgrads(st, st->stream_w, st->work_w);
+                    if (rc != BAPIPE_OK) return rc;
+                }
+            } else {
+                const int rc = run_wgrad(st, w, mf, s, st->work);
+                if (rc != BAPIPE_OK) return rc;
             }
-            const bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT, ws);
-            if (mf)                                       // the bias gradient rides along in either, and in the deferred GEMM
-                HIPCHK(conv_wgrad_mfma(x, g, L.dw, L.db, wwork, cs, ws));
-            else
-                HIPCHK(conv_wgrad_direct(dt, x, g, L.dw, L.db, st->work, cs, s));
-            st->tap_end(tp, flop, (double)A.bytes() + O.bytes() + 8.0 * L.w_elems);   // x, dy read; fp32 dw read and written
         }
         if (a_grad) {
             GatherConv dg = dgrad_geom(st, L);
@@ -1457,8 +1496,14 @@ int bapipe_stage_backward(bapipe_stage_t *st, int mb_id, const void *dy_dev_or_l
         }
         c.written[r] = 1;
     }
+    st->w_waiting.clear();                   // of a pass that failed
+    st->w_waiting_us = 0.0;
     for (int i = nl - 1; i >= 0; --i) {
         int rc = layer_backward(st, i, c);
+        if (rc != BAPIPE_OK) return rc;
+    }
+    {
+        const int rc = run_waiting_wgrads(st, s, st->work);
         if (rc != BAPIPE_OK) return rc;
     }
     for (const void *p : c.pending)
