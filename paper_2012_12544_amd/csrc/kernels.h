@@ -156,16 +156,17 @@ inline bool bn_takes_partials(int rows, int chunks) { return rows > 2048 || chun
 // pre_chunks > 0: the workspace already holds [2][pre_chunks][C] partial sums of x and x^2 (left there by
 // the kernel that produced x) and the first pass over x is skipped
 // res: the other input of a residual ADD fed only by this layer - y = [relu_sum](round(bn(x)) + res) in one pass
+// y2: a second destination for y
 hipError_t bn_fwd(int dt, const void *x, const float *gamma, const float *beta, float eps, void *y,
                   float *stats, int relu, int rows, int C, void *workspace, hipStream_t s, int pre_chunks = 0,
-                  const void *res = nullptr, int relu_sum = 0);
+                  const void *res = nullptr, int relu_sum = 0, void *y2 = nullptr);
 // pre_chunks > 0: the workspace already holds [2][pre_chunks][C] partial sums of dy and dy*xhat
 hipError_t bn_bwd(int dt, const void *x, const void *dy, const float *gamma, const float *stats,
                   void *dx, float *dgamma, float *dbeta, GradEpi epi, int rows, int C,
                   void *workspace, hipStream_t s, int pre_chunks = 0);
 
-// p = softmax(z) rows of K classes (float out)
-hipError_t softmax_fwd(int dt, const void *z, float *p, int rows, int K, hipStream_t s);
+// p = softmax(z) rows of K classes (float out), p2: a second destination
+hipError_t softmax_fwd(int dt, const void *z, float *p, int rows, int K, hipStream_t s, float *p2 = nullptr);
 // dz = scale*(p - onehot), loss[0] = -scale*sum_n log p[n,label]
 hipError_t xent_bwd(int dt, const float *p, const int32_t *labels, float scale, void *dz, float *loss,
                     int rows, int K, hipStream_t s);

@@ -543,6 +543,9 @@ struct FwdCtx {
     int mbid;
     const void *x_direct;
     bool profiling = false;      // layers are timed one at a time: nothing may rely on what the previous layer left behind
+    // where the caller wants the last tensor as it is stored here; the kernel that writes that tensor last may store both
+    void *y_direct = nullptr;
+    bool y_stored = false;
 };
 
 const void *in_ptr(bapipe_stage *st, int t, const FwdCtx &c)
@@ -552,7 +555,7 @@ const void *in_ptr(bapipe_stage *st, int t, const FwdCtx &c)
     return st->tptr(t, c.mbid);
 }
 
-int layer_forward(bapipe_stage *st, int li, const FwdCtx &c)
+int layer_forward(bapipe_stage *st, int li, FwdCtx &c)
 {
     Layer &L = st->layers[li];
     const Tensor &O = st->tensors[L.o];
@@ -614,16 +617,20 @@ int layer_forward(bapipe_stage *st, int li, const FwdCtx &c)
         // the partials of the producing conv are only there when that conv has just run (not when the
         // profiler times this layer alone)
         const int pre = (L.stats_given && !c.profiling) ? st->layers[li - 1].stat_chunks : 0;
+        // the stage's output goes to the caller in the pass that stores it (16-byte accesses, as in the stash)
+        const int stores = L.fuse_add >= 0 ? L.fuse_add : li;
+        void *y2 = stores + 1 == (int)st->layers.size() && (uintptr_t)c.y_direct % 16 == 0 ? c.y_direct : nullptr;
+        if (y2) c.y_stored = true;
         if (L.fuse_add >= 0) {                       // y of the ADD behind this layer, in the same pass
             const Layer &S = st->layers[L.fuse_add];
             const void *other = in_ptr(st, S.a == L.o ? S.b : S.a, c);
             HIPCHK(bn_fwd(dt, a, L.w, L.bias, L.d.eps, st->tptr(S.o, c.mbid), (float *)(st->slot(c.mbid) + L.aux_off), 0,
-                          st->mb * A.H * A.W, A.C, st->work, s, pre, other, S.d.fuse_relu));
+                          st->mb * A.H * A.W, A.C, st->work, s, pre, other, S.d.fuse_relu, y2));
             st->tap_end(tp, 0.0, 4.0 * A.bytes());                               // x twice, the other summand, y
             break;
         }
         HIPCHK(bn_fwd(dt, a, L.w, L.bias, L.d.eps, o, (float *)(st->slot(c.mbid) + L.aux_off), L.d.fuse_relu,
-                      st->mb * A.H * A.W, A.C, st->work, s, pre));
+                      st->mb * A.H * A.W, A.C, st->work, s, pre, nullptr, 0, y2));
         st->tap_end(tp, 0.0, 3.0 * A.bytes());                                   // read x twice, write y
         break;
     }
@@ -642,7 +649,8 @@ int layer_forward(bapipe_stage *st, int li, const FwdCtx &c)
         break;
     }
     case BAPIPE_SOFTMAX_XENT:
-        HIPCHK(softmax_fwd(dt, a, (float *)o, st->mb, O.C, s));
+        c.y_stored = c.y_direct && (uintptr_t)c.y_direct % sizeof(float) == 0;
+        HIPCHK(softmax_fwd(dt, a, (float *)o, st->mb, O.C, s, c.y_stored ? (float *)c.y_direct : nullptr));
         break;
     default:
         return st->fail(BAPIPE_E_UNSUPPORTED, "layer %d: kind %d", li, L.d.kind);
@@ -1431,18 +1439,20 @@ int bapipe_stage_forward(bapipe_stage_t *st, int mb_id, const void *x_dev, void 
     } else {
         c.x_direct = x_dev;
     }
+    const int last = (int)st->tensors.size() - 1;
+    const Tensor &O = st->tensors[last];
+    const Tensor &R = st->tensors[O.root];
+    // a flattened view of a spatial tensor is indexed c*H*W + h*W + w whatever the boundary layout is
+    const bool flat_of_spatial = O.root != last && R.H * R.W > 1;
+    const bool relayout = O.esize == dt_size(dt) && ((st->opts.io_layout == BAPIPE_NCHW && R.H * R.W > 1) || flat_of_spatial);
+    if (!relayout) c.y_direct = y_dev;
     for (int i = 0; i < (int)st->layers.size(); ++i) {
         int rc = layer_forward(st, i, c);
         if (rc != BAPIPE_OK) return rc;
     }
-    if (y_dev) {
-        const int last = (int)st->tensors.size() - 1;
-        const Tensor &O = st->tensors[last];
-        const Tensor &R = st->tensors[O.root];
+    if (y_dev && !c.y_stored) {
         const void *src = in_ptr(st, last, c);
-        // a flattened view of a spatial tensor is indexed c*H*W + h*W + w whatever the boundary layout is
-        const bool flat_of_spatial = O.root != last && R.H * R.W > 1;
-        if (O.esize == dt_size(dt) && ((st->opts.io_layout == BAPIPE_NCHW && R.H * R.W > 1) || flat_of_spatial))
+        if (relayout)
             HIPCHK(nhwc_to_nchw(dt, src, y_dev, st->mb, R.C, R.H, R.W, R.Cp, s));
         else
             HIPCHK(hipMemcpyAsync(y_dev, src, O.bytes(), hipMemcpyDeviceToDevice, s));

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_harness import GpuStage, compare_minibatch, gpu_minibatch, stage_io
+from gpu_harness import GpuStage, compare_minibatch, gpu_minibatch, stage_io, to_dev
 from oracle.stage import one_f_one_b_order
 from paper_2012_12544_amd import binding as B
 from stage_inputs import configs as C
@@ -246,6 +246,38 @@ def test_batch_norm_adds_partial_sums(dtype, c, hw, mb):
         b.addl(v, u, relu=1)
     st = single(build, c, hw, dtype, micro_batch=mb)
     compare_minibatch(st, verbose="batch-norm sums c%d %s x %d" % (c, hw, mb))
+
+
+# ------------------------------------------------------------------------------ a stage's output, stored by its last pass or copied
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("kind,c,hw", [("bn", 64, (9, 7)), ("bn", 128, (32, 33)), ("bn", 20, (48, 50)), ("sum", 64, (9, 7)),
+                                       ("sum", 128, (64, 33)), ("loss", 1000, (1, 1)), ("loss", 1500, (1, 1))])
+def test_output_wherever_it_lies(dtype, kind, c, hw):
+    """An address that no 16-byte access takes gets a copy; both are the stashed tensor bit for bit."""
+    b = C._Builder()
+    if kind == "loss":
+        b.linear(64, c, src=-1)
+        b.xent()
+    else:
+        u = b.bn(c, relu=kind == "bn", src=-1)
+        if kind == "sum":
+            b.addl(b.bn(c), u, relu=1)
+    cin = 64 if kind == "loss" else c
+    st = C._stage("out", b.layers, dtype, (cin,) + hw, 2, 1, 1, 1, 1, C.BASE_SEED + 79, "kaiming")
+    x = to_dev(st, stage_io(st)[0][0], B.NHWC)
+    t = torch.float32 if kind == "loss" or dtype == C.FP32 else torch.bfloat16
+    n = 2 * c * (1 if kind == "loss" else hw[0] * hw[1])
+    out = []
+    for at in (0, 8 // t.itemsize):
+        g = GpuStage(st, gen.all_params(st, perturb=True))
+        y = torch.full((n + 16,), float("nan"), device="cuda", dtype=t)
+        torch.cuda.synchronize()
+        B.bapipe_stage_forward(g.h, 0, x.data_ptr(), y[at:].data_ptr())
+        torch.cuda.synchronize()
+        assert torch.isnan(y[at + n:]).all() and torch.isnan(y[:at]).all()
+        out.append(y[at:at + n].clone())
+        g.close()
+    assert torch.equal(out[0], out[1]) and not torch.isnan(out[0]).any()
 
 
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
