@@ -91,8 +91,9 @@ hipError_t wgrad3x3_c8_mfma(const void *x, const void *dy, float *dw, float *db,
 bool conv_wgrad_mfma_supported(const ConvShape &c);
 size_t conv_wgrad_mfma_workspace(const ConvShape &c);
 // dw += dy^T x over all pixels; db (may be null) += column sums of dy
+// beside: kernels of other streams run beside the launch (as in GatherConv; results do not depend on it)
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &c, hipStream_t s);
+                           const ConvShape &c, hipStream_t s, bool beside = false);
 
 // ---- column sums over a [rows][C] matrix: out[c] += sum_r a[r][c]  (bias gradient)
 size_t colsum_workspace(int rows, int C);

@@ -958,11 +958,13 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
 #pragma unroll
         for (int b = 0; b < TB; ++b) fb[b] = tr_frag<BCI>(sb, wi * WT_CI + b * 32, k0, lane);
     };
-    auto mfma_all = [&](const bf16x8_t(&fa)[TA], const bf16x8_t(&fb)[TB]) {
+    auto add_bias = [&](const bf16x8_t(&fa)[TA]) {
         if (do_bias) {
 #pragma unroll
             for (int a = 0; a < TA; ++a) bsum[a] = frag_sum(fa[a], bsum[a]);
         }
+    };
+    auto mfma_all = [&](const bf16x8_t(&fa)[TA], const bf16x8_t(&fb)[TB]) {
 #pragma unroll
         for (int a = 0; a < TA; ++a)
 #pragma unroll
@@ -981,22 +983,56 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     WAIT_VMCNT((STAGES - 1) * NLOAD);
     WAIT_LGKMCNT(0);
     __builtin_amdgcn_s_barrier();
+    // Of large wave tiles the transposing reads of the next sub-step (two an operand fragment, 12 for 128 x 64) go out between
+    // the MFMAs, not in front of them: 512x4608 from 50176 rows 237 -> 232 us, 2304x512 132 -> 128.  (Tiles of few MFMAs, and the
+    // gather kernel's plain reads, half as many, are better off in front: 128x1152 from 10125 rows 15.9 us against 16.8.)
+    constexpr int NM = TA * TB, RPM = (2 * (TA + TB) + NM - 1) / NM;      // MFMAs of a sub-step, reads behind each
+    constexpr bool MIXED = NM >= 8;
     bf16x8_t fa0[TA], fb0[TB], fa1[TA], fb1[TB];
     load_frags(0, 0, fa0, fb0);
     int rd = 0;
     for (int kt = 0; kt < KT; ++kt) {
         const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-        load_frags(rd, 16, fa1, fb1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_all(fa0, fb0);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MIXED) {
+            add_bias(fa0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_frags(rd, 16, fa1, fb1);
+            mfma_all(fa0, fb0);
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            add_bias(fa1);
+        } else {
+            load_frags(rd, 16, fa1, fb1);
+            __builtin_amdgcn_sched_barrier(0);
+            add_bias(fa0);
+            mfma_all(fa0, fb0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         WAIT_LGKMCNT(0);
         WAIT_VMCNT((STAGES - 2) * NLOAD);
         __builtin_amdgcn_s_barrier();
-        load_frags(nx, 0, fa0, fb0);
-        __builtin_amdgcn_sched_barrier(0);
-        issue_tile(rd);
-        mfma_all(fa1, fb1);
+        if constexpr (MIXED) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_frags(nx, 0, fa0, fb0);
+            issue_tile(rd);
+            mfma_all(fa1, fb1);
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);        // address arithmetic of the loads
+                __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+            }
+        } else {
+            load_frags(nx, 0, fa0, fb0);
+            __builtin_amdgcn_sched_barrier(0);
+            issue_tile(rd);
+            add_bias(fa1);
+            mfma_all(fa1, fb1);
+        }
         __builtin_amdgcn_sched_barrier(0);
         advance_tile();
         rd = nx;
@@ -1144,7 +1180,9 @@ struct WgradPlan {
     int bko, bci, kg, tiles_ko, tiles_n, splits, pix_per_split;
 };
 
-WgradPlan wgrad_plan(const ConvShape &c)
+// beside: kernels of other streams run beside the launch.  Only the tile may depend on it, not the splits: every sum stays the
+// same, in the same order.
+WgradPlan wgrad_plan(const ConvShape &c, bool beside)
 {
     WgradPlan p;
     const int Ntot = c.R * c.S * c.C;
@@ -1170,6 +1208,15 @@ WgradPlan wgrad_plan(const ConvShape &c)
         p.kg = 1;
         p.bci = 128;
         p.bko = c.K > 128 && macs >= 8e9 && npix > 128 ? 256 : 128;
+        // One block of eight waves and 256 x 256 per unit fetches two thirds of what two of 256 x 128 do.  Where its tiles are
+        // whole and the pixels make a block per unit out of them (with the reduction: 512x4608 from 50176 rows 254 -> 231 us,
+        // 512x2304 139 -> 122, from 12544 rows 83 -> 75; 25088x4096 from 1024 rows, 1568 tiles, 316 -> 331).  Beside other kernels a
+        // short launch keeps the smaller blocks, which share a unit with theirs (512-channel 14x14 layers on three streams: 4774
+        // us per mini-batch against 4873; 28x28 13110 against 14010 for the larger).
+        const long long whole = tiles_of(256, 256);
+        if (p.bko == 256 && c.K % 256 == 0 && Ntot % 256 == 0 && whole <= 128 && whole * ((npix + 1023) / 1024) >= 224 &&
+            !(beside && npix < 25000))
+            p.bci = 256;
     }
     p.tiles_ko = (c.K + p.bko - 1) / p.bko;
     p.tiles_n = (Ntot + p.bci - 1) / p.bci;
@@ -1203,7 +1250,7 @@ WgradPlan wgrad_plan(const ConvShape &c)
     long long max_by_work = (npix + 511) / 512;
     if (max_by_work > 256) max_by_work = 256;
     if (max_by_work < 1) max_by_work = 1;
-    const long long slots = 512;
+    const long long slots = p.bci == 256 ? 256 : 512;      // half as many tiles, so the same split count
     long long want = 1;
     double best = 1e30;
     for (long long sp = 1; sp <= max_by_work; ++sp) {
@@ -1289,12 +1336,12 @@ size_t conv_wgrad_mfma_workspace(const ConvShape &c)
 {
     if (wgrad3x3_halo_supported(c)) return wgrad3x3_halo_workspace(c);
     if (wgrad3x3_c8_supported(c)) return wgrad3x3_c8_workspace(c);
-    WgradPlan p = wgrad_plan(c);
+    WgradPlan p = wgrad_plan(c, false);
     return p.splits == 1 ? 0 : (size_t)p.splits * ((size_t)c.K * c.R * c.S * c.C + c.K) * sizeof(float);
 }
 
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &shape, hipStream_t s)
+                           const ConvShape &shape, hipStream_t s, bool beside)
 {
     ConvShape c = shape;
     if (!conv_wgrad_mfma_supported(c)) return hipErrorInvalidValue;
@@ -1308,7 +1355,7 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
     }
     if (wgrad3x3_halo_supported(c)) return wgrad3x3_halo_mfma(x, dy, dw, db, workspace, c, s);
     if (wgrad3x3_c8_supported(c)) return wgrad3x3_c8_mfma(x, dy, dw, db, workspace, c, s);
-    WgradPlan p = wgrad_plan(c);
+    WgradPlan p = wgrad_plan(c, beside);
     dim3 grid((unsigned)(p.tiles_ko * p.tiles_n), (unsigned)p.splits);
     const int direct = p.splits == 1;
     const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (db ? c.K : 0);
@@ -1333,6 +1380,8 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
         WG_LAUNCH(64, 64, 2, 2, 2);
     else if (p.kg == 2)
         WG_LAUNCH(128, 64, 2, 2, 2);
+    else if (p.bci == 256)
+        WG_LAUNCH(256, 256, 2, 4, 1);
     else if (p.bko == 256)
         WG_LAUNCH(256, 128, 2, 2, 1);
     else

@@ -697,7 +697,7 @@ int run_wgrad(bapipe_stage *st, const WgradLaunch &w, bool mfma, hipStream_t s, 
 {
     const bool tp = st->tap_begin(mfma ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT, s);
     if (mfma)
-        HIPCHK(conv_wgrad_mfma(w.x, w.dy, w.layer->dw, w.layer->db, work, w.shape, s));
+        HIPCHK(conv_wgrad_mfma(w.x, w.dy, w.layer->dw, w.layer->db, work, w.shape, s, st->stream_b || st->stream_w));
     else
         HIPCHK(conv_wgrad_direct(st->dt, w.x, w.dy, w.layer->dw, w.layer->db, work, w.shape, s));
     st->tap_end(tp, w.flop, w.bytes);

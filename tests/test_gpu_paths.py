@@ -356,6 +356,7 @@ def test_wgrad_small_images(k, stride, cin, cout, hw, mb):
     (1, 1, 256, 1024, (11, 9), 2),       # one split, added to the gradient
     (3, 1, 520, 264, (30, 31), 3),       # 128-row tiles, the last of them ragged
     (1, 1, 24, 2056, (40, 40), 20),      # ... of a layer narrower than a tile
+    (3, 1, 256, 256, (56, 57), 8),       # 256 x 256 in one group, splits that end inside an image
 ])
 def test_wgrad_groups_of_waves(k, stride, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, relu=1, src=-1), cin, hw, C.BF16, micro_batch=mb)
