@@ -641,13 +641,12 @@ GatherPlan gather_plan(const GatherConv &g)
     p.bc = g.Co <= 64 ? 64 : 128;
     if (p.bp == 64) p.bc = 128;
     auto tiles_of = [&](int bp) { return p.busy * ((p.class_pix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
-    // 256-pixel tiles that cannot even fill 400 of the 512 block slots (14x14 layers, the 1x1 convs of
-    // the bottleneck blocks): halve the pixel tile rather than split K, whose fp32 partials cost more
-    // than the smaller tile loses (measured on 512-channel 14x14 layers: 73 us against 100 us)
-    // Beside kernels of other streams the 196-392 tiles of 256 x 128 stay (measured on the deep VGG stage with three
-    // streams: 18.8 -> 17.7 ms per mini-batch; alone on the chip the same choice loses 3 %).
-    const bool few = g.beside && p.bp == 256 && p.bc == 128 && tiles_of(256) < 400 && tiles_of(256) >= 128;
-    if (!few && p.bp == 256 && p.bc == 128 && tiles_of(256) < 400) p.bp = 128;
+    // Up to 400 tiles of 256 x 128 are one round of the chip (two blocks a unit); 256 x 256 would leave units without one, and
+    // twice as many of 128 x 128 come to a round and a half and fetch more (3x3 512->256 at 28x28, 64 samples, 392 tiles: 163 us
+    // against 134; 512->512 at 14x14, 196: 73 against 70; 4096->1024 from 6000 rows, 192: 77 against 70; 294 tiles, 256->128 at
+    // 56x56: 62 against 64).  Of fewer than 160 (900 rows, 4096->4096) the smaller tiles fill more of it.
+    const bool few = p.bp == 256 && p.bc == 128 && tiles_of(256) < 400;
+    if (few && tiles_of(256) < 160) p.bp = 128;
     // small products (the bottleneck blocks of ResNet: under ~8 GMAC) are bound by the latency of a block's
     // load - multiply - store chain, not by throughput: many 64-pixel blocks and no split of K were the
     // fastest choice on every such shape measured (e.g. 1x1 1024->256 at 14x14: 11.5 us against 22.2)
@@ -692,7 +691,7 @@ GatherPlan gather_plan(const GatherConv &g)
     // unit (that kernel's LDS and registers allow no more): 3x3 256->256 and 1x1 1024->256 at 14x14, 32 samples, 196
     // blocks, together 21.8 -> 18.1 us a launch; VGG-16's first linear layer 54.5 -> 48 us forward, 63.8 -> 52 gradient.
     // With more blocks than that the four smaller ones that fit a unit hide the latencies better (1x1 512->256 at 56x56,
-    // 3136 blocks: 53 us against 81).  Does not depend on `beside`: K is summed in another order.
+    // 3136 blocks: 53 us against 81).
     p.bk = p.kg == 2 ? (k64 ? 64 : 32) : p.kg == 1 && p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
     const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
