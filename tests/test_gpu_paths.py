@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from gpu_harness import GpuStage, compare_minibatch, gpu_minibatch, stage_io, to_dev
-from oracle.stage import one_f_one_b_order
+from oracle.stage import OracleStage, one_f_one_b_order
 from paper_2012_12544_amd import binding as B
 from stage_inputs import configs as C
 from stage_inputs import gen
@@ -332,6 +332,44 @@ def test_gradients_of_the_largest_linear_layers(cin, cout, mb):
 def test_avgpool_windows(dtype, k, c, hw):
     st = single(lambda b: b.avgpool(k, src=-1), c, hw, dtype)
     compare_minibatch(st, verbose="avgpool %d of %s" % (k, hw))
+
+
+# ------------------------------------------------------------------------------ max-pool gradient by cells of 2 x 2 positions
+CELLS = [
+    (2, 1, 8, (5, 6), 2),         # windows that do not overlap: position by position
+    (3, 0, 16, (8, 6), 3),        # the last row and column belong to no window
+    (3, 2, 8, (3, 1), 2),         # cells wholly in the padding, one column
+    (4, 0, 24, (4, 4), 1),        # one window
+    (4, 1, 5, (9, 10), 2),        # elements one by one in fp32
+    (4, 3, 8, (7, 2), 3),
+    (5, 2, 8, (9, 7), 2),         # wider than a cell's windows reach: so too
+]
+
+
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("k,pad,c,hw,mb", CELLS)
+def test_pool_gradient_at_stride_two(dtype, k, pad, c, hw, mb):
+    """Identical inputs on both sides; a position takes up to nine gradients, added in one order and rounded once."""
+    st = single(lambda b: b.pool(src=-1, k=k, stride=2, pad=pad), c, hw, dtype, micro_batch=mb, n_micro=1)
+    xs, gs = stage_io(st)
+    orc, gpu = OracleStage(st, gen.all_params(st)), GpuStage(st, gen.all_params(st))
+    assert np.array_equal(orc.forward(0, xs[0]), gpu.forward(0, xs[0]))
+    ref, dx = orc.backward(0, gs[0]), gpu.backward(0, gs[0])
+    gpu.close()
+    # fp32: eight additions of terms up to the largest |dy|, each within 2^-24 of a sum up to nine times that; bf16: one rounding, half an
+    # ulp of the result, on either side
+    top = float(np.max(np.abs(gs[0])))
+    assert np.allclose(ref, dx, rtol=2.0 ** -7 if dtype == C.BF16 else 0, atol=72 * 2.0 ** -24 * top)
+
+
+@pytest.mark.parametrize("k,pad,c,hw,mb", CELLS)
+def test_pool_gradient_at_stride_two_behind_a_gate_and_a_sum(k, pad, c, hw, mb):
+    def build(b):
+        t = b.conv(c, c, 1, relu=1, src=-1)
+        p = b.pool(src=t, k=k, stride=2, pad=pad)
+        u = b.conv(c, c, k, stride=2, pad=pad, src=t)
+        b.addl(p, u, relu=0)
+    compare_minibatch(single(build, c, hw, C.FP32, micro_batch=mb), verbose="pool k%d p%d of %s, gate and sum" % (k, pad, hw))
 
 
 # ------------------------------------------------------------------------------ weight gradient: steps of 32 pixels through small images
