@@ -732,32 +732,31 @@ __global__ void k_bn_bwd_apply(const T *__restrict__ x, const T *__restrict__ dy
     const int r0 = blockIdx.y * (p.RY * BN_ROWS_PER_THREAD);
     int r1 = r0 + p.RY * BN_ROWS_PER_THREAD;
     if (r1 > rows) r1 = rows;
-    constexpr int HALF = BN_ROWS_PER_THREAD / 2;
+    vec_t<T, V> a[BN_ROWS_PER_THREAD], g[BN_ROWS_PER_THREAD], old[BN_ROWS_PER_THREAD], gt[BN_ROWS_PER_THREAD];
+    // All loads of the thread first: dx may be one of the tensors read, so the compiler does not move a row's loads ahead of the
+    // store of the row before (100352 rows of 64 channels 13.5 -> 12.6 us, 25088 of 256 11.5 -> 10.6, of 512 with the gate
+    // 19.9 -> 19.7; four rows a thread 12.9, 10.8 and 21.2).
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {                               // four rows at a time: loads first, then stores
-        vec_t<T, V> a[HALF], g[HALF], old[HALF], gt[HALF];
+    for (int u = 0; u < BN_ROWS_PER_THREAD; ++u) {
+        const int r = r0 + ry + u * p.RY;
+        const size_t i = (size_t)(r < r1 ? r : r1 - 1) * p.CV + cg;
+        a[u] = xv[i];
+        g[u] = gv[i];
+        if (accum) old[u] = dv[i];
+        if (gate) gt[u] = tv[i];
+    }
 #pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int r = r0 + ry + (h * HALF + u) * p.RY;
-            const size_t i = (size_t)(r < r1 ? r : r1 - 1) * p.CV + cg;
-            a[u] = xv[i];
-            g[u] = gv[i];
-            if (accum) old[u] = dv[i];
-            if (gate) gt[u] = tv[i];
+    for (int u = 0; u < BN_ROWS_PER_THREAD; ++u) {
+        const int r = r0 + ry + u * p.RY;
+        if (r >= r1) break;
+        vec_t<T, V> o;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float xh = (to_f32(a[u].e[j]) - mu[j]) * inv[j];
+            float v = gi[j] * (to_f32(g[u].e[j]) - m1[j] - xh * m2[j]);
+            o.e[j] = grad_out<T>(v, accum != 0, old[u].e[j], gate != nullptr, gt[u].e[j]);
         }
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int r = r0 + ry + (h * HALF + u) * p.RY;
-            if (r >= r1) break;
-            vec_t<T, V> o;
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                float xh = (to_f32(a[u].e[j]) - mu[j]) * inv[j];
-                float v = gi[j] * (to_f32(g[u].e[j]) - m1[j] - xh * m2[j]);
-                o.e[j] = grad_out<T>(v, accum != 0, old[u].e[j], gate != nullptr, gt[u].e[j]);
-            }
-            dv[(size_t)r * p.CV + cg] = o;
-        }
+        dv[(size_t)r * p.CV + cg] = o;
     }
 }
 
