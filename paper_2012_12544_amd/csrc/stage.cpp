@@ -144,6 +144,7 @@ struct bapipe_stage {
     int flushed = 0;                         // micro-batches whose deferred weight gradients are already in dw
     float *losses = nullptr;
     size_t params_bytes = 0, slot_bytes = 0, transient_bytes = 0, grads_bytes = 0, work_bytes = 0;
+    size_t flush_bytes = 0;                  // workspace of flush_deferred, whatever part of a mini-batch it finds
     size_t accum_off = 0, accum_bytes = 0;   // the dw/db region inside params (zeroed together)
     // schedule
     int n_fwd = 0, n_bwd = 0;
@@ -1234,7 +1235,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         Bn.fuse_add = i;
         S.fused = true;
     }
-    size_t work = 256;
+    size_t work = 256, flush = 0;
     for (int i = 0; i < n_layers; ++i) {
         Layer &L = st->layers[i];
         const Tensor &A = st->tensors[L.a];
@@ -1316,6 +1317,14 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                     L.def_g_bytes = st->tensors[L.o].bytes();
                     size_t wd = conv_wgrad_mfma_workspace(all);
                     work = wd > work ? wd : work;
+                    // reading the gradients flushes what there is, any number of micro-batches, and the split count does
+                    // not grow with the rows alone: fewer of them can want more partial sums (128 -> 1000 features, 100
+                    // samples: 13 micro-batches 3.6 MB, 16 of them 2.6)
+                    for (int n = 1; n < n_micro; ++n) {
+                        all.N = micro_batch * n;
+                        wd = conv_wgrad_mfma_workspace(all);
+                        flush = wd > flush ? wd : flush;
+                    }
                 }
             }
             size_t w = use_mfma_wgrad(st, cs) ? conv_wgrad_mfma_workspace(cs) : conv_wgrad_direct_workspace(cs);
@@ -1343,6 +1352,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     st->transient_bytes = trans;
     st->grads_bytes = gr;
     st->work_bytes = work;
+    st->flush_bytes = flush > work ? flush : work;
 
     size_t pb = 0;
     std::vector<size_t> o_w(n_layers), o_b(n_layers), o_dw(n_layers), o_db(n_layers), o_ww(n_layers), o_wt(n_layers);
@@ -1367,14 +1377,14 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     st->stash = (char *)st->dev_alloc(st->slot_bytes * st->depth);
     st->transient = (char *)st->dev_alloc(st->transient_bytes);
     st->grads = (char *)st->dev_alloc(st->grads_bytes);
-    st->work = (char *)st->dev_alloc(st->work_bytes);
+    st->work = (char *)st->dev_alloc(st->flush_bytes);       // the handle's own; a pass on another stream or the static array needs work_bytes
     st->losses = (float *)st->dev_alloc(sizeof(float) * n_micro);
     if (defb) st->deferred = (char *)st->dev_alloc(defb);
     st->stream_f = st->stream;
     st->work_f = st->work;
     if (!st->params || !st->stash || !st->transient || !st->grads || !st->work || !st->losses || (defb && !st->deferred))
         return create_fail(BAPIPE_E_OOM, "device allocation failed (params %zu, stash %zu x %d, transient %zu, grads %zu, work %zu bytes)",
-                           st->params_bytes, st->slot_bytes, st->depth, st->transient_bytes, st->grads_bytes, st->work_bytes);
+                           st->params_bytes, st->slot_bytes, st->depth, st->transient_bytes, st->grads_bytes, st->flush_bytes);
     {
         size_t off = 0;
         for (auto &L : st->layers)

@@ -4,6 +4,7 @@ import ctypes as ct
 import pytest
 
 from paper_2012_12544_amd import binding as B
+from stage_inputs import configs as C
 
 
 def _lstm_seq_supported(n, hidden, compute_units, steps=50):
@@ -63,3 +64,45 @@ def test_pixel_tile_of_products_of_8_to_16_gmac(rows, cin, cout, k, hw, tile):
 
 def test_large_weights_are_not_streamed_by_more_rows_of_tiles_than_before():
     assert _pixel_tiles(128, 25088, 4096) == (0, 16 * 128 * 4096 * 4)
+
+
+# ------------------------------------------------------------------------------ workspace of the deferred weight gradients
+class _ConvShape(ct.Structure):
+    _fields_ = [(f, ct.c_int) for f in "N H W C P Q K R S stride pad".split()]
+
+
+def _wgrad_workspace(rows, cin, cout):
+    f = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
+    f.restype = ct.c_size_t
+    return f(ct.byref(_ConvShape(rows, 1, 1, cin, 1, 1, cout, 1, 1, 1, 0)))
+
+
+def _blocks_of_a_linear_stage(cin, cout, micro_batch, n_micro):
+    """Sizes a stage of one linear layer asks its allocator for: parameters, stash, transient, gradients, workspace.  The next
+    request is refused, so that nothing reaches a device."""
+    sizes = []
+
+    def alloc(nbytes, ctx):
+        sizes.append(nbytes)
+        return 256 * len(sizes) if len(sizes) <= 5 else None
+
+    b = C._Builder()
+    b.linear(cin, cout, src=-1)
+    st = C._stage("linear", b.layers, C.BF16, (cin, 1, 1), micro_batch, n_micro, 1, 1, 1, 0, "kaiming")
+    o = B.make_opts(st)
+    o.mem.alloc, o.mem.free = B.ALLOC_FN(alloc), B.FREE_FN(lambda ptr, ctx: None)
+    with pytest.raises(B.BapipeError) as e:
+        B.bapipe_stage_create(b.layers, micro_batch, n_micro, o)
+    assert e.value.status == B.E_OOM
+    return sizes[:5]
+
+
+@pytest.mark.parametrize("cin,cout,micro_batch,n_micro", [
+    (128, 1000, 100, 16),          # 13 micro-batches want more partial sums than 16
+    (256, 512, 100, 16), (256, 256, 128, 16), (512, 512, 96, 24), (64, 64, 50, 40), (1024, 1000, 64, 16), (4096, 4096, 100, 40),
+])
+def test_workspace_holds_the_weight_gradient_of_any_part_of_a_mini_batch(cin, cout, micro_batch, n_micro):
+    """Reading the gradients in the middle of a mini-batch runs the deferred product over the micro-batches so far, the update
+    runs it over the rest."""
+    have = _blocks_of_a_linear_stage(cin, cout, micro_batch, n_micro)[4]
+    assert have >= max(_wgrad_workspace(micro_batch * n, cin, cout) for n in range(1, n_micro + 1))

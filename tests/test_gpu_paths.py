@@ -401,6 +401,45 @@ def test_wgrad_groups_of_waves(k, stride, cin, cout, hw, mb):
     compare_minibatch(st, verbose="wgrad groups k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
 
 
+# ------------------------------------------------------------------------------ gradients read in the middle of a mini-batch
+@pytest.mark.parametrize("cin,cout,mb,n_micro,at", [
+    (128, 1000, 100, 16, (13,)),      # 13 micro-batches take seven copies of the partial sums, 16 take five
+    (256, 256, 128, 16, (15,)),
+    (64, 72, 9, 5, (1, 2, 4)),
+])
+def test_gradients_read_in_the_middle_of_a_mini_batch(monkeypatch, cin, cout, mb, n_micro, at):
+    """The deferred product over the micro-batches so far, then over the rest; what lies behind each block of the stage's
+    memory stays as it is."""
+    guard = 1 << 21
+
+    class Guarded(B.TorchAllocator):
+        def _alloc(self, nbytes, ctx):
+            p = super()._alloc(nbytes + guard, ctx)
+            t = self.live[p]
+            self.behind = getattr(self, "behind", []) + [t[p - t.data_ptr() + nbytes:][:guard].fill_(0xA5)]
+            torch.cuda.synchronize()
+            return p
+
+    monkeypatch.setattr(B, "TorchAllocator", Guarded)
+    st = single(lambda b: b.linear(cin, cout, src=-1), cin, (1, 1), C.BF16, micro_batch=mb, n_micro=n_micro)
+    g = GpuStage(st, gen.all_params(st))
+    xs, gs = stage_io(st)
+    bf16 = lambda a: torch.from_numpy(a.reshape(mb, -1)).bfloat16().double().numpy()
+    dw, db = np.zeros((cout, cin)), np.zeros(cout)
+    for m in range(n_micro):
+        g.forward(m, xs[m])
+        g.backward(m, gs[m])
+        dw += bf16(gs[m]).T @ bf16(xs[m])
+        db += bf16(gs[m]).sum(axis=0)
+        if m + 1 in at or m + 1 == n_micro:
+            got = g.grads(0)
+            # fp32 sums of up to 2048 products: the error of a random order is about sqrt(2048) 2^-24 = 3e-6
+            assert np.linalg.norm(got[0] - dw) < 1e-5 * np.linalg.norm(dw), m
+            assert np.linalg.norm(got[1] - db) < 1e-5 * np.linalg.norm(db), m
+    assert len(g.alloc.behind) >= 6 and all(bool((t == 0xA5).all()) for t in g.alloc.behind)
+    g.close()
+
+
 # ------------------------------------------------------------------------------ weight update: ragged tiles, both access widths, both copies
 def _mini_batch(gpu, stage, xs, gs):
     out = []
