@@ -101,6 +101,9 @@ __global__ void k_conv_gather(const T *__restrict__ in, const T *__restrict__ wt
 //   dy[n,p,q,k] * x[n, p*stride+r-pad, q*stride+s-pad, c] ;  chunk = blockIdx.y
 // The K elements behind the filter's (bias != 0) are the sums of dy alone.  As two launches of their own behind this one they
 // took as long as the rest of a small layer's weight gradient (16 channels, 3x3, four 32x32 images: 8.4 + 2.7 us, and 5.7 + 2.1).
+// A wide filter has few chunks, so these sums are long (512->512 3x3, four 28x28 images: 448 pixels a chunk): eights are added
+// in float and the eights in double (against 64 bits, normal gradients: 5.9e-8 there, 3.7e-7 one by one in float, 8.5e-8 by
+// column sums; all of it in double the smallest stage's mini-batch takes 229 us instead of 218).
 template <class T>
 __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restrict__ dy,
                                      float *__restrict__ part, ConvShape c, int rows_per_chunk, int bias)
@@ -114,14 +117,14 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
     if (i >= weights) {
         const T *d = dy + (i - weights);
         const size_t at = (size_t)row0 * c.Q, end = (size_t)row1 * c.Q;      // the chunk's pixels are consecutive
+        double sum = 0.0;
         for (size_t p = at; p < end; p += 8) {
             float a[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) a[u] = p + u < end ? to_f32(d[(p + u) * c.K]) : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += a[u];
+            sum += (double)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
         }
-        part[(size_t)blockIdx.y * total + i] = acc;
+        part[(size_t)blockIdx.y * total + i] = (float)sum;
         return;
     }
     int ci = (int)(i % c.C);
@@ -199,20 +202,21 @@ template <int LANES> __global__ void k_wgrad_reduce(const float *__restrict__ pa
 
 constexpr size_t DIRECT_PARTS = (size_t)16 << 20;              // floats of partial sums (64 MiB)
 inline size_t direct_wgrad_weights(const ConvShape &c) { return (size_t)c.K * c.R * c.S * c.C; }
-// the bias gradient rides along where one chunk of both is no more than that
-inline size_t direct_wgrad_elements(const ConvShape &c)
-{
-    const size_t w = direct_wgrad_weights(c);
-    return w + c.K <= DIRECT_PARTS ? w + c.K : w;
-}
 inline int direct_wgrad_chunks(const ConvShape &c)
 {
-    const size_t total = direct_wgrad_elements(c);
+    const size_t weights = direct_wgrad_weights(c);
     int rows = c.N * c.P;
-    size_t cap = DIRECT_PARTS / (total ? total : 1);
+    size_t cap = DIRECT_PARTS / (weights ? weights : 1);
     int chunks = rows < 1024 ? rows : 1024;
     if ((size_t)chunks > cap) chunks = (int)cap;
     return chunks < 1 ? 1 : chunks;
+}
+// The bias gradient rides along where that leaves the filter's sums their chunks (not for 2048->4096, or
+// 8->2048 from 911 image rows).
+inline size_t direct_wgrad_elements(const ConvShape &c)
+{
+    const size_t w = direct_wgrad_weights(c);
+    return direct_wgrad_chunks(c) * (w + c.K) <= DIRECT_PARTS ? w + c.K : w;
 }
 
 }  // namespace

@@ -326,6 +326,32 @@ def test_gradients_of_the_largest_linear_layers(cin, cout, mb):
         assert np.allclose(dw[k], dy[:, k].astype(np.float64) @ x.reshape(mb, cin), rtol=0, atol=2.0 ** -20)
 
 
+@pytest.mark.parametrize("dtype,k,cin,cout,hw,mb", [
+    (C.FP32, 3, 512, 512, 28, 8),      # seven chunks of 896 pixels
+    (C.FP32, 3, 12, 20, 224, 2),       # one image row a chunk
+    (C.FP32, 1, 8, 2048, 31, 30),      # 930 image rows: the bias gradient would cost the filter chunks, column sums
+    (C.FP32, 1, 2048, 4096, 8, 1),     # two chunks; the same
+    (C.BF16, 3, 252, 252, 28, 2),      # channels that the matrix kernels do not take
+])
+def test_direct_bias_gradient_of_wide_layers(dtype, k, cin, cout, hw, mb):
+    """Gradients of one sign, so a rounding is at most 2^-24 of the result.  Riding along: three levels of an eight, the chunk's sum,
+    the total.  Column sums of these shapes: a run of up to 57 floats (the k-th of its sums is k/57 of it: 29 in all), the total."""
+    st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, (hw, hw), dtype, micro_batch=mb, n_micro=1, need_input_grad=0)
+    g = GpuStage(st, [(None, None)])
+    rng = np.random.default_rng(cout)
+    dy = rng.random((mb, cout, hw, hw), dtype=np.float32)
+    if dtype == C.BF16:
+        dy = torch.from_numpy(dy).bfloat16().float().numpy()
+    g.forward(0, np.ones((mb, cin, hw, hw), np.float32))
+    g.backward(0, dy)
+    dw, db = B.bapipe_stage_get_grads(g.h, 0, (cout, cin, k, k), (cout,))
+    g.close()
+    exact = dy.sum(axis=(0, 2, 3), dtype=np.float64)
+    roundings = 30 if k == 1 else 5
+    worst = float(np.max(np.abs(db - exact) / exact))
+    assert worst <= roundings * 2.0 ** -24
+
+
 # ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("k,c,hw", [(1, 8, (3, 4)), (2, 24, (7, 4)), (3, 5, (10, 9)), (5, 16, (5, 11)), (6, 8, (13, 6))])
