@@ -808,7 +808,7 @@ template <int BKO, int BCI, int WKO, int WCI, int STAGES, int KG = 1>
 __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(const bf16_t *__restrict__ x,
                                                                   const bf16_t *__restrict__ dy,
                                                                   float *part, float *bpart, size_t split_stride,
-                                                                  ConvShape c, int tiles_n, int pix_per_split,
+                                                                  ConvShape c, int tiles_n, int pix_per_split, int part_tiles,
                                                                   int add_to_dst, unsigned x_bytes,
                                                                   unsigned dy_bytes)
 {
@@ -953,6 +953,36 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     float bsum[TA];
 #pragma unroll
     for (int a = 0; a < TA; ++a) bsum[a] = 0.0f;
+    // Groups of waves: a product takes fewer splits, so a group's sum has more terms than a split's had.  It is put aside and started
+    // anew every part_tiles tiles: 320x2880 from 3136 rows, one split, 1.08e-7 off 64 bits (normal operands) where one sum was
+    // 2.3e-7 and seven splits of 448 rows 1.24e-7; 16 registers of 128 more and 0.2 % of a mini-batch.
+    constexpr int FA = KG > 1 ? TA : 1, FB = KG > 1 ? TB : 1;
+    f32x16_t aside[FA][FB];
+    float baside[FA];
+#pragma unroll
+    for (int a = 0; a < FA; ++a) {
+        baside[a] = 0.0f;
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) aside[a][b][v] = 0.0f;
+    }
+    auto fold = [&]() {
+        if constexpr (KG > 1) {
+#pragma unroll
+            for (int a = 0; a < TA; ++a) {
+                baside[a] += bsum[a];
+                bsum[a] = 0.0f;
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        aside[a][b][v] += acc[a][b][v];
+                        acc[a][b][v] = 0.0f;
+                    }
+            }
+        }
+    };
 
     auto load_frags = [&](int stage, int k0, bf16x8_t(&fa)[TA], bf16x8_t(&fb)[TB]) {
         const uint16_t *sa = ring + stage * STAGE_ELEMS, *sb = sa + BKP * BKO;
@@ -993,53 +1023,57 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     constexpr bool MIXED = NM >= 8;
     bf16x8_t fa0[TA], fb0[TB], fa1[TA], fb1[TB];
     load_frags(0, 0, fa0, fb0);
-    int rd = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-        const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-        if constexpr (MIXED) {
-            add_bias(fa0);
-            __builtin_amdgcn_sched_barrier(0);
-            load_frags(rd, 16, fa1, fb1);
-            mfma_all(fa0, fb0);
+    int rd = 0, kt = 0, end = 0;
+    do {
+        end = KG == 1 || end + part_tiles > KT ? KT : end + part_tiles;
+        for (; kt < end; ++kt) {
+            const int nx = rd + 1 == STAGES ? 0 : rd + 1;
+            if constexpr (MIXED) {
+                add_bias(fa0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_frags(rd, 16, fa1, fb1);
+                mfma_all(fa0, fb0);
 #pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+                for (int i = 0; i < NM; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                add_bias(fa1);
+            } else {
+                load_frags(rd, 16, fa1, fb1);
+                __builtin_amdgcn_sched_barrier(0);
+                add_bias(fa0);
+                mfma_all(fa0, fb0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            WAIT_LGKMCNT(0);
+            WAIT_VMCNT((STAGES - 2) * NLOAD);
+            __builtin_amdgcn_s_barrier();
+            if constexpr (MIXED) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_frags(nx, 0, fa0, fb0);
+                issue_tile(rd);
+                mfma_all(fa1, fb1);
+#pragma unroll
+                for (int i = 0; i < NM; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);        // address arithmetic of the loads
+                    __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+                }
+            } else {
+                load_frags(nx, 0, fa0, fb0);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_tile(rd);
+                add_bias(fa1);
+                mfma_all(fa1, fb1);
             }
             __builtin_amdgcn_sched_barrier(0);
-            add_bias(fa1);
-        } else {
-            load_frags(rd, 16, fa1, fb1);
-            __builtin_amdgcn_sched_barrier(0);
-            add_bias(fa0);
-            mfma_all(fa0, fb0);
-            __builtin_amdgcn_sched_barrier(0);
+            advance_tile();
+            rd = nx;
         }
-        WAIT_LGKMCNT(0);
-        WAIT_VMCNT((STAGES - 2) * NLOAD);
-        __builtin_amdgcn_s_barrier();
-        if constexpr (MIXED) {
-            __builtin_amdgcn_sched_barrier(0);
-            load_frags(nx, 0, fa0, fb0);
-            issue_tile(rd);
-            mfma_all(fa1, fb1);
-#pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);        // address arithmetic of the loads
-                __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
-            }
-        } else {
-            load_frags(nx, 0, fa0, fb0);
-            __builtin_amdgcn_sched_barrier(0);
-            issue_tile(rd);
-            add_bias(fa1);
-            mfma_all(fa1, fb1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        advance_tile();
-        rd = nx;
-    }
+        fold();
+    } while (KG > 1 && end < KT);
     WAIT_VMCNT(0);
 
     if constexpr (KG > 1) {
@@ -1056,11 +1090,11 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
             for (int b = 0; b < TB; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    sums[(kg * BKO + wk * WT_KO + a * 32 + 8 * (v >> 2) + 4 * half + (v & 3)) * PITCH + wi * WT_CI + b * 32 + col] = acc[a][b][v];
+                    sums[(kg * BKO + wk * WT_KO + a * 32 + 8 * (v >> 2) + 4 * half + (v & 3)) * PITCH + wi * WT_CI + b * 32 + col] = aside[a][b][v];
         if (do_bias) {
 #pragma unroll
             for (int a = 0; a < TA; ++a) {
-                const float t = bsum[a] + __shfl_xor(bsum[a], 32, 64);
+                const float t = baside[a] + __shfl_xor(baside[a], 32, 64);
                 if (half == 0) sbias[kg * BKO + wk * WT_KO + a * 32 + col] = t;
             }
         }
@@ -1148,39 +1182,40 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
 }
 
 // dw[i] += sum_k part[k][i].  A block owns 64 float4 columns; its 4 split-lanes walk the partials
-// with stride 4 and are combined through LDS in lane order (the result does not depend on timing).
+// with stride 4 and are combined through LDS in lane order (the result does not depend on timing), in double: the layers of
+// most rows have up to 256 partials (64x64 from 100352 rows, normal operands, 8.9e-8 off 64 bits; in float 1.7e-7).
 // Entries past total_w are the bias partials and go to db.  total_w and total are multiples of 4
 // (channel counts are multiples of 8).
 __global__ void k_splitk_reduce(const float *__restrict__ part, float *dw, float *db, size_t total_w, size_t total,
                                 int splits)
 {
-    __shared__ float4 red[4][64];
+    __shared__ double red[4][4][64];
     const int col = threadIdx.x & 63, sl = threadIdx.x >> 6;
     const size_t i = ((size_t)blockIdx.x * 64 + col) * 4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
     if (i < total) {
 #pragma unroll 4
         for (int k = sl; k < splits; k += 4) {
-            float4 v = *reinterpret_cast<const float4 *>(part + (size_t)k * total + i);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+            const float4 v = *reinterpret_cast<const float4 *>(part + (size_t)k * total + i);
+            acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
         }
     }
-    red[sl][col] = acc;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[sl][q][col] = acc[q];
     __syncthreads();
     if (sl == 0 && i < total) {
         float *out = i < total_w ? dw + i : db + (i - total_w);
         float4 d = *reinterpret_cast<float4 *>(out);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float4 v = red[k][col];
-            d.x += v.x; d.y += v.y; d.z += v.z; d.w += v.w;
-        }
+        for (int q = 0; q < 4; ++q) acc[q] = ((red[0][q][col] + red[1][q][col]) + red[2][q][col]) + red[3][q][col];
+        d.x += (float)acc[0]; d.y += (float)acc[1]; d.z += (float)acc[2]; d.w += (float)acc[3];
         *reinterpret_cast<float4 *>(out) = d;
     }
 }
 
 struct WgradPlan {
     int bko, bci, kg, tiles_ko, tiles_n, splits, pix_per_split;
+    int part_tiles;          // wave groups: tiles of 32 pixels that a group adds up before it puts the sum aside
 };
 
 // beside: kernels of other streams run beside the launch.  Only the tile may depend on it, not the splits: every sum stays the
@@ -1203,6 +1238,7 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside)
     const bool narrow = c.K <= 64 || Ntot <= 64;
     p.kg = 2;
     p.bci = 64;
+    p.part_tiles = 0;
     if (tiles_of(64, 64) <= 1024 && (c.K <= 64 || macs < 3e9)) {
         p.bko = 64;
     } else if (tiles_of(128, 64) <= 512 && (narrow || macs < 14e9)) {
@@ -1243,6 +1279,9 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside)
         const long long pps = ((npix + want - 1) / want + 63) / 64 * 64;
         p.pix_per_split = (int)pps;
         p.splits = npix > 0 ? (int)((npix + pps - 1) / pps) : 1;
+        // equal parts of at most 12 tiles, 384 pixels
+        const int tiles_g = (int)(pps / 64), parts = (tiles_g + 11) / 12;
+        p.part_tiles = parts ? (tiles_g + parts - 1) / parts : 1;
         return p;
     }
     // Split count: the chip holds 512 blocks at once (256 CUs x 2), and a launch whose block count is
@@ -1375,7 +1414,7 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
             attr_set = true;                                                                               \
         }                                                                                                  \
         hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * KG_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)dy, part, bpart, \
-                           total, c, p.tiles_n, p.pix_per_split, direct, x_bytes, dy_bytes);               \
+                           total, c, p.tiles_n, p.pix_per_split, p.part_tiles, direct, x_bytes, dy_bytes); \
     } while (0)
     const unsigned x_bytes = (unsigned)((size_t)c.N * c.H * c.W * c.C * 2);
     const unsigned dy_bytes = (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2);

@@ -412,6 +412,31 @@ def test_wgrad_small_images(k, stride, cin, cout, hw, mb):
     compare_minibatch(st, verbose="wgrad k%d s%d %d->%d %s x %d" % (k, stride, cin, cout, hw, mb))
 
 
+@pytest.mark.parametrize("k,cin,cout,hw,mb", [
+    (3, 320, 320, 28, 4),       # one split: 49 tiles a group of waves
+    (1, 1024, 1024, 51, 1),     # 41 of them, ragged
+    (1, 1024, 4096, 40, 2),     # the wider of the two tiles
+    (1, 64, 64, 56, 32),        # many splits
+])
+def test_wgrad_sums_are_short(k, cin, cout, hw, mb):
+    """Operands of one sign.  A part of 384 pixels is 24 sums of 16 products, each rounded to half a unit, 2^-24/sqrt(3) of the sum so
+    far on average: sqrt(24/3) of that for the part, independent parts of a group added up the same way, a split's partial and
+    the total rounded once more: 6e-8 at most for the shapes here.  Twice that is allowed; one sum of 1568 pixels is at 1.5e-7."""
+    st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, (hw, hw), C.BF16, micro_batch=mb, n_micro=1, need_input_grad=0)
+    g = GpuStage(st, [(None, None)])
+    rng = np.random.default_rng(cin + cout)
+    x, dy = (torch.from_numpy(rng.random((mb, c, hw, hw), dtype=np.float32)).bfloat16().double() for c in (cin, cout))
+    g.forward(0, x.float().numpy())
+    g.backward(0, dy.float().numpy())
+    dw, db = B.bapipe_stage_get_grads(g.h, 0, (cout, cin, k, k), (cout,))
+    g.close()
+    cols = torch.nn.functional.unfold(x, k, padding=k // 2).permute(1, 0, 2).reshape(cin * k * k, -1)
+    rows = dy.permute(1, 0, 2, 3).reshape(cout, -1)
+    off = lambda got, exact: float(np.linalg.norm(got - exact) / np.linalg.norm(exact))
+    e = (off(dw.reshape(cout, -1), (rows @ cols.t().contiguous()).numpy()), off(db, rows.sum(dim=1).numpy()))
+    assert max(e) < 1.2e-7
+
+
 @pytest.mark.parametrize("k,stride,cin,cout,hw,mb", [
     (1, 1, 64, 64, (5, 6), 1),           # 30 pixels: the second group of waves has none
     (3, 1, 72, 136, (7, 9), 1),          # 63 pixels: one short of a step of both groups; ragged tiles both ways
