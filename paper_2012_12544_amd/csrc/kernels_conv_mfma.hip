@@ -555,11 +555,22 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     if (tid < BC && co0 + tid < g.Co) {
         float2 t = make_float2(0.0f, 0.0f);
         if (bn_x) {
-#pragma unroll 8
-            for (int k = 0; k < RG; ++k) {
-                t.x += red[(k * 2 + 0) * BC + tid];
-                t.y += red[(k * 2 + 1) * BC + tid];
+            // eights in float, the eights in double: one after the other, the 64 of a 64 x 64 tile of wave groups left dgamma of
+            // 784 rows 1.2e-7 off 64 bits (7.7e-8 so; 8.6e-8 where one launch reads such a tensor whole)
+            static_assert(RG % 8 == 0, "whole eights");
+            double tx = 0.0, ty = 0.0;
+#pragma unroll 2
+            for (int k = 0; k < RG; k += 8) {
+                float e[8], f[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    e[u] = red[((k + u) * 2 + 0) * BC + tid];
+                    f[u] = red[((k + u) * 2 + 1) * BC + tid];
+                }
+                tx += (double)(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
+                ty += (double)(((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])));
             }
+            t = make_float2((float)tx, (float)ty);
         } else {
 #pragma unroll
             for (int k = 0; k < GROUPS; ++k) {

@@ -248,6 +248,33 @@ def test_batch_norm_adds_partial_sums(dtype, c, hw, mb):
     compare_minibatch(st, verbose="batch-norm sums c%d %s x %d" % (c, hw, mb))
 
 
+@pytest.mark.parametrize("c,hw,mb", [(1024, 14, 4), (512, 7, 32), (256, 14, 10)])
+def test_batch_norm_sums_of_a_neighbouring_conv_are_exact(c, hw, mb):
+    """Between two convolutions that pass everything on, up to 2048 rows: the second one's gradient leaves the sums of dy and
+    dy*xhat.  Random terms: each carries three roundings (difference, product, product), is added up in eights (three levels),
+    the eights' total is rounded once per tile and the total once: a relative error of sqrt(8) 2^-24/sqrt(3) = 1e-7 if every
+    rounding were of the worst mantissa, 8e-8 on average; one after the other in float it is 1.2e-7."""
+    def build(b):
+        b.conv(c, c, 1, bias=0, src=-1)
+        b.bn(c, relu=1)
+        b.conv(c, c, 1, bias=0)
+    st = single(build, c, (hw, hw), C.BF16, micro_batch=mb, n_micro=1)
+    eye = np.eye(c, dtype=np.float32).reshape(c, c, 1, 1)
+    g = GpuStage(st, [(eye, None), (np.ones(c, np.float32), np.zeros(c, np.float32)), (eye, None)])
+    xs, gs = stage_io(st)
+    y = g.forward(0, xs[0])
+    g.backward(0, gs[0])
+    dgamma, dbeta = g.grads(1)
+    g.close()
+    x, dy = (torch.from_numpy(a[0]).bfloat16().double().numpy() for a in (xs, gs))
+    mean, var = (f(x, axis=(0, 2, 3), keepdims=True) for f in (np.mean, np.var))
+    dy = dy * (y > 0)
+    off = lambda got, exact: float(np.linalg.norm(got - exact) / np.linalg.norm(exact))
+    eps = float(np.float32(st["layers"][1]["eps"]))
+    e = (off(dgamma, (dy * (x - mean) / np.sqrt(var + eps)).sum(axis=(0, 2, 3))), off(dbeta, dy.sum(axis=(0, 2, 3))))
+    assert max(e) < 1e-7
+
+
 # ------------------------------------------------------------------------------ a stage's output, stored by its last pass or copied
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("kind,c,hw", [("bn", 64, (9, 7)), ("bn", 128, (32, 33)), ("bn", 20, (48, 50)), ("sum", 64, (9, 7)),
