@@ -53,7 +53,7 @@ template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, b
 __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
-    int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split,
+    int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split, int part_tiles,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
     const bf16_t *old_from)
 {
@@ -264,6 +264,33 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
 
+    // These tiles take all of a K that was split over blocks before, so that an accumulator would add more terms than a split's did.
+    // Its sum is put aside and started anew every part_tiles K-tiles: sums of one sign, 3x3 512->512 from 1568 pixels, 5.0e-8 off 64
+    // bits where one sum per group was 1.7e-7 and six splits 7.2e-8; 256->64 from 25088 6.1e-8, 2.9e-7 and 8.6e-8.  16 registers
+    // (32 of 128 x 64) more, and up to 0.4 % of a mini-batch of small layers.
+    constexpr bool PARTS = KG > 1 || BC == 64;
+    constexpr int AC = PARTS ? TC : 1, AP = PARTS ? TP : 1;
+    f32x16_t aside[AC][AP];
+#pragma unroll
+    for (int a = 0; a < AC; ++a)
+#pragma unroll
+        for (int b = 0; b < AP; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) aside[a][b][v] = 0.0f;
+    auto put_aside = [&]() {
+        if constexpr (PARTS) {
+#pragma unroll
+            for (int a = 0; a < TC; ++a)
+#pragma unroll
+                for (int b = 0; b < TP; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        aside[a][b][v] += acc[a][b][v];
+                        acc[a][b][v] = 0.0f;
+                    }
+        }
+    };
+
     const int frow = lane & 31, fhalf = lane >> 5;
     // operand fragments of K-sub-step ks16 of the tile in ring slot `stage`
     auto load_frags = [&](int stage, int ks16, bf16x8_t(&fa)[TC], bf16x8_t(&fb)[TP]) {
@@ -324,51 +351,65 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
 #pragma unroll
         for (int j = 0; j < KSUB; ++j) load_frags(0, j, fa[0][j], fb[0][j]);
         int rd = 0;
-        for (int it = 0; it < n_it; it += 2) {
+        int it = 0, end = 0;
+        do {
+            end = !PARTS || end + part_tiles > n_it ? n_it : end + part_tiles;       // part_tiles is even
+            for (; it < end; it += 2) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {             // two tiles a trip: which half holds what is known when compiling
-                if (it + h >= n_it) break;
-                const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-                WAIT_LGKMCNT(0);                      // this wave holds all of tile it + h
-                WAIT_VMCNT((STAGES - 2) * NLOAD);     // its share of the next one has landed
-                __builtin_amdgcn_s_barrier();
+                for (int h = 0; h < 2; ++h) {             // two tiles a trip: which half holds what is known when compiling
+                    if (it + h >= end) break;
+                    const int nx = rd + 1 == STAGES ? 0 : rd + 1;
+                    WAIT_LGKMCNT(0);                      // this wave holds all of tile it + h
+                    WAIT_VMCNT((STAGES - 2) * NLOAD);     // its share of the next one has landed
+                    __builtin_amdgcn_s_barrier();
 #pragma unroll
-                for (int j = 0; j < KSUB; ++j) load_frags(nx, j, fa[h ^ 1][j], fb[h ^ 1][j]);
-                __builtin_amdgcn_sched_barrier(0);
-                issue_tile(rd);
+                    for (int j = 0; j < KSUB; ++j) load_frags(nx, j, fa[h ^ 1][j], fb[h ^ 1][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_tile(rd);
 #pragma unroll
-                for (int j = 0; j < KSUB; ++j) mfma_all(fa[h][j], fb[h][j]);
-                __builtin_amdgcn_sched_barrier(0);
-                advance_tile();
-                rd = nx;
+                    for (int j = 0; j < KSUB; ++j) mfma_all(fa[h][j], fb[h][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    advance_tile();
+                    rd = nx;
+                }
             }
-        }
+            put_aside();
+        } while (PARTS && end < n_it);
     } else {
         static_assert(BK == 64 || KSUB == 2, "pipeline below is written for two sub-steps per tile");
         bf16x8_t fa0[TC], fb0[TP], fa1[TC], fb1[TP];
         load_frags(0, 0, fa0, fb0);
         int rd = 0;
-        for (int it = 0; it < n_it; ++it) {
-            const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-            load_frags(rd, 1, fa1, fb1);
-            __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
-            mfma_all(fa0, fb0);
-            __builtin_amdgcn_sched_barrier(0);
-            WAIT_LGKMCNT(0);                              // this wave has read all of tile kt
-            WAIT_VMCNT((STAGES - 2) * NLOAD);             // its share of tile kt+1 has landed
-            __builtin_amdgcn_s_barrier();
-            load_frags(nx, 0, fa0, fb0);
-            __builtin_amdgcn_sched_barrier(0);
-            issue_tile(rd);                               // tile kt+STAGES into the slot just retired; its address
-            mfma_all(fa1, fb1);                           // arithmetic is free to mix with these MFMAs
-            __builtin_amdgcn_sched_barrier(0);
-            advance_tile();
-            rd = nx;
-        }
+        int it = 0, end = 0;
+        do {
+            end = !PARTS || end + part_tiles > n_it ? n_it : end + part_tiles;
+            for (; it < end; ++it) {
+                const int nx = rd + 1 == STAGES ? 0 : rd + 1;
+                load_frags(rd, 1, fa1, fb1);
+                __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
+                mfma_all(fa0, fb0);
+                __builtin_amdgcn_sched_barrier(0);
+                WAIT_LGKMCNT(0);                              // this wave has read all of tile kt
+                WAIT_VMCNT((STAGES - 2) * NLOAD);             // its share of tile kt+1 has landed
+                __builtin_amdgcn_s_barrier();
+                load_frags(nx, 0, fa0, fb0);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_tile(rd);                               // tile kt+STAGES into the slot just retired; its address
+                mfma_all(fa1, fb1);                           // arithmetic is free to mix with these MFMAs
+                __builtin_amdgcn_sched_barrier(0);
+                advance_tile();
+                rd = nx;
+            }
+            put_aside();
+        } while (PARTS && end < n_it);
     }
     WAIT_VMCNT(0);
     __syncthreads();
 
+    auto &sums_of = [&]() -> auto & {
+        if constexpr (PARTS) return aside;
+        else return acc;
+    }();
     // threads that move the finished tile in 16-byte units
     constexpr int CH8 = BC / 8;                 // 16-byte units per pixel row
     constexpr int ET = NT < BP * CH8 ? NT : BP * CH8;
@@ -382,7 +423,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<float4 *>(park + (kg * BP + wp * WT_P + b * 32 + frow) * PITCH + wc * WT_C + a * 32 + 8 * q + 4 * fhalf) =
-                        make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
+                        make_float4(sums_of[a][b][4 * q], sums_of[a][b][4 * q + 1], sums_of[a][b][4 * q + 2], sums_of[a][b][4 * q + 3]);
         __syncthreads();
         constexpr int F4 = BC / 4;
         for (int i = tid; i < BP * F4; i += NT) {
@@ -422,7 +463,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
                     const int co = co0 + wc * WT_C + a * 32 + 8 * q + 4 * fhalf;
                     if (p < npix && co < g.Co)
                         *reinterpret_cast<float4 *>(dst + (size_t)p * g.Co + co) =
-                            make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
+                            make_float4(sums_of[a][b][4 * q], sums_of[a][b][4 * q + 1], sums_of[a][b][4 * q + 2], sums_of[a][b][4 * q + 3]);
                 }
             }
         return;
@@ -440,8 +481,8 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
 #pragma unroll
             for (int b = 0; b < TP; ++b) {
                 const int prow = wp * WT_P + b * 32 + frow;              // pixel inside the tile
-                float v0 = acc[a][b][4 * q] + bv.x, v1 = acc[a][b][4 * q + 1] + bv.y;
-                float v2 = acc[a][b][4 * q + 2] + bv.z, v3 = acc[a][b][4 * q + 3] + bv.w;
+                float v0 = sums_of[a][b][4 * q] + bv.x, v1 = sums_of[a][b][4 * q + 1] + bv.y;
+                float v2 = sums_of[a][b][4 * q + 2] + bv.z, v3 = sums_of[a][b][4 * q + 3] + bv.w;
                 if (relu) {
                     v0 = fmaxf(v0, 0.0f);
                     v1 = fmaxf(v1, 0.0f);
@@ -614,7 +655,7 @@ __global__ void k_gather_splitk_reduce(const float *__restrict__ part, int split
 }
 
 struct GatherPlan {
-    int bp, bc, bk, kg, splits, kt_per_split;
+    int bp, bc, bk, kg, splits, kt_per_split, part_tiles;
     int classes;             // 1, or the classes of a PHASED launch
     int busy;                // classes that have taps
     long long class_pix;     // output pixels of the largest class
@@ -717,6 +758,9 @@ GatherPlan gather_plan(const GatherConv &g)
     if (want < 1 || p.classes > 1) want = 1;
     p.kt_per_split = (int)((KT + want - 1) / want);
     p.splits = (KT + p.kt_per_split - 1) / p.kt_per_split;
+    // equal parts of at most 384 of K
+    const int in_group = (p.kt_per_split + p.kg - 1) / p.kg, parts = (in_group * BK + 383) / 384;
+    p.part_tiles = parts > 1 ? ((in_group + parts - 1) / parts + 1) / 2 * 2 : in_group + 1;
     return p;
 }
 
@@ -752,7 +796,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         }                                                                                                         \
         hipLaunchKernelGGL(kfn, grid, dim3(NT), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,          \
                            (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g, tiles_c, in_bytes, \
-                           wt_bytes, part, plan.kt_per_split, stat_part, (const bf16_t *)bn_x, bn_stats,         \
+                           wt_bytes, part, plan.kt_per_split, plan.part_tiles, stat_part, (const bf16_t *)bn_x, bn_stats,         \
                            (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask

@@ -229,6 +229,32 @@ def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
     compare_minibatch(st, verbose="bottleneck %d/%d %s x %d" % (cin, mid, hw, mb))
 
 
+@pytest.mark.parametrize("k,cin,cout,hw,mb", [
+    (3, 512, 512, 7, 32),       # 64 x 64, two groups: 36 K-tiles of 64 each
+    (1, 4096, 1000, 1, 64),     # 32 x 32, eight
+    (7, 1024, 32, 15, 4),       # 49 taps, flattened order of K
+    (3, 256, 64, 28, 32),       # 128 x 64, no groups
+    (3, 1024, 32, 47, 13),
+])
+def test_conv_sums_are_short(k, cin, cout, hw, mb):
+    """Terms of one sign on an image that is the same everywhere, and a bias that takes the exact sum away: what is left away from
+    the border is the error of the sum.  Each of the 24 sums of a part of 384 terms is rounded by at most 2^-24/sqrt(3) of itself
+    on average, the k-th of 24 being k/24 of the part: 1e-7 for a part, less for several; adding up to 24 parts the same."""
+    st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, (hw, hw), C.BF16, micro_batch=mb, n_micro=1)
+    rng = np.random.default_rng(k + cin)
+    bf16 = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().float().numpy()
+    w, x = bf16(np.abs(rng.standard_normal((cout, cin, k, k))) / (cin * k * k) ** 0.5), bf16(rng.random(cin))
+    exact = np.einsum("ocrs,c->o", w.astype(np.float64), x.astype(np.float64))
+    bias = -exact.astype(np.float32)
+    g = GpuStage(st, [(w, bias)])
+    y = g.forward(0, np.broadcast_to(x[None, :, None, None], (mb, cin, hw, hw)))
+    g.close()
+    p = k // 2
+    left = y[:, :, p:hw - p, p:hw - p] - (exact + bias)[None, :, None, None]
+    rms = float(np.sqrt(np.mean(left ** 2) / np.mean(exact ** 2)))
+    assert rms < 1e-7
+
+
 # ------------------------------------------------------------------------------ batch-norm passes that add the partial sums
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("c,hw,mb", [
