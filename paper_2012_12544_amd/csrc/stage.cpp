@@ -1448,7 +1448,10 @@ int bapipe_stage_forward(bapipe_stage_t *st, int mb_id, const void *x_dev, void 
     // a flattened view of a spatial tensor is indexed c*H*W + h*W + w whatever the boundary layout is
     const bool flat_of_spatial = O.root != last && R.H * R.W > 1;
     const bool relayout = O.esize == dt_size(dt) && ((st->opts.io_layout == BAPIPE_NCHW && R.H * R.W > 1) || flat_of_spatial);
-    if (!relayout) c.y_direct = y_dev;
+    // a layer that reads the caller's x in place must not find y there already: where they overlap y is copied behind the last layer
+    const uintptr_t x0 = (uintptr_t)c.x_direct, y0 = (uintptr_t)y_dev;
+    const bool overlap = c.x_direct && y_dev && y0 < x0 + In.bytes() && x0 < y0 + O.bytes();
+    if (!relayout && !overlap) c.y_direct = y_dev;
     for (int i = 0; i < (int)st->layers.size(); ++i) {
         int rc = layer_forward(st, i, c);
         if (rc != BAPIPE_OK) return rc;

@@ -333,6 +333,35 @@ def test_output_wherever_it_lies(dtype, kind, c, hw):
     assert torch.equal(out[0], out[1]) and not torch.isnan(out[0]).any()
 
 
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("kind,shift", [("loss", 0), ("loss", 3), ("sum", 0), ("sum", 1)])
+def test_output_that_overlaps_the_input(dtype, kind, shift):
+    """Layers may read the caller's x in place until the last of them has run; only then is y stored over it."""
+    c, hw, mb = (1500, (1, 1), 300) if kind == "loss" else (64, (40, 40), 4)
+    b = C._Builder()
+    if kind == "loss":
+        b.xent(src=-1)
+    else:
+        b.relu(src=-1)
+        b.addl(b.bn(c), -1, relu=0)
+    st = C._stage("over", b.layers, dtype, (c,) + hw, mb, 1, 1, 1, 1, C.BASE_SEED + 80, "kaiming")
+    x = to_dev(st, stage_io(st)[0][0], B.NHWC).reshape(-1)
+    row = shift * c * x.element_size()                       # bytes from x to y
+    n = x.numel() * (4 if kind == "loss" else x.element_size())
+    out = []
+    for apart in (True, False):
+        g = GpuStage(st, gen.all_params(st, perturb=True))
+        buf = torch.zeros(n + row + 256, device="cuda", dtype=torch.uint8)
+        buf[:x.numel() * x.element_size()] = x.view(torch.uint8)
+        y = torch.zeros_like(buf) if apart else buf
+        torch.cuda.synchronize()
+        B.bapipe_stage_forward(g.h, 0, buf.data_ptr(), y.data_ptr() + row)
+        torch.cuda.synchronize()
+        out.append(y[row:row + n].clone())
+        g.close()
+    assert torch.equal(out[0], out[1])
+
+
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 1, 1, 20, 12, (9, 11), 3),       # a last trip of one vector of channels
