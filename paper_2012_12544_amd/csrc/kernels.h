@@ -19,6 +19,10 @@ inline size_t dt_size(int dt) { return dt == DT_F32 ? 4 : 2; }
 //                  channel-transposed copy [C][R][S][K]
 struct GatherConv {
     int N, Hi, Wi, Ci, Ho, Wo, Co, R, S, s_out, s_in, pad_h, pad_w;
+    // Kernels of other streams run beside this launch.  Alone on the chip a launch wants every compute unit busy; beside others,
+    // units it leaves idle are not lost, and fewer, larger blocks (less operand traffic per FLOP) are the better neighbour.
+    // Only the pixel tile may depend on it: every output element is still one sum over K in the same order.
+    int beside = 0;
 };
 
 // Forward-convolution geometry (x: N,H,W,C ; y: N,P,Q,K ; filter R x S).
@@ -86,8 +90,7 @@ hipError_t wgrad3x3_c8_mfma(const void *x, const void *dy, float *dw, float *db,
 bool conv_wgrad_mfma_supported(const ConvShape &c);
 size_t conv_wgrad_mfma_workspace(const ConvShape &c);
 // dw += dy^T x over all pixels; db (may be null) += column sums of dy
-// beside: kernels of other streams run beside the launch.  Alone on the chip a launch wants every compute unit busy; beside
-// others, blocks that share a unit with theirs are the better neighbours.  Only the tile may depend on it: the sums are the same
+// beside: kernels of other streams run beside the launch (as in GatherConv; the sums do not depend on it)
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
                            const ConvShape &c, hipStream_t s, bool beside = false);
 

@@ -695,10 +695,14 @@ GatherPlan gather_plan(const GatherConv &g)
     auto tiles_of = [&](int bp) { return p.busy * ((p.class_pix + bp - 1) / bp) * ((g.Co + p.bc - 1) / p.bc); };
     // Up to 400 tiles of 256 x 128 are one round of the chip (two blocks a unit); 256 x 256 would leave units without one, and
     // twice as many of 128 x 128 come to a round and a half and fetch more (3x3 512->256 at 28x28, 64 samples, 392 tiles: 163 us
-    // against 134; 512->512 at 14x14, 196: 73 against 70; 4096->1024 from 6000 rows, 192: 77 against 70; 294 tiles, 256->128 at
-    // 56x56: 62 against 64).  Of fewer than 160 (900 rows, 4096->4096) the smaller tiles fill more of it.
-    const bool few = p.bp == 256 && p.bc == 128 && tiles_of(256) < 400;
-    if (few && tiles_of(256) < 160) p.bp = 128;
+    // against 134; 4096->1024 from 6000 rows, 192: 77 against 70; 294 tiles, 256->128 at 56x56: 62 against 64).  Of fewer than
+    // about 200 alone on the chip the smaller tiles fill more of it, beside other streams only of fewer than 128 (mini-batches of
+    // three 3x3 512->512 layers at 14x14, us, 256 x 128 against 128 x 128: one stream 132 tiles 3695 / 3500, 160 3956 / 3785,
+    // 184 4170 / 4062, 196 4253 / 4198, 248 4649 / 4920, of 256->256 at 28x28 210 tiles 2699 / 2705; three streams 120 tiles
+    // 3372 / 2740, 132 2779 / 3000, 144 2938 / 3192, 160 3180 / 3553).
+    const long long least = g.beside ? 128 : 192;
+    const bool few = p.bp == 256 && p.bc == 128 && tiles_of(256) < 400 && tiles_of(256) >= least;
+    if (!few && p.bp == 256 && p.bc == 128 && tiles_of(256) < 400) p.bp = 128;
     // small products (the bottleneck blocks of ResNet: under ~8 GMAC) are bound by the latency of a block's
     // load - multiply - store chain, not by throughput: many 64-pixel blocks and no split of K were the
     // fastest choice on every such shape measured (e.g. 1x1 1024->256 at 14x14: 11.5 us against 22.2)
@@ -747,7 +751,7 @@ GatherPlan gather_plan(const GatherConv &g)
     // unit (that kernel's LDS and registers allow no more): 3x3 256->256 and 1x1 1024->256 at 14x14, 32 samples, 196
     // blocks, together 21.8 -> 18.1 us a launch; VGG-16's first linear layer 54.5 -> 48 us forward, 63.8 -> 52 gradient.
     // With more blocks than that the four smaller ones that fit a unit hide the latencies better (1x1 512->256 at 56x56,
-    // 3136 blocks: 53 us against 81).
+    // 3136 blocks: 53 us against 81).  Does not depend on `beside`: K is summed in another order.
     p.bk = p.kg == 2 ? (k64 ? 64 : 32) : p.kg == 1 && p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
     const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
@@ -1305,8 +1309,9 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside)
         // One block of eight waves and 256 x 256 per unit fetches two thirds of what two of 256 x 128 do.  Where its tiles are
         // whole and the pixels make a block per unit out of them (with the reduction: 512x4608 from 50176 rows 254 -> 231 us,
         // 512x2304 139 -> 122, from 12544 rows 83 -> 75; 25088x4096 from 1024 rows, 1568 tiles, 316 -> 331).  Beside other kernels a
-        // short launch keeps the smaller blocks, which share a unit with theirs (512-channel 14x14 layers on three streams: 4774
-        // us per mini-batch against 4873; 28x28 13110 against 14010 for the larger).
+        // short launch keeps the smaller blocks, which share a unit with theirs (mini-batches of three 3x3 512->512 layers, three
+        // streams, us, 256 x 128 against 256 x 256: 12544 rows 3560 / 3715, 15680 4350 / 4400, 18816 5215 / 5170, 21952 5950 / 5890,
+        // 25088 6690 / 6630, 25600 6425 / 6200, 31360 7615 / 7170, 50176 12250 / 11650).
         const long long whole = tiles_of(256, 256);
         if (p.bko == 256 && c.K % 256 == 0 && Ntot % 256 == 0 && whole <= 128 && whole * ((npix + 1023) / 1024) >= 224 &&
             !(beside && npix < 25000))

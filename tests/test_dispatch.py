@@ -42,9 +42,9 @@ class _GatherConv(ct.Structure):
     _fields_ = [(f, ct.c_int) for f in "N Hi Wi Ci Ho Wo Co R S s_out s_in pad_h pad_w beside".split()]
 
 
-def _pixel_tiles(rows, cin, cout, k=1, hw=1):
+def _pixel_tiles(rows, cin, cout, k=1, hw=1, beside=0):
     """(pixel tiles of the product where K is not split, bytes of partial sums where it is)"""
-    lib, g = B.load(), _GatherConv(rows, hw, hw, cin, hw, hw, cout, k, k, 1, 1, k // 2, k // 2, 0)
+    lib, g = B.load(), _GatherConv(rows, hw, hw, cin, hw, hw, cout, k, k, 1, 1, k // 2, k // 2, beside)
     chunks = getattr(lib, "_ZN6bapipe28conv_gather_mfma_stat_chunksERKNS_10GatherConvE")
     work = getattr(lib, "_ZN6bapipe26conv_gather_mfma_workspaceERKNS_10GatherConvE")
     work.restype = ct.c_size_t
@@ -60,6 +60,16 @@ def _pixel_tiles(rows, cin, cout, k=1, hw=1):
 ])
 def test_pixel_tile_of_products_of_8_to_16_gmac(rows, cin, cout, k, hw, tile):
     assert _pixel_tiles(rows, cin, cout, k, hw) == ((rows * hw * hw + tile - 1) // tile, 0)
+
+
+@pytest.mark.parametrize("mb,beside,tile", [
+    (40, 1, 128), (41, 1, 256),        # 124 and 128 tiles of 256 x 128 beside other streams
+    (61, 0, 128), (62, 0, 256),        # 188 and 192 alone on the chip
+    (130, 0, 256), (131, 0, 256), (131, 1, 256),        # 400, 404 (from there 256 x 256)
+])
+def test_pixel_tile_of_few_large_tiles(mb, beside, tile):
+    """3x3, 512->512 at 14x14."""
+    assert _pixel_tiles(mb, 512, 512, 3, 14, beside) == ((mb * 196 + tile - 1) // tile, 0)
 
 
 def test_large_weights_are_not_streamed_by_more_rows_of_tiles_than_before():

@@ -136,8 +136,8 @@ def test_vgg16_deep_end_to_end_full_shapes():
 
 @pytest.mark.timeout(900)
 def test_vgg16_deep_further_streams_same_bits_full_shapes():
-    """Beside kernels of further streams the 14x14 layers take other pixel tiles than alone on the chip (a choice that
-    only exists at full size): every output must still agree bit for bit with the one-stream run.  GPU only."""
+    """Beside kernels of further streams the weight gradients of the 14x14 layers take other tiles than alone on the chip (a
+    choice that only exists at full size): every output must still agree bit for bit with the one-stream run.  GPU only."""
     from gpu_harness import gpu_minibatch
     stage = C.vgg16_deep(n_micro=4)                 # depth 2: backward passes overlap later forward passes
     ref = gpu_minibatch(stage)

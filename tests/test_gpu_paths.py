@@ -573,6 +573,19 @@ def test_gradients_read_in_the_middle_of_a_mini_batch(monkeypatch, cin, cout, mb
     g.close()
 
 
+# ------------------------------------------------------------------------------ pixel tiles that depend on other streams
+def test_pixel_tiles_beside_other_streams_same_bits():
+    """144 tiles of 256 x 128 stay whole beside other streams and are halved alone on the chip."""
+    def build(b):
+        b.conv(512, 512, 3, relu=1, src=-1)
+        b.conv(512, 512, 3, relu=1)
+    st = single(build, 512, (14, 14), C.BF16, micro_batch=46, n_micro=3)
+    ref, got = gpu_minibatch(st), gpu_minibatch(st, eager_sync=False, backward_stream=True)
+    assert sorted(got) == sorted(ref)
+    for k in ref:
+        assert np.array_equal(got[k], ref[k]), k
+
+
 # ------------------------------------------------------------------------------ weight update: ragged tiles, both access widths, both copies
 def _mini_batch(gpu, stage, xs, gs):
     out = []
