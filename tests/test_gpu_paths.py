@@ -573,6 +573,65 @@ def test_gradients_read_in_the_middle_of_a_mini_batch(monkeypatch, cin, cout, mb
     g.close()
 
 
+# ------------------------------------------------------------------------------ weight gradients on a stream of their own
+def _wide_chain(micro_batch=3, n_micro=4):
+    """Seven 1x1 convolutions of 1024 channels with batch-norms and residual sums, no gates: the filters alone are worth a
+    hand-over after four of them in a backward pass, the other three are left for its end.  (No batch-norm behind the second
+    of each pair: it would take away what a shift of the first one's output changes, and with it that gradient.)"""
+    b = C._Builder()
+    b.conv(1024, 1024, 1, bias=0, src=-1)
+    t = b.bn(1024)
+    for _ in range(3):
+        b.conv(1024, 1024, 1, bias=0)
+        b.bn(1024)
+        t = b.addl(b.conv(1024, 1024, 1, bias=0), t, relu=0)
+    return C._stage("wide chain", b.layers, C.BF16, (1024, 3, 3), micro_batch, n_micro, 1, 2, 1, C.BASE_SEED + 81, "kaiming")
+
+
+HANDED_OVER = [
+    ("bottlenecks", lambda: C.resnet50_stage(cin=128, mid3=64, mid4=128, hw=29, n3=2, n4=2, micro_batch=24, n_micro=5)),
+    ("wide chain", _wide_chain),
+    ("3x3", lambda: single(lambda b: (b.conv(256, 256, 3, relu=1, src=-1), b.conv(256, 256, 3, relu=1)), 256, (20, 20), C.BF16, micro_batch=16, n_micro=3)),
+]
+
+
+@pytest.mark.parametrize("name,make", HANDED_OVER)
+def test_weight_gradients_reach_their_stream(name, make):
+    """A backward pass ends behind what its weight-gradient stream was given before, so kernels of it run there."""
+    st = make()
+    g = GpuStage(st, gen.all_params(st), wgrad_stream=True)
+    xs, gs = stage_io(st)
+    g.forward(0, xs[0])
+    dy, dx = to_dev(st, gs[0], B.NHWC), to_dev(st, xs[0], B.NHWC)
+    a = torch.randn(8192, 8192, device="cuda")
+    busy, done = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(g.wstream):
+        for _ in range(4):
+            a @ a
+    busy.record(g.wstream)
+    B.bapipe_stage_backward(g.h, 0, dy.data_ptr(), dx.data_ptr())
+    done.record(g.stream)
+    torch.cuda.synchronize()
+    g.close()
+    assert busy.elapsed_time(done) > 0
+
+
+@pytest.mark.parametrize("name,make", HANDED_OVER)
+def test_handed_over_weight_gradients_give_the_same_results_bit_for_bit(name, make):
+    ref = gpu_minibatch(make())
+    for kw in (dict(backward_stream=True), dict(backward_stream=True, static=True), dict(backward_stream="no wgrad stream"),
+               dict(wgrad_stream=True)):
+        got = gpu_minibatch(make(), eager_sync=False, **kw)
+        assert sorted(got) == sorted(ref)
+        for k in ref:
+            assert np.array_equal(got[k], ref[k]), (kw, k)
+
+
+def test_handed_over_weight_gradients_against_the_oracle():
+    compare_minibatch(_wide_chain(), backward_stream=True, verbose="three streams, wide chain")
+
+
 # ------------------------------------------------------------------------------ pixel tiles that depend on other streams
 def test_pixel_tiles_beside_other_streams_same_bits():
     """144 tiles of 256 x 128 stay whole beside other streams and are halved alone on the chip."""
