@@ -72,6 +72,24 @@ def test_pixel_tile_of_few_large_tiles(mb, beside, tile):
     assert _pixel_tiles(mb, 512, 512, 3, 14, beside) == ((mb * 196 + tile - 1) // tile, 0)
 
 
+@pytest.mark.parametrize("rows,cin,cout,tile", [
+    (1024, 512, 256, 32),      # 256 tiles of 32 x 32
+    (1024, 504, 256, 64),      # K too short for them
+    (2048, 512, 256, 32),      # 512 of them, 256 of 32 x 64
+    (2049, 512, 256, 64),      # 260
+    (100352, 64, 64, 128),     # up to 64 channels: 128 x 64
+    (100352, 64, 72, 64),
+])
+def test_pixel_tile_of_few_small_tiles(rows, cin, cout, tile):
+    assert _pixel_tiles(rows, cin, cout) == ((rows + tile - 1) // tile, 0)
+
+
+@pytest.mark.parametrize("rows,splits", [(32, 2), (33, 4), (64, 4), (65, 8)])
+def test_splits_of_a_large_matrix_for_few_rows(rows, splits):
+    """Two rows of 32 x 32 tiles would fetch it twice, so 33 to 64 rows are one of 64 x 64; above, no groups of waves."""
+    assert _pixel_tiles(rows, 25088, 4096) == (0, splits * rows * 4096 * 4)
+
+
 def test_large_weights_are_not_streamed_by_more_rows_of_tiles_than_before():
     assert _pixel_tiles(128, 25088, 4096) == (0, 16 * 128 * 4096 * 4)
 
