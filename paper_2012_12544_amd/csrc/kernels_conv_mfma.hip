@@ -742,7 +742,7 @@ GatherPlan gather_plan(const GatherConv &g)
         p.kg = 2;
     }
     if (p.kg == 2) p.bp = p.bc = 64;
-    // Up to 64 channels the tile is 128 x 64, five blocks to a unit, not 256 x 64: half the fragments a wave waits for and twice
+    // Up to 64 channels the tile is 128 x 64, four blocks (37 KB of LDS each) to a unit, not 256 x 64: half the fragments a wave waits for and twice
     // the blocks that hide it (7x7 / 2 of the stem, 224x224, 32 images 54.7 -> 44.2 us; 64->64 from 401408 pixels 1x1 32.0 ->
     // 24.0, from 40500 3x3 13.8 -> 12.3, from 387200 61.4 -> 56.0, from 100352 20.2 -> 20.6).
     if (p.bc == 64 && p.bp == 256) p.bp = 128;

@@ -5,7 +5,7 @@
 // nearly all of it launch gaps and one block's load - multiply - store chain.  Here the matrix never moves: a block of
 // eight waves keeps the rows of 32 hidden units in registers for the whole sequence (128 registers a lane at hidden
 // 1024), and a step is the exchange of one small vector.  Hidden 1024, 50 steps, 64 sequences, one direction: 650 us
-// before, 207 us (forward) and 184 us (backward) here.  Of a backward step of 4.4 us, before all its loads were requested
+// before, 182 us (forward) and 178 us (backward) here.  Of a backward step of 4.4 us, before all its loads were requested
 // first (3.7 now), 1.9 us were the 16 MB that all blocks together read of the step before, 1.2 us the hand-over, 0.6 us the
 // cell.
 //

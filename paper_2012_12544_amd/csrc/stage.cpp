@@ -104,7 +104,8 @@ struct WgradLaunch {
 };
 // Handing kernels to the weight-gradient stream takes an event and a wait, 11 us of the host, and as much again at the end of
 // the pass, where a launch takes 2.5: stages of short kernels were slower with that stream than without.  Weight gradients
-// wait for each other until that pays, about 20 us of them by the rates below (what is left at the end of a pass runs on the pass's own stream).
+// wait for each other until that pays, at 10.5 us of them by the rates below, which add the time of a kernel's arithmetic and
+// that of its bytes (what is left at the end of a pass runs on the pass's own stream).
 // Mini-batches on three streams, us, each handed over by itself -> so: bottlenecks of 128 channels, 20x20, 16 samples 1450 -> 1075; of
 // 64, 23x23, 31 samples 1450 -> 1095; 10 samples of 16x16, projection, 720 -> 550; the ResNet stem of 8 images of 112x112
 // 2270 -> 1625; full-sized stages the same.
