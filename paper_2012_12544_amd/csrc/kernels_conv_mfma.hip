@@ -65,6 +65,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     constexpr int WT_P = BP / WP, WT_C = BC / WC;
     constexpr int TP = WT_P / 32, TC = WT_C / 32;
     constexpr int KSUB = BK / 16;
+    constexpr bool WHOLE = BK == 64 && NW == 4;
     constexpr int SROW = BC + 4;             // staging row (elements): 8-byte aligned, odd multiple of 8 bytes
     constexpr int STAGE_ELEMS = (BP + BC) * BK;
     static_assert(XL >= 1 && WL >= 1 && BP % (RPW * NW) == 0 && BC % (RPW * NW) == 0, "tile/thread mismatch");
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     WAIT_VMCNT((STAGES - 1) * NLOAD);
     WAIT_LGKMCNT(0);       // no scalar load may be pending at loop entry, or every LDS wait in the loop becomes a full drain
     __builtin_amdgcn_s_barrier();
-    if constexpr (BK == 64) {
+    if constexpr (WHOLE) {
         // Few MFMAs per wave and sub-step (two for a 64 x 32 wave tile) cannot cover the LDS latency of the next
         // sub-step's reads, and a launch of about one block per compute unit has nobody else to cover it: the tile is
         // read one whole K-tile ahead instead, so one barrier and one wait, both behind eight MFMAs, serve 64 channels.
@@ -376,26 +377,29 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
             put_aside();
         } while (PARTS && end < n_it);
     } else {
-        static_assert(BK == 64 || KSUB == 2, "pipeline below is written for two sub-steps per tile");
-        bf16x8_t fa0[TC], fb0[TP], fa1[TC], fb1[TP];
-        load_frags(0, 0, fa0, fb0);
+        static_assert(KSUB % 2 == 0, "fragments of even sub-steps in one set of registers, of odd ones in the other");
+        bf16x8_t fa[2][TC], fb[2][TP];
+        load_frags(0, 0, fa[0], fb[0]);
         int rd = 0;
         int it = 0, end = 0;
         do {
             end = !PARTS || end + part_tiles > n_it ? n_it : end + part_tiles;
             for (; it < end; ++it) {
                 const int nx = rd + 1 == STAGES ? 0 : rd + 1;
-                load_frags(rd, 1, fa1, fb1);
-                __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs that hide them
-                mfma_all(fa0, fb0);
-                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j + 1 < KSUB; ++j) {
+                    load_frags(rd, j + 1, fa[(j + 1) & 1], fb[(j + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);        // keep the reads ahead of the MFMAs that hide them
+                    mfma_all(fa[j & 1], fb[j & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 WAIT_LGKMCNT(0);                              // this wave has read all of tile kt
                 WAIT_VMCNT((STAGES - 2) * NLOAD);             // its share of tile kt+1 has landed
                 __builtin_amdgcn_s_barrier();
-                load_frags(nx, 0, fa0, fb0);
+                load_frags(nx, 0, fa[0], fb[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 issue_tile(rd);                               // tile kt+STAGES into the slot just retired; its address
-                mfma_all(fa1, fb1);                           // arithmetic is free to mix with these MFMAs
+                mfma_all(fa[1], fb[1]);                       // arithmetic is free to mix with these MFMAs
                 __builtin_amdgcn_sched_barrier(0);
                 advance_tile();
                 rd = nx;
@@ -742,6 +746,26 @@ GatherPlan gather_plan(const GatherConv &g)
         p.kg = 2;
     }
     if (p.kg == 2) p.bp = p.bc = 64;
+    // Tiles of eight waves, one block to a unit, with K-tiles of 64 channels.  A row of 64 channels is a whole cache line: of 32
+    // it is half of one, which costs the vector L1 the same request (rows 1 KB apart from the L2s: 75 against 139 bytes per ns
+    // and unit).  256 x 256 (us, BK = 32 -> so; 3x3 512->512 at 28x28, 64 samples, 236 -> 227, 256->512 132 -> 128, 512->256,
+    // 196 tiles, 147 as 392 of 256 x 128 -> 123); 256 x 128 where those come to one block a unit at most: 512->512 at 14x14, 64
+    // samples, 196 tiles, 82 -> 70, 52 samples 74 -> 66, 40 (124 tiles, 248 of 64 x 128) 47 against 64; 128 x 256 the same.  Beside other streams
+    // the units that few large tiles leave idle are not lost: mini-batches of three 3x3 layers on three streams, us, 256 x 256
+    // against 256 x 128: 512->512 at 14x14, 40 samples (124 halves) 2999 / 2845, 64 (196) 4496 / 4709, 256->256 at 28x28, 32
+    // (98 pixel tiles, 98 halves x 2) 2088 / 2171.  K below 1024 is bound by the epilogue, which a lone block does not overlap
+    // (residual block with 1x1 filters of 128 to 256 channels, three streams, 3477 -> 3540); other widths keep two blocks of four waves.
+    const long long halves = count(256, 128);
+    const bool eight = p.kg == 1 && g.s_in == 1 && k64 && K >= 1024 && p.bc >= 128 && halves >= 128 && (g.Co % 256 == 0 || halves <= 256);
+    p.bk = 32;
+    if (eight) {
+        p.bk = 64;
+        p.bp = p.bc = 256;
+        if (g.Co % 256 || halves <= (g.beside ? 180 : 256)) {
+            if (g.Co % 256 == 0 && halves < least) p.bp = 128;
+            else p.bc = 128;
+        }
+    }
     // Up to 64 channels the tile is 128 x 64, four blocks (37 KB of LDS each) to a unit, not 256 x 64: half the fragments a wave waits for and twice
     // the blocks that hide it (7x7 / 2 of the stem, 224x224, 32 images 54.7 -> 44.2 us; 64->64 from 401408 pixels 1x1 32.0 ->
     // 24.0, from 40500 3x3 13.8 -> 12.3, from 387200 61.4 -> 56.0, from 100352 20.2 -> 20.6).
@@ -752,10 +776,10 @@ GatherPlan gather_plan(const GatherConv &g)
     // blocks, together 21.8 -> 18.1 us a launch; VGG-16's first linear layer 54.5 -> 48 us forward, 63.8 -> 52 gradient.
     // With more blocks than that the four smaller ones that fit a unit hide the latencies better (1x1 512->256 at 56x56,
     // 3136 blocks: 53 us against 81).  Does not depend on `beside`: K is summed in another order.
-    p.bk = p.kg == 2 ? (k64 ? 64 : 32) : p.kg == 1 && p.bp == 64 && tiles <= 512 && g.Ci % 64 == 0 && g.R * g.S <= 32 && (g.s_in == 1 || p.classes > 1) ? 64 : 32;
+    if ((p.kg == 2 && k64) || (p.kg == 1 && p.bp == 64 && tiles <= 512 && k64 && (g.s_in == 1 || p.classes > 1))) p.bk = 64;
     const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
-    long long want = p.kg > 1 ? (large ? 256 / tiles : 1) : tiles >= 128 ? 1 : (512 + tiles - 1) / tiles;
+    long long want = p.kg > 1 ? (large ? 256 / tiles : 1) : tiles >= 128 || eight ? 1 : (512 + tiles - 1) / tiles;
     long long most = KT * BK / 512;                 // at least 512 of K per split
     if (want > most) want = most;
     if (want > 32) want = 32;
@@ -808,8 +832,10 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         if (taps_inner) GATHER_LAUNCH(true, true, false);
         else if constexpr (BK == 32) GATHER_LAUNCH(true, false, false);
     } else if constexpr (BK == 64) {
-        if (phased) GATHER_LAUNCH(true, true, true);
-        else GATHER_LAUNCH(true, true, false);
+        if constexpr (BP == 64) {
+            if (phased) GATHER_LAUNCH(true, true, true);
+            else GATHER_LAUNCH(true, true, false);
+        } else GATHER_LAUNCH(true, true, false);                    // one class
     } else if (phased) {
         if (taps_inner) GATHER_LAUNCH(true, true, true);
         else GATHER_LAUNCH(true, false, true);
@@ -838,7 +864,10 @@ hipError_t launch_plan(const void *in, const void *wt, const float *bias, void *
     if (p.kg == 4) TILE(32, 64, 1, 2, 32, 4, 4);
     if (p.kg == 2 && p.bk == 64) TILE(64, 64, 2, 2, 64, 3, 2);
     if (p.kg == 2) TILE(64, 64, 2, 2, 32, 4, 2);
-    if (p.bk == 64) TILE(64, 128, 1, 4, 64, 3);
+    if (p.bk == 64 && p.bp == 64) TILE(64, 128, 1, 4, 64, 3);
+    if (p.bk == 64 && p.bc == 256 && p.bp == 128) TILE(128, 256, 2, 4, 64, 3);
+    if (p.bk == 64 && p.bc == 256) TILE(256, 256, 2, 4, 64, 2);
+    if (p.bk == 64) TILE(256, 128, 4, 2, 64, 3);
     if (p.bp == 64) TILE(64, 128, 1, 4, 32, 3);
     if (p.bc == 64) TILE(128, 64, 4, 1, 32, 3);
     if (p.bc == 256) TILE(256, 256, 2, 4, 32, 3);

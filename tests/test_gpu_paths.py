@@ -645,6 +645,57 @@ def test_pixel_tiles_beside_other_streams_same_bits():
         assert np.array_equal(got[k], ref[k]), k
 
 
+@pytest.mark.parametrize("mb", [46, 60])
+def test_large_tiles_beside_other_streams_same_bits(mb):
+    """Alone tiles of 128 x 256; beside other streams, 144 halves of 256 x 128 and 188, which are 94 tiles of 256 x 256."""
+    def build(b):
+        b.conv(512, 512, 3, relu=1, src=-1)
+        b.conv(512, 512, 3, relu=1)
+    st = single(build, 512, (14, 14), C.BF16, micro_batch=mb, n_micro=2)
+    ref, got = gpu_minibatch(st), gpu_minibatch(st, eager_sync=False, backward_stream=True)
+    assert sorted(got) == sorted(ref)
+    for k in ref:
+        assert np.array_equal(got[k], ref[k]), k
+
+
+def _conv_in_doubles(x, w, pad):
+    """The convolution and the sum of its terms' magnitudes, float64, on the GPU."""
+    x, w = (torch.from_numpy(np.ascontiguousarray(a)).to("cuda").double() for a in (x, w))
+    n, _, h, wd = x.shape
+    cols = torch.nn.functional.unfold(x, w.shape[2:], padding=pad).transpose(1, 2).reshape(n * h * wd, -1).contiguous()
+    m = w.reshape(w.shape[0], -1).t().contiguous()
+    back = lambda t: t.reshape(n, h, wd, -1).permute(0, 3, 1, 2).cpu().numpy()
+    return back(cols @ m), back(cols.abs() @ m.abs())
+
+
+@pytest.mark.parametrize("k,cin,cout,hw,mb", [
+    (3, 128, 2048, (13, 17), 9),       # 128 x 256: 128 halves, pixels end inside a tile
+    (1, 1088, 2048, (11, 19), 9),      # ... 17 K-tiles
+    (3, 128, 2048, (13, 17), 13),      # 256 x 128: 192 halves
+    (3, 192, 1112, (15, 11), 21),      # ... of a width that ends inside a tile; 27 K-tiles
+    (3, 128, 2048, (13, 17), 19),      # 256 x 256: 272 halves
+    (1, 1024, 4352, (9, 8), 29),       # ... one tap; 17 channel tiles
+])
+def test_conv_tiles_of_eight_waves(k, cin, cout, hw, mb):
+    """Against float64: half a bf16 step of the result and a rounding of 2^-24 for each term of the sum."""
+    st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, hw, C.BF16, micro_batch=mb, n_micro=1)
+    params = gen.all_params(st)
+    g = GpuStage(st, params)
+    rng = np.random.default_rng(cout + mb)
+    bf16 = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().float().numpy()
+    x, dy = bf16(rng.standard_normal((mb, cin) + hw)), bf16(rng.standard_normal((mb, cout) + hw))
+    y = g.forward(0, x)
+    dx = g.backward(0, dy)
+    g.close()
+    w, b = params[0]
+    w = bf16(w)
+    ref, terms = _conv_in_doubles(x, w, k // 2)
+    ref += 0.0 if b is None else b.reshape(1, -1, 1, 1)
+    assert np.all(np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + (k * k * cin + 1) * 2.0 ** -24 * (terms + np.abs(ref)))
+    ref, terms = _conv_in_doubles(dy, np.flip(w, (2, 3)).transpose(1, 0, 2, 3), k // 2)
+    assert np.all(np.abs(dx - ref) <= 2.0 ** -8 * np.abs(ref) + (k * k * cout + 1) * 2.0 ** -24 * (terms + np.abs(ref)))
+
+
 # ------------------------------------------------------------------------------ weight update: ragged tiles, both access widths, both copies
 def _mini_batch(gpu, stage, xs, gs):
     out = []
