@@ -756,7 +756,11 @@ GatherPlan gather_plan(const GatherConv &g)
     // (98 pixel tiles, 98 halves x 2) 2088 / 2171.  K below 1024 is bound by the epilogue, which a lone block does not overlap
     // (residual block with 1x1 filters of 128 to 256 channels, three streams, 3477 -> 3540); other widths keep two blocks of four waves.
     const long long halves = count(256, 128);
-    const bool eight = p.kg == 1 && g.s_in == 1 && k64 && K >= 1024 && p.bc >= 128 && halves >= 128 && (g.Co % 256 == 0 || halves <= 256);
+    // Fewer than 144 halves, or rows of pixels that mostly end outside the image, are faster on the smaller tiles (3x3 128->2048 at
+    // 13x17, 9 samples, 128 halves: 18.4 us against 25.0 as 128 x 256; 4096->4096 from 900 rows 52.3 / 58.6, 1500 rows 75.6 / 63.9;
+    // 1x1 1024->2048 from 3136 pixels 32.2 / 23.0; 25088<-4096 from 64 rows, 196 tiles, 51.6 / 59.8).
+    const bool whole = 8 * npix >= 7 * 256 * ((npix + 255) / 256);
+    const bool eight = p.kg == 1 && g.s_in == 1 && k64 && K >= 1024 && p.bc >= 128 && halves >= 144 && whole && (g.Co % 256 == 0 || halves <= 256);
     p.bk = 32;
     if (eight) {
         p.bk = 64;

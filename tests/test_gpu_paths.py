@@ -647,7 +647,7 @@ def test_pixel_tiles_beside_other_streams_same_bits():
 
 @pytest.mark.parametrize("mb", [46, 60])
 def test_large_tiles_beside_other_streams_same_bits(mb):
-    """Alone tiles of 128 x 256; beside other streams, 144 halves of 256 x 128 and 188, which are 94 tiles of 256 x 256."""
+    """Alone tiles of 128 x 256; beside other streams, 144 halves of 256 x 128 and 184, which are 92 tiles of 256 x 256."""
     def build(b):
         b.conv(512, 512, 3, relu=1, src=-1)
         b.conv(512, 512, 3, relu=1)
@@ -669,10 +669,10 @@ def _conv_in_doubles(x, w, pad):
 
 
 @pytest.mark.parametrize("k,cin,cout,hw,mb", [
-    (3, 128, 2048, (13, 17), 9),       # 128 x 256: 128 halves, pixels end inside a tile
-    (1, 1088, 2048, (11, 19), 9),      # ... 17 K-tiles
+    (3, 128, 2048, (13, 17), 10),      # 128 x 256: 144 halves, pixels end inside a tile
+    (1, 1088, 2048, (11, 19), 10),     # ... 17 K-tiles
     (3, 128, 2048, (13, 17), 13),      # 256 x 128: 192 halves
-    (3, 192, 1112, (15, 11), 21),      # ... of a width that ends inside a tile; 27 K-tiles
+    (3, 192, 1112, (15, 11), 24),      # ... 144 of a width that ends inside a tile; 27 K-tiles
     (3, 128, 2048, (13, 17), 19),      # 256 x 256: 272 halves
     (1, 1024, 4352, (9, 8), 29),       # ... one tap; 17 channel tiles
 ])
