@@ -137,7 +137,7 @@ hipError_t lstm_cell_bwd(int dt, const void *dy, const float *r, int S, const fl
 // w_hh [4H][H] and wt_h [H][4H] are the recurrent matrix and its transpose in the storage type.  A block that has polled for
 // another one's step wait_polls times gives up, and its group of sequences is computed by one block alone: the results are
 // the same bit for bit, whatever the limit.
-constexpr unsigned kLstmWaitPolls = 1u << 16;      // of 0.13 to 0.21 us
+constexpr unsigned kLstmWaitPolls = 1u << 14;      // each a read of the slices that a wave needs, 0.5 to 1.5 us
 bool lstm_seq_supported(int N, int T, int H, int compute_units);
 size_t lstm_seq_workspace(int N, int H);
 hipError_t lstm_seq_fwd(const void *P, const void *w_hh, float *gates, float *cells, void *h, void *hs, int N, int T, int H,

@@ -5,9 +5,9 @@
 // nearly all of it launch gaps and one block's load - multiply - store chain.  Here the matrix never moves: a block of
 // eight waves keeps the rows of 32 hidden units in registers for the whole sequence (128 registers a lane at hidden
 // 1024), and a step is the exchange of one small vector.  Hidden 1024, 50 steps, 64 sequences, one direction: 650 us
-// before, 182 us (forward) and 178 us (backward) here.  Of a backward step of 4.4 us, before all its loads were requested
-// first (3.7 now), 1.9 us were the 16 MB that all blocks together read of the step before, 1.2 us the hand-over, 0.6 us the
-// cell.
+// before, 126 us (forward) and 156 us (backward) here, alone on the chip.  Of a step of 2.5 to 3.1 us most is the way of a
+// slice from one unit to the others; in backward all blocks together read 16 MB of the step before, which took 1.9 us of 4.4
+// before all its loads were requested first.
 //
 // Split.  16 sequences (the N of the MFMA) form a group, H/32 blocks work on a group, each owns 32 units: their four
 // gates in forward (M = 128 rows, K = H in eight pieces, a piece a wave), their rows of W_h^T in backward (M = 32,
@@ -17,21 +17,26 @@
 // backward pass runs on another stream, because both launches then want all compute units (11.5 against 10.5 ms for a
 // mini-batch of two layers).
 //
-// Exchange.  A block publishes its 16 x 32 slice with write-through stores (agent scope), waits for them, and then
-// raises its own flag word to the number of steps it has finished; a wave polls the flags of the blocks whose slices it
-// needs, one flag a lane, and reads the slices with loads of the same scope (a cache-wide acquire per wave and step cost
-// twice the whole step: 529 us instead of 228 for 50 steps).  The slices go through a buffer of their own, laid out as
+// Exchange.  A block publishes its 16 x 32 slice with write-through stores (agent scope), and that is all: a slice starts out
+// as words of kUnsent, which no published pair of values is, and a wave reads the slices it needs with loads of the same scope
+// until there is no such word left in them.  (A flag word per block that is raised once its stores are complete, polled before
+// the slices are read, puts two more trips through the fabric into each step: 172 / 166 us instead of 126 / 156.  Reading one
+// word a lane before the whole: 131; reading again only the fragments that had not come: 136 / 174, for its branches.)
+// The slices go through a buffer of their own, laid out as
 // the operand fragments that read them (1 KB per load instruction): the rows of the layer's tensors lie T * 8H bytes
-// apart, all in one L2 channel, and reading them there took 4.7 us of a backward step.  Two copies of the buffer, by the
-// parity of the step, are enough: a block that publishes step t+2 has seen every block of its group finish t+1, and
-// with that finish reading t.
+// apart, all in one L2 channel, and reading them there took 4.7 us of a backward step.
+// Four copies of the buffer go round.  At step t (counted from the first that reads a slice), after its barrier, a block has
+// seen every block's slice for step t, so every block is done reading those for step t - 1: it makes its own of them kUnsent
+// again.  It will publish there for step t + 3.  A block that looks for that slice has seen this block's for step t + 2 before,
+// which was stored after a wait for the words of kUnsent: it finds these or the new ones, never the old slice.
 //
 // Why the launch always ends, and with the right values.  Blocks number themselves by a ticket taken when they START, so
 // the blocks of the oldest unfinished group are resident or the next to start, and they find room unless other launches of
 // this kind hold every slot with incomplete groups of their own.  q launches at once hold at most q * (H/32 - 1) blocks that
 // way; lstm_seq_supported asks for more compute units than eight launches can hold.  More of them (several processes on one
 // GPU, a stream confined to a few units) can still leave groups incomplete, and nothing here can see that coming.  So every
-// wait is bounded (kLstmWaitPolls), the group's other blocks leave when they see that one has given up, and the first that
+// wait is bounded (kLstmWaitPolls), the group's other blocks leave when they see that one has given up (a word that they look
+// at every 16 polls), and the first that
 // did computes the group's sequences from the start by itself, with nobody to wait for and slices of its own: the same
 // operations in the same order, its weights read again for every 32 units and step (hidden 1024, 50 steps: 14 ms).  What the
 // others store meanwhile are the same values.
@@ -44,9 +49,10 @@ namespace {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kUnits = 32, kSeqs = 16, kThreads = 512;
-// words of the ticket line and of each group's line: flags of up to 32 blocks, and whether one of them has given up
-constexpr int kCtlWords = 64, kDeadWord = 63;
-constexpr unsigned kGaveUp = 0xFFFFFFFFu;                   // flag of a block that has
+// words of the ticket line and of each group's line; its first says whether a block of it has given up
+constexpr int kCtlWords = 64;
+constexpr unsigned kUnsent = 0xFFFFFFFFu;                   // word of a slice: not yet published
+constexpr int kCopies = 4;                                  // of a group's slices
 // Partial sums in LDS.  Forward: [wave][unit][16 sequences x 4 gates], 16 bytes a (unit, sequence), the pitch keeps the 16
 // lanes that are served together on different banks, those that write 16 sequences and those that read 16 units.  Backward:
 // [wave][sequence][32 units], a lane writes the four neighbouring units that it has the sums of.  (One word at a time, 32
@@ -55,26 +61,10 @@ constexpr int kPitch = 68, kRowPitch = 36;
 
 __device__ __forceinline__ float sigmoid_f(float v) { return 1.0f / (1.0f + expf(-v)); }
 
-// wait until flags[0..n) have all reached `need`; false: one of those blocks gave up, or this wave does
-__device__ bool wait_flags(const unsigned *flags, int n, unsigned need, int lane, unsigned polls)
-{
-    for (unsigned it = 0; it < polls; ++it) {
-        const unsigned v = lane < n ? __hip_atomic_load(flags + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : need;
-        if (__all(v >= need)) {
-            asm volatile("" ::: "memory");        // the reads of what was published stay below
-            return __all(lane >= n || v != kGaveUp);
-        }
-    }
-    return false;
-}
-
 // a block that gives up tells those that wait for it; true in the first of its group
-__device__ bool first_to_give_up(unsigned *line, int blk, int *shared)
+__device__ bool first_to_give_up(unsigned *given_up, int *shared)
 {
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(line + blk, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *shared = atomicExch(line + kDeadWord, 1u) == 0;
-    }
+    if (threadIdx.x == 0) *shared = atomicExch(given_up, 1u) == 0;
     __syncthreads();
     return *shared != 0;
 }
@@ -86,28 +76,55 @@ __device__ __forceinline__ int forget(int v)
     return v;
 }
 
-// the block's published values are complete in memory, then its flag says so
-__device__ __forceinline__ void publish(unsigned *flag, unsigned v)
+// barrier of a block whose waves have nothing in flight for each other but LDS accesses
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__device__ __forceinline__ void store_word(char *p, unsigned v)
 {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(reinterpret_cast<unsigned *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// two neighbouring lanes' bf16 values leave as one 32-bit write-through store (by the even lane)
+// two neighbouring lanes' bf16 values leave as one 32-bit write-through store (by the even lane); of two NaN one takes another
+// payload than the word that stands for nothing sent
 __device__ __forceinline__ void publish_pair(char *p, bf16_t v)
 {
-    const unsigned mine = v.v, other = __shfl_xor(mine, 1, 64);
-    if (!(threadIdx.x & 1))
-        __hip_atomic_store(reinterpret_cast<unsigned *>(p), mine | (other << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned mine = v.v, other = __shfl_xor(mine, 1, 64), word = mine | (other << 16);
+    if (!(threadIdx.x & 1)) store_word(p, word == kUnsent ? kUnsent - 1 : word);
 }
 
 __device__ __forceinline__ bf16x8_t load_frag(const bf16_t *p) { return as_frag(*reinterpret_cast<const chunk16 *>(p)); }
 
 // an operand fragment that another block has published: 16 bytes a lane, coherent at agent scope (sc1)
-__device__ __forceinline__ bf16x8_t load_published(__amdgpu_buffer_rsrc_t r, unsigned off)
+__device__ __forceinline__ chunk16 load_published(__amdgpu_buffer_rsrc_t r, unsigned off)
 {
-    return as_frag(__builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 16));
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 16);
+}
+
+// KW fragments of a wave, 1 KB apart from `src` on.  WAIT: until no word of them is kUnsent; false when some still are after
+// `polls` reads, or when a block of the group has given up.
+template <int KW, bool WAIT>
+__device__ __forceinline__ bool receive(__amdgpu_buffer_rsrc_t r, unsigned src, int lane, chunk16 (&b)[KW], unsigned polls,
+                                        const unsigned *given_up)
+{
+    for (unsigned it = 1; !WAIT || it <= polls; ++it) {
+#pragma unroll
+        for (int k = 0; k < KW; ++k) b[k] = load_published(r, src + (unsigned)(k * 64 + lane) * 16u);
+        if constexpr (!WAIT) return true;
+        // All of them on their way before the first is looked at: left alone the compiler keeps two or three in flight, to
+        // save registers that nobody else can have.
+        __builtin_amdgcn_sched_barrier(0);
+        unsigned most = 0;
+#pragma unroll
+        for (int k = 0; k < KW; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) most = b[k][j] > most ? b[k][j] : most;
+        asm volatile("" ::: "memory");                     // read again in the next round
+        if (__all(most != kUnsent)) return true;
+        if (it % 16 == 0 && __hip_atomic_load(given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+    }
+#pragma unroll
+    for (int k = 0; k < KW; ++k) b[k] = chunk16{0u, 0u, 0u, 0u};
+    return false;
 }
 
 // byte offset of (k, sequence) in a buffer of K-step fragments: [K/32][lane = (k/8 % 4, sequence)][8]
@@ -130,12 +147,13 @@ template <int KS> struct SeqFwd {
     __amdgpu_buffer_rsrc_t xr;
     int lane, wave, kp, sq, un;
     bool on;
+    int ring;
     size_t r0;
     bf16x8_t w[MT][KW];
     bf16_t p[4], hv;
     float s[4], ig, fg, gg, og, c;
 
-    __device__ __forceinline__ void place(int tid, int n0, int N, char *slice)
+    __device__ __forceinline__ void place(int tid, int n0, int N, char *slice, int copies)
     {
         lane = tid & 63;
         wave = tid >> 6;
@@ -146,7 +164,8 @@ template <int KS> struct SeqFwd {
         // sequences past the last repeat it; nothing of theirs is stored in the layer's tensors
         r0 = (size_t)(on ? n0 + sq : N - 1) * T;
         mine = slice;
-        xr = __builtin_amdgcn_make_buffer_rsrc(slice, 0, 2 * SLICES, 0x00020000);
+        ring = copies - 1;
+        xr = __builtin_amdgcn_make_buffer_rsrc(slice, 0, copies * SLICES, 0x00020000);
         c = 0.0f;
         start();
     }
@@ -171,20 +190,16 @@ template <int KS> struct SeqFwd {
 #pragma unroll
         for (int q = 0; q < 4; ++q) p[q] = P[(r0 + t) * 4 * H + q * H + u];
     }
-    __device__ __forceinline__ void multiply(int t)            // this wave's share of W_h h of step t - 1, to LDS
+    // this wave's share of W_h h of step t - 1, to LDS
+    template <bool WAIT> __device__ __forceinline__ bool multiply(int t, unsigned polls = 0, const unsigned *given_up = nullptr)
     {
         f32x4_t acc[MT] = {};
-        bf16x8_t b[KW];
-#pragma unroll
-        for (int k = 0; k < KW; ++k) b[k] = load_published(xr, (t & 1) * SLICES + (unsigned)((kp * KW + k) * 64 + lane) * 16u);
-        // All of them on their way before the first is waited for: left alone the compiler keeps two or three in flight, to
-        // save registers that nobody else can have (hidden 640, 64 sequences of 50 steps: 211 -> 180 us; 896, 576 of 20: 549
-        // -> 457).  At 1024 it requests them all by itself, in an order that is 4 % better.
-        if constexpr (KS < 8) __builtin_amdgcn_sched_barrier(0);
+        chunk16 b[KW];
+        const bool came = receive<KW, WAIT>(xr, (unsigned)(t & ring) * SLICES + (unsigned)(kp * KW) * 1024u, lane, b, polls, given_up);
 #pragma unroll
         for (int k = 0; k < KW; ++k)
 #pragma unroll
-            for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m][k], b[k], acc[m], 0, 0, 0);
+            for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m][k], as_frag(b[k]), acc[m], 0, 0, 0);
         // row 4 quad + r of a half's tile is a unit; its four gates are four tiles apart by two
         constexpr int HALVES = MT / 4;
 #pragma unroll
@@ -195,6 +210,7 @@ template <int KS> struct SeqFwd {
                 *reinterpret_cast<float4 *>(&red[kp][unit * kPitch + 4 * (lane & 15)]) =
                     make_float4(acc[a][r], acc[HALVES + a][r], acc[2 * HALVES + a][r], acc[3 * HALVES + a][r]);
             }
+        return came;
     }
     __device__ __forceinline__ void collect()
     {
@@ -220,7 +236,12 @@ template <int KS> struct SeqFwd {
         c = fmaf(fg, c, ig * gg);                  // one rounding wherever the compiler puts this
         hv = from_f32<bf16_t>(og * tanhf(c));
     }
-    __device__ __forceinline__ void send(int t, int u) { publish_pair(mine + ((t + 1) & 1) * SLICES + frag_at(u, sq), hv); }
+    __device__ __forceinline__ void send(int t, int u) { publish_pair(mine + ((t + 1) & ring) * SLICES + frag_at(u, sq), hv); }
+    // what step t - 1 has read is unsent again
+    __device__ __forceinline__ void clear(int t, int u)
+    {
+        if (!(threadIdx.x & 1)) store_word(mine + ((t - 1) & ring) * SLICES + frag_at(u, sq), kUnsent);
+    }
     __device__ __forceinline__ void store(int t, int u)
     {
         if (!on) return;
@@ -255,20 +276,16 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_fwd(const bf16_t *__re
     bool dead = false;
     {
         const int grp = s_ticket / GB, blk = s_ticket % GB;
-        unsigned *line = ctl + (1 + grp) * kCtlWords;
+        const unsigned *given_up = ctl + (1 + grp) * kCtlWords;
         S a{P, w_hh, gates, cells, h, hs, T, red};
-        a.place(threadIdx.x, grp * kSeqs, N, slices + (size_t)grp * 2 * S::SLICES);
+        a.place(threadIdx.x, grp * kSeqs, N, slices + (size_t)grp * kCopies * S::SLICES, kCopies);
         const int u = blk * kUnits + a.un;
         a.load_rows(blk * kUnits);
         a.fetch(0, u);
         if (a.on) hs[a.r0 * S::H + u] = from_f32<bf16_t>(0.0f);
         for (int t = 0; t < T; ++t) {
             if (t > 0) {
-                // the blocks whose units overlap this wave's piece of K
-                constexpr int per = 32 * S::KW;
-                const int f0 = a.kp * per / kUnits, f1 = ((a.kp + 1) * per + kUnits - 1) / kUnits;
-                if (!wait_flags(line + f0, f1 - f0, (unsigned)t, a.lane, polls)) s_dead = 1;
-                a.multiply(t);
+                if (!a.template multiply<true>(t, polls, given_up)) s_dead = 1;
                 __syncthreads();
                 a.collect();
                 dead = s_dead != 0;
@@ -276,8 +293,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_fwd(const bf16_t *__re
             }
             a.cell();
             if (t + 1 < T) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // clear() of the step before
                 a.send(t, u);
-                publish(line + blk, (unsigned)(t + 1));
+                if (t > 1) a.clear(t, u);
+                lds_barrier();
                 a.fetch(t + 1, u);
             }
             a.store(t, u);                         // what nobody waits for
@@ -285,9 +304,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_fwd(const bf16_t *__re
     }
     if (!dead) return;
     const int tid = forget(threadIdx.x), grp = s_ticket / GB;
-    if (!first_to_give_up(ctl + (1 + grp) * kCtlWords, s_ticket % GB, &s_first)) return;
+    if (!first_to_give_up(ctl + (1 + grp) * kCtlWords, &s_first)) return;
     S a{P, w_hh, gates, cells, h, hs, T, red};
-    a.place(tid, grp * kSeqs, N, slices + (size_t)(gridDim.x / GB + grp) * 2 * S::SLICES);
+    a.place(tid, grp * kSeqs, N, slices + ((size_t)(gridDim.x / GB) * kCopies + (size_t)grp * 2) * S::SLICES, 2);
     for (int t = 0; t < T; ++t) {
         for (int b = 0; b < GB; ++b) {
             const int u = b * kUnits + a.un;
@@ -295,7 +314,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_fwd(const bf16_t *__re
             a.c = t > 0 ? cells[(a.r0 + t - 1) * S::H + u] : 0.0f;
             if (t > 0) {
                 a.load_rows(b * kUnits);
-                a.multiply(t);
+                a.template multiply<false>(t);
                 __syncthreads();
                 a.collect();
                 __syncthreads();
@@ -322,12 +341,13 @@ template <int KS> struct SeqBwd {
     __amdgpu_buffer_rsrc_t xr;
     int lane, wave, sq, un, n;
     bool on;
+    int ring;
     size_t r0;
     bf16x8_t w[2][KW];
     float carry, g[4], c, cp, s;
     bf16_t dh0, dv[4];
 
-    __device__ __forceinline__ void place(int tid, int n0, int N, char *slice)
+    __device__ __forceinline__ void place(int tid, int n0, int N, char *slice, int copies)
     {
         lane = tid & 63;
         wave = tid >> 6;
@@ -337,7 +357,8 @@ template <int KS> struct SeqBwd {
         n = on ? n0 + sq : N - 1;
         r0 = (size_t)n * T;
         mine = slice;
-        xr = __builtin_amdgcn_make_buffer_rsrc(slice, 0, 2 * SLICES, 0x00020000);
+        ring = copies - 1;
+        xr = __builtin_amdgcn_make_buffer_rsrc(slice, 0, copies * SLICES, 0x00020000);
         carry = s = 0.0f;
     }
     __device__ __forceinline__ void load_rows(int u0)
@@ -357,24 +378,21 @@ template <int KS> struct SeqBwd {
         cp = t > 0 ? cells[(r - 1) * H + u] : 0.0f;
         dh0 = dy[r * H + u];
     }
-    __device__ __forceinline__ void multiply(int t)            // this wave's share of W_h^T D of step t + 1, to LDS
+    // this wave's share of W_h^T D of step t + 1, to LDS
+    template <bool WAIT> __device__ __forceinline__ bool multiply(int t, unsigned polls = 0, const unsigned *given_up = nullptr)
     {
         f32x4_t acc[2][2] = {};
-        const unsigned src = ((t + 1) & 1) * SLICES + (unsigned)(wave * KW * 64 + lane) * 16u;
-        bf16x8_t b[KW];
-#pragma unroll
-        for (int k = 0; k < KW; ++k) b[k] = load_published(xr, src + k * 1024);
-        // as in forward (hidden 1024, 64 sequences of 50 steps: 339 -> 310 us with the layer's products; 512: 258 -> 206); up
-        // to 384 two blocks fit a unit without
-        if constexpr (KS >= 4) __builtin_amdgcn_sched_barrier(0);
+        chunk16 b[KW];
+        const bool came = receive<KW, WAIT>(xr, (unsigned)((t + 1) & ring) * SLICES + (unsigned)(wave * KW) * 1024u, lane, b, polls, given_up);
 #pragma unroll
         for (int k = 0; k < KW; ++k)
 #pragma unroll
-            for (int m = 0; m < 2; ++m) acc[m][k & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m][k], b[k], acc[m][k & 1], 0, 0, 0);
+            for (int m = 0; m < 2; ++m) acc[m][k & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m][k], as_frag(b[k]), acc[m][k & 1], 0, 0, 0);
 #pragma unroll
         for (int m = 0; m < 2; ++m)
             *reinterpret_cast<float4 *>(&red[wave][(lane & 15) * kRowPitch + 16 * m + 4 * (lane >> 4)]) =
                 make_float4(acc[m][0][0] + acc[m][1][0], acc[m][0][1] + acc[m][1][1], acc[m][0][2] + acc[m][1][2], acc[m][0][3] + acc[m][1][3]);
+        return came;
     }
     __device__ __forceinline__ void collect()
     {
@@ -394,7 +412,14 @@ template <int KS> struct SeqBwd {
     __device__ __forceinline__ void send(int t, int u)
     {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) publish_pair(mine + (t & 1) * SLICES + frag_at(q * H + u, sq), dv[q]);
+        for (int q = 0; q < 4; ++q) publish_pair(mine + (t & ring) * SLICES + frag_at(q * H + u, sq), dv[q]);
+    }
+    // what step t + 1 has read is unsent again
+    __device__ __forceinline__ void clear(int t, int u)
+    {
+        if (threadIdx.x & 1) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) store_word(mine + ((t + 2) & ring) * SLICES + frag_at(q * H + u, sq), kUnsent);
     }
     __device__ __forceinline__ void store(int t, int u)
     {
@@ -424,16 +449,15 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_bwd(const bf16_t *__re
     bool dead = false;
     {
         const int grp = s_ticket / GB, blk = s_ticket % GB;
-        unsigned *line = ctl + (1 + grp) * kCtlWords;
+        const unsigned *given_up = ctl + (1 + grp) * kCtlWords;
         S a{dy, wt_h, gates, cells, D, T, red};
-        a.place(threadIdx.x, grp * kSeqs, N, slices + (size_t)grp * 2 * S::SLICES);
+        a.place(threadIdx.x, grp * kSeqs, N, slices + (size_t)grp * kCopies * S::SLICES, kCopies);
         const int u = blk * kUnits + a.un;
         a.load_rows(blk * kUnits);
         a.fetch(T - 1, u);
         for (int t = T - 1; t >= 0; --t) {
             if (t + 1 < T) {
-                if (!wait_flags(line + (a.wave & 1) * (GB / 2), GB / 2, (unsigned)(T - 1 - t), a.lane, polls)) s_dead = 1;
-                a.multiply(t);
+                if (!a.template multiply<true>(t, polls, given_up)) s_dead = 1;
                 __syncthreads();
                 a.collect();
                 dead = s_dead != 0;
@@ -441,8 +465,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_bwd(const bf16_t *__re
             }
             a.cell();
             if (t > 0) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // clear() of the step before
                 a.send(t, u);
-                publish(line + blk, (unsigned)(T - t));
+                if (t + 2 < T) a.clear(t, u);
+                lds_barrier();
                 a.fetch(t - 1, u);
             }
             a.store(t, u);
@@ -450,9 +476,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_bwd(const bf16_t *__re
     }
     if (!dead) return;
     const int tid = forget(threadIdx.x), grp = s_ticket / GB;
-    if (!first_to_give_up(ctl + (1 + grp) * kCtlWords, s_ticket % GB, &s_first)) return;
+    if (!first_to_give_up(ctl + (1 + grp) * kCtlWords, &s_first)) return;
     S a{dy, wt_h, gates, cells, D, T, red};
-    a.place(tid, grp * kSeqs, N, slices + (size_t)(gridDim.x / GB + grp) * 2 * S::SLICES);
+    a.place(tid, grp * kSeqs, N, slices + ((size_t)(gridDim.x / GB) * kCopies + (size_t)grp * 2) * S::SLICES, 2);
     for (int t = T - 1; t >= 0; --t) {
         for (int b = 0; b < GB; ++b) {
             const int u = b * kUnits + a.un;
@@ -460,7 +486,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_bwd(const bf16_t *__re
             if (t + 1 < T) {
                 a.carry = carry_of[(size_t)a.n * S::H + u];
                 a.load_rows(b * kUnits);
-                a.multiply(t);
+                a.template multiply<false>(t);
                 __syncthreads();
                 a.collect();
                 __syncthreads();
@@ -477,8 +503,24 @@ __global__ __launch_bounds__(kThreads, 1) void k_lstm_seq_bwd(const bf16_t *__re
     }
 }
 
+// no ticket drawn, nobody has given up, nothing sent: `zeros` 16-byte words of 0, then `ones` of kUnsent
+__global__ __launch_bounds__(256) void k_lstm_prepare(chunk16 *p, unsigned zeros, unsigned ones)
+{
+    for (unsigned i = blockIdx.x * 256u + threadIdx.x; i < zeros + ones; i += gridDim.x * 256u) {
+        const unsigned v = i < zeros ? 0u : kUnsent;
+        p[i] = chunk16{v, v, v, v};
+    }
+}
+
 int groups_of(int N) { return (N + kSeqs - 1) / kSeqs; }
 size_t ctl_bytes(int N) { return (size_t)(1 + groups_of(N)) * kCtlWords * sizeof(unsigned); }
+
+hipError_t prepare(void *workspace, int N, size_t slices, hipStream_t s)
+{
+    const unsigned zeros = (unsigned)(ctl_bytes(N) / 16), ones = (unsigned)(groups_of(N) * kCopies * slices / 16), want = (zeros + ones + 1023) / 1024;
+    hipLaunchKernelGGL(k_lstm_prepare, dim3(want < 1024 ? want : 1024), dim3(256), 0, s, (chunk16 *)workspace, zeros, ones);
+    return hipGetLastError();
+}
 
 }  // namespace
 
@@ -499,16 +541,16 @@ bool lstm_seq_supported(int N, int T, int H, int compute_units)
     return blocks <= 1024 && 2 * blocks <= 256ll * per_unit * T;
 }
 
-// ticket line and flags, then two copies of every group's slices (backward's, the wider ones), then those of the blocks that
-// compute a group by themselves
-size_t lstm_seq_workspace(int N, int H) { return ctl_bytes(N) + (size_t)groups_of(N) * 2 * 2 * 4 * H * kSeqs * 2; }
+// ticket line and groups' lines, then the copies of every group's slices (backward's, the wider ones), then two of those of the
+// blocks that compute a group by themselves
+size_t lstm_seq_workspace(int N, int H) { return ctl_bytes(N) + (size_t)groups_of(N) * (kCopies + 2) * 4 * H * kSeqs * 2; }
 
 #define LSTM_CASES(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
 
 hipError_t lstm_seq_fwd(const void *P, const void *w_hh, float *gates, float *cells, void *h, void *hs, int N, int T, int H,
                         void *workspace, hipStream_t s, unsigned wait_polls)
 {
-    const hipError_t e = fill_f32((float *)workspace, 0.0f, ctl_bytes(N) / sizeof(float), s);
+    const hipError_t e = prepare(workspace, N, (size_t)H * kSeqs * 2, s);
     if (e != hipSuccess) return e;
     const dim3 grid(groups_of(N) * (H / kUnits));
     switch (H / 128) {
@@ -527,7 +569,7 @@ hipError_t lstm_seq_fwd(const void *P, const void *w_hh, float *gates, float *ce
 hipError_t lstm_seq_bwd(const void *dy, const void *wt_h, const float *gates, const float *cells, float *dcn, void *D, int N, int T, int H,
                         void *workspace, hipStream_t s, unsigned wait_polls)
 {
-    const hipError_t e = fill_f32((float *)workspace, 0.0f, ctl_bytes(N) / sizeof(float), s);
+    const hipError_t e = prepare(workspace, N, (size_t)4 * H * kSeqs * 2, s);
     if (e != hipSuccess) return e;
     const dim3 grid(groups_of(N) * (H / kUnits));
     switch (H / 128) {

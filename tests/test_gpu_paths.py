@@ -43,7 +43,7 @@ def _lstm_seq(direction, signature):
     return f
 
 
-def _lstm_layer(n, t, h, polls):
+def _lstm_layer(n, t, h, polls, spoil=None):
     """Both directions of one layer's recurrence on seeded operands: every tensor they write, as integers."""
     g = torch.Generator("cuda")
     g.manual_seed(n + t + h)
@@ -51,6 +51,8 @@ def _lstm_layer(n, t, h, polls):
     rand = lambda *shape: (torch.rand(shape, device="cuda", generator=g) * 2 - 1).bfloat16()
     p, dy, w = rand(n, t, 4 * h), rand(n, t, h), rand(4 * h, h) / h ** 0.5
     wt = w.t().contiguous()
+    if spoil:
+        spoil(p, dy)
     gates, cells = torch.empty(n, t, 4 * h, device="cuda"), torch.empty(n, t, h, device="cuda")
     y, ys, d = torch.empty(n, t, h, **bf16), torch.empty(n, t, h, **bf16), torch.empty(n, t, 4 * h, **bf16)
     carry = torch.empty(n, h, device="cuda")
@@ -74,6 +76,23 @@ def test_lstm_sequence_kernels_finish_without_their_neighbours(h, t, n):
     for polls in (0, 1, 8, 64):
         for a, b in zip(_lstm_layer(n, t, h, polls), want):
             assert torch.equal(a, b), polls
+
+
+def test_lstm_sequence_kernels_pass_nan_on():
+    """Values that are not numbers travel between blocks too, whatever their bits: the sequence they are in has them from
+    its first on, in forward to the end, in backward to the start; the others do not, and nobody gives up."""
+    n, t, h = 20, 6, 256
+    want = _lstm_layer(n, t, h, 1 << 14)
+    spoil = lambda p, dy: (p[3, 2].view(torch.int16).fill_(-1), dy[17, 4].view(torch.int16).fill_(-1))
+    got, alone = _lstm_layer(n, t, h, 1 << 14, spoil), _lstm_layer(n, t, h, 0, spoil)
+    as_float = lambda x: x.view(torch.bfloat16 if x.dtype == torch.int16 else torch.float32).float()
+    y, d = as_float(got[2]), as_float(got[4])
+    assert torch.isnan(y[3, 2:]).all() and not torch.isnan(y[3, :2]).any()
+    assert torch.isnan(d[17, :5]).all() and not torch.isnan(d[17, 5]).any()
+    for a, b, c in zip(got, want, alone):
+        rest = [i for i in range(n) if i not in (3, 17)]
+        assert torch.equal(a[rest], b[rest])
+        assert torch.equal(torch.isnan(as_float(a)), torch.isnan(as_float(c)))
 
 
 @pytest.mark.parametrize("hidden,reads", [(128, 1), (64, 5)])       # the recurrent matrix: kept for the launch, read each step
