@@ -23,6 +23,8 @@ struct GatherConv {
     // units it leaves idle are not lost, and fewer, larger blocks (less operand traffic per FLOP) are the better neighbour.
     // Only the pixel tile may depend on it: every output element is still one sum over K in the same order.
     int beside = 0;
+    // The output is the input of a batch-norm, or the gradient of one's output: kernels that leave it the sums it needs are preferred.
+    int by_norm = 0;
 };
 
 // Forward-convolution geometry (x: N,H,W,C ; y: N,P,Q,K ; filter R x S).

@@ -1,5 +1,5 @@
 // 3x3 / stride 1 / pad 1 convolution (forward, and dgrad through the flipped filter) for feature
-// maps whose sides are multiples of 16: the layers of the first VGG stage (224x224 and 112x112,
+// maps that patches of 16x16 pixels cover well: the layers of the first VGG stage (224x224 and 112x112,
 // 64 / 128 channels), where the generic gather kernel is bound by L1/L2 traffic because every
 // input pixel is fetched again for each of the 9 taps.
 //
@@ -21,6 +21,11 @@ namespace {
 __device__ __forceinline__ int swz8(int row) { return (row >> 1) & 7; }
 
 constexpr int PATCH = 16, HALO = 18, HPIX = HALO * HALO;       // 324 halo pixels
+
+// patches along a side; of the last one what lies outside the image reads zeros and is not stored
+__host__ __device__ constexpr int patches(int side) { return (side + PATCH - 1) / PATCH; }
+inline bool whole_patches(const GatherConv &g) { return g.Ho % PATCH == 0 && g.Wo % PATCH == 0; }
+
 constexpr int HL = 11;                                          // halo wave-loads per wave (44 x 64 slots >= 2592)
 // A block's tile is 64 output channels wide, whatever the layer's width (a 128-channel layer is two tiles that
 // load the same halo): filter steps of 32 input channels (4 KB stages) through a ring of two, and exactly the 41
@@ -45,6 +50,8 @@ struct halo_cfg {
 // unrolled, so ring slots, halo rows and swizzles are compile-time or precomputed per tap: a fragment
 // read costs at most one XOR.  Fragments are double-buffered in registers and the barrier that
 // publishes the next filter tile sits before the last sub-step of a step, as in the gather kernel.
+// RAGGED: patches may end outside the image (their tests in the epilogue cost whole images 0.4 % of the first VGG stage).
+template <bool RAGGED>
 __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt,
                                                          const float *__restrict__ bias, bf16_t *out,
                                                          const bf16_t *__restrict__ gate, int accum, int relu,
@@ -76,7 +83,7 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_c = Co / BC, px_tiles = W / PATCH, py_tiles = H / PATCH;
+    const int tiles_c = Co / BC, px_tiles = patches(W), py_tiles = patches(H);
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
     const int tile_c = bid % tiles_c;
     int t = bid / tiles_c;
@@ -242,8 +249,8 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
         for (int it = 0; it < UNITS; ++it) {
             const int u = tid + it * 256;
             const int pj = u / CH8, c8i = u % CH8;
-            const size_t p = (size_t)(n * H + Y0 + (pj >> 4)) * W + X0 + (pj & 15);
-            glate[it] = *reinterpret_cast<const chunk16 *>(gate + p * Co + co0 + c8i * 8);
+            const int y = Y0 + (pj >> 4), x = X0 + (pj & 15);
+            if (!RAGGED || (y < H && x < W)) glate[it] = *reinterpret_cast<const chunk16 *>(gate + ((size_t)(n * H + y) * W + x) * Co + co0 + c8i * 8);
         }
     }
 
@@ -284,6 +291,7 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
             const int u = tid + it * 256;
             const int qp = u / CH8, c8i = u % CH8;
             const int qy = qp >> 3, qx = qp & 7;
+            if (RAGGED && (Y0 / 2 + qy >= Hq || X0 / 2 + qx >= Wq)) continue;
             uint32_t w[4][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -323,7 +331,9 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
     for (int it = 0; it < UNITS; ++it) {
         const int u = tid + it * 256;
         const int pj = u / CH8, c8i = u % CH8;
-        const size_t p = (size_t)(n * H + Y0 + (pj >> 4)) * W + X0 + (pj & 15);
+        const int y = Y0 + (pj >> 4), x = X0 + (pj & 15);
+        if (RAGGED && (y >= H || x >= W)) continue;
+        const size_t p = (size_t)(n * H + y) * W + x;
         const int co = co0 + c8i * 8;
         chunk8 lo = *reinterpret_cast<const chunk8 *>(sO + pj * SROW + c8i * 8);
         chunk8 hi = *reinterpret_cast<const chunk8 *>(sO + pj * SROW + c8i * 8 + 4);
@@ -350,17 +360,12 @@ hipError_t launch_halo(const void *in, const void *wt, const float *bias, void *
     constexpr size_t smem = ring_bytes + BC * sizeof(float);
     static_assert((size_t)256 * (BC + 4) * 2 <= ring_bytes, "epilogue staging fits");
     static_assert((smem + 1279) / 1280 * halo_cfg::BLOCKS_PER_CU <= 128, "blocks per CU (LDS is handed out in 1280-byte granules)");
-    auto kfn = k_conv3x3_halo;
-    static bool attr_set = false;
-    if (!attr_set && smem > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static_assert(smem <= 64 * 1024, "no attribute needed");
+    auto kfn = whole_patches(g) ? k_conv3x3_halo<false> : k_conv3x3_halo<true>;
     const int is_grad = (epi.gate != nullptr || epi.accum) ? 1 : 0;
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * 9 * g.Ci * 2);
-    dim3 grid((unsigned)(g.N * (g.Ho / PATCH) * (g.Wo / PATCH) * (g.Co / BC)));
+    dim3 grid((unsigned)(g.N * patches(g.Ho) * patches(g.Wo) * (g.Co / BC)));
     hipLaunchKernelGGL(kfn, grid, dim3(256), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias, (bf16_t *)out,
                        (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g.N, g.Hi, g.Wi, g.Ci, g.Co, in_bytes,
                        wt_bytes, (bf16_t *)pool_out, pool_idx);
@@ -376,6 +381,7 @@ hipError_t launch_halo(const void *in, const void *wt, const float *bias, void *
 // writing its output, so a block is kept small - one 16x16 patch, a 5 KB halo, the whole 64x72 filter
 // in registers straight from L2 - and four of them share a CU.  One pixel of the halo is exactly one
 // 16-byte MFMA operand chunk: sub-step kk multiplies taps 2kk and 2kk+1 (the 10th tap is a zero filter).
+template <bool RAGGED>
 __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt,
                                                        const float *__restrict__ bias, bf16_t *__restrict__ out,
                                                        int relu, int N, int H, int W, int Co, unsigned in_bytes)
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_c = Co / BC, px_tiles = W / PATCH, py_tiles = H / PATCH;
+    const int tiles_c = Co / BC, px_tiles = patches(W), py_tiles = patches(H);
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
     const int tile_c = bid % tiles_c;
     int t = bid / tiles_c;
@@ -484,7 +490,9 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
     for (int it = 0; it < 8; ++it) {
         const int u = tid + it * 256;
         const int pj = u >> 3, c8i = u & 7;
-        const size_t p = (size_t)(n * H + Y0 + (pj >> 4)) * W + X0 + (pj & 15);
+        const int y = Y0 + (pj >> 4), x = X0 + (pj & 15);
+        if (RAGGED && (y >= H || x >= W)) continue;
+        const size_t p = (size_t)(n * H + y) * W + x;
         const chunk8 lo = *reinterpret_cast<const chunk8 *>(sO + pj * SROW + c8i * 8);
         const chunk8 hi = *reinterpret_cast<const chunk8 *>(sO + pj * SROW + c8i * 8 + 4);
         const chunk16 v = {lo[0], lo[1], hi[0], hi[1]};
@@ -893,12 +901,28 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
 
 }  // namespace
 
+// Images whose sides are not multiples of 16 take whole patches too, where that is the faster way.  us, 3x3 on the gather
+// kernel -> here, with the blocks a launch comes to and the share of their pixels that exist: 64->64 at 90x90, 5 samples (180, 88 %)
+// 15.4 -> 12.5, 200x200, 16 (2704, 92 %) 92 -> 61, 56x56, 32 (512, 77 %) 23.2 -> 16.0, 60x60, 5 (80) 10.7 / 11.4; 64->128 at
+// 45x45, 10 (180, 88 %) 12.9 -> 11.8; 128->128 at 45x45, 20 (360) 25.4 -> 20.4, 10 (180) 15.9 / 17.4, at 28x28, 64 (512, 77 %)
+// 37 -> 22, 32 (256) 16.4 / 17.2, at 20x20, 32 (256, 39 %) 12.2 / 16.6; 192->192 at 40x40, 16 (432, 69 %) 30.5 -> 27.5; 320->320 at
+// 28x28, 64 (1280) 136 -> 93; 256->256 at 30x30, 32 (512, 88 %) 41 -> 37, but at 56x56, 16 (1024, 77 %) 62.8 / 63.1 and 20x20, 64
+// (1024, 61 %) 41 / 58: whole tiles of 256 channels leave the gather kernel less to gain.
+// Not next to a batch-norm, whose sums only the gather kernel leaves.
+static bool ragged_halo(const GatherConv &g)
+{
+    const long long n = (long long)g.N * patches(g.Ho) * patches(g.Wo), pixels = (long long)g.N * g.Ho * g.Wo, blocks = n * (g.Co / 64);
+    if (g.by_norm) return false;
+    if (g.Ci >= 256 && g.Co % 256 == 0) return blocks >= 512 && 100 * pixels >= 85 * 256 * n;
+    return blocks > (g.Ci <= 64 ? 160 : g.Ci <= 128 ? 300 : 400) && 100 * pixels >= 65 * 256 * n;
+}
+
 bool conv3x3_halo_supported(const GatherConv &g)
 {
     return g.R == 3 && g.S == 3 && g.s_out == 1 && g.s_in == 1 && g.pad_h == 1 && g.pad_w == 1 && g.Hi == g.Ho &&
-           g.Wi == g.Wo && g.Ho % PATCH == 0 && g.Wo % PATCH == 0 && g.Ci % 64 == 0 && g.Co % 64 == 0 &&
+           g.Wi == g.Wo && g.Ci % 64 == 0 && g.Co % 64 == 0 &&
            (long long)g.N * g.Hi * g.Wi * g.Ci * 2 < (1ll << 31) && (long long)g.Co * 9 * g.Ci * 2 < (1ll << 31) &&
-           (long long)g.N * g.Ho * g.Wo * g.Co < (1ll << 40);
+           (long long)g.N * g.Ho * g.Wo * g.Co < (1ll << 40) && (whole_patches(g) || ragged_halo(g));
 }
 
 hipError_t conv3x3_halo_mfma(const void *in, const void *wt, const float *bias, void *out, int relu,
@@ -908,10 +932,13 @@ hipError_t conv3x3_halo_mfma(const void *in, const void *wt, const float *bias, 
     return launch_halo(in, wt, bias, out, relu, epi, g, nullptr, nullptr, s);
 }
 
+// Of ragged images the first layer is always better off here, as long as the patches are not mostly empty (64 channels, us: 90x90, 5
+// samples 9.7 -> 6.7, 200x200, 16 38.5 -> 21.2, 45x45, 5 7.0 -> 5.0, 33x33, 32, patches 47 % full, 8.7 -> 6.6).
 bool conv3x3_c8_supported(const GatherConv &g)
 {
+    const long long room = 256ll * patches(g.Ho) * patches(g.Wo), pixels = (long long)g.Ho * g.Wo;
     return g.R == 3 && g.S == 3 && g.s_out == 1 && g.s_in == 1 && g.pad_h == 1 && g.pad_w == 1 && g.Hi == g.Ho &&
-           g.Wi == g.Wo && g.Ho % PATCH == 0 && g.Wo % PATCH == 0 && g.Ci == 8 && g.Co % 64 == 0 &&
+           g.Wi == g.Wo && (whole_patches(g) || (!g.by_norm && 100 * pixels >= 45 * room)) && g.Ci == 8 && g.Co % 64 == 0 &&
            (long long)g.N * g.Hi * g.Wi * 16 < (1ll << 31) && (long long)g.N * g.Ho * g.Wo * g.Co < (1ll << 40);
 }
 
@@ -922,8 +949,8 @@ hipError_t conv3x3_c8_mfma(const void *in, const void *wt, const float *bias, vo
     constexpr size_t smem = (size_t)256 * 68 * 2 + 64 * sizeof(float);
     static_assert(smem <= 40 * 1024, "four blocks per CU");
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * 16);
-    dim3 grid((unsigned)(g.N * (g.Ho / PATCH) * (g.Wo / PATCH) * (g.Co / 64)));
-    hipLaunchKernelGGL(k_conv3x3_c8, grid, dim3(256), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,
+    dim3 grid((unsigned)(g.N * patches(g.Ho) * patches(g.Wo) * (g.Co / 64)));
+    hipLaunchKernelGGL(whole_patches(g) ? k_conv3x3_c8<false> : k_conv3x3_c8<true>, grid, dim3(256), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,
                        (bf16_t *)out, relu, g.N, g.Hi, g.Wi, g.Co, in_bytes);
     return hipGetLastError();
 }

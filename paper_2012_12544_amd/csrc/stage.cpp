@@ -269,6 +269,7 @@ GatherConv fwd_geom(const bapipe_stage *st, const Layer &L)
     g.R = L.d.kh; g.S = L.d.kw;
     g.s_out = L.d.stride; g.s_in = 1;
     g.pad_h = g.pad_w = L.d.pad;
+    g.by_norm = L.o < (int)st->layers.size() && st->layers[L.o].d.kind == BAPIPE_BATCHNORM2D && st->layers[L.o].a == L.o;
     return g;
 }
 
@@ -282,6 +283,7 @@ GatherConv dgrad_geom(const bapipe_stage *st, const Layer &L)
     g.s_out = 1; g.s_in = f.s_out;
     g.pad_h = f.R - 1 - f.pad_h;
     g.pad_w = f.S - 1 - f.pad_w;
+    g.by_norm = L.a > 0 && st->layers[L.a - 1].d.kind == BAPIPE_BATCHNORM2D;
     return g;
 }
 
@@ -1222,7 +1224,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         Layer &P = st->layers[O.consumers[0]];
         if (P.d.kind != BAPIPE_MAXPOOL2D || P.a != L.o) continue;
         if (P.d.kh != 2 || P.d.kw != 2 || P.d.stride != 2 || P.d.pad != 0) continue;
-        if (!conv3x3_halo_supported(fwd_geom(st, L)) || (O.H & 1) || (O.W & 1)) continue;
+        if (!conv3x3_halo_supported(fwd_geom(st, L))) continue;
         L.fuse_pool = O.consumers[0];
         P.fused = true;
     }

@@ -696,6 +696,61 @@ def _conv_in_doubles(x, w, pad):
     (1, 1024, 4352, (9, 8), 29),       # ... one tap; 17 channel tiles
 ])
 def test_conv_tiles_of_eight_waves(k, cin, cout, hw, mb):
+    _conv_against_doubles(k, cin, cout, hw, mb)
+
+
+@pytest.mark.parametrize("cin,cout,hw,mb", [
+    (64, 64, (83, 81), 5),             # 180 patches, cut on both sides
+    (64, 64, (17, 145), 10),           # one row of pixels in the last patch, one column
+    (128, 64, (35, 47), 36),           # two slices of channels; gradient 64->128
+    (256, 256, (30, 31), 32),          # ... four
+    (64, 72, (90, 90), 5),             # an output width that the patches do not take
+    (8, 64, (45, 33), 2),              # first layer
+    (8, 128, (17, 31), 1),             # ... a last patch of one row
+])
+def test_conv_patches_of_ragged_images(cin, cout, hw, mb):
+    _conv_against_doubles(3, cin, cout, hw, mb)
+
+
+@pytest.mark.parametrize("hw", [(83, 81), (82, 95), (90, 84)])
+def test_ragged_patches_with_pool_and_gate(hw):
+    """Against the same layers without the pool, which is done here: odd sides lose their last row or column.  The ReLU gate of
+    the input gradient against float64 sums: two bf16 roundings of 2^-9 on the way, three of them allowed."""
+    def build(pool):
+        def layers(b):
+            b.conv(64, 64, 3, relu=1, src=-1)
+            b.conv(64, 64, 3, relu=1)
+            if pool:
+                b.pool()
+        return single(layers, 64, hw, C.BF16, micro_batch=6, n_micro=1)
+    params = gen.all_params(build(True))
+    rng = np.random.default_rng(hw[1])
+    bf16 = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().float().numpy()
+    x = bf16(rng.standard_normal((6, 64) + hw))
+    h, w = hw[0] // 2, hw[1] // 2
+    dy = bf16(rng.standard_normal((6, 64, h, w)))
+    g = GpuStage(build(True), params)
+    y, idx, dx = g.forward(0, x), g.pool_indices(2, 0), g.backward(0, dy)
+    g.close()
+    plain = GpuStage(build(False), params)
+    full = plain.forward(0, x)
+    windows = np.stack([full[:, :, i:2 * h:2, j:2 * w:2] for i in (0, 1) for j in (0, 1)])
+    at = np.argmax(windows, 0)                                     # the first of equals
+    assert np.array_equal(idx, at) and np.array_equal(y, np.take_along_axis(windows, at[None], 0)[0])
+    spread = np.zeros_like(full)
+    for k in range(4):
+        spread[:, :, k // 2:2 * h:2, k % 2:2 * w:2] = np.where(at == k, dy, 0)
+    assert np.array_equal(plain.backward(0, spread), dx)
+    plain.close()
+    first = GpuStage(single(lambda b: b.conv(64, 64, 3, relu=1, src=-1), 64, hw, C.BF16, micro_batch=6, n_micro=1), params[:1])
+    gate = first.forward(0, x) > 0
+    first.close()
+    turned = lambda p: np.flip(bf16(p[0]), (2, 3)).transpose(1, 0, 2, 3)
+    ref, _ = _conv_in_doubles(bf16(np.where(gate, _conv_in_doubles(spread * (full > 0), turned(params[1]), 1)[0], 0)), turned(params[0]), 1)
+    assert np.linalg.norm(dx - ref) <= 3 * 2.0 ** -9 * np.linalg.norm(ref)
+
+
+def _conv_against_doubles(k, cin, cout, hw, mb):
     """Against float64: half a bf16 step of the result and a rounding of 2^-24 for each term of the sum."""
     st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, hw, C.BF16, micro_batch=mb, n_micro=1)
     params = gen.all_params(st)
