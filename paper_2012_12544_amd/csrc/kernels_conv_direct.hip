@@ -97,6 +97,74 @@ __global__ void k_conv_gather(const T *__restrict__ in, const T *__restrict__ wt
     }
 }
 
+// The same for a small filter and s_in = 1, out of LDS.  What bounds k_conv_gather at these sizes is the chain of a thread's loads,
+// a round of 16 channels per tap, each of them a trip to an L2 that another unit has just written to, and then the L1, for the
+// lanes of a wave read as many filter rows as there are output channels.  A block keeps the whole filter in LDS, rows padded to an odd
+// number of 16 bytes, and takes tiles of `tw` neighbouring outputs of an image row, whose input it brings in at once: one round of
+// loads a tile.  Products are added in the same order, and taps outside the image not at all.  (us, forward: 16->16 channels,
+// 3x3, four 32x32 images 6.9 -> 5.1, 3->16 7.1 -> 4.4; 32->32, 16 of 64x64 311 -> 59, 3->32 63 -> 20; 8->8, one 16x16 6.8 -> 4.4.)
+constexpr int TILE_FILTER = 10240, TILE_COUT = 64;             // floats of the filter, output channels
+constexpr int TILE_INPUT = 4096;                               // floats of a tile's input
+template <int V>
+__global__ __launch_bounds__(TPB) void k_conv_tile(const float *__restrict__ in, const float *__restrict__ wt, const float *__restrict__ bias,
+                                                   float *out, const float *__restrict__ gate, int accum, int relu, int is_grad,
+                                                   GatherConv g, int tw, int segments, int tiles, int pitch)
+{
+    extern __shared__ __align__(16) float lds[];
+    typedef vec_t<float, V> vec;
+    float *x = lds, *w = lds + TILE_INPUT;
+    const int tid = threadIdx.x, K = g.R * g.S * g.Ci, row = ((tw - 1) * g.s_out + g.S) * g.Ci;
+    for (int e = tid; e < g.Co * K / V; e += TPB) {
+        const int ko = e / (K / V), k = (e - ko * (K / V)) * V;
+        *reinterpret_cast<vec *>(w + ko * pitch + k) = *reinterpret_cast<const vec *>(wt + (size_t)e * V);
+    }
+    const int col = tid / g.Co, ko = tid - col * g.Co;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int ow0 = tile % segments * tw, nh = tile / segments, n = nh / g.Ho, oh = nh - n * g.Ho;
+        const int hn = oh * g.s_out - g.pad_h, w0 = ow0 * g.s_out - g.pad_w;
+        for (int e = tid; e < g.R * row / V; e += TPB) {
+            const int r = e / (row / V), c = (e - r * (row / V)) * V, iw = w0 + c / g.Ci, ih = hn + r;
+            if ((unsigned)ih < (unsigned)g.Hi && (unsigned)iw < (unsigned)g.Wi)
+                *reinterpret_cast<vec *>(x + r * row + c) =
+                    *reinterpret_cast<const vec *>(in + (((size_t)n * g.Hi + ih) * g.Wi + w0) * g.Ci + c);
+        }
+        __syncthreads();
+        const int ow = ow0 + col;
+        if (col < tw && ow < g.Wo) {
+            float acc = bias ? bias[ko] : 0.0f;
+            const int wn = ow * g.s_out - g.pad_w;
+            const int r0 = hn < 0 ? -hn : 0, r1 = g.Hi - hn < g.R ? g.Hi - hn : g.R;
+            const int s0 = wn < 0 ? -wn : 0, s1 = g.Wi - wn < g.S ? g.Wi - wn : g.S, len = (s1 - s0) * g.Ci;
+            for (int r = r0; r < r1; ++r) {
+                const float *a = x + r * row + (col * g.s_out + s0) * g.Ci, *b = w + ko * pitch + (r * g.S + s0) * g.Ci;
+                int c = 0;
+                for (; c + 6 * V <= len; c += 6 * V) {
+                    vec va[6], vb[6];
+#pragma unroll
+                    for (int u = 0; u < 6; ++u) {
+                        va[u] = *reinterpret_cast<const vec *>(a + c + u * V);
+                        vb[u] = *reinterpret_cast<const vec *>(b + c + u * V);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 6; ++u)
+#pragma unroll
+                        for (int j = 0; j < V; ++j) acc = fmaf(va[u].e[j], vb[u].e[j], acc);
+                }
+                for (; c < len; c += V) {
+                    const vec va = *reinterpret_cast<const vec *>(a + c), vb = *reinterpret_cast<const vec *>(b + c);
+#pragma unroll
+                    for (int j = 0; j < V; ++j) acc = fmaf(va.e[j], vb.e[j], acc);
+                }
+            }
+            if (relu) acc = fmaxf(acc, 0.0f);
+            const size_t i = ((size_t)nh * g.Wo + ow) * g.Co + ko;
+            if (is_grad) acc = grad_out<float>(acc, accum != 0, accum ? out[i] : 0.0f, gate != nullptr, gate ? gate[i] : 0.0f);
+            out[i] = acc;
+        }
+        __syncthreads();
+    }
+}
+
 // part[chunk][k][r][s][c] = sum over the chunk's output rows (n,p) and all q of
 //   dy[n,p,q,k] * x[n, p*stride+r-pad, q*stride+s-pad, c] ;  chunk = blockIdx.y
 // The K elements behind the filter's (bias != 0) are the sums of dy alone.  As two launches of their own behind this one they
@@ -161,6 +229,76 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
     part[(size_t)blockIdx.y * total + i] = acc;
 }
 
+// The same of few channels, out of LDS.  k_conv_wgrad_partial loads two values per product and is bound by the L1 that they come from.
+// Here a block has the rows of dy and x that a row of outputs meets in LDS, and a thread adds up 4 x V weights of one tap: 4 + V
+// values for 4 * V products, each sum in the same order.  (us: 32->32 channels, 3x3, 16 of 64x64 198 -> 42, 3->32 98 -> 13;
+// 16->16, four 32x32 images 8.1 either way, and below that, where the two rounds of loads are all there is, the other is faster: 3->16 5.7
+// against 5.8, whole mini-batch of 8->8, one 16x16, 165 us against 172.)
+constexpr int TILE_ROWS = 10240;                               // floats of the rows in LDS
+constexpr long long TILE_PRODUCTS = 32768;                     // fewest products of a row of outputs
+template <int V>
+__global__ __launch_bounds__(TPB) void k_conv_wgrad_tile(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part,
+                                                         ConvShape c, int rows_per_chunk, int bias)
+{
+    extern __shared__ __align__(16) float lds[];
+    typedef vec_t<float, V> vec;
+    typedef vec_t<float, 4> vec4;
+    float *g = lds, *in = lds + c.Q * c.K;                     // [Q][K], [R][W][C]
+    const int tid = threadIdx.x, items = c.K / 4 * c.R * c.S * (c.C / V), item = blockIdx.x * TPB + tid;
+    const size_t weights = (size_t)c.K * c.R * c.S * c.C, total = weights + (bias ? c.K : 0);
+    const int c0 = item % (c.C / V) * V, tap = item / (c.C / V), s = tap % c.S, r = tap / c.S % c.R, k0 = tap / c.S / c.R * 4;
+    const int off = s - c.pad;
+    const int q0 = off < 0 ? (-off + c.stride - 1) / c.stride : 0;
+    const int qe = c.W > off ? (c.W - off + c.stride - 1) / c.stride : 0, q1 = qe < c.Q ? qe : c.Q;
+    const int kb = item - items;                               // >= 0: the sum of dy's column kb
+    const bool column = bias && kb >= 0 && kb < c.K;
+    float acc[4][V] = {};
+    double sum = 0.0;
+    const int row0 = blockIdx.y * rows_per_chunk, last = row0 + rows_per_chunk, row1 = last < c.N * c.P ? last : c.N * c.P;
+    for (int row = row0; row < row1; ++row) {
+        const int n = row / c.P, p = row - n * c.P, h0 = p * c.stride - c.pad;
+        if (row > row0) __syncthreads();
+        for (int e = tid; e < c.Q * c.K / 4; e += TPB)
+            *reinterpret_cast<vec4 *>(g + e * 4) = *reinterpret_cast<const vec4 *>(dy + (size_t)row * c.Q * c.K + e * 4);
+        const int line = c.W * c.C;
+        for (int e = tid; e < c.R * line / V; e += TPB) {
+            const int rr = e / (line / V), at = (e - rr * (line / V)) * V, ih = h0 + rr;
+            if ((unsigned)ih < (unsigned)c.H)
+                *reinterpret_cast<vec *>(in + rr * line + at) = *reinterpret_cast<const vec *>(x + ((size_t)n * c.H + ih) * line + at);
+        }
+        __syncthreads();
+        if (item < items && (unsigned)(h0 + r) < (unsigned)c.H) {
+            const float *a = g + k0, *b = in + r * line + off * c.C + c0;
+#pragma unroll 4
+            for (int q = q0; q < q1; ++q) {
+                const vec4 va = *reinterpret_cast<const vec4 *>(a + q * c.K);
+                const vec vb = *reinterpret_cast<const vec *>(b + q * c.stride * c.C);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < V; ++j) acc[i][j] = fmaf(va.e[i], vb.e[j], acc[i][j]);
+            }
+        }
+        if (column)
+            for (int q = 0; q < c.Q; q += 8) {
+                float a[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a[u] = q + u < c.Q ? g[(q + u) * c.K + kb] : 0.0f;
+                sum += (double)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+            }
+    }
+    float *dst = part + (size_t)blockIdx.y * total;
+    if (column) dst[weights + kb] = (float)sum;
+    if (item >= items) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        vec v;
+#pragma unroll
+        for (int j = 0; j < V; ++j) v.e[j] = acc[i][j];
+        *reinterpret_cast<vec *>(dst + (((size_t)(k0 + i) * c.R + r) * c.S + s) * c.C + c0) = v;
+    }
+}
+
 // dw[i] += sum_chunk part[chunk][i], the elements from `weights` on to db.  LANES threads per element walk the chunks, eight loads requested at once, and their
 // sums are added in lane order: a fixed order (bit-reproducible), and chains of chunks / LANES loads (128 chunks of 2304
 // elements: 30 us with one lane, 2.7 with 16).  Up to 16 chunks, of which there are that few where the elements alone fill
@@ -219,6 +357,23 @@ inline size_t direct_wgrad_elements(const ConvShape &c)
     return direct_wgrad_chunks(c) * (w + c.K) <= DIRECT_PARTS ? w + c.K : w;
 }
 
+// paddings and sides that cannot pass the range of int when they are added
+inline bool plain(int side, int pad) { return side > 0 && side < (1 << 20) && pad > -(1 << 20) && pad < (1 << 20); }
+inline bool tile_takes(const GatherConv &g)
+{
+    if (!(g.s_in == 1 && g.s_out >= 1 && g.s_out <= 16 && g.R <= 16 && g.S <= 16 && g.Co <= TILE_COUT && g.Ci <= TILE_FILTER && plain(g.Hi, g.pad_h) &&
+          plain(g.Wi, g.pad_w)))
+        return false;
+    const int K = g.R * g.S * g.Ci;
+    return g.Co * (K + 4) <= TILE_FILTER && K <= TILE_INPUT && (long long)g.N * g.Ho * g.Wo < (1ll << 31);
+}
+inline bool wgrad_tile_takes(const ConvShape &c)
+{
+    return c.K % 4 == 0 && c.R <= 16 && c.S <= 16 && c.stride >= 1 && c.stride <= 16 && plain(c.H, c.pad) && plain(c.W, c.pad) && c.Q < (1 << 20) &&
+           (long long)c.K * c.C <= 64 * 64 && (long long)c.Q * c.K + (long long)c.R * c.W * c.C <= TILE_ROWS &&
+           (long long)c.K * c.C * c.R * c.S * c.Q >= TILE_PRODUCTS;
+}
+
 }  // namespace
 
 hipError_t conv_gather_direct(int dt, const void *in, const void *wt, const float *bias, void *out,
@@ -230,6 +385,23 @@ hipError_t conv_gather_direct(int dt, const void *in, const void *wt, const floa
     int is_grad = (epi.gate != nullptr || epi.accum) ? 1 : 0;
     // whole 16-byte groups of four floats need a channel count that is a multiple of four and aligned operands
     const bool vec = dt == DT_F32 && g.Ci % 4 == 0 && ((uintptr_t)in | (uintptr_t)wt) % 16 == 0;
+    const int K = g.R * g.S * g.Ci;
+    if (dt == DT_F32 && tile_takes(g)) {
+        const int V = vec ? 4 : 1, pitch = V == 4 ? (K / 4 | 1) * 4 : K | 1;
+        int tw = TPB / g.Co;
+        while (tw > 1 && g.R * ((tw - 1) * g.s_out + g.S) * g.Ci > TILE_INPUT) --tw;
+        if (tw > g.Wo) tw = g.Wo;
+        const int segments = (g.Wo + tw - 1) / tw, tiles = g.N * g.Ho * segments;
+        const size_t smem = (size_t)(TILE_INPUT + g.Co * pitch) * sizeof(float);
+        const dim3 grid(tiles < 2048 ? tiles : 2048);
+        if (V == 4)
+            hipLaunchKernelGGL(k_conv_tile<4>, grid, dim3(TPB), smem, s, (const float *)in, (const float *)wt, bias, (float *)out,
+                               (const float *)epi.gate, epi.accum, relu, is_grad, g, tw, segments, tiles, pitch);
+        else
+            hipLaunchKernelGGL(k_conv_tile<1>, grid, dim3(TPB), smem, s, (const float *)in, (const float *)wt, bias, (float *)out,
+                               (const float *)epi.gate, epi.accum, relu, is_grad, g, tw, segments, tiles, pitch);
+        return hipGetLastError();
+    }
 #define GATHER_DIRECT(T_, V_)                                                                                        \
     hipLaunchKernelGGL((k_conv_gather<T_, V_>), dim3(nb), dim3(TPB), 0, s, (const T_ *)in, (const T_ *)wt, bias,      \
                        (T_ *)out, (const T_ *)epi.gate, epi.accum, relu, is_grad, g)
@@ -257,7 +429,15 @@ hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, f
     int rpc = (c.N * c.P + chunks - 1) / chunks;
     chunks = (c.N * c.P + rpc - 1) / rpc;
     float *part = (float *)workspace;
-    if (dt == DT_F32)
+    if (dt == DT_F32 && wgrad_tile_takes(c) && ((uintptr_t)x | (uintptr_t)dy) % 16 == 0) {
+        const int V = c.C % 4 == 0 ? 4 : 1, items = c.K / 4 * c.R * c.S * (c.C / V) + (along ? c.K : 0);
+        const size_t smem = (size_t)(c.Q * c.K + c.R * c.W * c.C) * sizeof(float);
+        const dim3 grid((items + TPB - 1) / TPB, chunks);
+        if (V == 4)
+            hipLaunchKernelGGL(k_conv_wgrad_tile<4>, grid, dim3(TPB), smem, s, (const float *)x, (const float *)dy, part, c, rpc, (int)along);
+        else
+            hipLaunchKernelGGL(k_conv_wgrad_tile<1>, grid, dim3(TPB), smem, s, (const float *)x, (const float *)dy, part, c, rpc, (int)along);
+    } else if (dt == DT_F32)
         hipLaunchKernelGGL((k_conv_wgrad_partial<float>), dim3(nb, chunks), dim3(TPB), 0, s,
                            (const float *)x, (const float *)dy, part, c, rpc, (int)along);
     else

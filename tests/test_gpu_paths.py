@@ -383,6 +383,22 @@ def test_output_that_overlaps_the_input(dtype, kind, shift):
 
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
+    (3, 1, 1, 16, 64, (9, 33), 2),       # four outputs a tile and channel, the last tile one column
+    (3, 1, 1, 64, 12, (6, 50), 1),       # 21 columns a tile, which their input does not allow
+    (3, 1, 1, 3, 12, (5, 8), 1),         # one channel at a time; fewer columns than a tile
+    (5, 2, 2, 8, 20, (11, 13), 2),       # every other column, taps outside on all sides
+    (1, 1, 0, 60, 60, (5, 7), 1),
+    (7, 1, 3, 4, 4, (6, 5), 1),          # a filter larger than the image
+    (3, 1, 0, 12, 8, (40, 64), 60),      # more tiles than blocks, several image rows a chunk
+    (3, 1, 1, 32, 32, (4, 80), 2),       # three times the threads of a block for the weights of a row
+    (3, 1, 1, 20, 64, (8, 9), 2),        # a filter that LDS does not take
+])
+def test_direct_conv_tiles(k, stride, pad, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.FP32, micro_batch=mb)
+    compare_minibatch(st, verbose="direct conv tiles k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
+
+
+@pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 1, 1, 20, 12, (9, 11), 3),       # a last trip of one vector of channels
     (3, 2, 2, 4, 8, (8, 7), 2),          # fewer channels than a trip, two columns of padding
     (1, 3, 0, 36, 5, (10, 10), 2),       # gradient operand with an odd channel count: one channel at a time
