@@ -55,7 +55,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
     int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split, int part_tiles,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
-    const bf16_t *old_from)
+    const bf16_t *old_from, int turned)
 {
     constexpr int NW = WP * WC, NT = NW * KG * 64;      // waves of a group, threads of the block
     constexpr int CPR = BK / 8;              // 16-byte chunks per tile row
@@ -179,14 +179,22 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
         cb = KT ? ti / taps * BK : g.Ci;               // a class without taps reads nothing
     }
 
+    // Turned: the block starts at a K-tile of its own and goes round.  Blocks that stream a filter of which the caches hold nothing
+    // would otherwise all ask for the same columns of its rows at a time, which in a matrix of 4096 columns lie on few memory
+    // channels (25088x4096, 64 rows of pixels, nothing of it cached, 80 -> 70 us; mini-batch of the classifier 3786 -> 3661).
+    constexpr bool TURNS = FAST && BP == 64 && BC == 128 && BK == 64 && KG == 1 && !PHASED;
+    const int from = TURNS && turned ? tile_c % (kt1 - kt0) * BK : 0;
     auto issue_tile = [&](int stage) {
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
             const bool kin = KG > 1 ? ti < kt1 : cb < g.Ci;
             const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
             const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
-            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + cb) * 2u;
-            const unsigned wo = kin ? (unsigned)(tap * g.Ci + cb) * 2u : OOB;
+            int c0 = cb;
+            if constexpr (TURNS)
+                if (from) c0 = cb + from < g.Ci ? cb + from : cb + from - g.Ci;
+            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + c0) * 2u;
+            const unsigned wo = kin ? (unsigned)(tap * g.Ci + c0) * 2u : OOB;
 #pragma unroll
             for (int i = 0; i < XL; ++i) {
                 unsigned vo = (tapmask[i] & bit) ? xoff[i] + xo : OOB;
@@ -816,6 +824,8 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
+    // one row of tiles, so that every byte of the filter is read once, and more of them than the L2s hold
+    const int turned = npix <= 64 && g.R * g.S == 1 && plan.classes == 1 && plan.splits == 1 && wt_bytes > (32u << 20);
     dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
 #define GATHER_LAUNCH(S1_, TI_, PH_)                                                                                   \
     do {                                                                                                          \
@@ -829,7 +839,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         hipLaunchKernelGGL(kfn, grid, dim3(NT), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,          \
                            (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g, tiles_c, in_bytes, \
                            wt_bytes, part, plan.kt_per_split, plan.part_tiles, stat_part, (const bf16_t *)bn_x, bn_stats,         \
-                           (const bf16_t *)epi.accum_from);                                                      \
+                           (const bf16_t *)epi.accum_from, turned);                                              \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
     if constexpr (KG > 1) {                                         // stride-1 operands

@@ -715,6 +715,12 @@ def test_conv_tiles_of_eight_waves(k, cin, cout, hw, mb):
     _conv_against_doubles(k, cin, cout, hw, mb)
 
 
+@pytest.mark.parametrize("cin,cout,mb", [(1088, 16400, 33), (1024, 16640, 64)])
+def test_conv_tiles_that_start_anywhere_in_k(cin, cout, mb):
+    """One row of 129 and 130 tiles over a filter of 35 MB: every block at another of the 17 and 16 K-tiles."""
+    _conv_against_doubles(1, cin, cout, (1, 1), mb)
+
+
 @pytest.mark.parametrize("cin,cout,hw,mb", [
     (64, 64, (83, 81), 5),             # 180 patches, cut on both sides
     (64, 64, (17, 145), 10),           # one row of pixels in the last patch, one column
