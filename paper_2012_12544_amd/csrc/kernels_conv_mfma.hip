@@ -907,9 +907,9 @@ constexpr size_t kWgradLds = KG > 1 && (size_t)KG * (BKO * (BCI + 4) + BKO) * 4 
                                  : (size_t)KG * STAGES * 32 * (BKO + BCI) * 2;
 
 template <int BKO, int BCI, int WKO, int WCI, int STAGES, int KG = 1>
-__global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(const bf16_t *__restrict__ x,
+__global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(const bf16_t *x_of0, const bf16_t *x_of1,
                                                                   const bf16_t *__restrict__ dy,
-                                                                  float *part, float *bpart, size_t split_stride,
+                                                                  float *part_of0, float *part_of1, float *bpart_of0, size_t split_stride,
                                                                   ConvShape c, int tiles_n, int pix_per_split, int part_tiles,
                                                                   int add_to_dst, unsigned x_bytes,
                                                                   unsigned dy_bytes)
@@ -936,8 +936,12 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     // The tiles of one pixel split read the same dy and x rows: number the blocks so that a split's tiles run on
     // one XCD (one L2) - consecutive block ids go round the eight XCDs, so each XCD gets a contiguous range of
     // (split, tile) positions.  With a single split (or few blocks) this is the identity up to a permutation.
-    const int pos = xcd_remap((int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
-    const int bx = pos % (int)gridDim.x, by = pos / (int)gridDim.x;
+    const int pos = xcd_remap((int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
+    const int bx = pos % (int)gridDim.x, by = pos / (int)gridDim.x % (int)gridDim.y;
+    // the second product of a pair: another x, the same dy
+    const bool second = pos >= (int)(gridDim.x * gridDim.y);
+    const bf16_t *x = second ? x_of1 : x_of0;
+    float *part = second ? part_of1 : part_of0, *bpart = second ? nullptr : bpart_of0;
     const int tn = bx % tiles_n, tko = bx / tiles_n;
     const int ko0 = tko * BKO, n0 = tn * BCI;
     const int Ntot = c.R * c.S * c.C;
@@ -1058,7 +1062,8 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     // Groups of waves: a product takes fewer splits, so a group's sum has more terms than a split's had.  It is put aside and started
     // anew every part_tiles tiles: 320x2880 from 3136 rows, one split, 1.08e-7 off 64 bits (normal operands) where one sum was
     // 2.3e-7 and seven splits of 448 rows 1.24e-7; 16 registers of 128 more and 0.2 % of a mini-batch.
-    constexpr int FA = KG > 1 ? TA : 1, FB = KG > 1 ? TB : 1;
+    constexpr bool PARTS = KG > 1 || (BKO == 256 && WKO == 4);
+    constexpr int FA = PARTS ? TA : 1, FB = PARTS ? TB : 1;
     f32x16_t aside[FA][FB];
     float baside[FA];
 #pragma unroll
@@ -1070,7 +1075,7 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
             for (int v = 0; v < 16; ++v) aside[a][b][v] = 0.0f;
     }
     auto fold = [&]() {
-        if constexpr (KG > 1) {
+        if constexpr (PARTS) {
 #pragma unroll
             for (int a = 0; a < TA; ++a) {
                 baside[a] += bsum[a];
@@ -1127,7 +1132,7 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     load_frags(0, 0, fa0, fb0);
     int rd = 0, kt = 0, end = 0;
     do {
-        end = KG == 1 || end + part_tiles > KT ? KT : end + part_tiles;
+        end = !PARTS || end + part_tiles > KT ? KT : end + part_tiles;
         for (; kt < end; ++kt) {
             const int nx = rd + 1 == STAGES ? 0 : rd + 1;
             if constexpr (MIXED) {
@@ -1175,8 +1180,16 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
             rd = nx;
         }
         fold();
-    } while (KG > 1 && end < KT);
+    } while (PARTS && end < KT);
     WAIT_VMCNT(0);
+    if constexpr (PARTS && KG == 1) {
+#pragma unroll
+        for (int a = 0; a < TA; ++a) {
+            bsum[a] = baside[a];
+#pragma unroll
+            for (int b = 0; b < TB; ++b) acc[a][b] = aside[a][b];
+        }
+    }
 
     if constexpr (KG > 1) {
         // Every group parks its sums in LDS ([row][column] floats over its own ring and the next ones), then all threads
@@ -1318,13 +1331,18 @@ __global__ void k_splitk_reduce(const float *__restrict__ part, float *dw, float
 struct WgradPlan {
     int bko, bci, kg, tiles_ko, tiles_n, splits, pix_per_split;
     int part_tiles;          // wave groups: tiles of 32 pixels that a group adds up before it puts the sum aside
+    int wko;                 // waves along the output channels of a 256 x 128 tile
+    bool pair;
 };
 
 // beside: kernels of other streams run beside the launch.  Only the tile may depend on it, not the splits: every sum stays the
 // same, in the same order.
-WgradPlan wgrad_plan(const ConvShape &c, bool beside)
+// pair: of two such products that share dy, in one launch without splits, if the plan says that they can be (`pair`).
+WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
 {
     WgradPlan p;
+    p.pair = false;
+    p.wko = 2;
     const int Ntot = c.R * c.S * c.C;
     const long long npix = (long long)c.N * c.P * c.Q;
     auto tiles_of = [&](int bko, int bci) { return (long long)((c.K + bko - 1) / bko) * ((Ntot + bci - 1) / bci); };
@@ -1360,6 +1378,22 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside)
             !(beside && npix < 25000))
             p.bci = 256;
     }
+    // Both products of a pair as tiles of 256 x 128, eight waves each, where that is about a block per unit: half the operand
+    // bytes of 128 x 64 (4096x1024 from 3200 rows, twice: 72 us against 2 x 45; rings of five or six stages 73).  Their sums are put
+    // aside every 8 tiles: a chain of 16 and one of 13 where a group of the smaller tiles has 24 and 5.
+    if (pair && c.R * c.S == 1 && c.K % 256 == 0 && c.C % 128 == 0 && npix >= 1024 && 2 * tiles_of(256, 128) >= 192 && 2 * tiles_of(256, 128) <= 256) {
+        p.pair = true;
+        p.kg = 1;
+        p.bko = 256;
+        p.bci = 128;
+        p.wko = 4;
+        p.tiles_ko = c.K / 256;
+        p.tiles_n = c.C / 128;
+        p.splits = 1;
+        p.pix_per_split = (int)((npix + 31) / 32 * 32);
+        p.part_tiles = 8;
+        return p;
+    }
     p.tiles_ko = (c.K + p.bko - 1) / p.bko;
     p.tiles_n = (Ntot + p.bci - 1) / p.bci;
     const long long tiles = (long long)p.tiles_ko * p.tiles_n;
@@ -1369,21 +1403,28 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside)
         double best = 1e30;
         long long want = 1;
         const double alone = p.bko == 64 ? 0.36 : 0.45, shared = p.bko == 64 ? 0.30 : 0.36;
+        auto cost_of = [&](long long tiles, long long sp) {
+            const long long per_unit = (tiles * sp + 255) / 256;
+            return (double)per_unit * (double)((npix + 64 * sp - 1) / (64 * sp)) * (per_unit == 1 ? alone : shared) +
+                   (sp > 1 ? 3.5 + (double)sp * c.K * Ntot * 2e-6 : 0.0);
+        };
         for (long long sp = 1; sp <= 256; ++sp) {
             if (sp > 1 && (npix < 64 * sp || tiles * sp > 2048 || (double)sp * c.K * (Ntot + 1) * 4 > 32e6)) break;
-            const long long per_unit = (tiles * sp + 255) / 256;
-            const double cost = (double)per_unit * (double)((npix + 64 * sp - 1) / (64 * sp)) * (per_unit == 1 ? alone : shared) +
-                                (sp > 1 ? 3.5 + (double)sp * c.K * Ntot * 2e-6 : 0.0);
+            const double cost = cost_of(tiles, sp);
             if (cost < best) {
                 best = cost;
                 want = sp;
             }
         }
+        // less than two launches of their own, by the same estimate and 2.5 us for a launch (512 hidden units, 50 steps of 64 sequences,
+        // mini-batch 3837 -> 3754 us; 256, 20 steps of 48 1962 -> 1828)
+        p.pair = c.R * c.S == 1 && cost_of(2 * tiles, 1) <= 2.0 * best + 2.5;
+        if (pair && p.pair) want = 1;
         const long long pps = ((npix + want - 1) / want + 63) / 64 * 64;
         p.pix_per_split = (int)pps;
         p.splits = npix > 0 ? (int)((npix + pps - 1) / pps) : 1;
-        // equal parts of at most 12 tiles, 384 pixels
-        const int tiles_g = (int)(pps / 64), parts = (tiles_g + 11) / 12;
+        // equal parts of at most 12 tiles, 384 pixels; of 8, which balances a longer chain of parts, where a pair takes no splits
+        const int most = pair && p.pair ? 8 : 12, tiles_g = (int)(pps / 64), parts = (tiles_g + most - 1) / most;
         p.part_tiles = parts ? (tiles_g + parts - 1) / parts : 1;
         return p;
     }
@@ -1486,7 +1527,7 @@ size_t conv_wgrad_mfma_workspace(const ConvShape &c)
 }
 
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &shape, hipStream_t s, bool beside)
+                           const ConvShape &shape, hipStream_t s, bool beside, const void *x2, float *dw2)
 {
     ConvShape c = shape;
     if (!conv_wgrad_mfma_supported(c)) return hipErrorInvalidValue;
@@ -1500,8 +1541,12 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
     }
     if (wgrad3x3_halo_supported(c)) return wgrad3x3_halo_mfma(x, dy, dw, db, workspace, c, s);
     if (wgrad3x3_c8_supported(c)) return wgrad3x3_c8_mfma(x, dy, dw, db, workspace, c, s);
-    WgradPlan p = wgrad_plan(c, beside);
-    dim3 grid((unsigned)(p.tiles_ko * p.tiles_n), (unsigned)p.splits);
+    WgradPlan p = wgrad_plan(c, beside, x2 != nullptr);
+    if (x2 && !p.pair) {
+        const hipError_t e = conv_wgrad_mfma(x, dy, dw, db, workspace, shape, s, beside);
+        return e == hipSuccess ? conv_wgrad_mfma(x2, dy, dw2, nullptr, workspace, shape, s, beside) : e;
+    }
+    dim3 grid((unsigned)(p.tiles_ko * p.tiles_n), (unsigned)p.splits, x2 ? 2 : 1);
     const int direct = p.splits == 1;
     const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (db ? c.K : 0);
     float *part = direct ? dw : (float *)workspace;
@@ -1516,8 +1561,8 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
             if (e != hipSuccess) return e;                                                                 \
             attr_set = true;                                                                               \
         }                                                                                                  \
-        hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * KG_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)dy, part, bpart, \
-                           total, c, p.tiles_n, p.pix_per_split, p.part_tiles, direct, x_bytes, dy_bytes); \
+        hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * KG_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)x2, \
+                           (const bf16_t *)dy, part, dw2, bpart, total, c, p.tiles_n, p.pix_per_split, p.part_tiles, direct, x_bytes, dy_bytes); \
     } while (0)
     const unsigned x_bytes = (unsigned)((size_t)c.N * c.H * c.W * c.C * 2);
     const unsigned dy_bytes = (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2);
@@ -1525,6 +1570,8 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
         WG_LAUNCH(64, 64, 2, 2, 2);
     else if (p.kg == 2)
         WG_LAUNCH(128, 64, 2, 2, 2);
+    else if (p.wko == 4)
+        WG_LAUNCH(256, 128, 4, 2, 1);
     else if (p.bci == 256)
         WG_LAUNCH(256, 256, 2, 4, 1);
     else if (p.bko == 256)

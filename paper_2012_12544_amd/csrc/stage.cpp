@@ -529,7 +529,9 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     ConvShape cx{N, T, 1, In, T, 1, G, 1, 1, 1, 0}, ch{N, T, 1, H, T, 1, G, 1, 1, 1, 0};
     float *dw_h = L.dw + (size_t)G * In;
     tp = st->tap_begin(mf ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT);
-    if (mf) {
+    if (mf && In == H) {
+        HIPCHK(conv_wgrad_mfma(x, D, L.dw, L.db, st->work, cx, s, false, hs, dw_h));
+    } else if (mf) {
         HIPCHK(conv_wgrad_mfma(x, D, L.dw, L.db, st->work, cx, s));
         HIPCHK(conv_wgrad_mfma(hs, D, dw_h, nullptr, st->work, ch, s));
     } else {

@@ -95,6 +95,41 @@ def test_lstm_sequence_kernels_pass_nan_on():
         assert torch.equal(torch.isnan(as_float(a)), torch.isnan(as_float(c)))
 
 
+class _ConvShape(ct.Structure):
+    _fields_ = [(f, ct.c_int) for f in "N H W C P Q K R S stride pad".split()]
+
+
+@pytest.mark.parametrize("c,k,rows,bias", [
+    (1024, 4096, 1043, True),     # 256 x 128, 33 tiles of rows, the last of 19: four parts and a short one
+    (896, 3584, 1024, False),     # ... 14 x 7 of them, twice
+    (512, 2048, 700, True),       # 128 x 64, two groups of waves
+    (128, 512, 333, True),        # 64 x 64
+    (1024, 4096, 40, False),      # two launches
+    (72, 40, 9, True),
+])
+def test_weight_gradients_of_a_pair(c, k, rows, bias):
+    """dw += dy^T x and dw2 += dy^T x2: against float64, a rounding of 2^-24 for each term of the sum and each of the additions."""
+    g = torch.Generator("cuda")
+    g.manual_seed(c + rows)
+    rand = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+    x, x2, dy = rand(rows, c).bfloat16(), rand(rows, c).bfloat16(), rand(rows, k).bfloat16()
+    dw, dw2, db = rand(k, c), rand(k, c), rand(k)
+    want = [dw.double() + dy.double().t() @ x.double(), dw2.double() + dy.double().t() @ x2.double(), db.double() + dy.double().sum(0)]
+    terms = [dw.abs() + dy.float().abs().t() @ x.float().abs(), dw2.abs() + dy.float().abs().t() @ x2.float().abs(), db.abs() + dy.float().abs().sum(0)]
+    shape = _ConvShape(rows, 1, 1, c, 1, 1, k, 1, 1, 1, 0)
+    size = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
+    size.restype = ct.c_size_t
+    work = torch.empty(size(ct.byref(shape)) + 256, device="cuda", dtype=torch.uint8)
+    ptr = lambda t: ct.c_void_p(t.data_ptr())
+    f = getattr(B.load(), "_ZN6bapipe15conv_wgrad_mfmaEPKvS1_PfS2_PvRKNS_9ConvShapeEP12ihipStream_tbS1_S2_")
+    f.restype = ct.c_int
+    assert f(ptr(x), ptr(dy), ptr(dw), ptr(db) if bias else None, ptr(work), ct.byref(shape),
+             ct.c_void_p(torch.cuda.current_stream().cuda_stream), ct.c_bool(False), ptr(x2), ptr(dw2)) == 0
+    torch.cuda.synchronize()
+    for got, ref, t in list(zip((dw, dw2, db), want, terms))[:3 if bias else 2]:
+        assert ((got.double() - ref).abs() <= (rows + 8) * 2.0 ** -24 * t).all()
+
+
 @pytest.mark.parametrize("hidden,reads", [(128, 1), (64, 5)])       # the recurrent matrix: kept for the launch, read each step
 def test_lstm_traffic_is_what_the_layer_moves(hidden, reads):
     cin, t, n, g = 24, 6, 5, 4 * hidden
