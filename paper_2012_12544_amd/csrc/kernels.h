@@ -97,6 +97,18 @@ size_t conv_wgrad_mfma_workspace(const ConvShape &c);
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
                            const ConvShape &c, hipStream_t s, bool beside = false, const void *x2 = nullptr, float *dw2 = nullptr);
 
+// Several of them, in as few launches as their tiles and the workspace allow: the same sums as one by one.  Each by itself must fit
+// the workspace.
+struct WgradJob {
+    const void *x, *dy;
+    float *dw, *db;
+    ConvShape c;
+    const void *x2 = nullptr;
+    float *dw2 = nullptr;
+};
+bool conv_wgrad_mfma_groups(const ConvShape &c);      // whether it is of the kind that shares launches
+hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s, bool beside);
+
 // ---- column sums over a [rows][C] matrix: out[c] += sum_r a[r][c]  (bias gradient)
 size_t colsum_workspace(int rows, int C);
 hipError_t colsum_accumulate(int dt, const void *a, int rows, int C, float *out, void *workspace,

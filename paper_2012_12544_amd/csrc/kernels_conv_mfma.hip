@@ -906,14 +906,47 @@ constexpr size_t kWgradLds = KG > 1 && (size_t)KG * (BKO * (BCI + 4) + BKO) * 4 
                                  ? (size_t)KG * (BKO * (BCI + 4) + BKO) * 4
                                  : (size_t)KG * STAGES * 32 * (BKO + BCI) * 2;
 
-template <int BKO, int BCI, int WKO, int WCI, int STAGES, int KG = 1>
-__global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(const bf16_t *x_of0, const bf16_t *x_of1,
-                                                                  const bf16_t *__restrict__ dy,
-                                                                  float *part_of0, float *part_of1, float *bpart_of0, size_t split_stride,
-                                                                  ConvShape c, int tiles_n, int pix_per_split, int part_tiles,
-                                                                  int add_to_dst, unsigned x_bytes,
-                                                                  unsigned dy_bytes)
+// One product of a launch, or two of one shape with the same dy.
+struct WgradArgs {
+    const bf16_t *x, *x2, *dy;
+    float *part, *part2, *bpart;
+    size_t split_stride;
+    ConvShape c;
+    int tiles, tiles_n, splits, blocks;          // tiles of a split, blocks of the product
+    int pix_per_split, part_tiles, add_to_dst;
+    unsigned x_bytes, dy_bytes;
+};
+// Products of one launch: small ones fill a fraction of the chip each, and a launch apiece lets them wait for each other (three
+// of a bottleneck of 256 channels at 14x14, four samples, 64 to 144 blocks each: mini-batch 868 -> 774 us; four of the first VGG stage, 90x90, five
+// samples, 252 blocks each and their reductions: 481 -> 390).  Ones that give every unit a block gain nothing (ResNet's end 2792 -> 2827).
+constexpr int WG_GROUP = 6;
+template <class Args> struct Group {
+    Args a[WG_GROUP];
+    int n;
+};
+typedef Group<WgradArgs> WgradGroup;
+
+// The product that a block of a launch belongs to, and the block's number in it.  A launch of one has it at hand: looking it up costs
+// a chain of scalar loads, 0.5 us of a short launch.
+template <class Args> __device__ __forceinline__ const Args &job_of(const Group<Args> &g, int &id)
 {
+    int job = 0;
+    while (job + 1 < g.n && id >= g.a[job].blocks) id -= g.a[job++].blocks;
+    return g.a[job];
+}
+template <class Args> __device__ __forceinline__ const Args &job_of(const Args &a, int &) { return a; }
+
+template <int BKO, int BCI, int WKO, int WCI, int STAGES, int KG, class In>
+__global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mfma(In in)
+{
+    int id = blockIdx.x;
+    const WgradArgs &job_args = job_of(in, id);
+    const ConvShape c = job_args.c;
+    const bf16_t *dy = job_args.dy;
+    const size_t split_stride = job_args.split_stride;
+    const int tiles = job_args.tiles, tiles_n = job_args.tiles_n, splits = job_args.splits, pix_per_split = job_args.pix_per_split;
+    const int part_tiles = job_args.part_tiles, add_to_dst = job_args.add_to_dst;
+    const unsigned x_bytes = job_args.x_bytes, dy_bytes = job_args.dy_bytes;
     constexpr int BKP = 32;
     constexpr int NW = WKO * WCI;                        // waves of a group
     constexpr int STEP = KG * BKP;                       // pixels from one tile of a group to its next
@@ -936,12 +969,12 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     // The tiles of one pixel split read the same dy and x rows: number the blocks so that a split's tiles run on
     // one XCD (one L2) - consecutive block ids go round the eight XCDs, so each XCD gets a contiguous range of
     // (split, tile) positions.  With a single split (or few blocks) this is the identity up to a permutation.
-    const int pos = xcd_remap((int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
-    const int bx = pos % (int)gridDim.x, by = pos / (int)gridDim.x % (int)gridDim.y;
+    const int pos = xcd_remap(id, job_args.blocks);
+    const int bx = pos % tiles, by = pos / tiles % splits;
     // the second product of a pair: another x, the same dy
-    const bool second = pos >= (int)(gridDim.x * gridDim.y);
-    const bf16_t *x = second ? x_of1 : x_of0;
-    float *part = second ? part_of1 : part_of0, *bpart = second ? nullptr : bpart_of0;
+    const bool second = pos >= tiles * splits;
+    const bf16_t *x = second ? job_args.x2 : job_args.x;
+    float *part = second ? job_args.part2 : job_args.part, *bpart = second ? nullptr : job_args.bpart;
     const int tn = bx % tiles_n, tko = bx / tiles_n;
     const int ko0 = tko * BKO, n0 = tn * BCI;
     const int Ntot = c.R * c.S * c.C;
@@ -1301,12 +1334,24 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
 // most rows have up to 256 partials (64x64 from 100352 rows, normal operands, 8.9e-8 off 64 bits; in float 1.7e-7).
 // Entries past total_w are the bias partials and go to db.  total_w and total are multiples of 4
 // (channel counts are multiples of 8).
-__global__ void k_splitk_reduce(const float *__restrict__ part, float *dw, float *db, size_t total_w, size_t total,
-                                int splits)
+struct SplitkArgs {
+    const float *part;
+    float *dw, *db;
+    size_t total_w, total;
+    int splits, blocks;
+};
+typedef Group<SplitkArgs> SplitkGroup;
+template <class In> __global__ void k_splitk_reduce(In in)
 {
+    int id = blockIdx.x;
+    const SplitkArgs &job = job_of(in, id);
+    const float *__restrict__ part = job.part;
+    float *dw = job.dw, *db = job.db;
+    const size_t total_w = job.total_w, total = job.total;
+    const int splits = job.splits;
     __shared__ double red[4][4][64];
     const int col = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    const size_t i = ((size_t)blockIdx.x * 64 + col) * 4;
+    const size_t i = ((size_t)id * 64 + col) * 4;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     if (i < total) {
 #pragma unroll 4
@@ -1526,63 +1571,130 @@ size_t conv_wgrad_mfma_workspace(const ConvShape &c)
     return p.splits == 1 ? 0 : (size_t)p.splits * ((size_t)c.K * c.R * c.S * c.C + c.K) * sizeof(float);
 }
 
-hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &shape, hipStream_t s, bool beside, const void *x2, float *dw2)
+// products of one tile shape that wait for their launch, and the partial sums that wait for theirs
+namespace {
+struct WgradBatch {
+    WgradGroup g;
+    SplitkGroup r;
+    int bko = 0, bci = 0, wko = 0, kg = 0;
+};
+
+hipError_t launch_batch(WgradBatch &b, hipStream_t s)
 {
-    ConvShape c = shape;
-    if (!conv_wgrad_mfma_supported(c)) return hipErrorInvalidValue;
-    if ((long long)c.N * c.P * c.Q == 0) return hipSuccess;
-    // A 1x1 filter at stride 1 contracts over a plain list of rows: as images of one pixel a tile step is one constant
-    // add.  (The step over image rows costs a lane up to 32 trips where a row is one pixel, as in a sequence: the LSTM's
-    // weight gradients, 3200 rows, 4096 x 1024, 99 -> 38 us.)
-    if (c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0) {
-        c.N *= c.P * c.Q;
-        c.H = c.W = c.P = c.Q = 1;
-    }
-    if (wgrad3x3_halo_supported(c)) return wgrad3x3_halo_mfma(x, dy, dw, db, workspace, c, s);
-    if (wgrad3x3_c8_supported(c)) return wgrad3x3_c8_mfma(x, dy, dw, db, workspace, c, s);
-    WgradPlan p = wgrad_plan(c, beside, x2 != nullptr);
-    if (x2 && !p.pair) {
-        const hipError_t e = conv_wgrad_mfma(x, dy, dw, db, workspace, shape, s, beside);
-        return e == hipSuccess ? conv_wgrad_mfma(x2, dy, dw2, nullptr, workspace, shape, s, beside) : e;
-    }
-    dim3 grid((unsigned)(p.tiles_ko * p.tiles_n), (unsigned)p.splits, x2 ? 2 : 1);
-    const int direct = p.splits == 1;
-    const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (db ? c.K : 0);
-    float *part = direct ? dw : (float *)workspace;
-    float *bpart = !db ? nullptr : (direct ? db : part + total_w);
-#define WG_LAUNCH(BKO_, BCI_, WKO_, WCI_, KG_)                                                             \
+    if (b.g.n == 0) return hipSuccess;
+    unsigned blocks = 0, sums = 0;
+    for (int i = 0; i < b.g.n; ++i) blocks += (unsigned)b.g.a[i].blocks;
+    for (int i = 0; i < b.r.n; ++i) sums += (unsigned)b.r.a[i].blocks;
+#define WG_LAUNCH(BKO_, BCI_, WKO_, WCI_, KG_, IN_, in_)                                                   \
     do {                                                                                                   \
         constexpr size_t smem = kWgradLds<BKO_, BCI_, 3, KG_>;                                             \
-        auto kfn = k_wgrad_mfma<BKO_, BCI_, WKO_, WCI_, 3, KG_>;                                              \
+        auto kfn = k_wgrad_mfma<BKO_, BCI_, WKO_, WCI_, 3, KG_, IN_>;                                      \
         static bool attr_set = false;                                                                      \
         if (!attr_set && smem > 64 * 1024) {                                                               \
             hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
             if (e != hipSuccess) return e;                                                                 \
             attr_set = true;                                                                               \
         }                                                                                                  \
-        hipLaunchKernelGGL(kfn, grid, dim3(WKO_ * WCI_ * KG_ * 64), smem, s, (const bf16_t *)x, (const bf16_t *)x2, \
-                           (const bf16_t *)dy, part, dw2, bpart, total, c, p.tiles_n, p.pix_per_split, p.part_tiles, direct, x_bytes, dy_bytes); \
+        hipLaunchKernelGGL(kfn, dim3(blocks), dim3(WKO_ * WCI_ * KG_ * 64), smem, s, in_);                 \
     } while (0)
-    const unsigned x_bytes = (unsigned)((size_t)c.N * c.H * c.W * c.C * 2);
-    const unsigned dy_bytes = (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2);
-    if (p.kg == 2 && p.bko == 64)
-        WG_LAUNCH(64, 64, 2, 2, 2);
-    else if (p.kg == 2)
-        WG_LAUNCH(128, 64, 2, 2, 2);
-    else if (p.wko == 4)
-        WG_LAUNCH(256, 128, 4, 2, 1);
-    else if (p.bci == 256)
-        WG_LAUNCH(256, 256, 2, 4, 1);
-    else if (p.bko == 256)
-        WG_LAUNCH(256, 128, 2, 2, 1);
+    const WgradArgs &one = b.g.a[0];
+    if (b.g.n > 1 && b.bko == 64)                          // products with wave groups
+        WG_LAUNCH(64, 64, 2, 2, 2, WgradGroup, b.g);
+    else if (b.g.n > 1)
+        WG_LAUNCH(128, 64, 2, 2, 2, WgradGroup, b.g);
+    else if (b.kg == 2 && b.bko == 64)
+        WG_LAUNCH(64, 64, 2, 2, 2, WgradArgs, one);
+    else if (b.kg == 2)
+        WG_LAUNCH(128, 64, 2, 2, 2, WgradArgs, one);
+    else if (b.wko == 4)
+        WG_LAUNCH(256, 128, 4, 2, 1, WgradArgs, one);
+    else if (b.bci == 256)
+        WG_LAUNCH(256, 256, 2, 4, 1, WgradArgs, one);
+    else if (b.bko == 256)
+        WG_LAUNCH(256, 128, 2, 2, 1, WgradArgs, one);
     else
-        WG_LAUNCH(128, 128, 2, 2, 1);
+        WG_LAUNCH(128, 128, 2, 2, 1, WgradArgs, one);
 #undef WG_LAUNCH
-    if (!direct)
-        hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, s, part,
-                           dw, db, total_w, total, p.splits);
+    if (b.r.n > 1) hipLaunchKernelGGL(k_splitk_reduce<SplitkGroup>, dim3(sums), dim3(256), 0, s, b.r);
+    else if (b.r.n) hipLaunchKernelGGL(k_splitk_reduce<SplitkArgs>, dim3(sums), dim3(256), 0, s, b.r.a[0]);
+    b.g.n = b.r.n = 0;
     return hipGetLastError();
+}
+}  // namespace
+
+bool conv_wgrad_mfma_groups(const ConvShape &c)
+{
+    if (!conv_wgrad_mfma_supported(c) || wgrad3x3_halo_supported(c) || wgrad3x3_c8_supported(c)) return false;
+    const WgradPlan p = wgrad_plan(c, false);
+    return p.kg == 2 && (long long)p.tiles_ko * p.tiles_n * p.splits < 256;
+}
+
+hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s, bool beside)
+{
+    WgradBatch batch[2] = {};                               // of 64 and of 128 output channels a tile
+    size_t used = 0;
+    auto launch_all = [&]() {
+        for (WgradBatch &b : batch) {
+            const hipError_t e = launch_batch(b, s);
+            if (e != hipSuccess) return e;
+        }
+        used = 0;
+        return hipSuccess;
+    };
+    for (int k = 0; k < n; ++k) {
+        const WgradJob &j = jobs[k];
+        ConvShape c = j.c;
+        if (!conv_wgrad_mfma_supported(c)) return hipErrorInvalidValue;
+        if ((long long)c.N * c.P * c.Q == 0) continue;
+        // A 1x1 filter at stride 1 contracts over a plain list of rows: as images of one pixel a tile step is one constant
+        // add.  (The step over image rows costs a lane up to 32 trips where a row is one pixel, as in a sequence: the LSTM's
+        // weight gradients, 3200 rows, 4096 x 1024, 99 -> 38 us.)
+        if (c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0) {
+            c.N *= c.P * c.Q;
+            c.H = c.W = c.P = c.Q = 1;
+        }
+        hipError_t e = hipSuccess;
+        if (wgrad3x3_halo_supported(c) || wgrad3x3_c8_supported(c)) {
+            if ((e = launch_all()) != hipSuccess) return e;
+            e = wgrad3x3_halo_supported(c) ? wgrad3x3_halo_mfma(j.x, j.dy, j.dw, j.db, workspace, c, s)
+                                           : wgrad3x3_c8_mfma(j.x, j.dy, j.dw, j.db, workspace, c, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        const WgradPlan p = wgrad_plan(c, beside, j.x2 != nullptr);
+        if (j.x2 && !p.pair) {
+            const WgradJob two[2] = {{j.x, j.dy, j.dw, j.db, c}, {j.x2, j.dy, j.dw2, nullptr, c}};
+            if ((e = launch_all()) != hipSuccess || (e = conv_wgrad_mfma_jobs(two, 2, workspace, workspace_bytes, s, beside)) != hipSuccess) return e;
+            continue;
+        }
+        const int direct = p.splits == 1;
+        const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (j.db ? c.K : 0);
+        const size_t want = direct ? 0 : ((size_t)p.splits * total * sizeof(float) + 255) / 256 * 256;
+        WgradBatch &b = batch[p.bko != 64];
+        // a product without wave groups fills the chip by itself
+        if ((p.kg == 1 || used + want > workspace_bytes || b.g.n == WG_GROUP) && (e = launch_all()) != hipSuccess) return e;
+        float *part = direct ? j.dw : (float *)((char *)workspace + used);
+        used += want;
+        b.bko = p.bko;
+        b.bci = p.bci;
+        b.wko = p.wko;
+        b.kg = p.kg;
+        const int tiles = p.tiles_ko * p.tiles_n;
+        b.g.a[b.g.n++] = {(const bf16_t *)j.x, (const bf16_t *)j.x2, (const bf16_t *)j.dy, part, j.dw2,
+                          !j.db ? nullptr : (direct ? j.db : part + total_w), total, c, tiles, p.tiles_n, p.splits,
+                          tiles * p.splits * (j.x2 ? 2 : 1), p.pix_per_split, p.part_tiles, direct,
+                          (unsigned)((size_t)c.N * c.H * c.W * c.C * 2), (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2)};
+        if (!direct) b.r.a[b.r.n++] = {part, j.dw, j.db, total_w, total, p.splits, (int)((total / 4 + 63) / 64)};
+        if (p.kg == 1 && (e = launch_all()) != hipSuccess) return e;
+    }
+    return launch_all();
+}
+
+hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
+                           const ConvShape &c, hipStream_t s, bool beside, const void *x2, float *dw2)
+{
+    const WgradJob job{x, dy, dw, db, c, x2, dw2};
+    return conv_wgrad_mfma_jobs(&job, 1, workspace, ~(size_t)0, s, beside);
 }
 
 }  // namespace bapipe

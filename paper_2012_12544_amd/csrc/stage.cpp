@@ -110,6 +110,9 @@ struct WgradLaunch {
 // 64, 23x23, 31 samples 1450 -> 1095; 10 samples of 16x16, projection, 720 -> 550; the ResNet stem of 8 images of 112x112
 // 2270 -> 1625; full-sized stages the same.
 constexpr double kForkUs = 10.5, kForkFlopPerUs = 6e8, kForkBytesPerUs = 2.5e6;
+// Without that stream, and at the end of a pass, weight gradients of less than this share launches.
+constexpr double kGroupUs = 15.0;
+constexpr size_t kGroupWorkspace = 24u << 20;      // for their partial sums, if they have that many
 // Events that order kernels of this device's streams and that nobody on the host waits for: without the fence that makes memory
 // visible to the host and other devices, which every stream's own synchronisation brings (mini-batches on three streams, us: bottleneck of
 // 256 channels at 14x14, 32 samples, 1400 -> 1355, of 128 at 56x56 3465 -> 3378, the ResNet stem 4994 -> 4872).
@@ -716,12 +719,19 @@ int run_wgrad(bapipe_stage *st, const WgradLaunch &w, bool mfma, hipStream_t s, 
 
 int run_waiting_wgrads(bapipe_stage *st, hipStream_t s, char *work)
 {
+    if (st->w_waiting.empty()) return BAPIPE_OK;
+    std::vector<WgradJob> jobs;
+    double flop = 0.0, bytes = 0.0;
     for (const WgradLaunch &w : st->w_waiting) {
-        const int rc = run_wgrad(st, w, true, s, work);
-        if (rc != BAPIPE_OK) return rc;
+        jobs.push_back({w.x, w.dy, w.layer->dw, w.layer->db, w.shape});
+        flop += w.flop;
+        bytes += w.bytes;
     }
     st->w_waiting.clear();
     st->w_waiting_us = 0.0;
+    const bool tp = st->tap_begin(BAPIPE_KC_CONV_WGRAD_MFMA, s);
+    HIPCHK(conv_wgrad_mfma_jobs(jobs.data(), (int)jobs.size(), work, st->work_bytes, s, st->stream_b || st->stream_w));
+    st->tap_end(tp, flop, bytes);
     return BAPIPE_OK;
 }
 
@@ -751,10 +761,12 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             const WgradLaunch w{x, g, &L, cs, flop, (double)A.bytes() + O.bytes() + 8.0 * L.w_elems};
             // a layer without an input gradient ends the pass's kernel chain: its weight gradient would only delay
             // the end of the pass from the other stream
-            if (mf && st->stream_w && !c.profiling && a_grad) {
+            const double us = w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
+            const bool small = us < kGroupUs && mf && conv_wgrad_mfma_groups(cs);
+            if (mf && !c.profiling && (small || (st->stream_w && a_grad))) {
                 st->w_waiting.push_back(w);
-                st->w_waiting_us += w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
-                if (st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
+                st->w_waiting_us += us;
+                if (st->stream_w && a_grad && st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
                     HIPCHK(hipEventRecord(st->ev_g, s));
                     HIPCHK(hipStreamWaitEvent(st->stream_w, st->ev_g, 0));
                     st->w_used = true;
@@ -1247,7 +1259,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         Bn.fuse_add = i;
         S.fused = true;
     }
-    size_t work = 256, flush = 0;
+    size_t work = 256, flush = 0, grouped = 0;
     for (int i = 0; i < n_layers; ++i) {
         Layer &L = st->layers[i];
         const Tensor &A = st->tensors[L.a];
@@ -1341,6 +1353,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             }
             size_t w = use_mfma_wgrad(st, cs) ? conv_wgrad_mfma_workspace(cs) : conv_wgrad_direct_workspace(cs);
             work = w > work ? w : work;
+            if (use_mfma_wgrad(st, cs) && !L.deferred && conv_wgrad_mfma_groups(cs)) grouped += align_up(w);
             w = colsum_workspace(cs.N * cs.P * cs.Q, cs.K);
             work = w > work ? w : work;
             GatherConv fg = fwd_geom(st, L), dg = dgrad_geom(st, L);
@@ -1367,6 +1380,8 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     st->slot_bytes = align_up(slot);
     st->transient_bytes = trans;
     st->grads_bytes = gr;
+    grouped = grouped < kGroupWorkspace ? grouped : kGroupWorkspace;
+    work = grouped > work ? grouped : work;
     st->work_bytes = work;
     st->flush_bytes = flush > work ? flush : work;
 

@@ -130,6 +130,47 @@ def test_weight_gradients_of_a_pair(c, k, rows, bias):
         assert ((got.double() - ref).abs() <= (rows + 8) * 2.0 ** -24 * t).all()
 
 
+class _WgradJob(ct.Structure):
+    _fields_ = [("x", ct.c_void_p), ("dy", ct.c_void_p), ("dw", ct.c_void_p), ("db", ct.c_void_p), ("c", _ConvShape), ("x2", ct.c_void_p), ("dw2", ct.c_void_p)]
+
+
+@pytest.mark.parametrize("room", [1 << 30, 0])      # of the workspace: for all partial sums, or for those of one product at a time
+def test_weight_gradients_that_share_launches(room):
+    """The same bits as one by one: products of both tile shapes, more than a launch takes, some with partial sums, one that
+    fills the chip by itself, one on patches."""
+    shapes = [(2, 9, 9, 64, 64, 3), (1, 20, 20, 128, 128, 3), (3, 14, 14, 256, 64, 1), (2, 14, 14, 128, 256, 3), (5, 7, 7, 512, 512, 1),
+              (4, 64, 64, 128, 128, 3), (1, 4, 4, 2048, 4096, 1), (2, 30, 30, 72, 40, 3), (4, 28, 28, 256, 256, 3), (1, 5, 5, 8, 64, 3), (2, 11, 13, 64, 192, 3)]
+    g = torch.Generator("cuda")
+    g.manual_seed(5)
+    rand = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+    size = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
+    size.restype = ct.c_size_t
+    f = getattr(B.load(), "_ZN6bapipe20conv_wgrad_mfma_jobsEPKNS_8WgradJobEiPvmP12ihipStream_tb")
+    f.restype = ct.c_int
+    keep, jobs, most = [], [], 0
+    for n, h, w, c, k, r in shapes:
+        t = [rand(n, h, w, c).bfloat16(), rand(n, h, w, k).bfloat16(), rand(k, r, r, c), rand(k)]
+        keep.append(t)
+        shape = _ConvShape(n, h, w, c, h, w, k, r, r, 1, r // 2)
+        most = max(most, size(ct.byref(shape)))
+        jobs.append(_WgradJob(t[0].data_ptr(), t[1].data_ptr(), t[2].data_ptr(), t[3].data_ptr(), shape, None, None))
+    start = [[a.clone() for a in t[2:]] for t in keep]
+    room = max(room, most) if room == 0 else 4 * most
+    work = torch.empty(room + 4096, device="cuda", dtype=torch.uint8)
+    stream = ct.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def run(batches):
+        for t, s0 in zip(keep, start):
+            for a, b in zip(t[2:], s0):
+                a.copy_(b)
+        for b in batches:
+            assert f((_WgradJob * len(b))(*b), ct.c_int(len(b)), ct.c_void_p(work.data_ptr()), ct.c_size_t(room), stream, ct.c_bool(False)) == 0
+        torch.cuda.synchronize()
+        return [a.clone() for t in keep for a in t[2:]]
+    for a, b in zip(run([jobs]), run([[j] for j in jobs])):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("hidden,reads", [(128, 1), (64, 5)])       # the recurrent matrix: kept for the launch, read each step
 def test_lstm_traffic_is_what_the_layer_moves(hidden, reads):
     cin, t, n, g = 24, 6, 5, 4 * hidden
