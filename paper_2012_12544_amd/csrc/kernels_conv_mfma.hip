@@ -49,13 +49,13 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // 3x3 / 2 with the gate and batch-norm sums of a bottleneck, 32 samples, 512 channels, 14x14 from 7x7: 104 -> 24 us; 128
 // channels, 56x56 from 28x28: 84 -> 41 us.  With the taps not innermost only for 1x1 filters, whose K is the channels of the
 // one tap either way.
-template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false>
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool TURNS = false>
 __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
     int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split, int part_tiles,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
-    const bf16_t *old_from, int turned)
+    const bf16_t *old_from)
 {
     constexpr int NW = WP * WC, NT = NW * KG * 64;      // waves of a group, threads of the block
     constexpr int CPR = BK / 8;              // 16-byte chunks per tile row
@@ -179,11 +179,12 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
         cb = KT ? ti / taps * BK : g.Ci;               // a class without taps reads nothing
     }
 
-    // Turned: the block starts at a K-tile of its own and goes round.  Blocks that stream a filter of which the caches hold nothing
+    // TURNS: the block starts at a K-tile of its own and goes round.  Blocks that stream a filter of which the caches hold nothing
     // would otherwise all ask for the same columns of its rows at a time, which in a matrix of 4096 columns lie on few memory
     // channels (25088x4096, 64 rows of pixels, nothing of it cached, 80 -> 70 us; mini-batch of the classifier 3786 -> 3661).
-    constexpr bool TURNS = FAST && BP == 64 && BC == 128 && BK == 64 && KG == 1 && !PHASED;
-    const int from = TURNS && turned ? tile_c % (kt1 - kt0) * BK : 0;
+    // A variant of its own: the test costs the others 3 % (784 rows, 400 blocks 13.9 -> 14.3).
+    static_assert(!TURNS || (TAPS_INNER && KG == 1 && !PHASED), "of one tap, K not split");
+    const int from = TURNS ? tile_c % (kt1 - kt0) * BK : 0;
     auto issue_tile = [&](int stage) {
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
@@ -191,8 +192,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
             const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
             const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
             int c0 = cb;
-            if constexpr (TURNS)
-                if (from) c0 = cb + from < g.Ci ? cb + from : cb + from - g.Ci;
+            if constexpr (TURNS) c0 = cb + from < g.Ci ? cb + from : cb + from - g.Ci;
             const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + c0) * 2u;
             const unsigned wo = kin ? (unsigned)(tap * g.Ci + c0) * 2u : OOB;
 #pragma unroll
@@ -825,11 +825,11 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
     // one row of tiles, so that every byte of the filter is read once, and more of them than the L2s hold
-    const int turned = npix <= 64 && g.R * g.S == 1 && plan.classes == 1 && plan.splits == 1 && wt_bytes > (32u << 20);
+    const bool turned = npix <= 64 && g.R * g.S == 1 && plan.classes == 1 && plan.splits == 1 && wt_bytes > (32u << 20);
     dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
-#define GATHER_LAUNCH(S1_, TI_, PH_)                                                                                   \
+#define GATHER_LAUNCH(S1_, TI_, ...)                                                                                   \
     do {                                                                                                          \
-        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, KG, S1_, TI_, PH_>;                                      \
+        auto kfn = k_gather_mfma<BP, BC, WP, WC, BK, STAGES, KG, S1_, TI_, __VA_ARGS__>;                              \
         static bool attr_set = false;                                                                             \
         if (!attr_set && smem > 64 * 1024) {                                                                      \
             hipError_t e = hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
@@ -839,7 +839,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         hipLaunchKernelGGL(kfn, grid, dim3(NT), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,          \
                            (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g, tiles_c, in_bytes, \
                            wt_bytes, part, plan.kt_per_split, plan.part_tiles, stat_part, (const bf16_t *)bn_x, bn_stats,         \
-                           (const bf16_t *)epi.accum_from, turned);                                              \
+                           (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
     if constexpr (KG > 1) {                                         // stride-1 operands
@@ -848,6 +848,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     } else if constexpr (BK == 64) {
         if constexpr (BP == 64) {
             if (phased) GATHER_LAUNCH(true, true, true);
+            else if (turned) GATHER_LAUNCH(true, true, false, true);
             else GATHER_LAUNCH(true, true, false);
         } else GATHER_LAUNCH(true, true, false);                    // one class
     } else if (phased) {
