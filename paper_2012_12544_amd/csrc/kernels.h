@@ -73,6 +73,7 @@ hipError_t conv3x3_c8_mfma(const void *in, const void *wt, const float *bias, vo
                            const GatherConv &g, hipStream_t s);
 // same convolution with a 2x2 stride-2 max-pool fused into the epilogue: writes the pooled output
 // [N][H/2][W/2][Co] and the arg-max indices (one byte each, same layout); the conv output is not stored
+bool conv3x3_halo_pool_supported(const GatherConv &g);
 hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *bias, int relu, void *pool_out,
                                   uint8_t *pool_idx, const GatherConv &g, hipStream_t s);
 // The same implicit GEMM leaving raw fp32 sums: part[split][pixel][co], *splits partial results the

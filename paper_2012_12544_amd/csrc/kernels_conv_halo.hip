@@ -908,22 +908,33 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
 // 37 -> 22, 32 (256) 16.4 / 17.2, at 20x20, 32 (256, 39 %) 12.2 / 16.6; 192->192 at 40x40, 16 (432, 69 %) 30.5 -> 27.5; 320->320 at
 // 28x28, 64 (1280) 136 -> 93; 256->256 at 30x30, 32 (512, 88 %) 41 -> 37, but at 56x56, 16 (1024, 77 %) 62.8 / 63.1 and 20x20, 64
 // (1024, 61 %) 41 / 58: whole tiles of 256 channels leave the gather kernel less to gain.
+// Whole images take them from 128 blocks on: fewer leave units idle, and the gather kernel has smaller tiles (64->64 at 32x32, 8 samples, 32
+// blocks 8.7 us against 10.8, at 48x48, 16, 144 14.1 / 11.4; 128->128 at 32x32, 16, 128 12.8 / 16.4; 256->256 at 16x16, 16, 64 14.9 / 26.7, 64
+// samples, 256 28.4 / 29.1; 512->512, 16 samples, 128 32.4 / 48.7, 64, 512 78 / 66).  The line lies where mini-batches on three streams, which the
+// larger blocks suit longer, and on one meet (three layers of 256 channels, 16x16, 24 samples, 96 blocks: one stream 977 -> 757, three 695 ->
+// 643; of 192, 32x32, 8, 96: 823 -> 666 and 577 -> 595; of 128, 32x32, 16, 128 blocks as gathers: 687 -> 607 and 565 / 567).
 // Not next to a batch-norm, whose sums only the gather kernel leaves.
-static bool ragged_halo(const GatherConv &g)
+static bool patches_pay(const GatherConv &g)
 {
     const long long n = (long long)g.N * patches(g.Ho) * patches(g.Wo), pixels = (long long)g.N * g.Ho * g.Wo, blocks = n * (g.Co / 64);
     if (g.by_norm) return false;
+    if (whole_patches(g)) return blocks >= 128;
     if (g.Ci >= 256 && g.Co % 256 == 0) return blocks >= 512 && 100 * pixels >= 85 * 256 * n;
     return blocks > (g.Ci <= 64 ? 160 : g.Ci <= 128 ? 300 : 400) && 100 * pixels >= 65 * 256 * n;
 }
 
-bool conv3x3_halo_supported(const GatherConv &g)
+static bool halo_takes(const GatherConv &g)
 {
     return g.R == 3 && g.S == 3 && g.s_out == 1 && g.s_in == 1 && g.pad_h == 1 && g.pad_w == 1 && g.Hi == g.Ho &&
            g.Wi == g.Wo && g.Ci % 64 == 0 && g.Co % 64 == 0 &&
            (long long)g.N * g.Hi * g.Wi * g.Ci * 2 < (1ll << 31) && (long long)g.Co * 9 * g.Ci * 2 < (1ll << 31) &&
-           (long long)g.N * g.Ho * g.Wo * g.Co < (1ll << 40) && (whole_patches(g) || ragged_halo(g));
+           (long long)g.N * g.Ho * g.Wo * g.Co < (1ll << 40);
 }
+
+bool conv3x3_halo_supported(const GatherConv &g) { return halo_takes(g) && patches_pay(g); }
+
+// A pool that rides along saves a launch and a tensor, which is worth what few blocks cost.
+bool conv3x3_halo_pool_supported(const GatherConv &g) { return halo_takes(g) && (whole_patches(g) || patches_pay(g)); }
 
 hipError_t conv3x3_halo_mfma(const void *in, const void *wt, const float *bias, void *out, int relu,
                              GradEpi epi, const GatherConv &g, hipStream_t s)
@@ -958,7 +969,7 @@ hipError_t conv3x3_c8_mfma(const void *in, const void *wt, const float *bias, vo
 hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *bias, int relu, void *pool_out,
                                   uint8_t *pool_idx, const GatherConv &g, hipStream_t s)
 {
-    if (!conv3x3_halo_supported(g) || !pool_out || !pool_idx || ((uintptr_t)pool_idx & 7)) return hipErrorInvalidValue;
+    if (!conv3x3_halo_pool_supported(g) || !pool_out || !pool_idx || ((uintptr_t)pool_idx & 7)) return hipErrorInvalidValue;
     GradEpi none{nullptr, 0};
     return launch_halo(in, wt, bias, nullptr, relu, none, g, pool_out, pool_idx, s);
 }
@@ -967,10 +978,11 @@ hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *b
 
 namespace bapipe {
 
+// (fewer pixels: 64 channels at 90x90, 5 samples 18.2 us here, 13.8 as 64 x 64 tiles of the general kernel; 200x200, 16, 39.1 / 38.3)
 bool wgrad3x3_c8_supported(const ConvShape &c)
 {
     return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 &&
-           c.W % UW == 0 && c.C == 8 && c.K % 64 == 0 && (long long)c.N * c.H * c.W * 16 < (1ll << 31) &&
+           c.W % UW == 0 && c.C == 8 && c.K % 64 == 0 && (long long)c.N * c.H * c.W >= 400000 && (long long)c.N * c.H * c.W * 16 < (1ll << 31) &&
            (long long)c.N * c.H * c.W * c.K * 2 < (1ll << 31);
 }
 
@@ -1015,10 +1027,19 @@ hipError_t wgrad3x3_c8_mfma(const void *x, const void *dy, float *dw, float *db,
     return hipGetLastError();
 }
 
+// A block of these units is a 64 x 576 tile.  Of small products, with their reductions, the 64 x 64 tiles of the general kernel are
+// faster, and share launches (us, 64->64 at 32x32, 8 samples 17.4 / 12.3, at 48x48, 16 21.6 / 18.7, 1.4 GMAC; 128->128 at 32x32, 16, 2.4 GMAC, 22.7 /
+// 24.4).  The first VGG stage at 64x64, 4 samples, one stream 673 -> 398, at 32x32, 32 samples, three 630 -> 488, with the lines above.
+static bool wgrad_units_pay(const ConvShape &c)
+{
+    const double macs = 9.0 * c.N * c.H * c.W * c.C * c.K;
+    return macs >= 2.4e9;
+}
+
 bool wgrad3x3_halo_supported(const ConvShape &c)
 {
     return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 &&
-           c.W % UW == 0 && c.C % 64 == 0 && c.K % 64 == 0 &&
+           c.W % UW == 0 && c.C % 64 == 0 && c.K % 64 == 0 && wgrad_units_pay(c) &&
            (long long)c.N * c.H * c.W * c.C * 2 < (1ll << 31) && (long long)c.N * c.H * c.W * c.K * 2 < (1ll << 31);
 }
 

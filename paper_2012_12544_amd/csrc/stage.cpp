@@ -91,6 +91,7 @@ struct Layer {
     // copy of h that the recurrent products read, the buffer shared by the input projection
     // (forward) and the pre-activation gradients (backward) and the cell-gradient carry
     size_t off_gates = 0, off_cells = 0, off_hs = 0, off_pd = 0, off_dcn = 0;
+    bool groups = false;                 // its weight gradient may share a launch with others
     bool permute_in = false;             // LINEAR fed by a flattened (C,H,W) tensor
     int pc = 0, ph = 0, pw = 0;
 };
@@ -762,7 +763,7 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             // a layer without an input gradient ends the pass's kernel chain: its weight gradient would only delay
             // the end of the pass from the other stream
             const double us = w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
-            const bool small = us < kGroupUs && mf && conv_wgrad_mfma_groups(cs);
+            const bool small = us < kGroupUs && L.groups;
             if (mf && !c.profiling && (small || (st->stream_w && a_grad))) {
                 st->w_waiting.push_back(w);
                 st->w_waiting_us += us;
@@ -1242,7 +1243,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         Layer &P = st->layers[O.consumers[0]];
         if (P.d.kind != BAPIPE_MAXPOOL2D || P.a != L.o) continue;
         if (P.d.kh != 2 || P.d.kw != 2 || P.d.stride != 2 || P.d.pad != 0) continue;
-        if (!conv3x3_halo_supported(fwd_geom(st, L))) continue;
+        if (!conv3x3_halo_pool_supported(fwd_geom(st, L))) continue;
         L.fuse_pool = O.consumers[0];
         P.fused = true;
     }
@@ -1353,7 +1354,8 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             }
             size_t w = use_mfma_wgrad(st, cs) ? conv_wgrad_mfma_workspace(cs) : conv_wgrad_direct_workspace(cs);
             work = w > work ? w : work;
-            if (use_mfma_wgrad(st, cs) && !L.deferred && conv_wgrad_mfma_groups(cs)) grouped += align_up(w);
+            L.groups = use_mfma_wgrad(st, cs) && !L.deferred && conv_wgrad_mfma_groups(cs);
+            if (L.groups) grouped += align_up(w);
             w = colsum_workspace(cs.N * cs.P * cs.Q, cs.K);
             work = w > work ? w : work;
             GatherConv fg = fwd_geom(st, L), dg = dgrad_geom(st, L);

@@ -810,6 +810,17 @@ def test_conv_patches_of_ragged_images(cin, cout, hw, mb):
     _conv_against_doubles(3, cin, cout, hw, mb)
 
 
+@pytest.mark.parametrize("cin,cout,hw,mb", [
+    (64, 64, (32, 64), 16),       # 128 patches, the fewest; weight gradient by 64 x 64 tiles
+    (128, 128, (64, 64), 4),      # ... and 2.4 GMAC, the least for units of 8 x 16 pixels
+    (256, 256, (16, 16), 32),     # ... one patch an image
+    (64, 64, (16, 16), 7),        # neither
+    (8, 64, (160, 160), 16),      # first layer, with the fewest pixels for its own weight gradient
+])
+def test_conv_patches_of_whole_images(cin, cout, hw, mb):
+    _conv_against_doubles(3, cin, cout, hw, mb)
+
+
 @pytest.mark.parametrize("hw", [(83, 81), (82, 95), (90, 84)])
 def test_ragged_patches_with_pool_and_gate(hw):
     """Against the same layers without the pool, which is done here: odd sides lose their last row or column.  The ReLU gate of
@@ -858,9 +869,16 @@ def _conv_against_doubles(k, cin, cout, hw, mb):
     x, dy = bf16(rng.standard_normal((mb, cin) + hw)), bf16(rng.standard_normal((mb, cout) + hw))
     y = g.forward(0, x)
     dx = g.backward(0, dy)
+    dw, _ = g.grads(0)
     g.close()
     w, b = params[0]
     w = bf16(w)
+    pixels = mb * hw[0] * hw[1]
+    xs, gs = (torch.from_numpy(a).to("cuda").double() for a in (x, dy))
+    cols = torch.nn.functional.unfold(xs, (k, k), padding=k // 2).transpose(0, 1).reshape(-1, pixels)
+    rows = gs.permute(0, 2, 3, 1).reshape(pixels, cout)
+    ref, terms = (a.t().reshape(dw.shape).cpu().numpy() for a in (cols @ rows, cols.abs() @ rows.abs()))
+    assert np.all(np.abs(dw - ref) <= (pixels + 1) * 2.0 ** -24 * terms)
     ref, terms = _conv_in_doubles(x, w, k // 2)
     ref += 0.0 if b is None else b.reshape(1, -1, 1, 1)
     assert np.all(np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + (k * k * cin + 1) * 2.0 ** -24 * (terms + np.abs(ref)))
