@@ -1695,7 +1695,8 @@ hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, 
                            const ConvShape &c, hipStream_t s, bool beside, const void *x2, float *dw2)
 {
     const WgradJob job{x, dy, dw, db, c, x2, dw2};
-    return conv_wgrad_mfma_jobs(&job, 1, workspace, ~(size_t)0, s, beside);
+    // no more than what the caller was told to bring: two products that are no pair take it in turn
+    return conv_wgrad_mfma_jobs(&job, 1, workspace, conv_wgrad_mfma_workspace(c), s, beside);
 }
 
 }  // namespace bapipe

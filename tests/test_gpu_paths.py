@@ -104,8 +104,11 @@ class _ConvShape(ct.Structure):
     (896, 3584, 1024, False),     # ... 14 x 7 of them, twice
     (512, 2048, 700, True),       # 128 x 64, two groups of waves
     (128, 512, 333, True),        # 64 x 64
-    (1024, 4096, 40, False),      # two launches
+    (1024, 4096, 40, False),      # ... of a step and a short one
     (72, 40, 9, True),
+    (128, 512, 3200, True),       # no pair: two launches, each with partial sums of its own
+    (64, 256, 2560, True),
+    (256, 1024, 6400, False),
 ])
 def test_weight_gradients_of_a_pair(c, k, rows, bias):
     """dw += dy^T x and dw2 += dy^T x2: against float64, a rounding of 2^-24 for each term of the sum and each of the additions."""
@@ -119,13 +122,15 @@ def test_weight_gradients_of_a_pair(c, k, rows, bias):
     shape = _ConvShape(rows, 1, 1, c, 1, 1, k, 1, 1, 1, 0)
     size = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
     size.restype = ct.c_size_t
-    work = torch.empty(size(ct.byref(shape)) + 256, device="cuda", dtype=torch.uint8)
+    room = size(ct.byref(shape))
+    work = torch.full((room + (1 << 20),), 0xA5, device="cuda", dtype=torch.uint8)         # behind it nothing may be written
     ptr = lambda t: ct.c_void_p(t.data_ptr())
     f = getattr(B.load(), "_ZN6bapipe15conv_wgrad_mfmaEPKvS1_PfS2_PvRKNS_9ConvShapeEP12ihipStream_tbS1_S2_")
     f.restype = ct.c_int
     assert f(ptr(x), ptr(dy), ptr(dw), ptr(db) if bias else None, ptr(work), ct.byref(shape),
              ct.c_void_p(torch.cuda.current_stream().cuda_stream), ct.c_bool(False), ptr(x2), ptr(dw2)) == 0
     torch.cuda.synchronize()
+    assert (work[room:] == 0xA5).all()
     for got, ref, t in list(zip((dw, dw2, db), want, terms))[:3 if bias else 2]:
         assert ((got.double() - ref).abs() <= (rows + 8) * 2.0 ** -24 * t).all()
 
