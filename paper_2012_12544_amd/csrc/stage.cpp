@@ -683,6 +683,7 @@ struct BwdCtx {
     std::vector<const void *> pending;   // per tensor: an ADD's share of its gradient that the tensor's conv will add (fanout_conv)
     bool profiling = false;        // profiler: run every kernel of the layer now (no deferral)
     int bn_sums_ready = -1;        // batch-norm layer whose backward sums the last conv left in the workspace
+    bool dx_over_dy = false;       // dx_direct overlaps dy_direct
 };
 
 void *grad_ptr(bapipe_stage *st, int t, BwdCtx &c)
@@ -764,7 +765,9 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             // the end of the pass from the other stream
             const double us = w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
             const bool small = us < kGroupUs && L.groups;
-            if (mf && !c.profiling && (small || (st->stream_w && a_grad))) {
+            // the caller's dy is read before dx may be stored over it
+            const bool now = c.dx_over_dy && g == c.dy_direct;
+            if (mf && !c.profiling && !now && (small || (st->stream_w && a_grad))) {
                 st->w_waiting.push_back(w);
                 st->w_waiting_us += us;
                 if (st->stream_w && a_grad && st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
@@ -1544,6 +1547,8 @@ int bapipe_stage_backward(bapipe_stage_t *st, int mb_id, const void *dy_dev_or_l
             c.dy_direct = dy_dev_or_labels;
         }
         c.written[r] = 1;
+        const uintptr_t dx0 = (uintptr_t)c.dx_direct, dy0 = (uintptr_t)c.dy_direct;
+        c.dx_over_dy = dx0 && dy0 && dx0 < dy0 + O.bytes() && dy0 < dx0 + In.bytes();
     }
     st->w_waiting.clear();                   // of a pass that failed
     st->w_waiting_us = 0.0;

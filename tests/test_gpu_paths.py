@@ -462,6 +462,42 @@ def test_output_that_overlaps_the_input(dtype, kind, shift):
     assert torch.equal(out[0], out[1])
 
 
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("kind,streams", [("plain", 1), ("sum", 1), ("linear", 1), ("plain", 3)])
+@pytest.mark.parametrize("shift", [0, 2])
+def test_gradient_that_overlaps_the_upstream_gradient(kind, streams, shift, static):
+    """dx may be stored over dy: whatever still reads dy has run by then."""
+    c, hw, mb = (512, (1, 1), 300) if kind == "linear" else (64, (14, 14), 4)
+    b = C._Builder()
+    if kind == "linear":
+        b.linear(c, c, relu=1, src=-1)
+        b.linear(c, c)
+    else:
+        u = b.conv(c, c, 3, relu=1, src=-1)
+        v = b.conv(c, c, 3)
+        if kind == "sum":
+            b.addl(v, u)
+    st = C._stage("over", b.layers, C.BF16, (c,) + hw, mb, 1, 1, 1, 1, C.BASE_SEED + 81, "kaiming")
+    xs, gs = stage_io(st)
+    dy = to_dev(st, gs[0], B.NHWC).reshape(-1)
+    n, at = dy.numel(), shift * c
+    entry = B.bapipe_stage_backward_static if static else B.bapipe_stage_backward
+    out = []
+    for apart in (True, False):
+        g = GpuStage(st, gen.all_params(st, perturb=True), backward_stream=streams == 3)
+        g.forward(0, xs[0])
+        buf = torch.zeros(n + at, device="cuda", dtype=dy.dtype)
+        buf[:n] = dy
+        dx = torch.zeros_like(buf) if apart else buf
+        torch.cuda.synchronize()
+        entry(g.h, 0, buf.data_ptr(), dx[at:].data_ptr())
+        torch.cuda.synchronize()
+        out.append([dx[at:at + n].float().cpu().numpy()] + [a for i, (w, _) in enumerate(g.params) if w is not None for a in g.grads(i)])
+        g.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b) and np.any(a)
+
+
 # ------------------------------------------------------------------------------ direct convolution (fp32 stages)
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 1, 1, 16, 64, (9, 33), 2),       # four outputs a tile and channel, the last tile one column
