@@ -51,8 +51,12 @@ struct halo_cfg {
 // read costs at most one XOR.  Fragments are double-buffered in registers and the barrier that
 // publishes the next filter tile sits before the last sub-step of a step, as in the gather kernel.
 // RAGGED: patches may end outside the image (their tests in the epilogue cost whole images 0.4 % of the first VGG stage).
-template <bool RAGGED>
-__global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt,
+// PARTS: a sum is put aside and started anew after at most 384 of K, as in the 128 x 64 tiles of the gather kernel, which ragged
+// layers of 64 output channels would take otherwise (sums of one sign, off 64 bits: 64->64 1.3e-7 without, 7.7e-8 with and there,
+// 256->64 3.2e-7, 6.5e-8 and 6.5e-8).  64 registers more, so two blocks share a unit, not three (us, gather kernel, with, without: 64->64 at 90x90,
+// 5 samples 15.0, 13.0, 12.1; 200x200, 16 88.6, 70.0, 58.6; 56x56, 32 29.1, 16.4, 17.8; 256->64 at 28x28, 110 51.7, 36.3, 34.8).
+template <bool RAGGED, bool PARTS>
+__global__ __launch_bounds__(256, PARTS ? 2 : halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt,
                                                          const float *__restrict__ bias, bf16_t *out,
                                                          const bf16_t *__restrict__ gate, int accum, int relu,
                                                          int is_grad, int N, int H, int W, int Ci, int Co,
@@ -137,6 +141,28 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
         for (int b = 0; b < TP; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+    constexpr int AC = PARTS ? TC : 1, AP = PARTS ? TP : 1;
+    f32x16_t aside[AC][AP];
+#pragma unroll
+    for (int a = 0; a < AC; ++a)
+#pragma unroll
+        for (int b = 0; b < AP; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) aside[a][b][v] = 0.0f;
+    auto put_aside = [&]() {
+        if constexpr (PARTS) {
+#pragma unroll
+            for (int a = 0; a < TC; ++a)
+#pragma unroll
+                for (int b = 0; b < TP; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        aside[a][b][v] += acc[a][b][v];
+                        acc[a][b][v] = 0.0f;
+                    }
+        }
+    };
 
     const int frow = lane & 31, fhalf = lane >> 5;
     const int py = 4 * wave + (frow >> 4), px = frow & 15;       // patch pixel of B tile 0 (tile 1: py + 2)
@@ -236,7 +262,23 @@ __global__ __launch_bounds__(256, halo_cfg::BLOCKS_PER_CU) void k_conv3x3_halo(c
                 __builtin_amdgcn_s_barrier();
                 load_frags(0, 0, fa0, fb0);
             }
+            // K has 18 steps of 32 a slice: two parts of nine where that is all, else parts of twelve
+            if constexpr (PARTS) {
+                if (pos == 5 || pos == 17) {
+                    if (slice & 1) put_aside();
+                } else if (pos == 8) {
+                    if (NS == 1) put_aside();
+                } else if (pos == 11) {
+                    if (NS > 1 && !(slice & 1)) put_aside();
+                }
+            }
         }
+    }
+    if constexpr (PARTS) {
+#pragma unroll
+        for (int a = 0; a < TC; ++a)
+#pragma unroll
+            for (int b = 0; b < TP; ++b) acc[a][b] += aside[a][b];
     }
     WAIT_VMCNT(0);
     __syncthreads();
@@ -361,7 +403,8 @@ hipError_t launch_halo(const void *in, const void *wt, const float *bias, void *
     static_assert((size_t)256 * (BC + 4) * 2 <= ring_bytes, "epilogue staging fits");
     static_assert((smem + 1279) / 1280 * halo_cfg::BLOCKS_PER_CU <= 128, "blocks per CU (LDS is handed out in 1280-byte granules)");
     static_assert(smem <= 64 * 1024, "no attribute needed");
-    auto kfn = whole_patches(g) ? k_conv3x3_halo<false> : k_conv3x3_halo<true>;
+    // wider layers have one sum over all of K in the gather kernel too
+    auto kfn = whole_patches(g) ? k_conv3x3_halo<false, false> : g.Co == 64 ? k_conv3x3_halo<true, true> : k_conv3x3_halo<true, false>;
     const int is_grad = (epi.gate != nullptr || epi.accum) ? 1 : 0;
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * 9 * g.Ci * 2);
@@ -903,7 +946,7 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
 
 // Images whose sides are not multiples of 16 take whole patches too, where that is the faster way.  us, 3x3 on the gather
 // kernel -> here, with the blocks a launch comes to and the share of their pixels that exist: 64->64 at 90x90, 5 samples (180, 88 %)
-// 15.4 -> 12.5, 200x200, 16 (2704, 92 %) 92 -> 61, 56x56, 32 (512, 77 %) 23.2 -> 16.0, 60x60, 5 (80) 10.7 / 11.4; 64->128 at
+// 15.0 -> 13.0, 200x200, 16 (2704, 92 %) 89 -> 70, 56x56, 32 (512, 77 %) 29 -> 16.4, 30x30, 50 (200, 88 %) 14.3 -> 13.4, 60x60, 5 (80) 10.7 / 11.4; 64->128 at
 // 45x45, 10 (180, 88 %) 12.9 -> 11.8; 128->128 at 45x45, 20 (360) 25.4 -> 20.4, 10 (180) 15.9 / 17.4, at 28x28, 64 (512, 77 %)
 // 37 -> 22, 32 (256) 16.4 / 17.2, at 20x20, 32 (256, 39 %) 12.2 / 16.6; 192->192 at 40x40, 16 (432, 69 %) 30.5 -> 27.5; 320->320 at
 // 28x28, 64 (1280) 136 -> 93; 256->256 at 30x30, 32 (512, 88 %) 41 -> 37, but at 56x56, 16 (1024, 77 %) 62.8 / 63.1 and 20x20, 64

@@ -335,6 +335,10 @@ def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
     (7, 1024, 32, 15, 4),       # 49 taps, flattened order of K
     (3, 256, 64, 28, 32),       # 128 x 64, no groups
     (3, 1024, 32, 47, 13),
+    (3, 64, 64, 90, 5),         # patches of ragged images: 18 steps of 32
+    (3, 128, 64, 45, 40),       # ... 36
+    (3, 192, 64, 40, 45),       # ... 54, the last part half as long
+    (3, 256, 64, 28, 110),      # ... 72
 ])
 def test_conv_sums_are_short(k, cin, cout, hw, mb):
     """Terms of one sign on an image that is the same everywhere, and a bias that takes the exact sum away: what is left away from
