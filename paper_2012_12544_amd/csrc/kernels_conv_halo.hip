@@ -956,12 +956,17 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
 // samples, 256 28.4 / 29.1; 512->512, 16 samples, 128 32.4 / 48.7, 64, 512 78 / 66).  The line lies where mini-batches on three streams, which the
 // larger blocks suit longer, and on one meet (three layers of 256 channels, 16x16, 24 samples, 96 blocks: one stream 977 -> 757, three 695 ->
 // 643; of 192, 32x32, 8, 96: 823 -> 666 and 577 -> 595; of 128, 32x32, 16, 128 blocks as gathers: 687 -> 607 and 565 / 567).
-// Not next to a batch-norm, whose sums only the gather kernel leaves.
+// Next to a batch-norm, whose sums only the gather kernel leaves, ragged images stay there, and whole ones up to 512 blocks, from where what
+// it fetches weighs more than a pass over the output for the sums.  Mini-batches of two 3x3 layers and their batch-norms, us, one stream and
+// three, gathers against patches: 64 channels at 32x32, 32 samples (128 blocks) 486, 473 / 622, 558; at 48x48 (288) 750, 752 / 796, 768;
+// 64x64 (512) 998, 874 / 1003, 874; 112x112 (1568) 2264, 2319 / 2125, 2145; 224x224, 16 (3136) 4084, 3929 / 3629, 3428; 128 at 32x32 (256) 764, 812 /
+// 818, 864; 64x64 (1024) 1803, 1671 / 1751, 1592; 112x112 (3136) 4912, 4915 / 4509, 4449; 256 at 16x16, 64 (256) 968, 887 / 1025, 832; 32x32, 32 (512)
+// 1435, 1488 / 1424, 1466; 512 at 16x16, 32 (256) 1500 / 1524, 64 (512) 2240, 2394 / 2169, 2218; 32x32, 32 (1024) 3781, 3857 / 3928, 3748.
 static bool patches_pay(const GatherConv &g)
 {
     const long long n = (long long)g.N * patches(g.Ho) * patches(g.Wo), pixels = (long long)g.N * g.Ho * g.Wo, blocks = n * (g.Co / 64);
+    if (whole_patches(g)) return blocks >= (g.by_norm ? 512 : 128);
     if (g.by_norm) return false;
-    if (whole_patches(g)) return blocks >= 128;
     if (g.Ci >= 256 && g.Co % 256 == 0) return blocks >= 512 && 100 * pixels >= 85 * 256 * n;
     return blocks > (g.Ci <= 64 ? 160 : g.Ci <= 128 ? 300 : 400) && 100 * pixels >= 65 * 256 * n;
 }

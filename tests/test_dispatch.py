@@ -94,6 +94,22 @@ def test_large_weights_are_not_streamed_by_more_rows_of_tiles_than_before():
     assert _pixel_tiles(128, 25088, 4096) == (0, 16 * 128 * 4096 * 4)
 
 
+@pytest.mark.parametrize("c,hw,least,beside_norm", [
+    (64, 32, 32, 128), (128, 32, 16, 64), (256, 16, 32, 128),       # whole patches: blocks of 64 channels x 256 pixels
+    (64, 90, 5, None), (128, 28, 38, None),                          # patches cut at the border: more than 160 and 300 of them
+])
+def test_3x3_layers_take_patches_from_so_many_samples_on(c, hw, least, beside_norm):
+    """Next to a batch-norm, whose sums the gather kernel leaves, later or not at all."""
+    f = getattr(B.load(), "_ZN6bapipe22conv3x3_halo_supportedERKNS_10GatherConvE")
+    f.restype = ct.c_bool
+    takes = lambda n, by_norm: f(ct.byref(_GatherConv(n, hw, hw, c, hw, hw, c, 3, 3, 1, 1, 1, 1, 0, by_norm)))
+    for by_norm, n in ((0, least), (1, beside_norm)):
+        if n is None:
+            assert not takes(1 << 10, by_norm)
+        else:
+            assert takes(n, by_norm) and not takes(n - 1, by_norm)
+
+
 # ------------------------------------------------------------------------------ workspace of the deferred weight gradients
 class _ConvShape(ct.Structure):
     _fields_ = [(f, ct.c_int) for f in "N H W C P Q K R S stride pad".split()]
