@@ -22,6 +22,7 @@
 // a workspace and a second kernel adds them in a fixed order into the fp32 accumulators.
 #include "kernels.h"
 #include "mfma_common.h"
+#include <type_traits>
 
 namespace bapipe {
 namespace {
@@ -896,7 +897,8 @@ hipError_t launch_plan(const void *in, const void *wt, const float *bias, void *
 // ------------------------------------------------------------------------------------------
 // The GEMM's N index is the flattened (r, s, c) filter position n = (r*S + s)*C + c, so a tile
 // of BCI columns covers one tap (or part of it) when C >= BCI and several taps when C is small.
-// grid: x = (ko tile, n tile) ; y = split over pixel chunks.  Same HBM -> LDS ring as the gather
+// grid: the blocks of one product after another (job_of); those of a product, renumbered over the XCDs, by split of the pixels and by
+// (ko tile, n tile) in it, the second product of a pair behind the first.  Same HBM -> LDS ring as the gather
 // kernel: STAGES tiles of 32 pixels, requests issued STAGES-1 tiles ahead, hand-placed vmcnt waits.
 // KG > 1: the block is KG groups of waves, each with a ring and a full set of sums of its own, that take the steps in turn;
 // their sums meet in LDS at the end.  A lone block's chain of steps is KG times shorter that way, and nothing is written and
@@ -917,9 +919,12 @@ struct WgradArgs {
     int pix_per_split, part_tiles, add_to_dst;
     unsigned x_bytes, dy_bytes;
 };
+struct WgradPair : WgradArgs {};
 // Products of one launch: small ones fill a fraction of the chip each, and a launch apiece lets them wait for each other (three
 // of a bottleneck of 256 channels at 14x14, four samples, 64 to 144 blocks each: mini-batch 868 -> 774 us; four of the first VGG stage, 90x90, five
-// samples, 252 blocks each and their reductions: 481 -> 390).  Ones that give every unit a block gain nothing (ResNet's end 2792 -> 2827).
+// samples, 252 blocks each and their reductions: 481 -> 390).  Ones that give every unit a block gain nothing and do not wait for
+// others (ResNet's end 2792 -> 2827).  Those that wait anyway, for the hand-over to a stream of their own, go out together whatever
+// their blocks: ones of 256 and more by themselves, conv4 block of ResNet 1392 us against 1361, its conv3 block and stem the same.
 constexpr int WG_GROUP = 6;
 template <class Args> struct Group {
     Args a[WG_GROUP];
@@ -971,9 +976,11 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     // one XCD (one L2) - consecutive block ids go round the eight XCDs, so each XCD gets a contiguous range of
     // (split, tile) positions.  With a single split (or few blocks) this is the identity up to a permutation.
     const int pos = xcd_remap(id, job_args.blocks);
-    const int bx = pos % tiles, by = pos / tiles % splits;
-    // the second product of a pair: another x, the same dy
-    const bool second = pos >= tiles * splits;
+    const int nth = pos / tiles, bx = pos - nth * tiles;
+    // The second product of a pair: another x, the same dy.  Launches that have none do not ask (1x1 512->2048 from 1568 rows 13.2 -> 12.8 us,
+    // 1024->256 from 6272 15.3 -> 15.0).
+    const bool second = !std::is_same<In, WgradArgs>::value && nth >= splits;
+    const int by = second ? nth - splits : nth;
     const bf16_t *x = second ? job_args.x2 : job_args.x;
     float *part = second ? job_args.part2 : job_args.part, *bpart = second ? nullptr : job_args.bpart;
     const int tn = bx % tiles_n, tko = bx / tiles_n;
@@ -1377,7 +1384,6 @@ template <class In> __global__ void k_splitk_reduce(In in)
 struct WgradPlan {
     int bko, bci, kg, tiles_ko, tiles_n, splits, pix_per_split;
     int part_tiles;          // wave groups: tiles of 32 pixels that a group adds up before it puts the sum aside
-    int wko;                 // waves along the output channels of a 256 x 128 tile
     bool pair;
 };
 
@@ -1388,7 +1394,6 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
 {
     WgradPlan p;
     p.pair = false;
-    p.wko = 2;
     const int Ntot = c.R * c.S * c.C;
     const long long npix = (long long)c.N * c.P * c.Q;
     auto tiles_of = [&](int bko, int bci) { return (long long)((c.K + bko - 1) / bko) * ((Ntot + bci - 1) / bci); };
@@ -1432,7 +1437,6 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
         p.kg = 1;
         p.bko = 256;
         p.bci = 128;
-        p.wko = 4;
         p.tiles_ko = c.K / 256;
         p.tiles_n = c.C / 128;
         p.splits = 1;
@@ -1577,7 +1581,7 @@ namespace {
 struct WgradBatch {
     WgradGroup g;
     SplitkGroup r;
-    int bko = 0, bci = 0, wko = 0, kg = 0;
+    int bko = 0, bci = 0, kg = 0;
 };
 
 hipError_t launch_batch(WgradBatch &b, hipStream_t s)
@@ -1599,16 +1603,21 @@ hipError_t launch_batch(WgradBatch &b, hipStream_t s)
         hipLaunchKernelGGL(kfn, dim3(blocks), dim3(WKO_ * WCI_ * KG_ * 64), smem, s, in_);                 \
     } while (0)
     const WgradArgs &one = b.g.a[0];
+    const WgradPair two{one};
     if (b.g.n > 1 && b.bko == 64)                          // products with wave groups
         WG_LAUNCH(64, 64, 2, 2, 2, WgradGroup, b.g);
     else if (b.g.n > 1)
         WG_LAUNCH(128, 64, 2, 2, 2, WgradGroup, b.g);
+    else if (one.x2 && b.kg == 2 && b.bko == 64)
+        WG_LAUNCH(64, 64, 2, 2, 2, WgradPair, two);
+    else if (one.x2 && b.kg == 2)
+        WG_LAUNCH(128, 64, 2, 2, 2, WgradPair, two);
+    else if (one.x2)                                       // the tile that is only taken for pairs
+        WG_LAUNCH(256, 128, 4, 2, 1, WgradPair, two);
     else if (b.kg == 2 && b.bko == 64)
         WG_LAUNCH(64, 64, 2, 2, 2, WgradArgs, one);
     else if (b.kg == 2)
         WG_LAUNCH(128, 64, 2, 2, 2, WgradArgs, one);
-    else if (b.wko == 4)
-        WG_LAUNCH(256, 128, 4, 2, 1, WgradArgs, one);
     else if (b.bci == 256)
         WG_LAUNCH(256, 256, 2, 4, 1, WgradArgs, one);
     else if (b.bko == 256)
@@ -1678,7 +1687,6 @@ hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, si
         used += want;
         b.bko = p.bko;
         b.bci = p.bci;
-        b.wko = p.wko;
         b.kg = p.kg;
         const int tiles = p.tiles_ko * p.tiles_n;
         b.g.a[b.g.n++] = {(const bf16_t *)j.x, (const bf16_t *)j.x2, (const bf16_t *)j.dy, part, j.dw2,
