@@ -43,8 +43,9 @@ def _lstm_seq(direction, signature):
     return f
 
 
-def _lstm_layer(n, t, h, polls, spoil=None):
-    """Both directions of one layer's recurrence on seeded operands: every tensor they write, as integers."""
+def _lstm_layer(n, t, h, polls, spoil=None, given_up=None):
+    """Both directions of one layer's recurrence on seeded operands: every tensor they write, as integers.  `given_up` receives, for
+    each direction, whether a block of a group of 16 sequences gave up: the first word of the groups' lines of 64."""
     g = torch.Generator("cuda")
     g.manual_seed(n + t + h)
     bf16 = dict(device="cuda", dtype=torch.bfloat16)
@@ -62,8 +63,13 @@ def _lstm_layer(n, t, h, polls, spoil=None):
     ptr = lambda x: ct.c_void_p(x.data_ptr())
     stream = ct.c_void_p(torch.cuda.current_stream().cuda_stream)
     dims = (ct.c_int(n), ct.c_int(t), ct.c_int(h), ptr(work), stream, ct.c_uint(polls))
+    lines = lambda: work.view(torch.int32)[64:64 * (1 + (n + 15) // 16):64].tolist()
     assert _lstm_seq("fwd", "PKvS1_PfS2_PvS3_iiiS3_P12ihipStream_tj")(ptr(p), ptr(w), ptr(gates), ptr(cells), ptr(y), ptr(ys), *dims) == 0
+    if given_up is not None:
+        given_up.append(lines())
     assert _lstm_seq("bwd", "PKvS1_PKfS3_PfPviiiS5_P12ihipStream_tj")(ptr(dy), ptr(wt), ptr(gates), ptr(cells), ptr(carry), ptr(d), *dims) == 0
+    if given_up is not None:
+        given_up.append(lines())
     torch.cuda.synchronize()
     return [x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32).clone() for x in (gates, cells, y, ys, d)]
 
@@ -84,7 +90,11 @@ def test_lstm_sequence_kernels_pass_nan_on():
     n, t, h = 20, 6, 256
     want = _lstm_layer(n, t, h, 1 << 14)
     spoil = lambda p, dy: (p[3, 2].view(torch.int16).fill_(-1), dy[17, 4].view(torch.int16).fill_(-1))
-    got, alone = _lstm_layer(n, t, h, 1 << 14, spoil), _lstm_layer(n, t, h, 0, spoil)
+    waited, left = [], []
+    got, alone = _lstm_layer(n, t, h, 1 << 14, spoil, waited), _lstm_layer(n, t, h, 0, spoil, left)
+    assert waited == [[0, 0]] * 2 and left == [[1, 1]] * 2
+    for bits in (got[2][3, 2:], got[4][17, :5]):               # pairs of values that would read as a slice not yet sent
+        assert (bits.reshape(-1, 2) == -1).all(dim=1).any()
     as_float = lambda x: x.view(torch.bfloat16 if x.dtype == torch.int16 else torch.float32).float()
     y, d = as_float(got[2]), as_float(got[4])
     assert torch.isnan(y[3, 2:]).all() and not torch.isnan(y[3, :2]).any()
