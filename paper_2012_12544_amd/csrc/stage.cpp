@@ -1626,8 +1626,8 @@ int bapipe_stage_backward_static(bapipe_stage_t *st, int mb_id, const void *dy_d
     char *ws = nullptr;
     HIPCHK(static_scratch(&ws));
     // every kernel of the backward pass writes its partial results before a later kernel of the same pass reads them, and
-    // the tickets and flags of an LSTM recurrence are cleared by a kernel in front of it, so what the previous call left
-    // there does not matter
+    // a kernel in front of an LSTM recurrence clears its tickets and the words that say who gave up, and marks all of its slices as not
+    // yet sent, so what the previous call left there does not matter
     char *own_f = st->work_f, *own_b = st->work_b;
     hipStream_t own_w = st->stream_w;
     st->work = st->work_f = ws;
