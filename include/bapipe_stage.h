@@ -251,7 +251,8 @@ int bapipe_stage_stash_bytes(const bapipe_stage_t *st, uint64_t *per_mb, int *de
  * bracketed by two HIP events on the stage's stream.  _read synchronises the stream and
  * returns the summed event time, the number of launches, and the algorithmic work of those
  * launches: FLOP (2 per multiply-accumulate) for the convolution classes, HBM bytes each
- * element must move once for the others.  Reading resets the counters.  The event pool grows
+ * element must move once for the others.  (Weight gradients of several layers that go out
+ * together share a pair of events and count one launch each.)  Reading resets the counters.  The event pool grows
  * as needed up to 262144 launches between reads; beyond that launches go unrecorded and the
  * next _read returns E_UNSUPPORTED instead of an understated sum.  kernel_class < 0 disables
  * the tap.  The events themselves cost a few per cent: time a workload with the tap off. */

@@ -162,7 +162,7 @@ struct bapipe_stage {
     // measurement tap: event pairs around launches of one kernel class
     int tap_class = -1;
     std::vector<hipEvent_t> tap_events;
-    size_t tap_used = 0;
+    size_t tap_used = 0, tap_shared = 0;      // events; products behind the first of a bracket
     double tap_flop = 0.0, tap_bytes = 0.0;
     size_t tap_dropped = 0;                  // launches of the class that found no event pair (pool limit reached)
     hipStream_t tap_stream = nullptr;        // stream of the launch being bracketed
@@ -182,9 +182,10 @@ struct bapipe_stage {
         (void)hipEventRecord(tap_events[tap_used], tap_stream);
         return true;
     }
-    void tap_end(bool on, double flop, double bytes)
+    void tap_end(bool on, double flop, double bytes, size_t products = 1)
     {
         if (!on) return;
+        tap_shared += products - 1;
         (void)hipEventRecord(tap_events[tap_used + 1], tap_stream);
         tap_used += 2;
         tap_flop += flop;
@@ -733,7 +734,7 @@ int run_waiting_wgrads(bapipe_stage *st, hipStream_t s, char *work)
     st->w_waiting_us = 0.0;
     const bool tp = st->tap_begin(BAPIPE_KC_CONV_WGRAD_MFMA, s);
     HIPCHK(conv_wgrad_mfma_jobs(jobs.data(), (int)jobs.size(), work, st->work_bytes, s, st->stream_b || st->stream_w));
-    st->tap_end(tp, flop, bytes);
+    st->tap_end(tp, flop, bytes, jobs.size());
     return BAPIPE_OK;
 }
 
@@ -1776,7 +1777,7 @@ int bapipe_stage_kernel_timing(bapipe_stage_t *st, int kernel_class)
         for (auto &e : st->tap_events) HIPCHK(hipEventCreate(&e));
     }
     st->tap_class = kernel_class < 0 ? -1 : kernel_class;
-    st->tap_used = 0;
+    st->tap_used = st->tap_shared = 0;
     st->tap_dropped = 0;
     st->tap_flop = st->tap_bytes = 0.0;
     return BAPIPE_OK;
@@ -1796,16 +1797,16 @@ int bapipe_stage_kernel_timing_read(bapipe_stage_t *st, double *total_ms, uint64
     const size_t dropped = st->tap_dropped;
     st->tap_dropped = 0;
     if (dropped) {
-        st->tap_used = 0;
+        st->tap_used = st->tap_shared = 0;
         st->tap_flop = st->tap_bytes = 0.0;
         return st->fail(BAPIPE_E_UNSUPPORTED, "kernel_timing_read: %zu launches were not recorded (more than %zu between reads)",
                         dropped, kTapMaxEvents / 2);
     }
     if (total_ms) *total_ms = ms;
-    if (launches) *launches = st->tap_used / 2;
+    if (launches) *launches = st->tap_used / 2 + st->tap_shared;
     if (flop) *flop = st->tap_flop;
     if (bytes) *bytes = st->tap_bytes;
-    st->tap_used = 0;
+    st->tap_used = st->tap_shared = 0;
     st->tap_flop = st->tap_bytes = 0.0;
     return BAPIPE_OK;
 }

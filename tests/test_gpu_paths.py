@@ -203,6 +203,25 @@ def test_lstm_traffic_is_what_the_layer_moves(hidden, reads):
     assert bwd["bytes"] == 2 * (n * t * (hidden + 2 * g + cin) + g * cin + reads * g * hidden) + floats
 
 
+@pytest.mark.parametrize("streams", [1, 3])
+def test_tap_counts_every_weight_gradient(streams):
+    """... also of those that share a launch."""
+    def build(b):
+        b.conv(64, 64, 3, relu=1, src=-1)
+        b.conv(64, 128, 1, pad=0, relu=1)
+        b.conv(128, 64, 3)
+    st = single(build, 64, (14, 14), C.BF16, micro_batch=4, n_micro=2)
+    gpu = GpuStage(st, gen.all_params(st), backward_stream=streams == 3)
+    xs, gs = stage_io(st)
+    B.bapipe_stage_kernel_timing(gpu.h, B.KC_CONV_WGRAD_MFMA)
+    for m in range(2):
+        gpu.forward(m, xs[m])
+        gpu.backward(m, gs[m])
+    tap = B.bapipe_stage_kernel_timing_read(gpu.h)
+    gpu.close()
+    assert tap["launches"] == 6 and tap["flop"] == 2 * 2.0 * 4 * 196 * (9 * 64 * 64 + 64 * 128 + 9 * 128 * 64)
+
+
 # ------------------------------------------------------------------------------ input gradient of a strided convolution
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 2, 1, 64, 32, (21, 19), 3),      # classes of unequal size, one K-tile a tap
