@@ -955,7 +955,9 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
 // blocks 8.7 us against 10.8, at 48x48, 16, 144 14.1 / 11.4; 128->128 at 32x32, 16, 128 12.8 / 16.4; 256->256 at 16x16, 16, 64 14.9 / 26.7, 64
 // samples, 256 28.4 / 29.1; 512->512, 16 samples, 128 32.4 / 48.7, 64, 512 78 / 66).  The line lies where mini-batches on three streams, which the
 // larger blocks suit longer, and on one meet (three layers of 256 channels, 16x16, 24 samples, 96 blocks: one stream 977 -> 757, three 695 ->
-// 643; of 192, 32x32, 8, 96: 823 -> 666 and 577 -> 595; of 128, 32x32, 16, 128 blocks as gathers: 687 -> 607 and 565 / 567).
+// 643; of 192, 32x32, 8, 96: 823 -> 666 and 577 -> 595; of 128, 32x32, 16, 128 blocks as gathers: 687 -> 607 and 565 / 567).  This line alone,
+// the other choices as they are, one stream and three, us: first VGG stage at 64x64, 4 samples 491, 436 -> 404, 387; at 32x32, 32 548, 497 ->
+// 493, 479; three layers of 256 channels at 16x16, 24 975, 692 -> 778, 634; of 512, 12 1566, 1024 -> 1182, 909; of 192 at 32x32, 8 824, 603 -> 678, 604.
 // Next to a batch-norm, whose sums only the gather kernel leaves, ragged images stay there, and whole ones up to 512 blocks, from where what
 // it fetches weighs more than a pass over the output for the sums.  Mini-batches of two 3x3 layers and their batch-norms, us, one stream and
 // three, gathers against patches: 64 channels at 32x32, 32 samples (128 blocks) 486, 473 / 622, 558; at 48x48 (288) 750, 752 / 796, 768;
@@ -1026,7 +1028,8 @@ hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *b
 
 namespace bapipe {
 
-// (fewer pixels: 64 channels at 90x90, 5 samples 18.2 us here, 13.8 as 64 x 64 tiles of the general kernel; 200x200, 16, 39.1 / 38.3)
+// (fewer pixels: 64 channels at 90x90, 5 samples 18.2 us here, 13.8 as 64 x 64 tiles of the general kernel; with their reductions 96x96, 16 20.8 /
+// 15.8, 128x128 23.3 / 21.9, 160x160 28.2 / 26.1, 224x224 41.0 / 39.1)
 bool wgrad3x3_c8_supported(const ConvShape &c)
 {
     return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 &&
@@ -1075,9 +1078,12 @@ hipError_t wgrad3x3_c8_mfma(const void *x, const void *dy, float *dw, float *db,
     return hipGetLastError();
 }
 
-// A block of these units is a 64 x 576 tile.  Of small products, with their reductions, the 64 x 64 tiles of the general kernel are
-// faster, and share launches (us, 64->64 at 32x32, 8 samples 17.4 / 12.3, at 48x48, 16 21.6 / 18.7, 1.4 GMAC; 128->128 at 32x32, 16, 2.4 GMAC, 22.7 /
-// 24.4).  The first VGG stage at 64x64, 4 samples, one stream 673 -> 398, at 32x32, 32 samples, three 630 -> 488, with the lines above.
+// A block of these units is a 64 x 576 tile.  Of small products the 64 x 64 tiles of the general kernel are faster, and share launches (us, with
+// the reductions, units against tiles: 64->64 at 32x32, 8 samples 15.7 / 10.6, at 48x48, 16, 1.4 GMAC 22.9 / 16.4, at 64x64, 16, 2.4 GMAC
+// 24.4 / 21.4, 32 26.2 / 28.0; 128->128 at 32x32, 8, 1.2 25.5 / 14.4, 16, 2.4 26.0 / 20.8, 32 26.7 / 28.1; 256->256 at 16x16, 8, 1.2 26.3 / 14.9, 16
+// 27.8 / 21.3, 32 30.0 / 27.4; 512->512, 4 26.4 / 16.9, 16 35.3 / 44.6).  This line alone, mini-batches on one stream and three, us: first VGG stage
+// at 64x64, 4 samples 593, 572 -> 404, 387, 16 731, 623 -> 686, 606; at 32x32, 32 647, 556 -> 493, 479; three layers of 128 channels at 32x32, 12 590, 502 ->
+// 464, 471.
 static bool wgrad_units_pay(const ConvShape &c)
 {
     const double macs = 9.0 * c.N * c.H * c.W * c.C * c.K;
