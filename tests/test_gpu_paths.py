@@ -888,6 +888,7 @@ def test_conv_patches_of_ragged_images(cin, cout, hw, mb):
     (64, 64, (32, 64), 16),       # 128 patches, the fewest; weight gradient by 64 x 64 tiles
     (128, 128, (64, 64), 4),      # ... and 2.4 GMAC, the least for units of 8 x 16 pixels
     (256, 256, (16, 16), 32),     # ... one patch an image
+    (128, 192, (32, 16), 24),     # ... 192 = 3 x 64 output channels
     (64, 64, (16, 16), 7),        # neither
     (8, 64, (160, 160), 16),      # first layer, with the fewest pixels for its own weight gradient
 ])

@@ -41,9 +41,9 @@ def test_conv_layer(dtype, k, stride, cin, cout, hw, relu):
     (1, 1, 128, 256, (9, 7), 5),      # 1x1
     (1, 2, 72, 40, (15, 15), 2),      # 1x1 stride 2
     (3, 1, 8, 8, (5, 4), 1),          # smaller than one tile in every dimension
-    (3, 1, 64, 64, (32, 48), 2),      # sides multiple of 16: halo-in-LDS kernel, 64-channel tile
-    (3, 1, 128, 128, (16, 32), 3),    # halo kernel, two 64-channel input slices, 128-channel tile
-    (3, 1, 128, 192, (32, 16), 1),    # halo kernel, 192 = 3 x 64 output channels
+    (3, 1, 64, 64, (32, 48), 2),      # sides multiple of 16, too few patches of 16x16 pixels: wave groups
+    (3, 1, 128, 128, (16, 32), 3),    # ... K = 1152
+    (3, 1, 128, 192, (32, 16), 1),    # ... 192 = 3 x 64 output channels
     (3, 1, 3, 64, (16, 32), 3),       # RGB input padded to 8 channels: first-layer kernel
     (3, 1, 3, 128, (32, 16), 2),      # ... two 64-channel output tiles
 ])
