@@ -94,13 +94,13 @@ bool conv_wgrad_mfma_supported(const ConvShape &c);
 size_t conv_wgrad_mfma_workspace(const ConvShape &c);
 // dw += dy^T x over all pixels; db (may be null) += column sums of dy
 // beside: kernels of other streams run beside the launch (as in GatherConv; the sums do not depend on it)
-// x2, dw2: another product of the same shape with the same dy, dw2 += dy^T x2, in the same launch where that is faster.  The
-// workspace is that of one product in any case
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &c, hipStream_t s, bool beside = false, const void *x2 = nullptr, float *dw2 = nullptr);
+                           const ConvShape &c, hipStream_t s, bool beside = false);
 
 // Several of them, in as few launches as their tiles and the workspace allow: the same sums as one by one.  Each by itself must fit
 // the workspace.
+// x2, dw2: another product of the same shape with the same dy, dw2 += dy^T x2; where both are tiles of one launch, their sums are those of
+// that launch
 struct WgradJob {
     const void *x, *dy;
     float *dw, *db;

@@ -979,7 +979,7 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     const int nth = pos / tiles, bx = pos - nth * tiles;
     // The second product of a pair: another x, the same dy.  Launches that have none do not ask (1x1 512->2048 from 1568 rows 13.2 -> 12.8 us,
     // 1024->256 from 6272 15.3 -> 15.0).
-    const bool second = !std::is_same<In, WgradArgs>::value && nth >= splits;
+    const bool second = std::is_same<In, WgradPair>::value && nth >= splits;
     const int by = second ? nth - splits : nth;
     const bf16_t *x = second ? job_args.x2 : job_args.x;
     float *part = second ? job_args.part2 : job_args.part, *bpart = second ? nullptr : job_args.bpart;
@@ -1103,17 +1103,18 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     // Groups of waves: a product takes fewer splits, so a group's sum has more terms than a split's had.  It is put aside and started
     // anew every part_tiles tiles: 320x2880 from 3136 rows, one split, 1.08e-7 off 64 bits (normal operands) where one sum was
     // 2.3e-7 and seven splits of 448 rows 1.24e-7; 16 registers of 128 more and 0.2 % of a mini-batch.
-    constexpr bool PARTS = KG > 1 || (BKO == 256 && WKO == 4);
+    constexpr bool PARTS = KG > 1 || std::is_same<In, WgradPair>::value;
     constexpr int FA = PARTS ? TA : 1, FB = PARTS ? TB : 1;
-    f32x16_t aside[FA][FB];
-    float baside[FA];
+    // Tiles of a pair take all of the rows: their parts are added up in double.
+    using side_t = typename std::conditional<KG == 1, double, float>::type;
+    side_t aside[FA][FB][16], baside[FA];
 #pragma unroll
     for (int a = 0; a < FA; ++a) {
-        baside[a] = 0.0f;
+        baside[a] = 0;
 #pragma unroll
         for (int b = 0; b < FB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) aside[a][b][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) aside[a][b][v] = 0;
     }
     auto fold = [&]() {
         if constexpr (PARTS) {
@@ -1225,11 +1226,11 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
     WAIT_VMCNT(0);
     if constexpr (PARTS && KG == 1) {
 #pragma unroll
-        for (int a = 0; a < TA; ++a) {
-            bsum[a] = baside[a];
+        for (int a = 0; a < TA; ++a)
 #pragma unroll
-            for (int b = 0; b < TB; ++b) acc[a][b] = aside[a][b];
-        }
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[a][b][v] = (float)aside[a][b][v];
     }
 
     if constexpr (KG > 1) {
@@ -1292,7 +1293,9 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
         float *bdst = bpart + (size_t)by * split_stride;
 #pragma unroll
         for (int a = 0; a < TA; ++a) {
-            const float t = bsum[a] + __shfl_xor(bsum[a], 32, 64);
+            float t;
+            if constexpr (PARTS) t = (float)(baside[a] + __shfl_xor(baside[a], 32, 64));
+            else t = bsum[a] + __shfl_xor(bsum[a], 32, 64);
             const int ko = ko0 + wk * WT_KO + a * 32 + col;
             if (half == 0 && ko < c.K) bdst[ko] = add_to_dst ? bdst[ko] + t : t;
         }
@@ -1389,7 +1392,7 @@ struct WgradPlan {
 
 // beside: kernels of other streams run beside the launch.  Only the tile may depend on it, not the splits: every sum stays the
 // same, in the same order.
-// pair: of two such products that share dy, in one launch without splits, if the plan says that they can be (`pair`).
+// pair: of two such products that share dy, if the plan says that they can be one (`pair`).
 WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
 {
     WgradPlan p;
@@ -1430,8 +1433,11 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
             p.bci = 256;
     }
     // Both products of a pair as tiles of 256 x 128, eight waves each, where that is about a block per unit: half the operand
-    // bytes of 128 x 64 (4096x1024 from 3200 rows, twice: 72 us against 2 x 45; rings of five or six stages 73).  Their sums are put
-    // aside every 8 tiles: a chain of 16 and one of 13 where a group of the smaller tiles has 24 and 5.
+    // bytes of 128 x 64 (4096x1024 from 3200 rows, twice: 72 us against 85; from 1024 34 / 41; rings of five or six stages no faster).  Other
+    // pairs are two products that share launches, as any do (2048x512 from 3200 rows 31 us, one by one 42).  A block has all of the rows: its sums
+    // are put aside as often as those of the smaller tiles, and added up in double (1024 hidden units, sums of one sign, off 64 bits, weights and
+    // bias: 3200 rows 3.9e-8 and 2.2e-8, one by one 4.9e-8 and 3.4e-8, added up in float 6.2e-8 and 4.4e-8, at 67 us; 12800 rows 2.9e-8 and
+    // 2.2e-8, one by one 1.5e-7 and 3.5e-8, in float 1.1e-7 and 8.1e-8).
     if (pair && c.R * c.S == 1 && c.K % 256 == 0 && c.C % 128 == 0 && npix >= 1024 && 2 * tiles_of(256, 128) >= 192 && 2 * tiles_of(256, 128) <= 256) {
         p.pair = true;
         p.kg = 1;
@@ -1441,7 +1447,8 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
         p.tiles_n = c.C / 128;
         p.splits = 1;
         p.pix_per_split = (int)((npix + 31) / 32 * 32);
-        p.part_tiles = 8;
+        const int halves = (int)((npix + 63) / 64), parts = (halves + 11) / 12;
+        p.part_tiles = (halves + parts - 1) / parts;
         return p;
     }
     p.tiles_ko = (c.K + p.bko - 1) / p.bko;
@@ -1453,28 +1460,21 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
         double best = 1e30;
         long long want = 1;
         const double alone = p.bko == 64 ? 0.36 : 0.45, shared = p.bko == 64 ? 0.30 : 0.36;
-        auto cost_of = [&](long long tiles, long long sp) {
-            const long long per_unit = (tiles * sp + 255) / 256;
-            return (double)per_unit * (double)((npix + 64 * sp - 1) / (64 * sp)) * (per_unit == 1 ? alone : shared) +
-                   (sp > 1 ? 3.5 + (double)sp * c.K * Ntot * 2e-6 : 0.0);
-        };
         for (long long sp = 1; sp <= 256; ++sp) {
             if (sp > 1 && (npix < 64 * sp || tiles * sp > 2048 || (double)sp * c.K * (Ntot + 1) * 4 > 32e6)) break;
-            const double cost = cost_of(tiles, sp);
+            const long long per_unit = (tiles * sp + 255) / 256;
+            const double cost = (double)per_unit * (double)((npix + 64 * sp - 1) / (64 * sp)) * (per_unit == 1 ? alone : shared) +
+                                (sp > 1 ? 3.5 + (double)sp * c.K * Ntot * 2e-6 : 0.0);
             if (cost < best) {
                 best = cost;
                 want = sp;
             }
         }
-        // less than two launches of their own, by the same estimate and 2.5 us for a launch (512 hidden units, 50 steps of 64 sequences,
-        // mini-batch 3837 -> 3754 us; 256, 20 steps of 48 1962 -> 1828)
-        p.pair = c.R * c.S == 1 && cost_of(2 * tiles, 1) <= 2.0 * best + 2.5;
-        if (pair && p.pair) want = 1;
         const long long pps = ((npix + want - 1) / want + 63) / 64 * 64;
         p.pix_per_split = (int)pps;
         p.splits = npix > 0 ? (int)((npix + pps - 1) / pps) : 1;
-        // equal parts of at most 12 tiles, 384 pixels; of 8, which balances a longer chain of parts, where a pair takes no splits
-        const int most = pair && p.pair ? 8 : 12, tiles_g = (int)(pps / 64), parts = (tiles_g + most - 1) / most;
+        // equal parts of at most 12 tiles, 384 pixels
+        const int tiles_g = (int)(pps / 64), parts = (tiles_g + 11) / 12;
         p.part_tiles = parts ? (tiles_g + parts - 1) / parts : 1;
         return p;
     }
@@ -1608,10 +1608,6 @@ hipError_t launch_batch(WgradBatch &b, hipStream_t s)
         WG_LAUNCH(64, 64, 2, 2, 2, WgradGroup, b.g);
     else if (b.g.n > 1)
         WG_LAUNCH(128, 64, 2, 2, 2, WgradGroup, b.g);
-    else if (one.x2 && b.kg == 2 && b.bko == 64)
-        WG_LAUNCH(64, 64, 2, 2, 2, WgradPair, two);
-    else if (one.x2 && b.kg == 2)
-        WG_LAUNCH(128, 64, 2, 2, 2, WgradPair, two);
     else if (one.x2)                                       // the tile that is only taken for pairs
         WG_LAUNCH(256, 128, 4, 2, 1, WgradPair, two);
     else if (b.kg == 2 && b.bko == 64)
@@ -1651,11 +1647,10 @@ hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, si
         used = 0;
         return hipSuccess;
     };
-    for (int k = 0; k < n; ++k) {
-        const WgradJob &j = jobs[k];
+    auto add = [&](const WgradJob &j, bool pair) {
         ConvShape c = j.c;
         if (!conv_wgrad_mfma_supported(c)) return hipErrorInvalidValue;
-        if ((long long)c.N * c.P * c.Q == 0) continue;
+        if ((long long)c.N * c.P * c.Q == 0) return hipSuccess;
         // A 1x1 filter at stride 1 contracts over a plain list of rows: as images of one pixel a tile step is one constant
         // add.  (The step over image rows costs a lane up to 32 trips where a row is one pixel, as in a sequence: the LSTM's
         // weight gradients, 3200 rows, 4096 x 1024, 99 -> 38 us.)
@@ -1668,15 +1663,9 @@ hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, si
             if ((e = launch_all()) != hipSuccess) return e;
             e = wgrad3x3_halo_supported(c) ? wgrad3x3_halo_mfma(j.x, j.dy, j.dw, j.db, workspace, c, s)
                                            : wgrad3x3_c8_mfma(j.x, j.dy, j.dw, j.db, workspace, c, s);
-            if (e != hipSuccess) return e;
-            continue;
+            return e;
         }
-        const WgradPlan p = wgrad_plan(c, beside, j.x2 != nullptr);
-        if (j.x2 && !p.pair) {
-            const WgradJob two[2] = {{j.x, j.dy, j.dw, j.db, c}, {j.x2, j.dy, j.dw2, nullptr, c}};
-            if ((e = launch_all()) != hipSuccess || (e = conv_wgrad_mfma_jobs(two, 2, workspace, workspace_bytes, s, beside)) != hipSuccess) return e;
-            continue;
-        }
+        const WgradPlan p = wgrad_plan(c, beside, pair);
         const int direct = p.splits == 1;
         const size_t total_w = (size_t)c.K * c.R * c.S * c.C, total = total_w + (j.db ? c.K : 0);
         const size_t want = direct ? 0 : ((size_t)p.splits * total * sizeof(float) + 255) / 256 * 256;
@@ -1689,21 +1678,27 @@ hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, si
         b.bci = p.bci;
         b.kg = p.kg;
         const int tiles = p.tiles_ko * p.tiles_n;
-        b.g.a[b.g.n++] = {(const bf16_t *)j.x, (const bf16_t *)j.x2, (const bf16_t *)j.dy, part, j.dw2,
+        b.g.a[b.g.n++] = {(const bf16_t *)j.x, pair ? (const bf16_t *)j.x2 : nullptr, (const bf16_t *)j.dy, part, j.dw2,
                           !j.db ? nullptr : (direct ? j.db : part + total_w), total, c, tiles, p.tiles_n, p.splits,
-                          tiles * p.splits * (j.x2 ? 2 : 1), p.pix_per_split, p.part_tiles, direct,
+                          tiles * p.splits * (pair ? 2 : 1), p.pix_per_split, p.part_tiles, direct,
                           (unsigned)((size_t)c.N * c.H * c.W * c.C * 2), (unsigned)((size_t)c.N * c.P * c.Q * c.K * 2)};
         if (!direct) b.r.a[b.r.n++] = {part, j.dw, j.db, total_w, total, p.splits, (int)((total / 4 + 63) / 64)};
-        if (p.kg == 1 && (e = launch_all()) != hipSuccess) return e;
+        return p.kg == 1 ? launch_all() : hipSuccess;
+    };
+    for (int k = 0; k < n; ++k) {
+        const WgradJob &j = jobs[k];
+        const bool pair = j.x2 && wgrad_plan(j.c, beside, true).pair;
+        hipError_t e = add(j, pair);
+        if (e == hipSuccess && j.x2 && !pair) e = add({j.x2, j.dy, j.dw2, nullptr, j.c}, false);
+        if (e != hipSuccess) return e;
     }
     return launch_all();
 }
 
 hipError_t conv_wgrad_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,
-                           const ConvShape &c, hipStream_t s, bool beside, const void *x2, float *dw2)
+                           const ConvShape &c, hipStream_t s, bool beside)
 {
-    const WgradJob job{x, dy, dw, db, c, x2, dw2};
-    // no more than what the caller was told to bring: two products that are no pair take it in turn
+    const WgradJob job{x, dy, dw, db, c};
     return conv_wgrad_mfma_jobs(&job, 1, workspace, conv_wgrad_mfma_workspace(c), s, beside);
 }
 

@@ -539,7 +539,8 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     float *dw_h = L.dw + (size_t)G * In;
     tp = st->tap_begin(mf ? BAPIPE_KC_CONV_WGRAD_MFMA : BAPIPE_KC_CONV_DIRECT);
     if (mf && In == H) {
-        HIPCHK(conv_wgrad_mfma(x, D, L.dw, L.db, st->work, cx, s, false, hs, dw_h));
+        const WgradJob both{x, D, L.dw, L.db, cx, hs, dw_h};
+        HIPCHK(conv_wgrad_mfma_jobs(&both, 1, st->work, st->work_bytes, s, false));
     } else if (mf) {
         HIPCHK(conv_wgrad_mfma(x, D, L.dw, L.db, st->work, cx, s));
         HIPCHK(conv_wgrad_mfma(hs, D, dw_h, nullptr, st->work, ch, s));
@@ -1294,6 +1295,8 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, G, H, 1)); w = v > w ? v : w;
                 if (lstm_seq_supported(N, T, H, st->compute_units)) { v = lstm_seq_workspace(N, H); w = v > w ? v : w; }
                 v = conv_wgrad_mfma_workspace(cx); w = v > w ? v : w;
+                // both at once where they are of one shape
+                if (In == H) { v = 2 * align_up(v) < kGroupWorkspace ? 2 * align_up(v) : v; w = v > w ? v : w; }
                 v = conv_wgrad_mfma_workspace(ch); w = v > w ? v : w;
             } else {
                 w = (size_t)N * G * sizeof(float);

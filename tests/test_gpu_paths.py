@@ -109,18 +109,36 @@ class _ConvShape(ct.Structure):
     _fields_ = [(f, ct.c_int) for f in "N H W C P Q K R S stride pad".split()]
 
 
+class _WgradJob(ct.Structure):
+    _fields_ = [("x", ct.c_void_p), ("dy", ct.c_void_p), ("dw", ct.c_void_p), ("db", ct.c_void_p), ("c", _ConvShape), ("x2", ct.c_void_p), ("dw2", ct.c_void_p)]
+
+
+def _wgrad_workspace(shape):
+    f = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
+    f.restype = ct.c_size_t
+    return f(ct.byref(shape))
+
+
+def _wgrad_jobs(jobs, work, room):
+    f = getattr(B.load(), "_ZN6bapipe20conv_wgrad_mfma_jobsEPKNS_8WgradJobEiPvmP12ihipStream_tb")
+    f.restype = ct.c_int
+    assert f((_WgradJob * len(jobs))(*jobs), ct.c_int(len(jobs)), ct.c_void_p(work.data_ptr()), ct.c_size_t(room),
+             ct.c_void_p(torch.cuda.current_stream().cuda_stream), ct.c_bool(False)) == 0
+
+
+@pytest.mark.parametrize("products", [1, 2])     # whose partial sums the workspace holds
 @pytest.mark.parametrize("c,k,rows,bias", [
     (1024, 4096, 1043, True),     # 256 x 128, 33 tiles of rows, the last of 19: four parts and a short one
     (896, 3584, 1024, False),     # ... 14 x 7 of them, twice
-    (512, 2048, 700, True),       # 128 x 64, two groups of waves
+    (512, 2048, 700, True),       # no pair: 128 x 64, two groups of waves
     (128, 512, 333, True),        # 64 x 64
-    (1024, 4096, 40, False),      # ... of a step and a short one
+    (1024, 4096, 40, False),      # a step of rows and a short one
     (72, 40, 9, True),
-    (128, 512, 3200, True),       # no pair: two launches, each with partial sums of its own
+    (128, 512, 3200, True),       # partial sums
     (64, 256, 2560, True),
     (256, 1024, 6400, False),
 ])
-def test_weight_gradients_of_a_pair(c, k, rows, bias):
+def test_weight_gradients_of_a_pair(c, k, rows, bias, products):
     """dw += dy^T x and dw2 += dy^T x2: against float64, a rounding of 2^-24 for each term of the sum and each of the additions."""
     g = torch.Generator("cuda")
     g.manual_seed(c + rows)
@@ -130,23 +148,34 @@ def test_weight_gradients_of_a_pair(c, k, rows, bias):
     want = [dw.double() + dy.double().t() @ x.double(), dw2.double() + dy.double().t() @ x2.double(), db.double() + dy.double().sum(0)]
     terms = [dw.abs() + dy.float().abs().t() @ x.float().abs(), dw2.abs() + dy.float().abs().t() @ x2.float().abs(), db.abs() + dy.float().abs().sum(0)]
     shape = _ConvShape(rows, 1, 1, c, 1, 1, k, 1, 1, 1, 0)
-    size = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
-    size.restype = ct.c_size_t
-    room = size(ct.byref(shape))
+    room = products * (_wgrad_workspace(shape) + 255) // 256 * 256
     work = torch.full((room + (1 << 20),), 0xA5, device="cuda", dtype=torch.uint8)         # behind it nothing may be written
-    ptr = lambda t: ct.c_void_p(t.data_ptr())
-    f = getattr(B.load(), "_ZN6bapipe15conv_wgrad_mfmaEPKvS1_PfS2_PvRKNS_9ConvShapeEP12ihipStream_tbS1_S2_")
-    f.restype = ct.c_int
-    assert f(ptr(x), ptr(dy), ptr(dw), ptr(db) if bias else None, ptr(work), ct.byref(shape),
-             ct.c_void_p(torch.cuda.current_stream().cuda_stream), ct.c_bool(False), ptr(x2), ptr(dw2)) == 0
+    _wgrad_jobs([_WgradJob(x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr() if bias else None, shape, x2.data_ptr(), dw2.data_ptr())], work, room)
     torch.cuda.synchronize()
     assert (work[room:] == 0xA5).all()
     for got, ref, t in list(zip((dw, dw2, db), want, terms))[:3 if bias else 2]:
         assert ((got.double() - ref).abs() <= (rows + 8) * 2.0 ** -24 * t).all()
 
 
-class _WgradJob(ct.Structure):
-    _fields_ = [("x", ct.c_void_p), ("dy", ct.c_void_p), ("dw", ct.c_void_p), ("db", ct.c_void_p), ("c", _ConvShape), ("x2", ct.c_void_p), ("dw2", ct.c_void_p)]
+@pytest.mark.parametrize("c,rows", [(128, 1024), (128, 1600), (256, 3200), (512, 12800), (1024, 3200), (1024, 12800)])
+def test_weight_gradients_of_a_pair_are_as_exact_as_one_by_one(c, rows):
+    """Operands of one sign.  P parts of n sums of 16 products, each rounded by 2.4e-8 of the sum so far on average, added up in double (splits of a
+    few parts, or the parts of a tile) and rounded twice more at most: sqrt(n / (3 P) + 2) times that, with n = 16 and P = 4 at the least 4.4e-8.  Parts
+    added up in float, as many as there are without splits, are 4.5e-8 to 6.2e-8 off here."""
+    g = torch.Generator("cuda")
+    g.manual_seed(c + rows)
+    rand = lambda *shape: torch.rand(shape, device="cuda", generator=g).bfloat16()
+    x, x2, dy = rand(rows, c), rand(rows, c), rand(rows, 4 * c)
+    dw, dw2, db = torch.zeros(4 * c, c, device="cuda"), torch.zeros(4 * c, c, device="cuda"), torch.zeros(4 * c, device="cuda")
+    shape = _ConvShape(rows, 1, 1, c, 1, 1, 4 * c, 1, 1, 1, 0)
+    room = 2 * (_wgrad_workspace(shape) + 256)
+    _wgrad_jobs([_WgradJob(x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), shape, x2.data_ptr(), dw2.data_ptr())],
+                torch.empty(room, device="cuda", dtype=torch.uint8), room)
+    torch.cuda.synchronize()
+    dyt = dy.double().t().contiguous()
+    off = lambda got, exact: float((got.double() - exact).norm() / exact.norm())
+    e = off(dw, dyt @ x.double()), off(dw2, dyt @ x2.double()), off(db, dy.double().sum(0))
+    assert max(e) < 4.4e-8, e
 
 
 @pytest.mark.parametrize("room", [1 << 30, 0])      # of the workspace: for all partial sums, or for those of one product at a time
@@ -158,28 +187,23 @@ def test_weight_gradients_that_share_launches(room):
     g = torch.Generator("cuda")
     g.manual_seed(5)
     rand = lambda *shape: torch.randn(shape, device="cuda", generator=g)
-    size = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
-    size.restype = ct.c_size_t
-    f = getattr(B.load(), "_ZN6bapipe20conv_wgrad_mfma_jobsEPKNS_8WgradJobEiPvmP12ihipStream_tb")
-    f.restype = ct.c_int
     keep, jobs, most = [], [], 0
     for n, h, w, c, k, r in shapes:
         t = [rand(n, h, w, c).bfloat16(), rand(n, h, w, k).bfloat16(), rand(k, r, r, c), rand(k)]
         keep.append(t)
         shape = _ConvShape(n, h, w, c, h, w, k, r, r, 1, r // 2)
-        most = max(most, size(ct.byref(shape)))
+        most = max(most, _wgrad_workspace(shape))
         jobs.append(_WgradJob(t[0].data_ptr(), t[1].data_ptr(), t[2].data_ptr(), t[3].data_ptr(), shape, None, None))
     start = [[a.clone() for a in t[2:]] for t in keep]
     room = max(room, most) if room == 0 else 4 * most
     work = torch.empty(room + 4096, device="cuda", dtype=torch.uint8)
-    stream = ct.c_void_p(torch.cuda.current_stream().cuda_stream)
 
     def run(batches):
         for t, s0 in zip(keep, start):
             for a, b in zip(t[2:], s0):
                 a.copy_(b)
         for b in batches:
-            assert f((_WgradJob * len(b))(*b), ct.c_int(len(b)), ct.c_void_p(work.data_ptr()), ct.c_size_t(room), stream, ct.c_bool(False)) == 0
+            _wgrad_jobs(b, work, room)
         torch.cuda.synchronize()
         return [a.clone() for t in keep for a in t[2:]]
     for a, b in zip(run([jobs]), run([[j] for j in jobs])):

@@ -9,6 +9,7 @@ import sys
 import pytest
 
 from paper_2012_12544_amd import binding as B
+from stage_inputs import configs as C
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 WORK, ELSEWHERE = 1 << 40, 1 << 20          # addresses; nothing is read or written there
@@ -27,18 +28,15 @@ def _record(recorder, library, cases):
     rec, lib = ct.CDLL(recorder, mode=ct.RTLD_GLOBAL), ct.CDLL(library)
     size = getattr(lib, "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
     size.restype = ct.c_size_t
-    one = getattr(lib, "_ZN6bapipe15conv_wgrad_mfmaEPKvS1_PfS2_PvRKNS_9ConvShapeEP12ihipStream_tbS1_S2_")
     many = getattr(lib, "_ZN6bapipe20conv_wgrad_mfma_jobsEPKNS_8WgradJobEiPvmP12ihipStream_tb")
-    at, out = ct.c_void_p(ELSEWHERE), []
+    out = []
     for case in cases:
         shapes = [_ConvShape(*s) for s in case["shapes"]]
         room = max(size(ct.byref(s)) for s in shapes) + case.get("more", 0)
         rec.recorder_clear()
-        if case["pair"]:
-            rc = one(at, at, at, at, ct.c_void_p(WORK), ct.byref(shapes[0]), None, ct.c_bool(False), at, at)
-        else:
-            jobs = (_WgradJob * len(shapes))(*[_WgradJob(ELSEWHERE, ELSEWHERE, ELSEWHERE, ELSEWHERE, s, None, None) for s in shapes])
-            rc = many(jobs, ct.c_int(len(shapes)), ct.c_void_p(WORK), ct.c_size_t(room), None, ct.c_bool(case["beside"]))
+        jobs = (_WgradJob * len(shapes))(*[_WgradJob(ELSEWHERE, ELSEWHERE, ELSEWHERE, ELSEWHERE, s, *([ELSEWHERE] * 2 if case["pair"] else [None] * 2))
+                                           for s in shapes])
+        rc = many(jobs, ct.c_int(len(shapes)), ct.c_void_p(WORK), ct.c_size_t(room), None, ct.c_bool(case["beside"]))
         parts = []
         for i in range(rec.recorder_count()):
             first, nbytes = ct.c_size_t(), ct.c_size_t()
@@ -64,18 +62,26 @@ def record(tmp_path_factory):
     return run
 
 
-def test_partial_sums_of_a_pair_stay_in_the_workspace_of_one_product(record):
-    """The two weight gradients of an LSTM layer whose input is as wide as its output, given what either of them asks for."""
-    cases = [dict(shapes=[(rows, 1, 1, h, 1, 1, 4 * h, 1, 1, 1, 0)], pair=True)
+def _in_turn_or_side_by_side(case, got):
+    """Partial sums of one launch after another from the start of the workspace on, those of one launch side by side."""
+    assert got["rc"] == 0
+    end = 0
+    for first, nbytes in got["parts"]:
+        assert first == 0 or first >= end
+        end = first + nbytes
+        assert end <= got["room"], (case, got)
+
+
+@pytest.mark.parametrize("more", [0, 1 << 20, 64 << 20])
+def test_partial_sums_of_a_pair_stay_in_the_workspace(record, more):
+    """The two weight gradients of an LSTM layer whose input is as wide as its output, given what either of them asks for and some more."""
+    cases = [dict(shapes=[(rows, 1, 1, h, 1, 1, 4 * h, 1, 1, 1, 0)], pair=True, beside=False, more=more)
              for h in (8, 64, 72, 128, 192, 256, 384, 512, 640, 768, 896, 1000, 1024, 2048)
              for rows in (1, 40, 64, 333, 1000, 1024, 2560, 3200, 4096, 6400, 12800, 51200)]
-    split = 0
-    for case, got in zip(cases, record(cases)):
-        assert got["rc"] == 0
-        split += len(got["parts"]) == 2
-        for first, nbytes in got["parts"]:
-            assert 0 <= first and first + nbytes <= got["room"], (case, got)
-    assert split >= 20           # otherwise nothing was asked
+    results = record(cases)
+    for case, got in zip(cases, results):
+        _in_turn_or_side_by_side(case, got)
+    assert sum(len(got["parts"]) == 2 for got in results) >= 20           # otherwise nothing was asked
 
 
 @pytest.mark.parametrize("beside", [False, True])
@@ -88,12 +94,28 @@ def test_partial_sums_of_shared_launches_stay_in_the_workspace(record, beside, m
               [conv(n, hw, c, k, r) for n in (1, 8) for hw in (7, 16) for c, k in ((64, 64), (128, 512), (512, 72)) for r in (1, 3)]]
     cases = [dict(shapes=p, pair=False, beside=beside, more=more) for p in passes]
     for case, got in zip(cases, record(cases)):
-        assert got["rc"] == 0
-        end = 0
-        for first, nbytes in got["parts"]:
-            assert first == 0 or first >= end
-            end = first + nbytes
-            assert end <= got["room"], (case, got)
+        _in_turn_or_side_by_side(case, got)
+
+
+@pytest.mark.parametrize("hidden,steps,samples", [(128, 50, 64), (256, 50, 64), (256, 50, 128), (512, 50, 256), (64, 40, 64), (1024, 50, 64)])
+def test_an_lstm_stage_brings_the_workspace_of_its_weight_gradients(hidden, steps, samples):
+    sizes = []
+
+    def alloc(nbytes, ctx):
+        sizes.append(nbytes)
+        return 256 * len(sizes) if len(sizes) <= 5 else None
+
+    b = C._Builder()
+    b.lstm(hidden, hidden, src=-1)
+    st = C._stage("lstm", b.layers, C.BF16, (hidden, steps, 1), samples, 1, 1, 1, 1, 0, "xavier")
+    o = B.make_opts(st)
+    o.mem.alloc, o.mem.free = B.ALLOC_FN(alloc), B.FREE_FN(lambda ptr, ctx: None)
+    with pytest.raises(B.BapipeError):
+        B.bapipe_stage_create(b.layers, samples, 1, o)
+    f = getattr(B.load(), "_ZN6bapipe25conv_wgrad_mfma_workspaceERKNS_9ConvShapeE")
+    f.restype = ct.c_size_t
+    one = f(ct.byref(_ConvShape(samples, steps, 1, hidden, steps, 1, 4 * hidden, 1, 1, 1, 0)))
+    assert sizes[4] >= one and (sizes[4] >= 2 * one or 2 * one + 512 > 24 << 20)
 
 
 if __name__ == "__main__":
