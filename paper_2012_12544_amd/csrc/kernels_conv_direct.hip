@@ -103,6 +103,11 @@ __global__ void k_conv_gather(const T *__restrict__ in, const T *__restrict__ wt
 // number of 16 bytes, and takes tiles of `tw` neighbouring outputs of an image row, whose input it brings in at once: one round of
 // loads a tile.  Products are added in the same order, and taps outside the image not at all.  (us, forward: 16->16 channels,
 // 3x3, four 32x32 images 6.9 -> 5.1, 3->16 7.1 -> 4.4; 32->32, 16 of 64x64 311 -> 59, 3->32 63 -> 20; 8->8, one 16x16 6.8 -> 4.4.)
+// A tile costs a block two barriers and a round of loads whatever is in it, so more tiles than the chip holds blocks must be worth it: 48
+// outputs and 4000 products (us, k_conv_gather / here, 1x1 from 16384 rows: 64->64 39.6 / 25.0, 64->16 11.7 / 21.5, 30->64 15.0 / 22.4; 3x3, 2048 images:
+// 8->16 at 4x4 22.4 / 17.3, 8->4 at 14x14 64.7 / 57.8, 3->4 there 28.6 / 43.9, 16->4 at 8x8 29.5 / 33.0).  Up to 1024 tiles it is the number of rounds in the
+// other kernel's chain that counts (1x1 from 64 rows: 64->4, four, 3.9 / 3.3, 16->4, one, 2.2 / 3.0; 3x3 3->4 at 4x4, 256 images, nine, 5.3 / 4.1),
+// and that a filter of 4-byte loads is not fetched for a quarter of a block's threads (150->64, 512 rows 7.8 / 8.9; 150->16 7.5 / 6.0).
 constexpr int TILE_FILTER = 10240, TILE_COUT = 64;             // floats of the filter, output channels
 constexpr int TILE_INPUT = 4096;                               // floats of a tile's input
 template <int V>
@@ -233,9 +238,12 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
 // Here a block has the rows of dy and x that a row of outputs meets in LDS, and a thread adds up 4 x V weights of one tap: 4 + V
 // values for 4 * V products, each sum in the same order.  (us: 32->32 channels, 3x3, 16 of 64x64 198 -> 42, 3->32 98 -> 13;
 // 16->16, four 32x32 images 8.1 either way, and below that, where the two rounds of loads are all there is, the other is faster: 3->16 5.7
-// against 5.8, whole mini-batch of 8->8, one 16x16, 165 us against 172.)
+// against 5.8, whole mini-batch of 8->8, one 16x16, 165 us against 172.  A thread has 4 x V times the work of the other kernel's, so few rows leave
+// the chip idle: a wave and a half for every unit at the least (us with the reductions, other / here, one 64x64 image 8->8 (2816 threads) 8.6 / 12.8, 16->16 (10240)
+// 11.0 / 14.0, four (40960) 24.6 / 18.7; 4->64, one (13312) 11.9 / 13.2, one 128x128 (26624) 25.1 / 20.6; 16->16 there (20480) 20.8 / 21.5).)
 constexpr int TILE_ROWS = 10240;                               // floats of the rows in LDS
 constexpr long long TILE_PRODUCTS = 32768;                     // fewest products of a row of outputs
+constexpr long long TILE_THREADS = 24576;                      // fewest threads with weights or sums of their own
 template <int V>
 __global__ __launch_bounds__(TPB) void k_conv_wgrad_tile(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part,
                                                          ConvShape c, int rows_per_chunk, int bias)
@@ -359,19 +367,32 @@ inline size_t direct_wgrad_elements(const ConvShape &c)
 
 // paddings and sides that cannot pass the range of int when they are added
 inline bool plain(int side, int pad) { return side > 0 && side < (1 << 20) && pad > -(1 << 20) && pad < (1 << 20); }
-inline bool tile_takes(const GatherConv &g)
+// outputs of an image row that a tile of k_conv_tile takes
+inline int tile_columns(const GatherConv &g)
+{
+    int tw = TPB / g.Co;
+    while (tw > 1 && g.R * ((tw - 1) * g.s_out + g.S) * g.Ci > TILE_INPUT) --tw;
+    return tw < g.Wo ? tw : g.Wo;
+}
+inline bool tile_takes(const GatherConv &g, bool vec)
 {
     if (!(g.s_in == 1 && g.s_out >= 1 && g.s_out <= 16 && g.R <= 16 && g.S <= 16 && g.Co <= TILE_COUT && g.Ci <= TILE_FILTER && plain(g.Hi, g.pad_h) &&
           plain(g.Wi, g.pad_w)))
         return false;
     const int K = g.R * g.S * g.Ci;
-    return g.Co * (K + 4) <= TILE_FILTER && K <= TILE_INPUT && (long long)g.N * g.Ho * g.Wo < (1ll << 31);
+    if (!(g.Co * (K + 4) <= TILE_FILTER && K <= TILE_INPUT && (long long)g.N * g.Ho * g.Wo < (1ll << 31))) return false;
+    const int tw = tile_columns(g), outputs = tw * g.Co;
+    const long long tiles = (long long)g.N * g.Ho * ((g.Wo + tw - 1) / tw);
+    if (!vec && outputs < TPB / 2 && g.Co * K > 4096) return false;
+    return (outputs >= 48 && outputs * K >= 4000) || (tiles <= 1024 && g.R * g.S * ((g.Ci + 15) / 16) >= 4);
 }
-inline bool wgrad_tile_takes(const ConvShape &c)
+// weights (4 x V) and column sums that a chunk of rows has for the threads of k_conv_wgrad_tile
+inline int wgrad_tile_items(const ConvShape &c, bool along) { return c.K / 4 * c.R * c.S * (c.C % 4 == 0 ? c.C / 4 : c.C) + (along ? c.K : 0); }
+inline bool wgrad_tile_takes(const ConvShape &c, int chunks, bool along)
 {
     return c.K % 4 == 0 && c.R <= 16 && c.S <= 16 && c.stride >= 1 && c.stride <= 16 && plain(c.H, c.pad) && plain(c.W, c.pad) && c.Q < (1 << 20) &&
            (long long)c.K * c.C <= 64 * 64 && (long long)c.Q * c.K + (long long)c.R * c.W * c.C <= TILE_ROWS &&
-           (long long)c.K * c.C * c.R * c.S * c.Q >= TILE_PRODUCTS;
+           (long long)c.K * c.C * c.R * c.S * c.Q >= TILE_PRODUCTS && (long long)chunks * wgrad_tile_items(c, along) >= TILE_THREADS;
 }
 
 }  // namespace
@@ -386,11 +407,8 @@ hipError_t conv_gather_direct(int dt, const void *in, const void *wt, const floa
     // whole 16-byte groups of four floats need a channel count that is a multiple of four and aligned operands
     const bool vec = dt == DT_F32 && g.Ci % 4 == 0 && ((uintptr_t)in | (uintptr_t)wt) % 16 == 0;
     const int K = g.R * g.S * g.Ci;
-    if (dt == DT_F32 && tile_takes(g)) {
-        const int V = vec ? 4 : 1, pitch = V == 4 ? (K / 4 | 1) * 4 : K | 1;
-        int tw = TPB / g.Co;
-        while (tw > 1 && g.R * ((tw - 1) * g.s_out + g.S) * g.Ci > TILE_INPUT) --tw;
-        if (tw > g.Wo) tw = g.Wo;
+    if (dt == DT_F32 && tile_takes(g, vec)) {
+        const int V = vec ? 4 : 1, pitch = V == 4 ? (K / 4 | 1) * 4 : K | 1, tw = tile_columns(g);
         const int segments = (g.Wo + tw - 1) / tw, tiles = g.N * g.Ho * segments;
         const size_t smem = (size_t)(TILE_INPUT + g.Co * pitch) * sizeof(float);
         const dim3 grid(tiles < 2048 ? tiles : 2048);
@@ -429,8 +447,8 @@ hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, f
     int rpc = (c.N * c.P + chunks - 1) / chunks;
     chunks = (c.N * c.P + rpc - 1) / rpc;
     float *part = (float *)workspace;
-    if (dt == DT_F32 && wgrad_tile_takes(c) && ((uintptr_t)x | (uintptr_t)dy) % 16 == 0) {
-        const int V = c.C % 4 == 0 ? 4 : 1, items = c.K / 4 * c.R * c.S * (c.C / V) + (along ? c.K : 0);
+    if (dt == DT_F32 && wgrad_tile_takes(c, chunks, along) && ((uintptr_t)x | (uintptr_t)dy) % 16 == 0) {
+        const int V = c.C % 4 == 0 ? 4 : 1, items = wgrad_tile_items(c, along);
         const size_t smem = (size_t)(c.Q * c.K + c.R * c.W * c.C) * sizeof(float);
         const dim3 grid((items + TPB - 1) / TPB, chunks);
         if (V == 4)

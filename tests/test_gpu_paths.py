@@ -564,12 +564,25 @@ def test_gradient_that_overlaps_the_upstream_gradient(kind, streams, shift, stat
     (1, 1, 0, 60, 60, (5, 7), 1),
     (7, 1, 3, 4, 4, (6, 5), 1),          # a filter larger than the image
     (3, 1, 0, 12, 8, (40, 64), 60),      # more tiles than blocks, several image rows a chunk
-    (3, 1, 1, 32, 32, (4, 80), 2),       # three times the threads of a block for the weights of a row
+    (3, 1, 1, 32, 32, (4, 80), 2),
     (3, 1, 1, 20, 64, (8, 9), 2),        # a filter that LDS does not take
 ])
 def test_direct_conv_tiles(k, stride, pad, cin, cout, hw, mb):
     st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, relu=1, src=-1), cin, hw, C.FP32, micro_batch=mb)
     compare_minibatch(st, verbose="direct conv tiles k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
+
+
+@pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
+    (3, 1, 1, 3, 64, (9, 33), 6),        # one channel at a time; two blocks for the weights of a row
+    (3, 1, 1, 16, 64, (9, 33), 5),
+    (5, 2, 2, 8, 20, (11, 61), 30),      # every other column
+    (1, 1, 0, 60, 60, (5, 70), 18),
+    (3, 1, 1, 32, 32, (4, 80), 11),      # three times the threads of a block for the weights of a row
+    (7, 1, 3, 4, 4, (6, 45), 80),        # rows outside the image on both sides at once
+])
+def test_direct_weight_gradient_tiles(k, stride, pad, cin, cout, hw, mb):
+    st = single(lambda b: b.conv(cin, cout, k, stride=stride, pad=pad, src=-1), cin, hw, C.FP32, micro_batch=mb)
+    compare_minibatch(st, verbose="direct weight gradient tiles k%d s%d p%d %d->%d %s" % (k, stride, pad, cin, cout, hw))
 
 
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
