@@ -108,7 +108,7 @@ struct WgradJob {
     const void *x2 = nullptr;
     float *dw2 = nullptr;
 };
-bool conv_wgrad_mfma_groups(const ConvShape &c);      // whether it is of the kind that shares launches
+bool conv_wgrad_mfma_groups(const ConvShape &c);      // whether it fills so little of the chip that it should wait for others
 hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s, bool beside);
 
 // ---- column sums over a [rows][C] matrix: out[c] += sum_r a[r][c]  (bias gradient)
