@@ -81,6 +81,7 @@ hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *b
 size_t conv_gather_mfma_raw_workspace(const GatherConv &g);
 hipError_t conv_gather_mfma_raw(const void *in, const void *wt, const GatherConv &g, float *part, int *splits,
                                 hipStream_t s);
+bool wgrad3x3_units(const ConvShape &c);          // whether the map comes apart into units of 8x16 pixels, as both of these need it
 bool wgrad3x3_halo_supported(const ConvShape &c);
 size_t wgrad3x3_halo_workspace(const ConvShape &c);
 hipError_t wgrad3x3_halo_mfma(const void *x, const void *dy, float *dw, float *db, void *workspace,

@@ -1028,12 +1028,17 @@ hipError_t conv3x3_halo_pool_mfma(const void *in, const void *wt, const float *b
 
 namespace bapipe {
 
+bool wgrad3x3_units(const ConvShape &c)
+{
+    return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 && c.W % UW == 0 &&
+           (c.C == 8 || c.C % 64 == 0) && c.K % 64 == 0;
+}
+
 // (fewer pixels: 64 channels at 90x90, 5 samples 18.2 us here, 13.8 as 64 x 64 tiles of the general kernel; with their reductions 96x96, 16 20.8 /
 // 15.8, 128x128 23.3 / 21.9, 160x160 28.2 / 26.1, 224x224 41.0 / 39.1)
 bool wgrad3x3_c8_supported(const ConvShape &c)
 {
-    return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 &&
-           c.W % UW == 0 && c.C == 8 && c.K % 64 == 0 && (long long)c.N * c.H * c.W >= 400000 && (long long)c.N * c.H * c.W * 16 < (1ll << 31) &&
+    return wgrad3x3_units(c) && c.C == 8 && (long long)c.N * c.H * c.W >= 400000 && (long long)c.N * c.H * c.W * 16 < (1ll << 31) &&
            (long long)c.N * c.H * c.W * c.K * 2 < (1ll << 31);
 }
 
@@ -1080,20 +1085,20 @@ hipError_t wgrad3x3_c8_mfma(const void *x, const void *dy, float *dw, float *db,
 
 // A block of these units is a 64 x 576 tile.  Of small products the 64 x 64 tiles of the general kernel are faster, and share launches (us, with
 // the reductions, units against tiles: 64->64 at 32x32, 8 samples 15.7 / 10.6, at 48x48, 16, 1.4 GMAC 22.9 / 16.4, at 64x64, 16, 2.4 GMAC
-// 24.4 / 21.4, 32 26.2 / 28.0; 128->128 at 32x32, 8, 1.2 25.5 / 14.4, 16, 2.4 26.0 / 20.8, 32 26.7 / 28.1; 256->256 at 16x16, 8, 1.2 26.3 / 14.9, 16
-// 27.8 / 21.3, 32 30.0 / 27.4; 512->512, 4 26.4 / 16.9, 16 35.3 / 44.6).  This line alone, mini-batches on one stream and three, us: first VGG stage
+// 24.4 / 21.4, 32 26.2 / 28.0; 128->128 at 32x32, 8, 1.2 25.5 / 14.4, 16, 2.4 26.0 / 20.8, 32 26.7 / 28.1; 256->256 at 16x16, 8, 1.2 26.6 / 18.6, 15
+// 27.8 / 23.0, 32 30.0 / 27.4; 320->320 at 32x32, 2 25.4 / 23.5; 512->512 at 16x16, 2 24.8 / 12.0, 16 35.3 / 44.6).  This line alone, mini-batches on one stream and three, us: first VGG stage
 // at 64x64, 4 samples 593, 572 -> 404, 387, 16 731, 623 -> 686, 606; at 32x32, 32 647, 556 -> 493, 479; three layers of 128 channels at 32x32, 12 590, 502 ->
 // 464, 471.
+// More than 1024 tiles (704->704) would come without wave groups, whose sums are put aside, and stay here.
 static bool wgrad_units_pay(const ConvShape &c)
 {
     const double macs = 9.0 * c.N * c.H * c.W * c.C * c.K;
-    return macs >= 2.4e9;
+    return macs >= 2.4e9 || 9ll * (c.C / 64) * (c.K / 64) > 1024;
 }
 
 bool wgrad3x3_halo_supported(const ConvShape &c)
 {
-    return c.R == 3 && c.S == 3 && c.stride == 1 && c.pad == 1 && c.H == c.P && c.W == c.Q && c.H % UH == 0 &&
-           c.W % UW == 0 && c.C % 64 == 0 && c.K % 64 == 0 && wgrad_units_pay(c) &&
+    return wgrad3x3_units(c) && c.C % 64 == 0 && wgrad_units_pay(c) &&
            (long long)c.N * c.H * c.W * c.C * 2 < (1ll << 31) && (long long)c.N * c.H * c.W * c.K * 2 < (1ll << 31);
 }
 

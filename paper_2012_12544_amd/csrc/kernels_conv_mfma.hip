@@ -1470,11 +1470,16 @@ WgradPlan wgrad_plan(const ConvShape &c, bool beside, bool pair = false)
                 want = sp;
             }
         }
+        // Where larger products of a map take units of 128 pixels, these are no less exact below that line: parts of 4 tiles, and at least
+        // four splits of 2048 pixels and more, of which wide layers would take two or three (sums of one sign, off 64 bits, units, as any other
+        // product, so: 64->64 at 16x16, 2 samples 4.3e-8, 6.0e-8, 4.0e-8; 256->256, 8 3.9e-8, 5.3e-8, 2.9e-8, and 26.6 us, 15.3, 18.6).
+        const bool units = wgrad3x3_units(c);
+        if (units && tiles >= 128 && npix >= 2048 && want < 4) want = 4;
         const long long pps = ((npix + want - 1) / want + 63) / 64 * 64;
         p.pix_per_split = (int)pps;
         p.splits = npix > 0 ? (int)((npix + pps - 1) / pps) : 1;
         // equal parts of at most 12 tiles, 384 pixels
-        const int tiles_g = (int)(pps / 64), parts = (tiles_g + 11) / 12;
+        const int most = units ? 4 : 12, tiles_g = (int)(pps / 64), parts = (tiles_g + most - 1) / most;
         p.part_tiles = parts ? (tiles_g + parts - 1) / parts : 1;
         return p;
     }

@@ -726,6 +726,25 @@ def test_wgrad_sums_are_short(k, cin, cout, hw, mb):
     """Operands of one sign.  A part of 384 pixels is 24 sums of 16 products, each rounded to half a unit, 2^-24/sqrt(3) of the sum so
     far on average: sqrt(24/3) of that for the part, independent parts of a group added up the same way, a split's partial and
     the total rounded once more: 6e-8 at most for the shapes here.  Twice that is allowed; one sum of 1568 pixels is at 1.5e-7."""
+    assert max(_wgrad_errors(k, cin, cout, hw, mb)) < 1.2e-7
+
+
+@pytest.mark.parametrize("cin,cout,hw,mb", [
+    (64, 64, 16, 2),            # one split, two groups of two parts
+    (256, 256, 16, 8),          # four splits
+    (128, 512, 32, 2),
+    (256, 256, 48, 1),          # parts of 96 pixels
+    (768, 768, 16, 1),          # too many tiles for wave groups: units
+])
+def test_wgrad_sums_of_small_whole_maps_are_as_short_as_units(cin, cout, hw, mb):
+    """Operands of one sign.  P parts of 8 sums of 16 products, rounded to 2^-24/sqrt(3) of the sum so far: 8/(3 P) of that squared, two parts
+    of a group added up 2/P, two groups of a split 2 (2/P), and the total 1, P = 4 at the least, where the groups' sum is the total: sqrt(8/12 + 1/2 + 1)
+    times 3.4e-8.  Parts of 384 pixels are 5.3e-8 to 6.4e-8 off here."""
+    assert _wgrad_errors(3, cin, cout, hw, mb)[0] < 5.1e-8
+
+
+def _wgrad_errors(k, cin, cout, hw, mb):
+    """Of dw and db against float64, operands of one sign."""
     st = single(lambda b: b.conv(cin, cout, k, src=-1), cin, (hw, hw), C.BF16, micro_batch=mb, n_micro=1, need_input_grad=0)
     g = GpuStage(st, [(None, None)])
     rng = np.random.default_rng(cin + cout)
@@ -737,8 +756,7 @@ def test_wgrad_sums_are_short(k, cin, cout, hw, mb):
     cols = torch.nn.functional.unfold(x, k, padding=k // 2).permute(1, 0, 2).reshape(cin * k * k, -1)
     rows = dy.permute(1, 0, 2, 3).reshape(cout, -1)
     off = lambda got, exact: float(np.linalg.norm(got - exact) / np.linalg.norm(exact))
-    e = (off(dw.reshape(cout, -1), (rows @ cols.t().contiguous()).numpy()), off(db, rows.sum(dim=1).numpy()))
-    assert max(e) < 1.2e-7
+    return off(dw.reshape(cout, -1), (rows @ cols.t().contiguous()).numpy()), off(db, rows.sum(dim=1).numpy())
 
 
 @pytest.mark.parametrize("k,stride,cin,cout,hw,mb", [
