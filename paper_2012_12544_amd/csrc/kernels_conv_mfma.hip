@@ -1345,7 +1345,7 @@ __global__ __launch_bounds__(WKO *WCI *KG * 64, KG == 1 ? 2 : 1) void k_wgrad_mf
 // most rows have up to 256 partials (64x64 from 100352 rows, normal operands, 8.9e-8 off 64 bits; in float 1.7e-7).
 // Entries past total_w are the bias partials and go to db.  total_w and total are multiples of 4
 // (channel counts are multiples of 8).
-struct SplitkArgs {
+struct SplitkArgs {                              // tests/launch_recorder.c reads it
     const float *part;
     float *dw, *db;
     size_t total_w, total;
