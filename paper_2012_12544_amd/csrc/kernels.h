@@ -25,6 +25,9 @@ struct GatherConv {
     int beside = 0;
     // The output is the input of a batch-norm, or the gradient of one's output: kernels that leave it the sums it needs are preferred.
     int by_norm = 0;
+    // wt is kept in panels of 32 columns, [Ci / 32][Co][32] (1x1 filters, Ci a multiple of 32): neighbouring rows of a K-tile are one
+    // piece of memory.  No plan depends on it.
+    int wt_panels = 0;
 };
 
 // Forward-convolution geometry (x: N,H,W,C ; y: N,P,Q,K ; filter R x S).
@@ -195,10 +198,11 @@ hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s);
 // the same for a weight matrix [K][R][S][C] with its working copy and transposed copy (see recast and
 // make_dgrad_filter), and for its bias b / db [K] (may be NULL)
 hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
-                      float *db, hipStream_t s);
-hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s);
+                      float *db, hipStream_t s, bool work_panels = false, bool wt_panels = false);
+// panels_of: columns of the matrix whose copy is kept in panels (GatherConv::wt_panels), 0: as it is
+hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s, int panels_of = 0);
 // wt[c][R-1-r][S-1-s][k] = work(w[k][r][s][c])   (dgrad filter)
-hipError_t make_dgrad_filter(int dt, const float *w, void *wt, int K, int R, int S, int C, hipStream_t s);
+hipError_t make_dgrad_filter(int dt, const float *w, void *wt, int K, int R, int S, int C, hipStream_t s, bool panels = false);
 hipError_t fill_f32(float *p, float v, size_t n, hipStream_t s);
 
 // ---- boundary layout conversion NCHW <-> NHWC (same storage type); optional ReLU gate.

@@ -50,7 +50,10 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // 3x3 / 2 with the gate and batch-norm sums of a bottleneck, 32 samples, 512 channels, 14x14 from 7x7: 104 -> 24 us; 128
 // channels, 56x56 from 28x28: 84 -> 41 us.  With the taps not innermost only for 1x1 filters, whose K is the channels of the
 // one tap either way.
-template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool TURNS = false>
+// PANELS: the filter is kept in panels of 32 columns (GatherConv::wt_panels).  A wave-wide load fetches whole cache lines whatever BK,
+// and what a tile streams is one or two pieces of memory (25088->4096, 64 rows, 50.0 -> 45 us; 4096->4096 16.1 -> 15.1).  A variant of
+// its own: layouts as arguments cost the others up to 0.7 % of a mini-batch.
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool PANELS = false>
 __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
@@ -126,6 +129,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     // that fall inside the image - so that a K-tile costs one scalar offset, one mask test and one
     // add per load.
     constexpr bool FAST = TAPS_INNER;
+    static_assert(!PANELS || (FAST && !PHASED), "1x1 filters of whole K-tiles");
     static_assert(!TAPS_INNER || S1, "a strided operand takes its taps in the flattened order");
     int hb[XL], wb[XL];
     unsigned xoff[XL];                       // generic: byte offset of pixel (n, 0, 0), channel 0; FAST: see above
@@ -159,8 +163,12 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
         int co = co0 + (i * NW + wave) * RPW + lrow;
-        woff[i] = co < g.Co ? (unsigned)co * (unsigned)K * 2u : OOB;
-        if (FAST && co < g.Co) woff[i] += 16u * lc;
+        if constexpr (PANELS) {
+            woff[i] = co < g.Co ? (unsigned)((lc >> 2) * g.Co + co) * 64u + 16u * (lc & 3) : OOB;
+        } else {
+            woff[i] = co < g.Co ? (unsigned)co * (unsigned)K * 2u : OOB;
+            if (FAST && co < g.Co) woff[i] += 16u * lc;
+        }
     }
     // K order.  TAPS_INNER (Ci a multiple of BK): tile kt covers channels [cit*BK, +BK) of tap
     // (kt % RS), taps innermost, so that consecutive tiles re-read almost the same pixels (shifted
@@ -180,22 +188,14 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
         cb = KT ? ti / taps * BK : g.Ci;               // a class without taps reads nothing
     }
 
-    // TURNS: the block starts at a K-tile of its own and goes round.  Blocks that stream a filter of which the caches hold nothing
-    // would otherwise all ask for the same columns of its rows at a time, which in a matrix of 4096 columns lie on few memory
-    // channels (25088x4096, 64 rows of pixels, nothing of it cached, 80 -> 70 us; mini-batch of the classifier 3786 -> 3661).
-    // A variant of its own: the test costs the others 3 % (784 rows, 400 blocks 13.9 -> 14.3).
-    static_assert(!TURNS || (TAPS_INNER && KG == 1 && !PHASED), "of one tap, K not split");
-    const int from = TURNS ? tile_c % (kt1 - kt0) * BK : 0;
     auto issue_tile = [&](int stage) {
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
             const bool kin = KG > 1 ? ti < kt1 : cb < g.Ci;
             const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
             const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
-            int c0 = cb;
-            if constexpr (TURNS) c0 = cb + from < g.Ci ? cb + from : cb + from - g.Ci;
-            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + c0) * 2u;
-            const unsigned wo = kin ? (unsigned)(tap * g.Ci + c0) * 2u : OOB;
+            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + cb) * 2u;
+            const unsigned wo = !kin ? OOB : PANELS ? (unsigned)(cb * g.Co) * 2u : (unsigned)(tap * g.Ci + cb) * 2u;
 #pragma unroll
             for (int i = 0; i < XL; ++i) {
                 unsigned vo = (tapmask[i] & bit) ? xoff[i] + xo : OOB;
@@ -818,15 +818,13 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     const bool phased = plan.classes > 1;
     constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
     const size_t smem = phased ? smem_phased : smem_flat;
-    static_assert(smem_phased <= (NT >= 512 ? 160 : 80) * 1024, "two blocks of 4 waves (one of 8) must fit the 160 KB LDS of a CU");
+    static_assert(smem_phased <= (NT >= 512 || STAGES > 4 ? 160 : 80) * 1024, "two blocks of 4 waves (one of 8, or with a deep ring) must fit the 160 KB LDS of a CU");
     const long long npix = (long long)g.N * g.Ho * g.Wo;
     const int tiles_p = (int)((plan.class_pix + BP - 1) / BP), tiles_c = (g.Co + BC - 1) / BC;
     const int is_grad = (epi.gate != nullptr || epi.accum) ? 1 : 0;
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
-    // one row of tiles, so that every byte of the filter is read once, and more of them than the L2s hold
-    const bool turned = npix <= 64 && g.R * g.S == 1 && plan.classes == 1 && plan.splits == 1 && wt_bytes > (32u << 20);
     dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
 #define GATHER_LAUNCH(S1_, TI_, ...)                                                                                   \
     do {                                                                                                          \
@@ -843,13 +841,17 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
                            (const bf16_t *)epi.accum_from);                                                      \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
-    if constexpr (KG > 1) {                                         // stride-1 operands
+    if (g.wt_panels) {
+        if (taps_inner && !phased && g.s_in == 1) GATHER_LAUNCH(true, true, false, true);
+        else return hipErrorInvalidValue;
+    } else if constexpr (STAGES > 4) {
+        return hipErrorInvalidValue;                                // only filters in panels take the deep ring
+    } else if constexpr (KG > 1) {                                  // stride-1 operands
         if (taps_inner) GATHER_LAUNCH(true, true, false);
         else if constexpr (BK == 32) GATHER_LAUNCH(true, false, false);
     } else if constexpr (BK == 64) {
         if constexpr (BP == 64) {
             if (phased) GATHER_LAUNCH(true, true, true);
-            else if (turned) GATHER_LAUNCH(true, true, false, true);
             else GATHER_LAUNCH(true, true, false);
         } else GATHER_LAUNCH(true, true, false);                    // one class
     } else if (phased) {
@@ -880,6 +882,9 @@ hipError_t launch_plan(const void *in, const void *wt, const float *bias, void *
     if (p.kg == 4) TILE(32, 64, 1, 2, 32, 4, 4);
     if (p.kg == 2 && p.bk == 64) TILE(64, 64, 2, 2, 64, 3, 2);
     if (p.kg == 2) TILE(64, 64, 2, 2, 32, 4, 2);
+    // A filter that is streamed from memory, by blocks that have a unit to themselves: five K-tiles on their way instead of two
+    // (25088<-4096, 64 rows, in panels, 41.2 -> 39.4 us; from rows of 8 KB, two on their way and every block from a K-tile of its own, 43.8)
+    if (p.bk == 64 && p.bp == 64 && g.wt_panels && p.class_pix <= 64 && (g.Co + 127) / 128 * p.splits <= 256) TILE(64, 128, 1, 4, 64, 6);
     if (p.bk == 64 && p.bp == 64) TILE(64, 128, 1, 4, 64, 3);
     if (p.bk == 64 && p.bc == 256 && p.bp == 128) TILE(128, 256, 2, 4, 64, 3);
     if (p.bk == 64 && p.bc == 256) TILE(256, 256, 2, 4, 64, 2);
@@ -1540,7 +1545,7 @@ hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, v
                             GradEpi epi, const GatherConv &g, void *workspace, hipStream_t s, float *stat_part,
                             const void *bn_x, const float *bn_stats)
 {
-    if (!conv_gather_mfma_supported(g)) return hipErrorInvalidValue;
+    if (!conv_gather_mfma_supported(g) || (g.wt_panels && (g.R * g.S != 1 || g.s_in != 1 || g.Ci % 32))) return hipErrorInvalidValue;
     if (stat_part && conv_gather_mfma_stat_chunks(g) == 0) return hipErrorInvalidValue;
     if (bn_x && (!stat_part || !bn_stats || !(epi.gate || epi.accum))) return hipErrorInvalidValue;   // gradient epilogue only
     if ((long long)g.N * g.Ho * g.Wo == 0) return hipSuccess;

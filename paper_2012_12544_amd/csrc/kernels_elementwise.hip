@@ -1277,6 +1277,9 @@ __global__ void k_sgd(float *__restrict__ w, float *__restrict__ g, float lr, si
     g[i] = 0.0f;
 }
 
+// Element (row, col) of a matrix of `rows` rows kept in panels of 32 columns, [col / 32][row][32] (GatherConv::wt_panels)
+__device__ __forceinline__ size_t panel_at(int row, int col, int rows) { return ((size_t)(col >> 5) * rows + row) * 32 + (col & 31); }
+
 // The whole update of a weight matrix [K][R*S][C]: w -= lr g, g = 0, the working copy, the transposed (flipped) copy of
 // the input gradient (see k_dgrad_filter) and the bias, in one pass on 64 x 64 tiles of one tap through LDS; V channels a
 // thread and access.  HBM-bound for the big linear layers: as an update and a transposing pass that read the masters
@@ -1285,7 +1288,7 @@ __global__ void k_sgd(float *__restrict__ w, float *__restrict__ g, float lr, si
 template <class T, int V>
 __global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work,
                                                     T *__restrict__ wt, int K, int R, int S, int C, float *__restrict__ b,
-                                                    float *__restrict__ db)
+                                                    float *__restrict__ db, bool work_panels, bool wt_panels)
 {
     constexpr int LANES = 64 / V, ROWS = TPB / LANES, TRIPS = 64 / ROWS;
     __shared__ float tile[64][65];
@@ -1317,7 +1320,7 @@ __global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float
             }
             *reinterpret_cast<vec_t<float, V> *>(w + at) = wv[i];
             *reinterpret_cast<vec_t<float, V> *>(g + at) = zero;
-            *reinterpret_cast<vec_t<T, V> *>(work + at) = o;
+            *reinterpret_cast<vec_t<T, V> *>(work + (work_panels ? panel_at(k, c, K) : at)) = o;
         }
     }
     if (b && blockIdx.x == 0 && tap == 0 && threadIdx.x < 64 && k0 + (int)threadIdx.x < K) {
@@ -1333,22 +1336,23 @@ __global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float
             vec_t<T, V> o;
 #pragma unroll
             for (int j = 0; j < V; ++j) o.e[j] = from_f32<T>(tile[V * tx + j][ty + ROWS * i]);
-            *reinterpret_cast<vec_t<T, V> *>(wt + ((size_t)c * RS + tap_t) * K + k) = o;
+            *reinterpret_cast<vec_t<T, V> *>(wt + (wt_panels ? panel_at(c, k, C) : ((size_t)c * RS + tap_t) * K + k)) = o;
         }
     }
 }
 
-template <class T> __global__ void k_recast(const float *__restrict__ w, T *__restrict__ work, size_t n)
+// C > 0: the matrix has rows of C elements and its copy is kept in panels
+template <class T> __global__ void k_recast(const float *__restrict__ w, T *__restrict__ work, size_t n, int C)
 {
     size_t i = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (i < n) work[i] = from_f32<T>(w[i]);
+    if (i < n) work[C ? panel_at((int)(i / C), (int)(i % C), (int)(n / C)) : i] = from_f32<T>(w[i]);
 }
 
 // wt[c][r][s][k] = w[k][R-1-r][S-1-s][c] in storage type: per tap a K x C -> C x K transpose, done
 // on 64 x 64 tiles through LDS so that both the fp32 reads (along c) and the writes (along k) are
 // contiguous.  grid: (C tiles, K tiles, R*S)
 template <class T>
-__global__ void k_dgrad_filter(const float *__restrict__ w, T *__restrict__ wt, int K, int R, int S, int C)
+__global__ void k_dgrad_filter(const float *__restrict__ w, T *__restrict__ wt, int K, int R, int S, int C, bool panels)
 {
     __shared__ float tile[64][65];
     const int c0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
@@ -1364,7 +1368,7 @@ __global__ void k_dgrad_filter(const float *__restrict__ w, T *__restrict__ wt, 
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int c = c0 + ty + 4 * i, k = k0 + tx;
-        if (c < C && k < K) wt[((size_t)c * R * S + tap) * K + k] = from_f32<T>(tile[tx][ty + 4 * i]);
+        if (c < C && k < K) wt[panels ? panel_at(c, k, C) : ((size_t)c * R * S + tap) * K + k] = from_f32<T>(tile[tx][ty + 4 * i]);
     }
 }
 
@@ -1860,36 +1864,39 @@ hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s)
 }
 
 hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
-                      float *db, hipStream_t s)
+                      float *db, hipStream_t s, bool work_panels, bool wt_panels)
 {
     if ((size_t)K * R * S * C == 0) return hipSuccess;
+    if ((work_panels && (R * S != 1 || C % 32)) || (wt_panels && (R * S != 1 || K % 32))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((C + 63) / 64), (unsigned)((K + 63) / 64), (unsigned)(R * S));
     const size_t es = dt_size(dt);
     // four values per access where rows of both copies and their starts allow it
     const bool vec = C % 4 == 0 && K % 4 == 0 && aligned16(w) && aligned16(g) && (uintptr_t)work % (4 * es) == 0 && (uintptr_t)wt % (4 * es) == 0;
     DISPATCH_T(dt, {
         if (vec)
-            hipLaunchKernelGGL((k_sgd_matrix<T, 4>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db);
+            hipLaunchKernelGGL((k_sgd_matrix<T, 4>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db, work_panels, wt_panels);
         else
-            hipLaunchKernelGGL((k_sgd_matrix<T, 1>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db);
+            hipLaunchKernelGGL((k_sgd_matrix<T, 1>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db, work_panels, wt_panels);
     });
     return hipGetLastError();
 }
 
-hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s)
+hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s, int panels_of)
 {
     if (n == 0) return hipSuccess;
-    DISPATCH_T(dt, { hipLaunchKernelGGL((k_recast<T>), dim3(blocks_for(n)), dim3(TPB), 0, s, w, (T *)work, n); });
+    if (panels_of % 32 || (panels_of && n % panels_of)) return hipErrorInvalidValue;
+    DISPATCH_T(dt, { hipLaunchKernelGGL((k_recast<T>), dim3(blocks_for(n)), dim3(TPB), 0, s, w, (T *)work, n, panels_of); });
     return hipGetLastError();
 }
 
-hipError_t make_dgrad_filter(int dt, const float *w, void *wt, int K, int R, int S, int C, hipStream_t s)
+hipError_t make_dgrad_filter(int dt, const float *w, void *wt, int K, int R, int S, int C, hipStream_t s, bool panels)
 {
     size_t n = (size_t)K * R * S * C;
     if (n == 0) return hipSuccess;
+    if (panels && (R * S != 1 || K % 32)) return hipErrorInvalidValue;
     DISPATCH_T(dt, {
         hipLaunchKernelGGL((k_dgrad_filter<T>), dim3((unsigned)((C + 63) / 64), (unsigned)((K + 63) / 64), (unsigned)(R * S)),
-                           dim3(256), 0, s, w, (T *)wt, K, R, S, C);
+                           dim3(256), 0, s, w, (T *)wt, K, R, S, C, panels);
     });
     return hipGetLastError();
 }

@@ -92,6 +92,8 @@ struct Layer {
     // (forward) and the pre-activation gradients (backward) and the cell-gradient carry
     size_t off_gates = 0, off_cells = 0, off_hs = 0, off_pd = 0, off_dcn = 0;
     bool groups = false;                 // its weight gradient may share a launch with others
+    // LINEAR on the MFMA kernels: the copies that forward and input gradient read are kept in panels (GatherConv::wt_panels)
+    bool w_panels = false, wt_panels = false;
     bool permute_in = false;             // LINEAR fed by a flattened (C,H,W) tensor
     int pc = 0, ph = 0, pw = 0;
 };
@@ -271,6 +273,7 @@ GatherConv fwd_geom(const bapipe_stage *st, const Layer &L)
         g.R = g.S = 1;
         g.s_out = g.s_in = 1;
         g.pad_h = g.pad_w = 0;
+        g.wt_panels = L.w_panels;
         return g;
     }
     g.Hi = A.H; g.Wi = A.W; g.Ci = A.Cp;
@@ -293,6 +296,7 @@ GatherConv dgrad_geom(const bapipe_stage *st, const Layer &L)
     g.pad_h = f.R - 1 - f.pad_h;
     g.pad_w = f.S - 1 - f.pad_w;
     g.by_norm = L.a > 0 && st->layers[L.a - 1].d.kind == BAPIPE_BATCHNORM2D;
+    g.wt_panels = L.wt_panels;
     return g;
 }
 
@@ -400,7 +404,7 @@ hipError_t refresh_transposed(bapipe_stage *st, Layer &L)
         return make_dgrad_filter(st->dt, L.w + (size_t)G * In, (char *)L.w_t + (size_t)G * In * es, G, 1, 1, H, st->stream);
     }
     int R = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kh, S = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kw;
-    return make_dgrad_filter(st->dt, L.w, L.w_t, L.d.cout, R, S, L.cin_p, st->stream);
+    return make_dgrad_filter(st->dt, L.w, L.w_t, L.d.cout, R, S, L.cin_p, st->stream, L.wt_panels);
 }
 
 // weights, bias and working copies of one layer after a mini-batch
@@ -420,13 +424,13 @@ hipError_t update_layer(bapipe_stage *st, Layer &L, float lr)
                           nullptr, nullptr, st->stream);
     }
     const int R = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kh, S = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kw;
-    return sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, L.d.cout, R, S, L.cin_p, b, L.db, st->stream);
+    return sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, L.d.cout, R, S, L.cin_p, b, L.db, st->stream, L.w_panels, L.wt_panels);
 }
 
 hipError_t refresh_work(bapipe_stage *st, Layer &L)
 {
     if (!has_matrix(L.d.kind)) return hipSuccess;
-    hipError_t e = recast(st->dt, L.w, L.w_work, L.w_elems, st->stream);
+    hipError_t e = recast(st->dt, L.w, L.w_work, L.w_elems, st->stream, L.w_panels ? L.cin_p : 0);
     if (e != hipSuccess) return e;
     return refresh_transposed(st, L);
 }
@@ -1337,6 +1341,10 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                     work = w > work ? w : work;
                 }
             }
+        }
+        if (L.d.kind == BAPIPE_LINEAR) {
+            L.w_panels = L.cin_p % 32 == 0 && use_mfma_gather(st, fwd_geom(st, L));
+            L.wt_panels = L.d.cout % 32 == 0 && use_mfma_gather(st, dgrad_geom(st, L));
         }
         if (L.d.kind == BAPIPE_CONV2D || L.d.kind == BAPIPE_LINEAR) {
             ConvShape cs = conv_shape(st, L);

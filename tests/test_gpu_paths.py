@@ -364,6 +364,33 @@ def test_linear_groups_of_waves(cin, cout, mb):
     compare_minibatch(st, verbose="linear groups %d->%d x %d" % (cin, cout, mb))
 
 
+@pytest.mark.parametrize("cin,cout,mb", [
+    (32, 32, 1),           # one panel either way
+    (96, 160, 70),         # panels and a half of 64 columns, ragged tiles of rows
+    (64, 40, 3),           # panels forward, rows backward
+    (1088, 4128, 64),      # deep ring of the gradient: K-tiles of 64, channels that end inside a tile
+    (1056, 4128, 64),      # K-tiles of 32
+    (64, 128, 4200),       # 256 x 128
+    (1024, 512, 19000),    # 256 x 256
+])
+def test_linear_filters_in_panels(cin, cout, mb):
+    """Matrices whose copies are kept in panels of 32 columns, before and after an update.  (No ReLU: of the gates of 10^7 outputs a
+    few would differ, and a row of dx with each.)"""
+    b = C._Builder()
+    b.linear(cin, cout, src=-1)
+    st = C._stage("panels", b.layers, C.BF16, (cin, 1, 1), mb, 2, 1, 2, 1, C.BASE_SEED + 79, "kaiming")
+    compare_minibatch(st, verbose="linear %d->%d x %d" % (cin, cout, mb))
+    xs, gs = stage_io(st)
+    one = GpuStage(st, gen.all_params(st, perturb=True))
+    _mini_batch(one, st, xs, gs)
+    B.bapipe_stage_step(one.h, 0.05)
+    other = GpuStage(st, [one.get_params(0)])
+    for u, v in zip(_mini_batch(one, st, xs, gs), _mini_batch(other, st, xs, gs)):
+        assert np.array_equal(u, v)
+    one.close()
+    other.close()
+
+
 @pytest.mark.parametrize("cin,mid,hw,mb", [(512, 64, (7, 7), 3), (512, 72, (10, 9), 2)])
 def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
     """Every epilogue on tiles of wave groups: statistics, sums of dy and dy*xhat behind a gate, a residual share.  Small
