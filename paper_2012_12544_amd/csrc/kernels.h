@@ -62,8 +62,10 @@ size_t conv_gather_mfma_workspace(const GatherConv &g);      // split-K partials
 // the values it stores - [2][chunks][Co] floats with chunks = conv_gather_mfma_stat_chunks(g) - which is what
 // bn_fwd would otherwise compute in a pass of its own; only where that function returns a non-zero count
 int conv_gather_mfma_stat_chunks(const GatherConv &g);
+// tickets: kGatherTickets words that are zero, and zero again behind every launch; launches that may run at once need words of their own
+constexpr int kGatherTickets = 128;
 hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, void *out, int relu,
-                            GradEpi epi, const GatherConv &g, void *workspace, hipStream_t s,
+                            GradEpi epi, const GatherConv &g, void *workspace, unsigned *tickets, hipStream_t s,
                             float *stat_part = nullptr, const void *bn_x = nullptr, const float *bn_stats = nullptr);
 // 3x3 / stride 1 / pad 1 with the input halo of a 16x16 output patch resident in LDS
 // (kernels_conv_halo.hip); conv_gather_mfma routes to it when it applies

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
     int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split, int part_tiles,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
-    const bf16_t *old_from)
+    const bf16_t *old_from, unsigned *tickets)
 {
     constexpr int NW = WP * WC, NT = NW * KG * 64;      // waves of a group, threads of the block
     constexpr int CPR = BK / 8;              // 16-byte chunks per tile row
@@ -438,6 +438,58 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
                     *reinterpret_cast<float4 *>(park + (kg * BP + wp * WT_P + b * 32 + frow) * PITCH + wc * WT_C + a * 32 + 8 * q + 4 * fhalf) =
                         make_float4(sums_of[a][b][4 * q], sums_of[a][b][4 * q + 1], sums_of[a][b][4 * q + 2], sums_of[a][b][4 * q + 3]);
         __syncthreads();
+        // a float4 of the tile to the staging tile, with bias and ReLU
+        auto to_tile = [&](int prow, int col, float4 v) {
+            const float4 bv = *reinterpret_cast<const float4 *>(sBias + col);
+            v.x += bv.x; v.y += bv.y; v.z += bv.z; v.w += bv.w;
+            if (relu) v = make_float4(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f), fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f));
+            chunk8 c8;
+            c8[0] = pack_bf16(v.x, v.y);
+            c8[1] = pack_bf16(v.z, v.w);
+            *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
+        };
+        // K split over blocks: part[split][pixel][co].  Where there are tickets (PANELS: linear layers) the blocks of a tile count themselves, and the one that comes
+        // last adds all the sums, in the order of the splits, and goes on to the epilogue: nobody waits.  Stores and loads are of agent
+        // scope, and a block counts itself when its stores are complete, so that no cache has to be written back.  It takes 2.5 us, a launch
+        // that adds them 4.8 and the gap in front of it.  Without tickets the sums are left to the next launch.
+        const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)((unsigned)gridDim.y * npix * g.Co * 4u), 0x00020000);
+        auto part_at = [&](int split, int prow, int col) {
+            const int p = pix0 + prow, co = co0 + col;
+            return p < npix && co < g.Co ? ((unsigned)(split * npix + p) * g.Co + co) * 4u : OOB;
+        };
+        auto put_part = [&](int prow, int col, float4 v) {
+            if (PANELS && tickets)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(chunk16, v), prsrc, part_at(blockIdx.y, prow, col), 0, 16);
+            else if (pix0 + prow < npix && co0 + col < g.Co)
+                *reinterpret_cast<float4 *>(part + ((size_t)blockIdx.y * npix + pix0 + prow) * g.Co + co0 + col) = v;
+        };
+        auto all_parts = [&](int prow, int col) {
+            float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (int k = 0; k < (int)gridDim.y; k += 4) {
+                chunk16 c[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c[u] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, k + u < (int)gridDim.y ? part_at(k + u, prow, col) : OOB, 0, 16);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float4 v = __builtin_bit_cast(float4, c[u]);
+                    t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+                }
+            }
+            return t;
+        };
+        auto last_split = [&]() {
+            if (!tickets) return false;
+            int *last = reinterpret_cast<int *>(sBias + BC);                 // where a PHASED tile, whose K is whole, has its pixels
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) {
+                unsigned *t = tickets + blockIdx.x;
+                *last = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1;
+                if (*last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            return *last != 0;
+        };
         constexpr int F4 = BC / 4;
         for (int i = tid; i < BP * F4; i += NT) {
             const int prow = i / F4, col = i % F4 * 4;
@@ -447,21 +499,13 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
                 const float4 w = *reinterpret_cast<const float4 *>(park + (u * BP + prow) * PITCH + col);
                 v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
             }
-            if (part) {
-                const int p = pix0 + prow;
-                if (p < npix && co0 + col < g.Co)
-                    *reinterpret_cast<float4 *>(part + ((size_t)blockIdx.y * npix + p) * g.Co + co0 + col) = v;
-                continue;
-            }
-            const float4 bv = *reinterpret_cast<const float4 *>(sBias + col);
-            v.x += bv.x; v.y += bv.y; v.z += bv.z; v.w += bv.w;
-            if (relu) v = make_float4(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f), fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f));
-            chunk8 c8;
-            c8[0] = pack_bf16(v.x, v.y);
-            c8[1] = pack_bf16(v.z, v.w);
-            *reinterpret_cast<chunk8 *>(sO + prow * SROW + col) = c8;
+            if (part) put_part(prow, col, v);
+            else to_tile(prow, col, v);
         }
-        if (part) return;
+        if (part) {
+            if (!PANELS || !last_split()) return;
+            for (int i = tid; i < BP * F4; i += NT) to_tile(i / F4, i % F4 * 4, all_parts(i / F4, i % F4 * 4));
+        }
     } else if (part) {
         // split-K: raw fp32 sums, 4 consecutive channels of one pixel per store; bias, ReLU and the
         // gradient epilogue are applied by the reduction kernel
@@ -741,8 +785,13 @@ GatherPlan gather_plan(const GatherConv &g)
     const long long K = (long long)g.R * g.S * g.Ci;
     auto count = [&](int bp, int bc) { return ((npix + bp - 1) / bp) * ((g.Co + bc - 1) / bc); };
     const bool large = 2.0 * g.Co * K > 40e6, k64 = g.Ci % 64 == 0 && g.R * g.S <= 32;
+    // Few rows of a linear layer: four blocks share a tile's K and the last one adds (4096->4096, 64 rows, 256 blocks: 14.4 us, one launch
+    // of 32 x 32 15.1; 2048->2048, of whose K four blocks would take 512 each, 11 and 7.8)
+    const bool flat = g.Hi == 1 && g.Wi == 1 && g.R * g.S == 1 && !g.by_norm && 2.0 * g.Co * K > 30e6;
     p.kg = 1;
-    if (g.s_in == 1 && large && npix > 32) {
+    if (flat && npix > 32 && npix <= 64 && k64 && count(64, 64) <= 128) {
+        p.kg = 2;
+    } else if (g.s_in == 1 && large && npix > 32) {
         if (npix <= 64 && k64 && count(64, 64) <= 128) p.kg = 2;
     } else if (g.s_in == 1 && K >= 512 && count(32, 32) <= 256) {
         p.kg = 8;
@@ -792,7 +841,7 @@ GatherPlan gather_plan(const GatherConv &g)
     if ((p.kg == 2 && k64) || (p.kg == 1 && p.bp == 64 && tiles <= 512 && k64 && (g.s_in == 1 || p.classes > 1))) p.bk = 64;
     const int BK = p.bk;
     const int KT = g.Ci % BK == 0 ? (g.Ci / BK) * g.R * g.S : (g.R * g.S * g.Ci + BK - 1) / BK;
-    long long want = p.kg > 1 ? (large ? 256 / tiles : 1) : tiles >= 128 || eight ? 1 : (512 + tiles - 1) / tiles;
+    long long want = p.kg > 1 ? (large || (flat && p.kg == 2) ? 256 / tiles : 1) : tiles >= 128 || eight ? 1 : (512 + tiles - 1) / tiles;
     long long most = KT * BK / 512;                 // at least 512 of K per split
     if (want > most) want = most;
     if (want > 32) want = 32;
@@ -807,14 +856,14 @@ GatherPlan gather_plan(const GatherConv &g)
 
 template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG = 1>
 hipError_t launch_gather(const void *in, const void *wt, const float *bias, void *out, int relu, GradEpi epi,
-                         const GatherConv &g, const GatherPlan &plan, void *workspace, hipStream_t s, bool raw = false,
+                         const GatherConv &g, const GatherPlan &plan, void *workspace, unsigned *tickets, hipStream_t s, bool raw = false,
                          float *stat_part = nullptr, const void *bn_x = nullptr, const float *bn_stats = nullptr)
 {
     constexpr int NT = WP * WC * KG * 64;
     constexpr size_t main_bytes = (size_t)KG * STAGES * (BP + BC) * BK * 2;
     // the groups' sums, staging tile, per-thread sums
     constexpr size_t epi_bytes = (KG > 1 ? (size_t)KG * BP * (BC + 4) * 4 : 0) + (size_t)BP * (BC + 4) * 2 + NT * 8;
-    constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float);
+    constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float) + sizeof(int);
     const bool phased = plan.classes > 1;
     constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
     const size_t smem = phased ? smem_phased : smem_flat;
@@ -825,6 +874,11 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
+    // One block of wave groups, which has its tile in rows, adds up to four sums faster than a launch would start; of eight the launch,
+    // whose blocks share them, is the faster way, and so it is where a thread has its sums in pieces of 16 bytes (64 rows, us: 12544<-2048,
+    // four splits of 64 x 128, 16.0 and 4.9 by launch, 25.2)
+    if (raw || KG == 1 || plan.splits > 4 || !g.wt_panels) tickets = nullptr;
+    else if (plan.splits > 1 && (!tickets || tiles_p * tiles_c > kGatherTickets)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(tiles_p * tiles_c), (unsigned)plan.splits, (unsigned)plan.classes);
 #define GATHER_LAUNCH(S1_, TI_, ...)                                                                                   \
     do {                                                                                                          \
@@ -838,7 +892,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         hipLaunchKernelGGL(kfn, grid, dim3(NT), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,          \
                            (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g, tiles_c, in_bytes, \
                            wt_bytes, part, plan.kt_per_split, plan.part_tiles, stat_part, (const bf16_t *)bn_x, bn_stats,         \
-                           (const bf16_t *)epi.accum_from);                                                      \
+                           (const bf16_t *)epi.accum_from, tickets);                                             \
     } while (0)
     const bool taps_inner = g.Ci % BK == 0 && g.R * g.S <= 32;      // the stride-1 variant keeps a 32-bit tap mask
     if (g.wt_panels) {
@@ -864,7 +918,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
         GATHER_LAUNCH(false, false, false);
     }
 #undef GATHER_LAUNCH
-    if (part && !raw) {
+    if (part && !raw && !tickets) {
         const size_t total = (size_t)npix * g.Co;
         hipLaunchKernelGGL(k_gather_splitk_reduce, dim3((unsigned)((total / 8 + 255) / 256)), dim3(256), 0, s, part,
                            plan.splits, total, g.Co, bias, (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu,
@@ -874,10 +928,10 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
 }
 
 hipError_t launch_plan(const void *in, const void *wt, const float *bias, void *out, int relu, GradEpi epi, const GatherConv &g,
-                       const GatherPlan &p, void *workspace, hipStream_t s, bool raw = false, float *stat_part = nullptr,
+                       const GatherPlan &p, void *workspace, unsigned *tickets, hipStream_t s, bool raw = false, float *stat_part = nullptr,
                        const void *bn_x = nullptr, const float *bn_stats = nullptr)
 {
-#define TILE(...) return launch_gather<__VA_ARGS__>(in, wt, bias, out, relu, epi, g, p, workspace, s, raw, stat_part, bn_x, bn_stats)
+#define TILE(...) return launch_gather<__VA_ARGS__>(in, wt, bias, out, relu, epi, g, p, workspace, tickets, s, raw, stat_part, bn_x, bn_stats)
     if (p.kg == 8) TILE(32, 32, 1, 1, 32, 4, 8);
     if (p.kg == 4) TILE(32, 64, 1, 2, 32, 4, 4);
     if (p.kg == 2 && p.bk == 64) TILE(64, 64, 2, 2, 64, 3, 2);
@@ -1542,7 +1596,7 @@ int conv_gather_mfma_stat_chunks(const GatherConv &g)
 }
 
 hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, void *out, int relu,
-                            GradEpi epi, const GatherConv &g, void *workspace, hipStream_t s, float *stat_part,
+                            GradEpi epi, const GatherConv &g, void *workspace, unsigned *tickets, hipStream_t s, float *stat_part,
                             const void *bn_x, const float *bn_stats)
 {
     if (!conv_gather_mfma_supported(g) || (g.wt_panels && (g.R * g.S != 1 || g.s_in != 1 || g.Ci % 32))) return hipErrorInvalidValue;
@@ -1552,7 +1606,7 @@ hipError_t conv_gather_mfma(const void *in, const void *wt, const float *bias, v
     if (epi.accum_from && (!epi.accum || conv3x3_halo_supported(g))) return hipErrorInvalidValue;   // gather kernel only
     if (conv3x3_halo_supported(g)) return conv3x3_halo_mfma(in, wt, bias, out, relu, epi, g, s);
     if (!epi.gate && !epi.accum && conv3x3_c8_supported(g)) return conv3x3_c8_mfma(in, wt, bias, out, relu, g, s);
-    return launch_plan(in, wt, bias, out, relu, epi, g, gather_plan(g), workspace, s, false, stat_part, bn_x, bn_stats);
+    return launch_plan(in, wt, bias, out, relu, epi, g, gather_plan(g), workspace, tickets, s, false, stat_part, bn_x, bn_stats);
 }
 
 size_t conv_gather_mfma_raw_workspace(const GatherConv &g)
@@ -1568,7 +1622,7 @@ hipError_t conv_gather_mfma_raw(const void *in, const void *wt, const GatherConv
     *splits = p.splits;
     if ((long long)g.N * g.Ho * g.Wo == 0) return hipSuccess;
     const GradEpi none{nullptr, 0};
-    return launch_plan(in, wt, nullptr, nullptr, 0, none, g, p, part, s, true);
+    return launch_plan(in, wt, nullptr, nullptr, 0, none, g, p, part, nullptr, s, true);
 }
 
 bool conv_wgrad_mfma_supported(const ConvShape &c)

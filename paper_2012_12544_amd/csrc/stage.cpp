@@ -92,7 +92,7 @@ struct Layer {
     // (forward) and the pre-activation gradients (backward) and the cell-gradient carry
     size_t off_gates = 0, off_cells = 0, off_hs = 0, off_pd = 0, off_dcn = 0;
     bool groups = false;                 // its weight gradient may share a launch with others
-    // LINEAR on the MFMA kernels: the copies that forward and input gradient read are kept in panels (GatherConv::wt_panels)
+    // LINEAR, and a 1x1 convolution of 1x1 maps, on the MFMA kernels: the copies that forward and input gradient read are kept in panels (GatherConv::wt_panels)
     bool w_panels = false, wt_panels = false;
     bool permute_in = false;             // LINEAR fed by a flattened (C,H,W) tensor
     int pc = 0, ph = 0, pw = 0;
@@ -153,7 +153,8 @@ struct bapipe_stage {
     char *deferred = nullptr;
     size_t deferred_bytes = 0;
     int flushed = 0;                         // micro-batches whose deferred weight gradients are already in dw
-    float *losses = nullptr;
+    float *losses = nullptr;                 // and, behind them, the tickets of conv_gather_mfma: of the handle's stream, of the backward stream
+    unsigned *tickets = nullptr, *tickets_f = nullptr, *tickets_b = nullptr;      // as work: of the pass being enqueued, of either
     size_t params_bytes = 0, slot_bytes = 0, transient_bytes = 0, grads_bytes = 0, work_bytes = 0;
     size_t flush_bytes = 0;                  // workspace of flush_deferred, whatever part of a mini-batch it finds
     size_t accum_off = 0, accum_bytes = 0;   // the dw/db region inside params (zeroed together)
@@ -281,6 +282,7 @@ GatherConv fwd_geom(const bapipe_stage *st, const Layer &L)
     g.R = L.d.kh; g.S = L.d.kw;
     g.s_out = L.d.stride; g.s_in = 1;
     g.pad_h = g.pad_w = L.d.pad;
+    g.wt_panels = L.w_panels;
     g.by_norm = L.o < (int)st->layers.size() && st->layers[L.o].d.kind == BAPIPE_BATCHNORM2D && st->layers[L.o].a == L.o;
     return g;
 }
@@ -480,7 +482,7 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
     const GatherConv gx = rows_geom(N, T, In, G);
     const bool tp = st->tap_begin(st->dt == DT_BF16 ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
     if (st->dt == DT_BF16)
-        HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, s));
+        HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, st->tickets, s));
     else
         HIPCHK(conv_gather_direct(st->dt, x, L.w_work, L.bias, P, 0, none, gx, s));
     const bool one_launch = st->dt == DT_BF16 && lstm_seq_supported(N, T, H, st->compute_units);
@@ -530,7 +532,7 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     if (dx) {
         const GatherConv gd = rows_geom(N, T, G, In);
         if (mf)
-            HIPCHK(conv_gather_mfma(D, wt_x, nullptr, dx, 0, e, gd, st->work, s));
+            HIPCHK(conv_gather_mfma(D, wt_x, nullptr, dx, 0, e, gd, st->work, st->tickets, s));
         else
             HIPCHK(conv_gather_direct(st->dt, D, wt_x, nullptr, dx, 0, e, gd, s));
         flop += 2.0 * N * T * (double)G * L.d.cin;
@@ -597,7 +599,7 @@ int layer_forward(bapipe_stage *st, int li, FwdCtx &c)
             HIPCHK(conv3x3_halo_pool_mfma(a, L.w_work, L.bias, L.d.fuse_relu, st->tptr(P.o, c.mbid),
                                           (uint8_t *)(st->slot(c.mbid) + P.aux_off), g, s));
         } else if (mf)
-            HIPCHK(conv_gather_mfma(a, L.w_work, L.bias, o, L.d.fuse_relu, none, g, st->work, s,
+            HIPCHK(conv_gather_mfma(a, L.w_work, L.bias, o, L.d.fuse_relu, none, g, st->work, st->tickets, s,
                                     (L.stat_chunks && !c.profiling) ? (float *)st->work : nullptr));
         else
             HIPCHK(conv_gather_direct(dt, a, L.w_work, L.bias, o, L.d.fuse_relu, none, g, s));
@@ -801,11 +803,11 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             const bool tp = st->tap_begin(mf ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
             if (mf && L.bnb_chunks && !c.profiling && (e.gate || e.accum)) {
                 const Layer &B = st->layers[li - 1];
-                HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, dx, 0, e, dg, st->work, s, (float *)st->work,
+                HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, dx, 0, e, dg, st->work, st->tickets, s, (float *)st->work,
                                         st->tptr(B.a, c.mbid), (const float *)(st->slot(c.mbid) + B.aux_off)));
                 c.bn_sums_ready = li - 1;
             } else if (mf)
-                HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, dx, 0, e, dg, st->work, s));
+                HIPCHK(conv_gather_mfma(g, L.w_t, nullptr, dx, 0, e, dg, st->work, st->tickets, s));
             else
                 HIPCHK(conv_gather_direct(dt, g, L.w_t, nullptr, dx, 0, e, dg, s));
             // dy and filter read, dx written, plus the gate and the previous dx where the epilogue uses them
@@ -1342,7 +1344,8 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
                 }
             }
         }
-        if (L.d.kind == BAPIPE_LINEAR) {
+        const bool flat_conv = L.d.kind == BAPIPE_CONV2D && L.d.kh * L.d.kw == 1 && L.d.stride == 1 && A.H * A.W == 1 && L.d.pad == 0;
+        if (L.d.kind == BAPIPE_LINEAR || flat_conv) {
             L.w_panels = L.cin_p % 32 == 0 && use_mfma_gather(st, fwd_geom(st, L));
             L.wt_panels = L.d.cout % 32 == 0 && use_mfma_gather(st, dgrad_geom(st, L));
         }
@@ -1426,10 +1429,13 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     st->transient = (char *)st->dev_alloc(st->transient_bytes);
     st->grads = (char *)st->dev_alloc(st->grads_bytes);
     st->work = (char *)st->dev_alloc(st->flush_bytes);       // the handle's own; a pass on another stream or the static array needs work_bytes
-    st->losses = (float *)st->dev_alloc(sizeof(float) * n_micro);
+    const size_t loss_words = align_up(sizeof(float) * n_micro) / sizeof(float);
+    st->losses = (float *)st->dev_alloc(sizeof(float) * (loss_words + 2 * kGatherTickets));
     if (defb) st->deferred = (char *)st->dev_alloc(defb);
     st->stream_f = st->stream;
     st->work_f = st->work;
+    st->tickets = st->tickets_f = (unsigned *)(st->losses + loss_words);
+    st->tickets_b = st->tickets_f + kGatherTickets;
     if (!st->params || !st->stash || !st->transient || !st->grads || !st->work || !st->losses || (defb && !st->deferred))
         return create_fail(BAPIPE_E_OOM, "device allocation failed (params %zu, stash %zu x %d, transient %zu, grads %zu, work %zu bytes)",
                            st->params_bytes, st->slot_bytes, st->depth, st->transient_bytes, st->grads_bytes, st->flush_bytes);
@@ -1459,7 +1465,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
     hipError_t e = fill_f32((float *)st->params, 0.f, st->params_bytes / 4, st->stream);
     for (int i = 0; i < n_layers && e == hipSuccess; ++i)
         if (st->layers[i].d.kind == BAPIPE_BATCHNORM2D) e = fill_f32(st->layers[i].w, 1.f, st->layers[i].w_elems, st->stream);
-    if (e == hipSuccess) e = fill_f32(st->losses, 0.f, n_micro, st->stream);
+    if (e == hipSuccess) e = fill_f32(st->losses, 0.f, loss_words + 2 * kGatherTickets, st->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(st->stream);
     if (e != hipSuccess) return create_fail(BAPIPE_E_DEVICE, "initialisation: %s", hipGetErrorString(e));
     guard.s = nullptr;
@@ -1525,8 +1531,8 @@ int bapipe_stage_backward(bapipe_stage_t *st, int mb_id, const void *dy_dev_or_l
     const int dt = st->dt;
     struct Lane {           // the backward pass runs on its own stream and workspace when there is one
         bapipe_stage *st;
-        explicit Lane(bapipe_stage *s_) : st(s_) { if (st->stream_b) { st->stream = st->stream_b; st->work = st->work_b; } }
-        ~Lane() { st->stream = st->stream_f; st->work = st->work_f; }
+        explicit Lane(bapipe_stage *s_) : st(s_) { if (st->stream_b) { st->stream = st->stream_b; st->work = st->work_b; st->tickets = st->tickets_b; } }
+        ~Lane() { st->stream = st->stream_f; st->work = st->work_f; st->tickets = st->tickets_f; }
     } lane(st);
     hipStream_t s = st->stream;
     if (st->stream_b) HIPCHK(hipStreamWaitEvent(s, st->ev_fwd[mb_id], 0));

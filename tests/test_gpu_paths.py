@@ -370,6 +370,7 @@ def test_linear_groups_of_waves(cin, cout, mb):
     (64, 40, 3),           # panels forward, rows backward
     (1088, 4128, 64),      # deep ring of the gradient: K-tiles of 64, channels that end inside a tile
     (1056, 4128, 64),      # K-tiles of 32
+    (4096, 4096, 61),      # K split over four blocks a tile, the last of which adds, in both directions
     (64, 128, 4200),       # 256 x 128
     (1024, 512, 19000),    # 256 x 256
 ])
@@ -389,6 +390,14 @@ def test_linear_filters_in_panels(cin, cout, mb):
         assert np.array_equal(u, v)
     one.close()
     other.close()
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("cin,cout,mb", [(96, 64, 5), (4096, 4096, 40)])
+def test_conv_of_single_pixels(cin, cout, mb, stride):
+    """A 1x1 convolution of 1x1 maps is a linear layer."""
+    st = single(lambda b: b.conv(cin, cout, 1, stride=stride, src=-1), cin, (1, 1), C.BF16, micro_batch=mb)
+    compare_minibatch(st, verbose="1x1 / %d of 1x1 maps %d->%d x %d" % (stride, cin, cout, mb))
 
 
 @pytest.mark.parametrize("cin,mid,hw,mb", [(512, 64, (7, 7), 3), (512, 72, (10, 9), 2)])
