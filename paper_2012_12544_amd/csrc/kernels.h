@@ -125,15 +125,17 @@ hipError_t colsum_accumulate(int dt, const void *a, int rows, int C, float *out,
 // ---- element-wise / pooling / normalisation
 hipError_t relu_fwd(int dt, const void *x, void *y, size_t n, hipStream_t s);
 hipError_t relu_bwd(int dt, const void *y, const void *dy, void *dx, GradEpi epi, size_t n, hipStream_t s);
+// y_nchw: a second destination of y, in NCHW; *stored says whether it was taken
 hipError_t maxpool2x2_fwd(int dt, const void *x, void *y, uint8_t *idx, int N, int H, int W, int C,
-                          hipStream_t s);
-// gate (if any) is indexed like dy (the pooled tensor), not like dx.
+                          hipStream_t s, void *y_nchw = nullptr, bool *stored = nullptr);
+// gate (if any) is indexed like dy (the pooled tensor), not like dx.  nchw: dy is in that layout, where the other function says yes
 hipError_t maxpool2x2_bwd(int dt, const void *dy, const uint8_t *idx, void *dx, GradEpi epi_pooled_gate,
-                          int N, int H, int W, int C, hipStream_t s);
+                          int N, int H, int W, int C, hipStream_t s, bool nchw = false);
+bool maxpool2x2_bwd_takes_nchw(int dt, const void *dy, const uint8_t *idx, const void *dx, const void *gate, int N, int H, int W, int C);
 // any window / stride / padding (kh*kw <= 255): idx = dh*kw + dw of the first maximum inside the
 // padded window; backward adds the gradients of all windows that chose an input (fixed order)
 hipError_t maxpool_fwd(int dt, const void *x, void *y, uint8_t *idx, int N, int H, int W, int C, int kh,
-                       int kw, int stride, int pad, hipStream_t s);
+                       int kw, int stride, int pad, hipStream_t s, void *y_nchw = nullptr, bool *stored = nullptr);
 hipError_t maxpool_bwd(int dt, const void *dy, const uint8_t *idx, void *dx, GradEpi epi_pooled_gate, int N,
                        int H, int W, int C, int kh, int kw, int stride, int pad, hipStream_t s);
 // mean over kh x kw windows at stride (kh, kw), no padding; gate (if any) indexed like dx

@@ -567,6 +567,7 @@ struct FwdCtx {
     bool profiling = false;      // layers are timed one at a time: nothing may rely on what the previous layer left behind
     // where the caller wants the last tensor as it is stored here; the kernel that writes that tensor last may store both
     void *y_direct = nullptr;
+    void *y_nchw = nullptr;      // ... or wants it in NCHW
     bool y_stored = false;
 };
 
@@ -622,7 +623,7 @@ int layer_forward(bapipe_stage *st, int li, FwdCtx &c)
         const Tensor &A = st->tensors[L.a];
         const bool tp = st->tap_begin(BAPIPE_KC_POOL);
         HIPCHK(maxpool_fwd(dt, a, o, (uint8_t *)(st->slot(c.mbid) + L.aux_off), st->mb, A.H, A.W, A.C, L.d.kh, L.d.kw,
-                           L.d.stride, L.d.pad, s));
+                           L.d.stride, L.d.pad, s, li + 1 == (int)st->layers.size() ? c.y_nchw : nullptr, &c.y_stored));
         st->tap_end(tp, 0.0, (double)A.bytes() + O.bytes() + O.elems);           // read x, write y + idx
         break;
     }
@@ -687,6 +688,7 @@ struct BwdCtx {
     const void *dy_direct;         // caller's NHWC gradient used in place of grads[last]
     void *dx_direct;               // caller's NHWC buffer used in place of grads[0]
     const int32_t *labels;
+    const void *dy_nchw = nullptr;       // caller's NCHW gradient, read where it lies by the max-pool that is the last layer
     std::vector<char> written;
     std::vector<const void *> pending;   // per tensor: an ADD's share of its gradient that the tensor's conv will add (fanout_conv)
     bool profiling = false;        // profiler: run every kernel of the layer now (no deferral)
@@ -828,8 +830,13 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
         if (a_grad) {
             GradEpi e = epi_for(st, L.a, c, L.o);
             const bool tp = st->tap_begin(BAPIPE_KC_POOL);
-            HIPCHK(maxpool_bwd(dt, grad_ptr(st, L.o, c), (const uint8_t *)(st->slot(c.mbid) + L.aux_off),
-                               grad_ptr(st, L.a, c), e, st->mb, A.H, A.W, A.C, L.d.kh, L.d.kw, L.d.stride, L.d.pad, s));
+            const uint8_t *idx = (const uint8_t *)(st->slot(c.mbid) + L.aux_off);
+            if (c.dy_nchw)
+                HIPCHK(maxpool2x2_bwd(dt, c.dy_nchw, idx, grad_ptr(st, L.a, c), e, st->mb, A.H, A.W, A.C, s, true));
+            else
+                HIPCHK(maxpool_bwd(dt, grad_ptr(st, L.o, c), idx, grad_ptr(st, L.a, c), e, st->mb, A.H, A.W, A.C, L.d.kh, L.d.kw,
+                                   L.d.stride, L.d.pad, s));
+            c.dy_nchw = nullptr;
             st->tap_end(tp, 0.0, (double)O.bytes() + O.elems + A.bytes() + (e.gate ? O.bytes() : 0));
         }
         break;
@@ -1506,6 +1513,7 @@ int bapipe_stage_forward(bapipe_stage_t *st, int mb_id, const void *x_dev, void 
     const uintptr_t x0 = (uintptr_t)c.x_direct, y0 = (uintptr_t)y_dev;
     const bool overlap = c.x_direct && y_dev && y0 < x0 + In.bytes() && x0 < y0 + O.bytes();
     if (!relayout && !overlap) c.y_direct = y_dev;
+    if (relayout && !c.x_direct && R.Cp == R.C) c.y_nchw = y_dev;
     for (int i = 0; i < (int)st->layers.size(); ++i) {
         int rc = layer_forward(st, i, c);
         if (rc != BAPIPE_OK) return rc;
@@ -1557,7 +1565,15 @@ int bapipe_stage_backward(bapipe_stage_t *st, int mb_id, const void *dy_dev_or_l
         GradEpi e{nullptr, 0};
         if (st->tensors[r].gated) e.gate = st->tptr(r, mb_id);
         const bool flat_of_spatial = r != last && R.H * R.W > 1;      // dy arrives indexed c*H*W + h*W + w
-        if ((!nhwc && R.H * R.W > 1) || flat_of_spatial) {
+        const Layer &P = st->layers[nl - 1];
+        const Tensor &PA = st->tensors[P.a];
+        const bool pooled = P.d.kind == BAPIPE_MAXPOOL2D && P.d.kh == 2 && P.d.kw == 2 && P.d.stride == 2 && P.d.pad == 0 && !e.gate &&
+                            st->tensors[PA.root].need_grad && R.H * R.W > 1;
+        if (!nhwc && pooled && maxpool2x2_bwd_takes_nchw(dt, dy_dev_or_labels, (const uint8_t *)(st->slot(mb_id) + P.aux_off),
+                                                         grad_ptr(st, P.a, c), st->tensors[PA.root].gated ? st->tptr(P.o, mb_id) : nullptr, st->mb,
+                                                         PA.H, PA.W, PA.C)) {
+            c.dy_nchw = dy_dev_or_labels;
+        } else if ((!nhwc && R.H * R.W > 1) || flat_of_spatial) {
             HIPCHK(nchw_to_nhwc(dt, dy_dev_or_labels, st->gptr(last), e, st->mb, R.C, R.H, R.W, R.Cp, s));
         } else if (e.gate || r == 0) {
             HIPCHK(grad_copy(dt, dy_dev_or_labels, st->gptr(last), e, O.elems, s));

@@ -694,6 +694,23 @@ def test_direct_bias_gradient_of_wide_layers(dtype, k, cin, cout, hw, mb):
 
 # ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("c,hw,mb", [
+    (64, (16, 16), 3),       # whole tiles of 64 channels and of positions
+    (72, (15, 9), 2),        # a second tile of 8 channels, the last row and column in no window
+    (8, (2, 3), 1), (136, (33, 2), 2), (16, (32, 32), 4),
+    (12, (7, 10), 3),        # bf16: channels that no 16-byte access holds, launches of their own
+])
+def test_pool_at_the_end_of_a_stage_in_either_layout(dtype, relu, c, hw, mb):
+    """The pooled tensor leaves, and its gradient comes, in the layout of the boundary."""
+    st = single(lambda b: (b.conv(c, c, 1, relu=relu, src=-1), b.pool()), c, hw, dtype, micro_batch=mb)
+    compare_minibatch(st, verbose="pool at the end c%d %s x %d" % (c, hw, mb), layout=B.NCHW)
+    a, b = gpu_minibatch(st, layout=B.NCHW), gpu_minibatch(st, layout=B.NHWC)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("k,c,hw", [(1, 8, (3, 4)), (2, 24, (7, 4)), (3, 5, (10, 9)), (5, 16, (5, 11)), (6, 8, (13, 6))])
 def test_avgpool_windows(dtype, k, c, hw):
     st = single(lambda b: b.avgpool(k, src=-1), c, hw, dtype)
