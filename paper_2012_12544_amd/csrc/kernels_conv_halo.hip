@@ -553,6 +553,10 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
 // stages) and the nine taps read shifted views of the same halo through the transposing LDS read,
 // so x is fetched 1.4 times instead of 9.  Units are split over blockIdx.y; partial tiles are
 // reduced by k_wg_halo_reduce in a fixed order.
+// A wave owns 32 x 32 channels of all nine taps, so that one read of a halo row serves three rows of dy: 38 fragments from LDS for the
+// 72 MFMAs of a unit instead of 80 (with the taps dealt out to the waves).  Alone the launch is bound by the way of its units from memory,
+// 121 -> 119 us for 64 channels at 224x224, 67 -> 66 for 64->128 at 112x112; beside convolutions on other streams, whose LDS it shares, the
+// mini-batch of VGG stage 1 is 8770 -> 8620 us.  266 registers a lane: one block to a unit as before, and still room for one of theirs.
 constexpr int UH = 8, UW = 16, UPIX = UH * UW;                 // unit of 8 x 16 pixels
 constexpr int WH_ROWS = UH + 2, WH_COLS = UW + 2, WH_PIX = WH_ROWS * WH_COLS;      // 10 x 18 halo = 180 pixels
 constexpr int WG_DY_ELEMS = UPIX * 64;                         // 16 KB
@@ -560,7 +564,7 @@ constexpr int WG_HALO_ELEMS = WH_PIX * 64 + 256;               // 1440 slots + 3
 constexpr int WG_STAGE_ELEMS = WG_DY_ELEMS + WG_HALO_ELEMS;
 constexpr int WG_HL = 6, WG_DL = 4;                            // wave-loads per wave: halo (24 >= 22.5), dy (16)
 
-__global__ __launch_bounds__(256, 2) void k_wgrad3x3_halo(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy,
+__global__ __launch_bounds__(256, 1) void k_wgrad3x3_halo(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy,
                                                           float *__restrict__ part, int N, int H, int W, int C,
                                                           int K, int units_per_split, unsigned x_bytes,
                                                           unsigned dy_bytes, int with_bias)
@@ -574,7 +578,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad3x3_halo(const bf16_t *__restri
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wk = wave & 1, wn = wave >> 1;                   // 32 output channels x 9 column tiles per wave
+    const int wk = wave & 1, wn = wave >> 1;                   // 32 output channels x 32 input channels x 9 taps per wave
     const int cslices = C / 64;
     // The (output-channel, input-channel) tiles of one split read the same dy rows and x halos: number the
     // blocks so that they run on the same XCD (one L2) at the same time - consecutive block ids go round the
@@ -668,44 +672,75 @@ __global__ __launch_bounds__(256, 2) void k_wgrad3x3_halo(const bf16_t *__restri
         return __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     const int offA = frag_off(wk * 32, 0);
-    int offB[9][2];
+    int offB[3][2];                                                // of x, filter column and parity of the halo row
 #pragma unroll
-    for (int b = 0; b < 9; ++b) {
-        const int ct = wn * 9 + b, tap = ct >> 1;
-        const int r = tap / 3, q = tap - r * 3;
-        offB[b][0] = WG_DY_ELEMS + frag_off((ct & 1) * 32, r * WH_COLS + q);
-        offB[b][1] = WG_DY_ELEMS + frag_off((ct & 1) * 32, (r + 1) * WH_COLS + q);
+    for (int q = 0; q < 3; ++q) {
+        offB[q][0] = WG_DY_ELEMS + frag_off(wn * 32, q);
+        offB[q][1] = WG_DY_ELEMS + frag_off(wn * 32, WH_COLS + q);
     }
 
-    // Main loop.  One unit = 8 pixel rows x 9 column tiles = 72 MFMAs per wave, fully unrolled; the
-    // x fragment of MFMA j+2 and the dy fragment of the next row are requested before MFMA j is
-    // issued (sched_barrier keeps that order), so the LDS latency hides behind two MFMAs.
+    // Main loop.  One unit = ten halo rows of x, each of which meets up to three rows of dy: 72 MFMAs per wave, fully unrolled.
+    // A row's three x fragments (filter columns) serve its nine MFMAs and are requested two rows ahead, as is the row of dy that
+    // joins (sched_barrier keeps that order).  The barrier that publishes the next unit sits two rows before the end, when every
+    // wave holds all that is left of this one in registers: its stage is refilled at once, and the next unit's first two rows are
+    // read behind the last MFMAs.  An accumulator meets the rows of dy in their order.
+    typedef bf16x8_t frags3[3];
+    auto ld_x = [&](const uint16_t *sd, int row, frags3 &to) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) to[q] = frag_at(sd + offB[q][row & 1] + (row & ~1) * WH_COLS * 64);
+    };
+    auto ld_g = [&](const uint16_t *sd, int y) { return frag_at(sd + offA + y * 16 * 64); };
     issue_unit(u0, 0);
+    issue_unit(u0 + 1, 1);
+    WAIT_VMCNT(WG_DL + WG_HL);
     WAIT_LGKMCNT(0);           // no scalar load pending at loop entry (else every LDS wait becomes a full drain)
+    __builtin_amdgcn_s_barrier();
+    frags3 x0, x1;             // rows 0 and 1 of the unit to come
+    bf16x8_t g0, g1;
+    ld_x(stage0, 0, x0);
+    g0 = ld_g(stage0, 0);
+    ld_x(stage0, 1, x1);
+    g1 = ld_g(stage0, 1);
     for (int u = u0; u < u1; ++u) {
         const int st = (u - u0) & 1;
-        WAIT_VMCNT(0);
-        __builtin_amdgcn_s_barrier();
-        issue_unit(u + 1, st ^ 1);
-        const uint16_t *sd = stage0 + st * WG_STAGE_ELEMS;
-        auto ld_b = [&](int j) {                                   // x fragment of MFMA j = (row j/9, tile j%9)
-            const int y = j / 9, bb = j % 9;
-            return frag_at(sd + offB[bb][y & 1] + (y & ~1) * WH_COLS * 64);
-        };
-        bf16x8_t fa_cur = frag_at(sd + offA), fa_nxt = fa_cur;
-        bf16x8_t fbq[3];
-        fbq[0] = ld_b(0);
-        fbq[1] = ld_b(1);
+        const uint16_t *sd = stage0 + st * WG_STAGE_ELEMS, *sn = stage0 + (st ^ 1) * WG_STAGE_ELEMS;
+        frags3 xf[UH + 2];
+        bf16x8_t gf[UH];
 #pragma unroll
-        for (int j = 0; j < UH * 9; ++j) {
-            const int y = j / 9, bb = j % 9;
-            if (j + 2 < UH * 9) fbq[(j + 2) % 3] = ld_b(j + 2);
-            if (bb == 4 && y + 1 < UH) fa_nxt = frag_at(sd + offA + (y + 1) * 16 * 64);
+        for (int q = 0; q < 3; ++q) {
+            xf[0][q] = x0[q];
+            xf[1][q] = x1[q];
+        }
+        gf[0] = g0;
+        gf[1] = g1;
+#pragma unroll
+        for (int row = 0; row < UH + 2; ++row) {
+            if (row + 2 < UH + 2) {
+                ld_x(sd, row + 2, xf[row + 2]);
+                if (row + 2 < UH) gf[row + 2] = ld_g(sd, row + 2);
+            } else if (row == UH) {
+                WAIT_LGKMCNT(0);
+                WAIT_VMCNT(0);
+                __builtin_amdgcn_s_barrier();
+                ld_x(sn, 0, x0);
+                g0 = ld_g(sn, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_unit(u + 2, st);
+            } else {
+                ld_x(sn, 1, x1);
+                g1 = ld_g(sn, 1);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if (bb == 0 && do_bias) bsum = frag_sum(fa_cur, bsum);
-            acc[bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_cur, fbq[j % 3], acc[bb], 0, 0, 0);
+            if (row < UH && do_bias) bsum = frag_sum(gf[row], bsum);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const int y = row - r;
+                if (y < 0 || y >= UH) continue;
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    acc[3 * r + q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf[y], xf[row][q], acc[3 * r + q], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if (bb == 8) fa_cur = fa_nxt;
         }
     }
     WAIT_VMCNT(0);
@@ -721,12 +756,11 @@ __global__ __launch_bounds__(256, 2) void k_wgrad3x3_halo(const bf16_t *__restri
     }
 #pragma unroll
     for (int b = 0; b < 9; ++b) {
-        const int ct = wn * 9 + b, tap = ct >> 1;
-        const int c = ci0 + (ct & 1) * 32 + col;
+        const int c = ci0 + wn * 32 + col;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int ko = ko0 + wk * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-            dst[((size_t)ko * 9 + tap) * C + c] = acc[b][v];
+            dst[((size_t)ko * 9 + b) * C + c] = acc[b][v];
         }
     }
 }
