@@ -197,12 +197,17 @@ hipError_t xent_bwd(int dt, const float *p, const int32_t *labels, float scale, 
                     int rows, int K, hipStream_t s);
 
 // ---- parameters
-// w <- w - lr*g ; g <- 0
-hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s);
-// the same for a weight matrix [K][R][S][C] with its working copy and transposed copy (see recast and
-// make_dgrad_filter), and for its bias b / db [K] (may be NULL)
-hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
-                      float *db, hipStream_t s, bool work_panels = false, bool wt_panels = false);
+// w <- w - lr*g ; g <- 0 of a plain vector (K = 0, C elements), or of a weight matrix [K][RS][C] with its working copy and transposed
+// copy (see recast and make_dgrad_filter), and of its bias b / db [K] (may be NULL)
+struct SgdJob {
+    float *w, *g;
+    void *work, *wt;
+    float *b, *db;
+    int K, RS, C;
+    bool work_panels, wt_panels;
+};
+// the updates of a stage, small ones together
+hipError_t sgd_update(int dt, const SgdJob *jobs, int n, float lr, hipStream_t s);
 // panels_of: columns of the matrix whose copy is kept in panels (GatherConv::wt_panels), 0: as it is
 hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s, int panels_of = 0);
 // wt[c][R-1-r][S-1-s][k] = work(w[k][r][s][c])   (dgrad filter)

@@ -5,6 +5,7 @@
 // groups, which keeps every wavefront's HBM access contiguous.
 #include "dev_common.h"
 #include "kernels.h"
+#include <type_traits>
 
 namespace bapipe {
 namespace {
@@ -1372,14 +1373,12 @@ __device__ __forceinline__ size_t panel_at(int row, int col, int rows) { return 
 // again VGG-16's first linear layer took 310 + 193 us, 400 us here; for a convolution layer it is one launch of a few
 // microseconds instead of three.
 template <class T, int V>
-__global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work,
-                                                    T *__restrict__ wt, int K, int R, int S, int C, float *__restrict__ b,
-                                                    float *__restrict__ db, bool work_panels, bool wt_panels)
+__device__ __forceinline__ void sgd_tile(float (&tile)[64][65], float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work, T *__restrict__ wt, int K,
+                                         int RS, int C, float *__restrict__ b, float *__restrict__ db, bool work_panels, bool wt_panels, int bx,
+                                         int by, int tap)
 {
     constexpr int LANES = 64 / V, ROWS = TPB / LANES, TRIPS = 64 / ROWS;
-    __shared__ float tile[64][65];
-    const int c0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
-    const int tap = blockIdx.z, RS = R * S, tap_t = RS - 1 - tap;
+    const int c0 = bx * 64, k0 = by * 64, tap_t = RS - 1 - tap;
     const int tx = threadIdx.x % LANES, ty = threadIdx.x / LANES;
     vec_t<float, V> wv[TRIPS], gv[TRIPS];
 #pragma unroll
@@ -1409,7 +1408,7 @@ __global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float
             *reinterpret_cast<vec_t<T, V> *>(work + (work_panels ? panel_at(k, c, K) : at)) = o;
         }
     }
-    if (b && blockIdx.x == 0 && tap == 0 && threadIdx.x < 64 && k0 + (int)threadIdx.x < K) {
+    if (b && bx == 0 && tap == 0 && threadIdx.x < 64 && k0 + (int)threadIdx.x < K) {
         const int k = k0 + threadIdx.x;
         b[k] -= lr * db[k];
         db[k] = 0.0f;
@@ -1425,6 +1424,51 @@ __global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float
             *reinterpret_cast<vec_t<T, V> *>(wt + (wt_panels ? panel_at(c, k, C) : ((size_t)c * RS + tap_t) * K + k)) = o;
         }
     }
+}
+
+template <class T, int V>
+__global__ __launch_bounds__(TPB) void k_sgd_matrix(float *__restrict__ w, float *__restrict__ g, float lr, T *__restrict__ work,
+                                                    T *__restrict__ wt, int K, int RS, int C, float *__restrict__ b,
+                                                    float *__restrict__ db, bool work_panels, bool wt_panels)
+{
+    __shared__ float tile[64][65];
+    sgd_tile<T, V>(tile, w, g, lr, work, wt, K, RS, C, b, db, work_panels, wt_panels, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// The updates of a stage's small layers in one launch: matrices (64 x 64 tiles of a tap as above) and plain vectors (K = 0, C elements).
+// One by one each was 2 to 6 us and the gap in front of it, nine of them for a bottleneck.
+constexpr int SGD_GROUP = 16;
+struct sgd_args {
+    SgdJob job;
+    unsigned blocks;
+    bool vec;
+};
+struct sgd_group {
+    sgd_args a[SGD_GROUP];
+    int n;
+};
+template <class T> __global__ __launch_bounds__(TPB) void k_sgd_group(sgd_group in, float lr)
+{
+    __shared__ float tile[64][65];
+    unsigned id = blockIdx.x;
+    int i = 0;
+    while (i + 1 < in.n && id >= in.a[i].blocks) id -= in.a[i++].blocks;
+    const SgdJob &j = in.a[i].job;
+    if (j.K == 0) {
+        const int at = (int)id * TPB + (int)threadIdx.x;
+        if (at < j.C) {
+            j.w[at] -= lr * j.g[at];
+            j.g[at] = 0.0f;
+        }
+        return;
+    }
+    const int tiles_c = (j.C + 63) / 64, tiles_k = (j.K + 63) / 64, t = (int)id / tiles_c;
+    auto run = [&](auto width) {
+        sgd_tile<T, decltype(width)::value>(tile, j.w, j.g, lr, (T *)j.work, (T *)j.wt, j.K, j.RS, j.C, j.b, j.db, j.work_panels, j.wt_panels,
+                                            (int)id % tiles_c, t % tiles_k, t / tiles_k);
+    };
+    if (in.a[i].vec) run(std::integral_constant<int, 4>());
+    else run(std::integral_constant<int, 1>());
 }
 
 // C > 0: the matrix has rows of C elements and its copy is kept in panels
@@ -1975,29 +2019,63 @@ hipError_t xent_bwd(int dt, const float *p, const int32_t *labels, float scale, 
     return hipGetLastError();
 }
 
-hipError_t sgd_step(float *w, float *g, float lr, size_t n, hipStream_t s)
+static bool sgd_vec(int dt, const SgdJob &j)
 {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sgd, dim3(blocks_for(n)), dim3(TPB), 0, s, w, g, lr, n);
+    // four values per access where rows of both copies and their starts allow it
+    const size_t es = dt_size(dt);
+    return j.C % 4 == 0 && j.K % 4 == 0 && aligned16(j.w) && aligned16(j.g) && (uintptr_t)j.work % (4 * es) == 0 && (uintptr_t)j.wt % (4 * es) == 0;
+}
+
+static hipError_t sgd_alone(int dt, const SgdJob &j, float lr, hipStream_t s)
+{
+    if (j.K == 0) {
+        hipLaunchKernelGGL(k_sgd, dim3(blocks_for(j.C)), dim3(TPB), 0, s, j.w, j.g, lr, (size_t)j.C);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((j.C + 63) / 64), (unsigned)((j.K + 63) / 64), (unsigned)j.RS);
+    DISPATCH_T(dt, {
+        if (sgd_vec(dt, j))
+            hipLaunchKernelGGL((k_sgd_matrix<T, 4>), grid, dim3(TPB), 0, s, j.w, j.g, lr, (T *)j.work, (T *)j.wt, j.K, j.RS, j.C, j.b, j.db,
+                               j.work_panels, j.wt_panels);
+        else
+            hipLaunchKernelGGL((k_sgd_matrix<T, 1>), grid, dim3(TPB), 0, s, j.w, j.g, lr, (T *)j.work, (T *)j.wt, j.K, j.RS, j.C, j.b, j.db,
+                               j.work_panels, j.wt_panels);
+    });
     return hipGetLastError();
 }
 
-hipError_t sgd_matrix(int dt, float *w, float *g, float lr, void *work, void *wt, int K, int R, int S, int C, float *b,
-                      float *db, hipStream_t s, bool work_panels, bool wt_panels)
+hipError_t sgd_update(int dt, const SgdJob *jobs, int n, float lr, hipStream_t s)
 {
-    if ((size_t)K * R * S * C == 0) return hipSuccess;
-    if ((work_panels && (R * S != 1 || C % 32)) || (wt_panels && (R * S != 1 || K % 32))) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((C + 63) / 64), (unsigned)((K + 63) / 64), (unsigned)(R * S));
-    const size_t es = dt_size(dt);
-    // four values per access where rows of both copies and their starts allow it
-    const bool vec = C % 4 == 0 && K % 4 == 0 && aligned16(w) && aligned16(g) && (uintptr_t)work % (4 * es) == 0 && (uintptr_t)wt % (4 * es) == 0;
-    DISPATCH_T(dt, {
-        if (vec)
-            hipLaunchKernelGGL((k_sgd_matrix<T, 4>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db, work_panels, wt_panels);
-        else
-            hipLaunchKernelGGL((k_sgd_matrix<T, 1>), grid, dim3(TPB), 0, s, w, g, lr, (T *)work, (T *)wt, K, R, S, C, b, db, work_panels, wt_panels);
-    });
-    return hipGetLastError();
+    sgd_group group;
+    group.n = 0;
+    unsigned blocks = 0;
+    hipError_t e = hipSuccess;
+    auto flush = [&]() {
+        if (group.n == 1) e = sgd_alone(dt, group.a[0].job, lr, s);
+        else if (group.n > 1) {
+            DISPATCH_T(dt, { hipLaunchKernelGGL((k_sgd_group<T>), dim3(blocks), dim3(TPB), 0, s, group, lr); });
+            e = hipGetLastError();
+        }
+        group.n = 0;
+        blocks = 0;
+        return e;
+    };
+    for (int i = 0; i < n; ++i) {
+        const SgdJob &j = jobs[i];
+        if ((j.work_panels && (j.RS != 1 || j.C % 32)) || (j.wt_panels && (j.RS != 1 || j.K % 32))) return hipErrorInvalidValue;
+        const size_t own = j.K == 0 ? ((size_t)j.C + TPB - 1) / TPB : (size_t)((j.C + 63) / 64) * ((j.K + 63) / 64) * j.RS;
+        if (own == 0) continue;
+        // Two rounds of the chip are no launch's length: a larger matrix gains nothing by company (two LSTM layers of 1024, four matrices of
+        // 1024 tiles, 6200 us a mini-batch by themselves, 6234 together)
+        if (own > 512) {
+            if ((e = sgd_alone(dt, j, lr, s)) != hipSuccess) return e;
+            continue;
+        }
+        group.a[group.n++] = sgd_args{j, (unsigned)own, j.K && sgd_vec(dt, j)};
+        blocks += (unsigned)own;
+        if (group.n == SGD_GROUP && flush() != hipSuccess) return e;
+    }
+    return flush();
 }
 
 hipError_t recast(int dt, const float *w, void *work, size_t n, hipStream_t s, int panels_of)

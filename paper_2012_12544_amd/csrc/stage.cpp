@@ -410,23 +410,23 @@ hipError_t refresh_transposed(bapipe_stage *st, Layer &L)
 }
 
 // weights, bias and working copies of one layer after a mini-batch
-hipError_t update_layer(bapipe_stage *st, Layer &L, float lr)
+void update_jobs(const bapipe_stage *st, const Layer &L, std::vector<SgdJob> &jobs)
 {
     float *b = L.b_elems ? L.bias : nullptr;
-    if (!has_matrix(L.d.kind)) {
-        const hipError_t e = sgd_step(L.w, L.dw, lr, L.w_elems, st->stream);
-        return e != hipSuccess || !b ? e : sgd_step(b, L.db, lr, L.b_elems, st->stream);
+    if (!has_matrix(L.d.kind)) {         // gamma and beta
+        jobs.push_back({L.w, L.dw, nullptr, nullptr, nullptr, nullptr, 0, 1, (int)L.w_elems, false, false});
+        if (b) jobs.push_back({b, L.db, nullptr, nullptr, nullptr, nullptr, 0, 1, (int)L.b_elems, false, false});
+        return;
     }
     if (L.d.kind == BAPIPE_LSTM) {       // the input block [4H][In], then the recurrent block [4H][H]
         const int In = L.d.cin, H = L.d.cout, G = 4 * H;
         const size_t at = (size_t)G * In, es = dt_size(st->dt);
-        const hipError_t e = sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, G, 1, 1, In, b, L.db, st->stream);
-        if (e != hipSuccess) return e;
-        return sgd_matrix(st->dt, L.w + at, L.dw + at, lr, (char *)L.w_work + at * es, (char *)L.w_t + at * es, G, 1, 1, H,
-                          nullptr, nullptr, st->stream);
+        jobs.push_back({L.w, L.dw, L.w_work, L.w_t, b, L.db, G, 1, In, false, false});
+        jobs.push_back({L.w + at, L.dw + at, (char *)L.w_work + at * es, (char *)L.w_t + at * es, nullptr, nullptr, G, 1, H, false, false});
+        return;
     }
-    const int R = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kh, S = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kw;
-    return sgd_matrix(st->dt, L.w, L.dw, lr, L.w_work, L.w_t, L.d.cout, R, S, L.cin_p, b, L.db, st->stream, L.w_panels, L.wt_panels);
+    const int RS = L.d.kind == BAPIPE_LINEAR ? 1 : L.d.kh * L.d.kw;
+    jobs.push_back({L.w, L.dw, L.w_work, L.w_t, b, L.db, L.d.cout, RS, L.cin_p, L.w_panels, L.wt_panels});
 }
 
 hipError_t refresh_work(bapipe_stage *st, Layer &L)
@@ -1685,10 +1685,10 @@ int bapipe_stage_step(bapipe_stage_t *st, float lr)
         int rc = flush_deferred(st);
         if (rc != BAPIPE_OK) return rc;
     }
-    for (auto &L : st->layers) {
-        if (!L.w_elems) continue;
-        HIPCHK(update_layer(st, L, lr));
-    }
+    std::vector<SgdJob> jobs;
+    for (const auto &L : st->layers)
+        if (L.w_elems) update_jobs(st, L, jobs);
+    HIPCHK(sgd_update(st->dt, jobs.data(), (int)jobs.size(), lr, st->stream));
     st->n_fwd = st->n_bwd = 0;
     st->flushed = 0;
     return BAPIPE_OK;
