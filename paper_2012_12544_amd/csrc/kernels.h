@@ -114,6 +114,9 @@ struct WgradJob {
     const void *x2 = nullptr;
     float *dw2 = nullptr;
 };
+// the same for small float layers with a bias, for which the first function says yes
+bool conv_wgrad_direct_groups(const ConvShape &c);
+hipError_t conv_wgrad_direct_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s);
 bool conv_wgrad_mfma_groups(const ConvShape &c);      // whether it fills so little of the chip that it should wait for others
 hipError_t conv_wgrad_mfma_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s, bool beside);
 

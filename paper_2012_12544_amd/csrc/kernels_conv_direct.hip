@@ -178,13 +178,13 @@ __global__ __launch_bounds__(TPB) void k_conv_tile(const float *__restrict__ in,
 // in float and the eights in double (against 64 bits, normal gradients: 5.9e-8 there, 3.7e-7 one by one in float, 8.5e-8 by
 // column sums; all of it in double the smallest stage's mini-batch takes 229 us instead of 218).
 template <class T>
-__global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restrict__ dy,
-                                     float *__restrict__ part, ConvShape c, int rows_per_chunk, int bias)
+__device__ __forceinline__ void wgrad_partial(const T *__restrict__ x, const T *__restrict__ dy, float *__restrict__ part, const ConvShape &c,
+                                              int rows_per_chunk, int bias, int bx, int chunk)
 {
-    size_t i = (size_t)blockIdx.x * TPB + threadIdx.x;
+    size_t i = (size_t)bx * TPB + threadIdx.x;
     const size_t weights = (size_t)c.K * c.R * c.S * c.C, total = weights + (bias ? c.K : 0);
     if (i >= total) return;
-    int row0 = blockIdx.y * rows_per_chunk, row1 = row0 + rows_per_chunk;
+    int row0 = chunk * rows_per_chunk, row1 = row0 + rows_per_chunk;
     if (row1 > c.N * c.P) row1 = c.N * c.P;
     float acc = 0.0f;
     if (i >= weights) {
@@ -197,7 +197,7 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
             for (int u = 0; u < 8; ++u) a[u] = p + u < end ? to_f32(d[(p + u) * c.K]) : 0.0f;
             sum += (double)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
         }
-        part[(size_t)blockIdx.y * total + i] = (float)sum;
+        part[(size_t)chunk * total + i] = (float)sum;
         return;
     }
     int ci = (int)(i % c.C);
@@ -231,7 +231,14 @@ __global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restric
                 if (q + u < q1) acc = fmaf(a[u], b[u], acc);
         }
     }
-    part[(size_t)blockIdx.y * total + i] = acc;
+    part[(size_t)chunk * total + i] = acc;
+}
+
+template <class T>
+__global__ void k_conv_wgrad_partial(const T *__restrict__ x, const T *__restrict__ dy,
+                                     float *__restrict__ part, ConvShape c, int rows_per_chunk, int bias)
+{
+    wgrad_partial(x, dy, part, c, rows_per_chunk, bias, blockIdx.x, blockIdx.y);
 }
 
 // The same of few channels, out of LDS.  k_conv_wgrad_partial loads two values per product and is bound by the L1 that they come from.
@@ -313,12 +320,12 @@ __global__ __launch_bounds__(TPB) void k_conv_wgrad_tile(const float *__restrict
 // the chip, one lane takes them all, for lanes without a chunk are not free (backward pass of a 4096 -> 4096 linear layer,
 // one chunk, 3674 -> 3224 us).
 constexpr int RED_LANES = 16;
-template <int LANES> __global__ void k_wgrad_reduce(const float *__restrict__ part, float *dw, float *db,
-                                                      size_t weights, size_t total, int chunks)
+template <int LANES>
+__device__ __forceinline__ void wgrad_reduce(const float *__restrict__ part, float *dw, float *db, size_t weights, size_t total, int chunks, int bx)
 {
     constexpr int EL = TPB / LANES;
     const int el = threadIdx.x % EL, ln = threadIdx.x / EL;
-    const size_t i = (size_t)blockIdx.x * EL + el;
+    const size_t i = (size_t)bx * EL + el;
     double acc = 0.0;
     if (i < total)
         for (int k = ln; k < chunks; k += 8 * LANES) {
@@ -344,6 +351,42 @@ template <int LANES> __global__ void k_wgrad_reduce(const float *__restrict__ pa
             *(i < weights ? dw + i : db + (i - weights)) += (float)t;
         }
     }
+}
+
+template <int LANES> __global__ void k_wgrad_reduce(const float *__restrict__ part, float *dw, float *db,
+                                                      size_t weights, size_t total, int chunks)
+{
+    wgrad_reduce<LANES>(part, dw, db, weights, total, chunks, blockIdx.x);
+}
+
+// Several small layers' in one launch each (one by one they are 4 to 8 us and a gap, twice a layer: smallest stage, two layers, 175 us a
+// mini-batch -> 148): the same sums, the workspace side by side.
+constexpr int DIRECT_GROUP = 8;
+struct direct_args {
+    const float *x, *dy;
+    float *part, *dw, *db;
+    ConvShape c;
+    int rpc, chunks, blocks;                       // rows of a chunk, chunks, blocks of a chunk
+    unsigned weights, total;
+};
+struct direct_group {
+    direct_args a[DIRECT_GROUP];
+    int n;
+};
+__global__ __launch_bounds__(TPB) void k_conv_wgrad_partial_group(direct_group in)
+{
+    int id = blockIdx.x, i = 0;
+    while (i + 1 < in.n && id >= in.a[i].blocks * in.a[i].chunks) { id -= in.a[i].blocks * in.a[i].chunks; ++i; }
+    const direct_args &j = in.a[i];
+    wgrad_partial(j.x, j.dy, j.part, j.c, j.rpc, 1, id % j.blocks, id / j.blocks);
+}
+__device__ __forceinline__ int direct_sums(unsigned total) { return (int)((total + TPB / RED_LANES - 1) / (TPB / RED_LANES)); }
+__global__ __launch_bounds__(TPB) void k_wgrad_reduce_group(direct_group in)
+{
+    int id = blockIdx.x, i = 0;
+    while (i + 1 < in.n && id >= direct_sums(in.a[i].total)) id -= direct_sums(in.a[i++].total);
+    const direct_args &j = in.a[i];
+    wgrad_reduce<RED_LANES>(j.part, j.dw, j.db, j.weights, j.total, j.chunks, id);
 }
 
 constexpr size_t DIRECT_PARTS = (size_t)16 << 20;              // floats of partial sums (64 MiB)
@@ -469,6 +512,59 @@ hipError_t conv_wgrad_direct(int dt, const void *x, const void *dy, float *dw, f
     }
     const hipError_t e = hipGetLastError();
     return db && !along && e == hipSuccess ? colsum_accumulate(dt, dy, c.N * c.P * c.Q, c.K, db, workspace, s) : e;
+}
+
+// Small ones that run on k_conv_wgrad_partial with their bias sums and sixteen lanes to add their chunks
+bool conv_wgrad_direct_groups(const ConvShape &c)
+{
+    const size_t weights = direct_wgrad_weights(c), total = direct_wgrad_elements(c);
+    if (weights == 0 || (long long)c.N * c.P == 0 || total == weights || total > (1u << 20)) return false;
+    int chunks = direct_wgrad_chunks(c);
+    const int rpc = (c.N * c.P + chunks - 1) / chunks;
+    chunks = (c.N * c.P + rpc - 1) / rpc;
+    return chunks > RED_LANES && chunks * ((total + TPB - 1) / TPB) <= 4096 && !wgrad_tile_takes(c, chunks, true);
+}
+
+hipError_t conv_wgrad_direct_jobs(const WgradJob *jobs, int n, void *workspace, size_t workspace_bytes, hipStream_t s)
+{
+    direct_group g;
+    g.n = 0;
+    size_t used = 0;
+    unsigned blocks = 0, sums = 0;
+    auto flush = [&]() {
+        if (g.n > 1) {
+            hipLaunchKernelGGL(k_conv_wgrad_partial_group, dim3(blocks), dim3(TPB), 0, s, g);
+            hipLaunchKernelGGL(k_wgrad_reduce_group, dim3(sums), dim3(TPB), 0, s, g);
+        } else if (g.n) {
+            const direct_args &j = g.a[0];
+            const hipError_t e = conv_wgrad_direct(DT_F32, j.x, j.dy, j.dw, j.db, workspace, j.c, s);
+            if (e != hipSuccess) return e;
+        }
+        g.n = 0;
+        used = 0;
+        blocks = sums = 0;
+        return hipGetLastError();
+    };
+    for (int i = 0; i < n; ++i) {
+        const WgradJob &j = jobs[i];
+        if (!j.db || j.x2 || !conv_wgrad_direct_groups(j.c)) return hipErrorInvalidValue;
+        const size_t own = (conv_wgrad_direct_workspace(j.c) + 255) / 256 * 256;
+        if (g.n == DIRECT_GROUP || (g.n && used + own > workspace_bytes)) {
+            const hipError_t e = flush();
+            if (e != hipSuccess) return e;
+        }
+        direct_args &a = g.a[g.n++];
+        const int want = direct_wgrad_chunks(j.c);
+        a = direct_args{(const float *)j.x, (const float *)j.dy, (float *)((char *)workspace + used), j.dw, j.db, j.c, 0, 0, 0,
+                        (unsigned)direct_wgrad_weights(j.c), (unsigned)direct_wgrad_elements(j.c)};
+        a.rpc = (j.c.N * j.c.P + want - 1) / want;
+        a.chunks = (j.c.N * j.c.P + a.rpc - 1) / a.rpc;
+        a.blocks = (int)((a.total + TPB - 1) / TPB);
+        used += own;
+        blocks += (unsigned)(a.blocks * a.chunks);
+        sums += (a.total + TPB / RED_LANES - 1) / (TPB / RED_LANES);
+    }
+    return flush();
 }
 
 }  // namespace bapipe

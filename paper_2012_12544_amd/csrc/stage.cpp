@@ -741,8 +741,12 @@ int run_waiting_wgrads(bapipe_stage *st, hipStream_t s, char *work)
     }
     st->w_waiting.clear();
     st->w_waiting_us = 0.0;
-    const bool tp = st->tap_begin(BAPIPE_KC_CONV_WGRAD_MFMA, s);
-    HIPCHK(conv_wgrad_mfma_jobs(jobs.data(), (int)jobs.size(), work, st->work_bytes, s, st->stream_b || st->stream_w));
+    const bool direct = st->dt == DT_F32;
+    const bool tp = st->tap_begin(direct ? BAPIPE_KC_CONV_DIRECT : BAPIPE_KC_CONV_WGRAD_MFMA, s);
+    if (direct)
+        HIPCHK(conv_wgrad_direct_jobs(jobs.data(), (int)jobs.size(), work, st->work_bytes, s));
+    else
+        HIPCHK(conv_wgrad_mfma_jobs(jobs.data(), (int)jobs.size(), work, st->work_bytes, s, st->stream_b || st->stream_w));
     st->tap_end(tp, flop, bytes, jobs.size());
     return BAPIPE_OK;
 }
@@ -774,13 +778,13 @@ int layer_backward(bapipe_stage *st, int li, BwdCtx &c)
             // a layer without an input gradient ends the pass's kernel chain: its weight gradient would only delay
             // the end of the pass from the other stream
             const double us = w.flop / kForkFlopPerUs + w.bytes / kForkBytesPerUs;
-            const bool small = us < kGroupUs && L.groups;
+            const bool small = L.groups && (!mf || us < kGroupUs);
             // the caller's dy is read before dx may be stored over it
             const bool now = c.dx_over_dy && g == c.dy_direct;
-            if (mf && !c.profiling && !now && (small || (st->stream_w && a_grad))) {
+            if (!c.profiling && !now && (small || (mf && st->stream_w && a_grad))) {
                 st->w_waiting.push_back(w);
                 st->w_waiting_us += us;
-                if (st->stream_w && a_grad && st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
+                if (mf && st->stream_w && a_grad && st->w_waiting_us >= kForkUs) {    // what waits is complete on the backward stream at this point
                     HIPCHK(hipEventRecord(st->ev_g, s));
                     HIPCHK(hipStreamWaitEvent(st->stream_w, st->ev_g, 0));
                     st->w_used = true;
@@ -1379,7 +1383,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             }
             size_t w = use_mfma_wgrad(st, cs) ? conv_wgrad_mfma_workspace(cs) : conv_wgrad_direct_workspace(cs);
             work = w > work ? w : work;
-            L.groups = use_mfma_wgrad(st, cs) && !L.deferred && conv_wgrad_mfma_groups(cs);
+            L.groups = use_mfma_wgrad(st, cs) ? !L.deferred && conv_wgrad_mfma_groups(cs) : st->dt == DT_F32 && L.b_elems > 0 && conv_wgrad_direct_groups(cs);
             if (L.groups) grouped += align_up(w);
             w = colsum_workspace(cs.N * cs.P * cs.Q, cs.K);
             work = w > work ? w : work;

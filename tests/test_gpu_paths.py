@@ -247,6 +247,20 @@ def test_tap_counts_every_weight_gradient(streams):
 
 
 # ------------------------------------------------------------------------------ input gradient of a strided convolution
+def test_direct_weight_gradients_that_share_launches():
+    """More float layers of a pass than a launch takes, of different shapes, in one order of streams and in another."""
+    def build(b):
+        b.conv(5, 8, 3, relu=1, src=-1)
+        for k in (1, 3, 5, 3, 1, 3, 3, 1, 3):
+            b.conv(8, 8, k, relu=1)
+        b.conv(8, 3, 3, stride=2)
+    st = single(build, 5, (9, 11), C.FP32, micro_batch=3, n_micro=3)
+    compare_minibatch(st, verbose="shared direct weight gradients")
+    a, b = gpu_minibatch(st), gpu_minibatch(st, backward_stream=True, wgrad_stream=True)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+
+
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 2, 1, 64, 32, (21, 19), 3),      # classes of unequal size, one K-tile a tap
     (3, 2, 1, 72, 64, (8, 7), 2),        # a ragged channel tile
