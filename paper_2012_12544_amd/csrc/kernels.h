@@ -17,7 +17,9 @@ inline size_t dt_size(int dt) { return dt == DT_F32 ? 4 : 2; }
 //   forward conv : in = x,  s_out = stride, s_in = 1,      pad = pad,       wt = w [K][R][S][C]
 //   dgrad        : in = dy, s_out = 1,      s_in = stride, pad = R-1-pad,   wt = flipped,
 //                  channel-transposed copy [C][R][S][K]
-struct GatherConv {
+// GatherGeom is what k_gather_mfma is handed: a member more moves the arguments behind it off their 16-byte places, 0.2 % of a mini-batch of
+// two LSTM layers.
+struct GatherGeom {
     int N, Hi, Wi, Ci, Ho, Wo, Co, R, S, s_out, s_in, pad_h, pad_w;
     // Kernels of other streams run beside this launch.  Alone on the chip a launch wants every compute unit busy; beside others,
     // units it leaves idle are not lost, and fewer, larger blocks (less operand traffic per FLOP) are the better neighbour.
@@ -25,6 +27,8 @@ struct GatherConv {
     int beside = 0;
     // The output is the input of a batch-norm, or the gradient of one's output: kernels that leave it the sums it needs are preferred.
     int by_norm = 0;
+};
+struct GatherConv : GatherGeom {
     // wt is kept in panels of 32 columns, [Ci / 32][Co][32] (1x1 filters, Ci a multiple of 32): neighbouring rows of a K-tile are one
     // piece of memory.  No plan depends on it.
     int wt_panels = 0;

@@ -56,7 +56,7 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool PANELS = false>
 __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
-    bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherConv g,
+    bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherGeom g,
     int tiles_c, unsigned in_bytes, unsigned wt_bytes, float *__restrict__ part, int kt_per_split, int part_tiles,
     float *__restrict__ stat_part, const bf16_t *__restrict__ bn_x, const float *__restrict__ bn_stats,
     const bf16_t *old_from, unsigned *tickets)
@@ -890,7 +890,7 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
             attr_set = true;                                                                                      \
         }                                                                                                         \
         hipLaunchKernelGGL(kfn, grid, dim3(NT), smem, s, (const bf16_t *)in, (const bf16_t *)wt, bias,          \
-                           (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, g, tiles_c, in_bytes, \
+                           (bf16_t *)out, (const bf16_t *)epi.gate, epi.accum, relu, is_grad, (GatherGeom)g, tiles_c, in_bytes, \
                            wt_bytes, part, plan.kt_per_split, plan.part_tiles, stat_part, (const bf16_t *)bn_x, bn_stats,         \
                            (const bf16_t *)epi.accum_from, tickets);                                             \
     } while (0)
