@@ -787,7 +787,7 @@ GatherPlan gather_plan(const GatherConv &g)
     const bool large = 2.0 * g.Co * K > 40e6, k64 = g.Ci % 64 == 0 && g.R * g.S <= 32;
     // Few rows of a linear layer: four blocks share a tile's K and the last one adds (4096->4096, 64 rows, 256 blocks: 14.4 us, one launch
     // of 32 x 32 15.1; 2048->2048, of whose K four blocks would take 512 each, 11 and 7.8)
-    const bool flat = g.Hi == 1 && g.Wi == 1 && g.R * g.S == 1 && !g.by_norm && 2.0 * g.Co * K > 30e6;
+    const bool flat = g.s_in == 1 && g.Hi == 1 && g.Wi == 1 && g.R * g.S == 1 && !g.by_norm && 2.0 * g.Co * K > 30e6;
     p.kg = 1;
     if (flat && npix > 32 && npix <= 64 && k64 && count(64, 64) <= 128) {
         p.kg = 2;
@@ -865,6 +865,8 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     constexpr size_t epi_bytes = (KG > 1 ? (size_t)KG * BP * (BC + 4) * 4 : 0) + (size_t)BP * (BC + 4) * 2 + NT * 8;
     constexpr size_t smem_flat = (main_bytes > epi_bytes ? main_bytes : epi_bytes) + BC * sizeof(float) + sizeof(int);
     const bool phased = plan.classes > 1;
+    // Of a kernel that does not look at the grid's z axis every class would store all tiles
+    if (phased && (KG > 1 || (BK == 64 && BP != 64))) return hipErrorInvalidValue;
     constexpr size_t smem_phased = smem_flat + BP * sizeof(int);
     const size_t smem = phased ? smem_phased : smem_flat;
     static_assert(smem_phased <= (NT >= 512 || STAGES > 4 ? 160 : 80) * 1024, "two blocks of 4 waves (one of 8, or with a deep ring) must fit the 160 KB LDS of a CU");

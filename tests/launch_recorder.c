@@ -1,17 +1,18 @@
 /* Stands in for the parts of the HIP runtime that launching a kernel needs, on a machine without a GPU: nothing runs, and the
- * argument of every split-K reduction, which says where its product's partial sums lie, is kept. */
+ * argument of every split-K reduction, which says where its product's partial sums lie, is kept, as are name and grid of every launch. */
 #include <stddef.h>
 #include <string.h>
 
 typedef struct { unsigned x, y, z; } dim3;
 typedef struct { const void *part; void *dw, *db; size_t total_w, total; int splits, blocks; } splitk_args;
 
-enum { GROUP = 6, KERNELS = 1024, RECORDS = 4096 };
+enum { GROUP = 6, KERNELS = 1024, RECORDS = 4096, LAUNCHES = 65536 };
 
 static struct { const void *host; const char *name; } kernels[KERNELS];
 static int n_kernels;
 static struct { dim3 grid, block; size_t lds; void *stream; } config;
 static splitk_args records[RECORDS];
+static struct { const char *name; dim3 grid; } launches[LAUNCHES];
 static int n_records, n_launches;
 static void *handle;
 
@@ -37,10 +38,15 @@ int hipGetLastError(void) { return 0; }
 int hipFuncSetAttribute(const void *f, int attr, int value) { (void)f; (void)attr; (void)value; return 0; }
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream)
 {
-    (void)grid; (void)block; (void)lds; (void)stream;
+    (void)block; (void)lds; (void)stream;
+    const int at = n_launches < LAUNCHES ? n_launches : LAUNCHES - 1;
+    launches[at].name = "?";
+    launches[at].grid = grid;
     n_launches++;
     for (int k = 0; k < n_kernels; ++k) {
-        if (kernels[k].host != f || !strstr(kernels[k].name, "k_splitk_reduce")) continue;
+        if (kernels[k].host != f) continue;
+        launches[at].name = kernels[k].name;
+        if (!strstr(kernels[k].name, "k_splitk_reduce")) continue;
         const splitk_args *a = args[0];                     /* one of them, or GROUP and how many they are */
         int n = 1;
         if (strstr(kernels[k].name, "Group")) memcpy(&n, a + GROUP, sizeof n);
@@ -51,6 +57,11 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t ld
 
 void recorder_clear(void) { n_records = n_launches = 0; }
 int recorder_launches(void) { return n_launches; }
+const char *recorder_launch(int i, unsigned *grid)
+{
+    grid[0] = launches[i].grid.x; grid[1] = launches[i].grid.y; grid[2] = launches[i].grid.z;
+    return launches[i].name;
+}
 int recorder_count(void) { return n_records; }
 void recorder_get(int i, size_t *first, size_t *bytes)
 {

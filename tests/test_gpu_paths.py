@@ -406,6 +406,13 @@ def test_linear_filters_in_panels(cin, cout, mb):
     other.close()
 
 
+def test_strided_convolutions_to_single_pixels_add_their_gradients():
+    """Two 1x1 / 2 convolutions read one 2x2 map: the second gradient, of four pixel classes, is added to the first."""
+    st = single(lambda b: (b.conv(4096, 4096, 1, stride=2, src=-1), b.conv(4096, 4096, 1, stride=2, src=-1), b.addl(0, 1, relu=0)), 4096, (2, 2), C.BF16,
+                micro_batch=10)
+    compare_minibatch(st, verbose="two 1x1 / 2 of one 2x2 map")
+
+
 @pytest.mark.parametrize("stride", [1, 2])
 @pytest.mark.parametrize("cin,cout,mb", [(96, 64, 5), (4096, 4096, 40)])
 def test_conv_of_single_pixels(cin, cout, mb, stride):

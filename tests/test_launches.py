@@ -1,0 +1,95 @@
+"""Which kernels a call launches and on what grids, asked without a GPU: tests/launch_recorder.c takes the place of the runtime."""
+import ctypes as ct
+import json
+import os
+import re
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from paper_2012_12544_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SOMEWHERE = 1 << 40          # an address; nothing is read or written there
+
+
+class _GatherConv(ct.Structure):
+    _fields_ = [(f, ct.c_int) for f in "N Hi Wi Ci Ho Wo Co R S s_out s_in pad_h pad_w beside by_norm wt_panels".split()]
+
+
+class _GradEpi(ct.Structure):
+    _fields_ = [("gate", ct.c_void_p), ("accum", ct.c_int), ("accum_from", ct.c_void_p)]
+
+
+def _gather(lib, case):
+    f = getattr(lib, "_ZN6bapipe16conv_gather_mfmaEPKvS1_PKfPviNS_7GradEpiERKNS_10GatherConvES4_PjP12ihipStream_tPfS1_S3_")
+    at = ct.c_void_p(SOMEWHERE)
+    return f(at, at, None, at, ct.c_int(0), _GradEpi(None, case.get("accum", 0), None), ct.byref(_GatherConv(*case["g"])), at, at, None, None, None, None)
+
+
+def _record(recorder, library, cases):
+    """In a process of its own: for each case the returned status and (kernel, template arguments, grid) of every launch."""
+    rec, lib = ct.CDLL(recorder, mode=ct.RTLD_GLOBAL), ct.CDLL(library)
+    rec.recorder_launch.restype = ct.c_char_p
+    out = []
+    for case in cases:
+        rec.recorder_clear()
+        rc = globals()["_" + case["call"]](lib, case)
+        launches = []
+        for i in range(rec.recorder_launches()):
+            grid = (ct.c_uint * 3)()
+            name = rec.recorder_launch(i, grid).decode()
+            m = re.search(r"\d(k_[a-z0-9_]+?)(?:I((?:L[ib]\d+E)+)E|E?v|E?P|I)", name)
+            launches.append((m.group(1) if m else name, [int(a) for a in re.findall(r"L[ib](\d+)E", m.group(2) or "")] if m else [], list(grid)))
+        out.append(dict(rc=rc, launches=launches))
+    return out
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    if shutil.which("gcc") is None:
+        pytest.skip("needs gcc")
+    B.load()
+    so = str(tmp_path_factory.mktemp("recorder") / "recorder.so")
+    subprocess.check_call(["gcc", "-O1", "-std=c11", "-shared", "-fPIC", "-Wall", "-o", so, os.path.join(HERE, "launch_recorder.c")])
+
+    def run(cases):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), so, B.LIB_PATH], input=json.dumps(cases), capture_output=True, text=True, timeout=120,
+                           env=dict(os.environ, PYTHONPATH=os.path.dirname(HERE)))
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout)
+    return run
+
+
+# ------------------------------------------------------------------------------ gather convolution
+# Template arguments of k_gather_mfma: BP, BC, WP, WC, BK, STAGES, KG, S1, TAPS_INNER, PHASED, PANELS
+KG, PHASED = 6, 9
+
+
+def _strided_gradient(n, c, k, side, r, stride):
+    """Input gradient of an r x r convolution c -> k at that stride, no padding, of `side` x `side` maps."""
+    out = (side - r) // stride + 1
+    return [n, out, out, k, side, side, c, r, r, 1, stride, r - 1, r - 1, 0, 0, 0]
+
+
+def test_a_launch_of_pixel_classes_is_of_a_kernel_that_knows_them(record):
+    """The classes of a strided gradient are the grid's z axis.  A kernel that does not look at it stores each tile once per class,
+    and where it adds to what is stored, adds that often."""
+    cases = [dict(call="gather", accum=accum, g=_strided_gradient(n, c, k, side, r, stride))
+             for c, k in ((4096, 4096), (6144, 3072), (2048, 9216), (4096, 4608), (1024, 256), (64, 64), (256, 72))
+             for side, r, stride in ((2, 1, 2), (3, 1, 2), (3, 1, 3), (7, 1, 2), (3, 3, 2), (8, 3, 2), (5, 2, 4))
+             for n in (1, 5, 9, 12, 16, 40) for accum in (0, 1)]
+    classes = 0
+    for case, got in zip(cases, record(cases)):
+        assert got["rc"] == 0, case
+        name, args, grid = got["launches"][0]
+        assert name == "k_gather_mfma", got
+        assert grid[2] == 1 or (args[PHASED] and args[KG] == 1), (case, got)
+        classes += grid[2] > 1
+    assert classes > len(cases) // 2           # otherwise nothing was asked
+
+
+if __name__ == "__main__":
+    print(json.dumps(_record(sys.argv[1], sys.argv[2], json.load(sys.stdin))))
