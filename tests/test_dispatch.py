@@ -39,7 +39,7 @@ def test_one_launch_recurrence_needs_two_steps_a_round(n, hidden, least):
 
 
 class _GatherConv(ct.Structure):
-    _fields_ = [(f, ct.c_int) for f in "N Hi Wi Ci Ho Wo Co R S s_out s_in pad_h pad_w beside by_norm".split()]
+    _fields_ = [(f, ct.c_int) for f in "N Hi Wi Ci Ho Wo Co R S s_out s_in pad_h pad_w beside by_norm wt_panels".split()]
 
 
 def _pixel_tiles(rows, cin, cout, k=1, hw=1, beside=0):
