@@ -413,6 +413,36 @@ def test_strided_convolutions_to_single_pixels_add_their_gradients():
     compare_minibatch(st, verbose="two 1x1 / 2 of one 2x2 map")
 
 
+@pytest.mark.parametrize("layer,cout,mb", [
+    ("linear", 4096, 40),        # four blocks share a tile's K
+    ("linear", 4608, 64),        # three
+    ("conv", 4096, 33),          # and add what the sum's gradient left, from where it lies
+    ("linear", 8192, 48),        # two
+])
+def test_last_block_of_a_tile_runs_every_epilogue(layer, cout, mb):
+    """Bias and ReLU forward; behind a ReLU and beside a residual sum, a gate and the gradient that is already there."""
+    make = (lambda b, *c, **kw: b.conv(*c, 1, **kw)) if layer == "conv" else (lambda b, *c, **kw: b.linear(*c, **kw))
+    cin = 4096 if cout < 8192 else 2048
+    st = single(lambda b: (make(b, 64, cin, relu=1, src=-1), make(b, cin, cout, relu=1), make(b, cout, cin), b.addl(0, 2, relu=0)), 64, (1, 1), C.BF16,
+                micro_batch=mb)
+    compare_minibatch(st, verbose="%s %d->%d->%d x %d, added" % (layer, cin, cout, cin, mb))
+
+
+def test_blocks_of_a_tile_count_themselves_on_every_stream():
+    """Passes that overlap, the static workspace, one stream: the same bits."""
+    b = C._Builder()
+    b.linear(4096, 4096, src=-1)
+    b.linear(4096, 4608)
+    b.linear(4608, 4096)
+    st = C._stage("shared K", b.layers, C.BF16, (4096, 1, 1), 48, 3, 1, 2, 1, C.BASE_SEED + 80, "kaiming")
+    ref = gpu_minibatch(st)
+    for kw in (dict(backward_stream=True, eager_sync=False), dict(backward_stream="no wgrad stream", eager_sync=False), dict(static=True),
+               dict(static=True, backward_stream=True, eager_sync=False)):
+        got = gpu_minibatch(st, **kw)
+        for k in ref:
+            assert np.array_equal(got[k], ref[k]), (kw, k)
+
+
 @pytest.mark.parametrize("stride", [1, 2])
 @pytest.mark.parametrize("cin,cout,mb", [(96, 64, 5), (4096, 4096, 40)])
 def test_conv_of_single_pixels(cin, cout, mb, stride):

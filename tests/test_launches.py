@@ -9,7 +9,9 @@ import sys
 
 import pytest
 
+from oracle.stage import one_f_one_b_order
 from paper_2012_12544_amd import binding as B
+from stage_inputs import configs as C
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOMEWHERE = 1 << 40          # an address; nothing is read or written there
@@ -29,9 +31,40 @@ def _gather(lib, case):
     return f(at, at, None, at, ct.c_int(0), _GradEpi(None, case.get("accum", 0), None), ct.byref(_GatherConv(*case["g"])), at, at, None, None, None, None)
 
 
+STREAMS = dict(own=1 << 20, backward=2 << 20, wgrad=3 << 20)
+
+
+def _mini_batch(lib, case):
+    """One mini-batch in 1F1B order and the update; None, and the blocks that the stage asked its allocator for in case["blocks"]."""
+    blocks = case["blocks"] = []
+
+    def alloc(nbytes, ctx):
+        blocks.append((SOMEWHERE + (sum(n for _, n in blocks) + 4095) // 4096 * 4096 + 4096 * len(blocks), nbytes))
+        return blocks[-1][0]
+
+    b = C._Builder()
+    for kind, args in case["layers"]:
+        getattr(b, kind)(*args[0], **args[1])
+    st = C._stage("recorded", b.layers, C.BF16, tuple(case["input"]), case["micro_batch"], case["n_micro"], 1, case["in_flight"], 1, 0, "kaiming")
+    o = B.make_opts(st, stream=STREAMS["own"])
+    o.mem.alloc, o.mem.free = B.ALLOC_FN(alloc), B.FREE_FN(lambda ptr, ctx: None)
+    h = B.bapipe_stage_create(b.layers, case["micro_batch"], case["n_micro"], o)
+    if case["streams"] > 1:
+        B.bapipe_stage_set_streams(h, STREAMS["backward"], STREAMS["wgrad"] if case["streams"] == 3 else None)
+    backward = B.bapipe_stage_backward_static if case.get("static") else B.bapipe_stage_backward
+    for what, m in one_f_one_b_order(case["n_micro"], B.bapipe_stage_stash_bytes(h)[1]):
+        if what == "F":
+            B.bapipe_stage_forward(h, m, SOMEWHERE >> 1, SOMEWHERE >> 2)
+        else:
+            backward(h, m, SOMEWHERE >> 3, SOMEWHERE >> 4)
+    B.bapipe_stage_step(h, 0.1)
+    B.bapipe_stage_destroy(h)
+
+
 def _record(recorder, library, cases):
-    """In a process of its own: for each case the returned status and (kernel, template arguments, grid) of every launch."""
+    """In a process of its own: for each case what the call returned and (kernel, template arguments, grid, stream, tickets) of every launch."""
     rec, lib = ct.CDLL(recorder, mode=ct.RTLD_GLOBAL), ct.CDLL(library)
+    B.LIB_PATH = library
     rec.recorder_launch.restype = ct.c_char_p
     out = []
     for case in cases:
@@ -39,11 +72,12 @@ def _record(recorder, library, cases):
         rc = globals()["_" + case["call"]](lib, case)
         launches = []
         for i in range(rec.recorder_launches()):
-            grid = (ct.c_uint * 3)()
-            name = rec.recorder_launch(i, grid).decode()
+            grid, stream, tickets = (ct.c_uint * 3)(), ct.c_size_t(), ct.c_size_t()
+            name = rec.recorder_launch(i, grid, ct.byref(stream), ct.byref(tickets)).decode()
             m = re.search(r"\d(k_[a-z0-9_]+?)(?:I((?:L[ib]\d+E)+)E|E?v|E?P|I)", name)
-            launches.append((m.group(1) if m else name, [int(a) for a in re.findall(r"L[ib](\d+)E", m.group(2) or "")] if m else [], list(grid)))
-        out.append(dict(rc=rc, launches=launches))
+            launches.append((m.group(1) if m else name, [int(a) for a in re.findall(r"L[ib](\d+)E", m.group(2) or "")] if m else [], list(grid),
+                             stream.value, tickets.value))
+        out.append(dict(rc=rc, launches=launches, blocks=case.get("blocks")))
     return out
 
 
@@ -84,7 +118,7 @@ def test_a_launch_of_pixel_classes_is_of_a_kernel_that_knows_them(record):
     classes = 0
     for case, got in zip(cases, record(cases)):
         assert got["rc"] == 0, case
-        name, args, grid = got["launches"][0]
+        name, args, grid = got["launches"][0][:3]
         assert name == "k_gather_mfma", got
         assert grid[2] == 1 or (args[PHASED] and args[KG] == 1), (case, got)
         classes += grid[2] > 1
@@ -117,6 +151,26 @@ def test_few_rows_of_a_filter_in_panels_share_k(record, rows, shares):
             assert [launch[0] for launch in got["launches"][1:]] == (["k_gather_splitk_reduce"] if grid[1] > 4 else []), (case, got)
         else:
             assert grid[1] == 1 and len(got["launches"]) == 1, (case, got)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("streams", [1, 2, 3])
+def test_passes_that_may_run_at_once_have_tickets_of_their_own(record, streams, static):
+    """A block that counts itself among another launch's would add sums that are not there yet."""
+    linear = lambda cin, cout: ("linear", [[cin, cout], {}])
+    case = dict(call="mini_batch", layers=[("linear", [[4096, 4096], dict(src=-1)]), linear(4096, 4608), linear(4608, 4096)], input=[4096, 1, 1],
+                micro_batch=48, n_micro=3, in_flight=2, streams=streams, static=static)
+    got = record([case])[0]
+    words = {}
+    for name, args, grid, stream, tickets in got["launches"]:
+        if name == "k_gather_mfma" and 1 < grid[1] <= 4:
+            assert tickets and grid[0] <= 128, got
+            words.setdefault(stream, set()).add(tickets)
+    assert set(words) == {STREAMS[s] for s in ("own", "backward")[:min(streams, 2)]}
+    assert sum(len(w) for w in words.values()) == len(set().union(*words.values())) == len(words), words
+    assert all(any(at <= t and t + 128 * 4 <= at + n for at, n in got["blocks"]) for w in words.values() for t in w)
+    starts = sorted(set().union(*words.values()))
+    assert all(b - a >= 128 * 4 for a, b in zip(starts, starts[1:]))
 
 
 if __name__ == "__main__":
