@@ -554,9 +554,12 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
 // so x is fetched 1.4 times instead of 9.  Units are split over blockIdx.y; partial tiles are
 // reduced by k_wg_halo_reduce in a fixed order.
 // A wave owns 32 x 32 channels of all nine taps, so that one read of a halo row serves three rows of dy: 38 fragments from LDS for the
-// 72 MFMAs of a unit instead of 80 (with the taps dealt out to the waves).  Alone the launch is bound by the way of its units from memory,
-// 121 -> 119 us for 64 channels at 224x224, 67 -> 66 for 64->128 at 112x112; beside convolutions on other streams, whose LDS it shares, the
-// mini-batch of VGG stage 1 is 8770 -> 8620 us.  266 registers a lane: one block to a unit as before, and still room for one of theirs.
+// 72 MFMAs of a unit instead of 80 (with the taps dealt out to the waves).  Alone the launch is bound by the way of its units from memory;
+// with the reduction, 134 -> 121 us for 64 channels at 224x224, 65.7 -> 61.0 for 64->128 at 112x112 (of that fewer instructions for the
+// addresses of a unit: 135 -> 121, 65.1 -> 61.0); beside convolutions on other streams, whose LDS it shares, VGG stage 1 takes 8825 -> 8520 us a
+// mini-batch.
+// At 256 registers a lane two blocks fit a unit, which launches of more than a block a unit need (192->192 at 64x64, 32 samples, 261
+// blocks: 117 us, with 266 registers 156; 320->320 at 32x32, 275: 84, 112).
 constexpr int UH = 8, UW = 16, UPIX = UH * UW;                 // unit of 8 x 16 pixels
 constexpr int WH_ROWS = UH + 2, WH_COLS = UW + 2, WH_PIX = WH_ROWS * WH_COLS;      // 10 x 18 halo = 180 pixels
 constexpr int WG_DY_ELEMS = UPIX * 64;                         // 16 KB
@@ -564,7 +567,7 @@ constexpr int WG_HALO_ELEMS = WH_PIX * 64 + 256;               // 1440 slots + 3
 constexpr int WG_STAGE_ELEMS = WG_DY_ELEMS + WG_HALO_ELEMS;
 constexpr int WG_HL = 6, WG_DL = 4;                            // wave-loads per wave: halo (24 >= 22.5), dy (16)
 
-__global__ __launch_bounds__(256, 1) void k_wgrad3x3_halo(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy,
+__global__ __launch_bounds__(256, 2) void k_wgrad3x3_halo(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy,
                                                           float *__restrict__ part, int N, int H, int W, int C,
                                                           int K, int units_per_split, unsigned x_bytes,
                                                           unsigned dy_bytes, int with_bias)
@@ -596,45 +599,42 @@ __global__ __launch_bounds__(256, 1) void k_wgrad3x3_halo(const bf16_t *__restri
     __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(x), 0, (int)x_bytes, 0x00020000);
     __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(dy), 0, (int)dy_bytes, 0x00020000);
 
-    // halo slots of this lane (fixed relative to the unit origin)
-    int hdy[WG_HL], hdx[WG_HL];
-    unsigned hco[WG_HL];
+    // Halo slots of this lane: the byte offset from the unit's first pixel, and a nibble that says beyond which of the unit's edges (top,
+    // bottom, left, right) the slot lies.  A slot past the halo has an offset that no unit brings back into the tensor.  (Rows, columns and
+    // channels of every slot took 30 registers, with which two blocks do not fit a unit.)
+    unsigned hoff[WG_HL], hedge = 0;
+    static_assert(WG_HL * 4 <= 32, "a nibble a slot");
 #pragma unroll
     for (int i = 0; i < WG_HL; ++i) {
         const int slot = (i * NW + wave) * 64 + lane;
         const int hr = slot >> 3, cq = slot & 7;
         const int c = ((((cq >> 1) ^ wg_swz<64>(hr)) << 1) | (cq & 1));
         const int hy = hr / WH_COLS, hx = hr - hy * WH_COLS;
-        hdy[i] = hr < WH_PIX ? hy - 1 : -(1 << 20);
-        hdx[i] = hx - 1;
-        hco[i] = (unsigned)(ci0 + c * 8) * 2u;
+        hoff[i] = hr < WH_PIX ? (unsigned)(((hy - 1) * W + hx - 1) * C + ci0 + c * 8) * 2u : OOB;
+        if (hr < WH_PIX)
+            hedge |= (unsigned)((hy == 0) | (hy == WH_ROWS - 1) << 1 | (hx == 0) << 2 | (hx == WH_COLS - 1) << 3) << (4 * i);
     }
-    unsigned dco[WG_DL];
-    int ddy[WG_DL], ddx[WG_DL];
-#pragma unroll
-    for (int i = 0; i < WG_DL; ++i) {
-        const int slot = (i * NW + wave) * 64 + lane;
-        const int px = slot >> 3, cq = slot & 7;
+    // dy slots: a load covers two rows of the unit, so the next one's are two rows further
+    unsigned doff;
+    {
+        static_assert(NW * 64 / 8 == 2 * UW, "two rows a load");
+        const int px = wave * 8 + (lane >> 3), cq = lane & 7;
         const int c = ((((cq >> 1) ^ wg_swz<64>(px)) << 1) | (cq & 1));
-        ddy[i] = px >> 4;
-        ddx[i] = px & 15;
-        dco[i] = (unsigned)(ko0 + c * 8) * 2u;
+        doff = (unsigned)(((px >> 4) * W + (px & 15)) * K + ko0 + c * 8) * 2u;
     }
     auto issue_unit = [&](int u, int st) {
         uint16_t *sd = stage0 + st * WG_STAGE_ELEMS, *sh = sd + WG_DY_ELEMS;
         const bool live = u < u1;
         const int n = u / upi, rem = u - n * upi;
         const int Y0 = (rem / ux) * UH, X0 = (rem % ux) * UW;
+        const unsigned pixel = (unsigned)((n * H + Y0) * W + X0);
 #pragma unroll
-        for (int i = 0; i < WG_DL; ++i) {
-            unsigned vo = live ? (unsigned)(((n * H + Y0 + ddy[i]) * W + X0 + ddx[i]) * K) * 2u + dco[i] : OOB;
-            dma16(grsrc, lds_of(sd + (i * NW + wave) * 512), vo);
-        }
+        for (int i = 0; i < WG_DL; ++i)
+            dma16(grsrc, lds_of(sd + (i * NW + wave) * 512), live ? (pixel + (unsigned)(2 * i * W)) * (unsigned)K * 2u + doff : OOB);
+        const unsigned beyond = ((Y0 == 0) | (Y0 + UH == H) << 1 | (X0 == 0) << 2 | (X0 + UW == W) << 3) * 0x11111111u & hedge;
 #pragma unroll
         for (int i = 0; i < WG_HL; ++i) {
-            const int y = Y0 + hdy[i], xx = X0 + hdx[i];
-            const bool ok = live && (unsigned)y < (unsigned)H && (unsigned)xx < (unsigned)W;
-            unsigned vo = ok ? (unsigned)(((n * H + y) * W + xx) * C) * 2u + hco[i] : OOB;
+            const unsigned vo = live && !(beyond & 15u << (4 * i)) ? pixel * (unsigned)C * 2u + hoff[i] : OOB;
             const int q = i * NW + wave;                             // wave-load 23 lies wholly past the halo
             uint16_t *dst = q * 64 < WH_PIX * 8 ? sh + q * 512 : dump;
             dma16(xrsrc, lds_of(dst), vo);
@@ -1146,11 +1146,14 @@ hipError_t wgrad3x3_halo_mfma(const void *x, const void *dy, float *dw, float *d
 {
     if (!wgrad3x3_halo_supported(c)) return hipErrorInvalidValue;
     const WgHaloPlan p = wg_halo_plan(c);
-    constexpr size_t smem = (size_t)(2 * WG_STAGE_ELEMS + 512) * 2;
-    static_assert(smem <= 80 * 1024, "two blocks per CU");
+    constexpr size_t used = (size_t)(2 * WG_STAGE_ELEMS + 512) * 2, more_than_half = 84 * 1024;
+    static_assert(used <= 80 * 1024, "two blocks fit a unit");
+    // Where every unit is to have one block, no unit must take two, as it would where blocks of other streams keep its neighbours
+    // (VGG stage 1 on three streams 8655 -> 8325 us a mini-batch, on another card; alone the same)
+    const size_t smem = p.tiles * p.splits > 256 ? used : more_than_half;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_wgrad3x3_halo, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipError_t e = hipFuncSetAttribute((const void *)k_wgrad3x3_halo, hipFuncAttributeMaxDynamicSharedMemorySize, (int)more_than_half);
         if (e != hipSuccess) return e;
         attr_set = true;
     }

@@ -1,6 +1,6 @@
 /* Stands in for the parts of the HIP runtime that launching a kernel and enqueueing a mini-batch need, on a machine without a GPU:
- * nothing runs, and the argument of every split-K reduction, which says where its product's partial sums lie, is kept, as are name, grid
- * and stream of every launch and the tickets that a gather convolution is handed. */
+ * nothing runs, and the argument of every split-K reduction, which says where its product's partial sums lie, is kept, as are name, grid,
+ * stream and LDS of every launch and the tickets that a gather convolution is handed. */
 #include <stddef.h>
 #include <string.h>
 
@@ -13,7 +13,7 @@ static struct { const void *host; const char *name; } kernels[KERNELS];
 static int n_kernels;
 static struct { dim3 grid, block; size_t lds; void *stream; } config;
 static splitk_args records[RECORDS];
-static struct { const char *name; dim3 grid; void *stream; const void *tickets; } launches[LAUNCHES];
+static struct { const char *name; dim3 grid; void *stream; const void *tickets; size_t lds; } launches[LAUNCHES];
 static int n_records, n_launches;
 static void *handle;
 
@@ -39,12 +39,13 @@ int hipGetLastError(void) { return 0; }
 int hipFuncSetAttribute(const void *f, int attr, int value) { (void)f; (void)attr; (void)value; return 0; }
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream)
 {
-    (void)block; (void)lds;
+    (void)block;
     const int at = n_launches < LAUNCHES ? n_launches : LAUNCHES - 1;
     launches[at].name = "?";
     launches[at].grid = grid;
     launches[at].stream = stream;
     launches[at].tickets = NULL;
+    launches[at].lds = lds;
     n_launches++;
     for (int k = 0; k < n_kernels; ++k) {
         if (kernels[k].host != f) continue;
@@ -71,8 +72,9 @@ int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream)
 
 void recorder_clear(void) { n_records = n_launches = 0; }
 int recorder_launches(void) { return n_launches; }
-const char *recorder_launch(int i, unsigned *grid, size_t *stream, size_t *tickets)
+const char *recorder_launch(int i, unsigned *grid, size_t *stream, size_t *tickets, size_t *lds)
 {
+    *lds = launches[i].lds;
     *stream = (size_t)launches[i].stream; *tickets = (size_t)launches[i].tickets;
     grid[0] = launches[i].grid.x; grid[1] = launches[i].grid.y; grid[2] = launches[i].grid.z;
     return launches[i].name;

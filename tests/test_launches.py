@@ -4,6 +4,7 @@ import json
 import os
 import re
 import shutil
+import struct
 import subprocess
 import sys
 
@@ -62,7 +63,7 @@ def _mini_batch(lib, case):
 
 
 def _record(recorder, library, cases):
-    """In a process of its own: for each case what the call returned and (kernel, template arguments, grid, stream, tickets) of every launch."""
+    """In a process of its own: for each case what the call returned and (kernel, template arguments, grid, stream, tickets, LDS) of every launch."""
     rec, lib = ct.CDLL(recorder, mode=ct.RTLD_GLOBAL), ct.CDLL(library)
     B.LIB_PATH = library
     rec.recorder_launch.restype = ct.c_char_p
@@ -72,11 +73,11 @@ def _record(recorder, library, cases):
         rc = globals()["_" + case["call"]](lib, case)
         launches = []
         for i in range(rec.recorder_launches()):
-            grid, stream, tickets = (ct.c_uint * 3)(), ct.c_size_t(), ct.c_size_t()
-            name = rec.recorder_launch(i, grid, ct.byref(stream), ct.byref(tickets)).decode()
+            grid, stream, tickets, lds = (ct.c_uint * 3)(), ct.c_size_t(), ct.c_size_t(), ct.c_size_t()
+            name = rec.recorder_launch(i, grid, ct.byref(stream), ct.byref(tickets), ct.byref(lds)).decode()
             m = re.search(r"\d(k_[a-z0-9_]+?)(?:I((?:L[ib]\d+E)+)E|E?v|E?P|I)", name)
             launches.append((m.group(1) if m else name, [int(a) for a in re.findall(r"L[ib](\d+)E", m.group(2) or "")] if m else [], list(grid),
-                             stream.value, tickets.value))
+                             stream.value, tickets.value, lds.value))
         out.append(dict(rc=rc, launches=launches, blocks=case.get("blocks")))
     return out
 
@@ -162,7 +163,7 @@ def test_passes_that_may_run_at_once_have_tickets_of_their_own(record, streams, 
                 micro_batch=48, n_micro=3, in_flight=2, streams=streams, static=static)
     got = record([case])[0]
     words = {}
-    for name, args, grid, stream, tickets in got["launches"]:
+    for name, args, grid, stream, tickets, _ in got["launches"]:
         if name == "k_gather_mfma" and 1 < grid[1] <= 4:
             assert tickets and grid[0] <= 128, got
             words.setdefault(stream, set()).add(tickets)
@@ -171,6 +172,52 @@ def test_passes_that_may_run_at_once_have_tickets_of_their_own(record, streams, 
     assert all(any(at <= t and t + 128 * 4 <= at + n for at, n in got["blocks"]) for w in words.values() for t in w)
     starts = sorted(set().union(*words.values()))
     assert all(b - a >= 128 * 4 for a, b in zip(starts, starts[1:]))
+
+
+# ------------------------------------------------------------------------------ blocks of a kernel that fit a compute unit
+def _kernels_of_the_library():
+    """What the code objects of the built library say of each kernel: name -> its metadata."""
+    msgpack = pytest.importorskip("msgpack")
+    B.load()
+    data, out, at = open(B.LIB_PATH, "rb").read(), {}, 0
+    while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        entry = at + 32
+        for _ in range(struct.unpack_from("<Q", data, at + 24)[0]):
+            first, size, n = struct.unpack_from("<3Q", data, entry)
+            elf = data[at + first:at + first + size]
+            if data[entry + 24:entry + 24 + n].endswith(b"gfx950"):
+                sections, = struct.unpack_from("<Q", elf, 40)
+                for i in range(struct.unpack_from("<H", elf, 60)[0]):
+                    kind, where, length = struct.unpack_from("<I", elf, sections + 64 * i + 4)[0], *struct.unpack_from("<2Q", elf, sections + 64 * i + 24)
+                    if kind == 7 and struct.unpack_from("<3I", elf, where)[2] == 32:          # a note with AMDGPU metadata
+                        owner, desc, _ = struct.unpack_from("<3I", elf, where)
+                        start = where + 12 + (owner + 3) // 4 * 4
+                        out.update((k[".name"], k) for k in msgpack.unpackb(elf[start:start + desc])["amdhsa.kernels"])
+            entry += 24 + n
+        at += 1
+    return out
+
+
+def _wgrad_halo(lib, case):
+    at = ct.c_void_p(SOMEWHERE)
+    shape = (ct.c_int * 11)(*case["shape"])
+    return getattr(lib, "_ZN6bapipe18wgrad3x3_halo_mfmaEPKvS1_PfS2_PvRKNS_9ConvShapeEP12ihipStream_t")(at, at, at, at, at, shape, None)
+
+
+def test_blocks_of_the_halo_weight_gradient_are_one_round(record):
+    """A block for every unit is rounded up to whole splits of a tile, so that a unit may be handed a second block: one that has to wait for
+    the first would take the launch as long again.  Where there is one for each unit none takes two."""
+    shapes = [(96, 32, 32, c, 32, 32, k, 3, 3, 1, 1) for c, k in ((64, 64), (64, 192), (192, 192), (320, 320), (448, 448), (704, 704))]
+    most = 0
+    for got in record([dict(call="wgrad_halo", shape=s) for s in shapes]):
+        name, _, grid, _, _, lds = got["launches"][0]
+        assert got["rc"] == 0 and name == "k_wgrad3x3_halo"
+        most = max(most, grid[0] * grid[1])
+        assert (2 * lds <= 160 << 10) == (grid[0] * grid[1] > 256), got
+    kernel, = [k for name, k in _kernels_of_the_library().items() if "k_wgrad3x3_halo" in name]
+    assert 256 < most <= 512
+    # a block has a wave on each SIMD, of whose 512 registers a lane a wave of two has half
+    assert kernel[".vgpr_count"] <= 256 and kernel[".vgpr_spill_count"] == 0 and kernel[".max_flat_workgroup_size"] == 256
 
 
 if __name__ == "__main__":
