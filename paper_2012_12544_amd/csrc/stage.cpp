@@ -153,6 +153,7 @@ struct bapipe_stage {
     char *deferred = nullptr;
     size_t deferred_bytes = 0;
     int flushed = 0;                         // micro-batches whose deferred weight gradients are already in dw
+    std::vector<SgdJob> updates;             // of all layers: an update allocates nothing
     float *losses = nullptr;                 // and, behind them, the tickets of conv_gather_mfma: of the handle's stream, of the backward stream
     unsigned *tickets = nullptr, *tickets_f = nullptr, *tickets_b = nullptr;      // as work: of the pass being enqueued, of either
     size_t params_bytes = 0, slot_bytes = 0, transient_bytes = 0, grads_bytes = 0, work_bytes = 0;
@@ -1471,6 +1472,7 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
         L.dw = (float *)(st->params + o_dw[i]);
         if (L.b_elems) { L.bias = (float *)(st->params + o_b[i]); L.db = (float *)(st->params + o_db[i]); }
         if (L.d.kind != BAPIPE_BATCHNORM2D) { L.w_work = st->params + o_ww[i]; L.w_t = st->params + o_wt[i]; }
+        update_jobs(st, L, st->updates);
     }
     // parameters start at zero (gamma at one); all of it through kernels on the stage's stream
     hipError_t e = fill_f32((float *)st->params, 0.f, st->params_bytes / 4, st->stream);
@@ -1689,10 +1691,7 @@ int bapipe_stage_step(bapipe_stage_t *st, float lr)
         int rc = flush_deferred(st);
         if (rc != BAPIPE_OK) return rc;
     }
-    std::vector<SgdJob> jobs;
-    for (const auto &L : st->layers)
-        if (L.w_elems) update_jobs(st, L, jobs);
-    HIPCHK(sgd_update(st->dt, jobs.data(), (int)jobs.size(), lr, st->stream));
+    HIPCHK(sgd_update(st->dt, st->updates.data(), (int)st->updates.size(), lr, st->stream));
     st->n_fwd = st->n_bwd = 0;
     st->flushed = 0;
     return BAPIPE_OK;

@@ -2,6 +2,7 @@
  * nothing runs, and the argument of every split-K reduction, which says where its product's partial sums lie, is kept, as are name, grid,
  * stream and LDS of every launch and the tickets that a gather convolution is handed. */
 #include <stddef.h>
+#include <stdlib.h>
 #include <string.h>
 
 typedef struct { unsigned x, y, z; } dim3;
@@ -69,6 +70,12 @@ int hipEventCreateWithFlags(void **event, unsigned flags) { (void)flags; *event 
 int hipEventRecord(void *event, void *stream) { (void)event; (void)stream; return 0; }
 int hipEventDestroy(void *event) { (void)event; return 0; }
 int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream) { (void)to; (void)from; (void)n; (void)kind; (void)stream; return 0; }
+
+/* operator new of the library */
+static long n_news;
+void *_Znwm(size_t n) { n_news++; return malloc(n ? n : 1); }
+void _ZdlPvm(void *p, size_t n) { (void)n; free(p); }
+long recorder_news(void) { return n_news; }
 
 void recorder_clear(void) { n_records = n_launches = 0; }
 int recorder_launches(void) { return n_launches; }
