@@ -17,8 +17,7 @@ inline size_t dt_size(int dt) { return dt == DT_F32 ? 4 : 2; }
 //   forward conv : in = x,  s_out = stride, s_in = 1,      pad = pad,       wt = w [K][R][S][C]
 //   dgrad        : in = dy, s_out = 1,      s_in = stride, pad = R-1-pad,   wt = flipped,
 //                  channel-transposed copy [C][R][S][K]
-// GatherGeom is what k_gather_mfma is handed: a member more moves the arguments behind it off their 16-byte places, 0.2 % of a mini-batch of
-// two LSTM layers.
+// GatherGeom is what k_gather_mfma reads and is handed; the rest is for the plan and the launcher.
 struct GatherGeom {
     int N, Hi, Wi, Ci, Ho, Wo, Co, R, S, s_out, s_in, pad_h, pad_w;
     // Kernels of other streams run beside this launch.  Alone on the chip a launch wants every compute unit busy; beside others,

@@ -246,7 +246,7 @@ def test_tap_counts_every_weight_gradient(streams):
     assert tap["launches"] == 6 and tap["flop"] == 2 * 2.0 * 4 * 196 * (9 * 64 * 64 + 64 * 128 + 9 * 128 * 64)
 
 
-# ------------------------------------------------------------------------------ input gradient of a strided convolution
+# ------------------------------------------------------------------------------ direct weight gradients that share launches
 def test_direct_weight_gradients_that_share_launches():
     """More float layers of a pass than a launch takes, of different shapes, in one order of streams and in another."""
     def build(b):
@@ -261,6 +261,7 @@ def test_direct_weight_gradients_that_share_launches():
         assert np.array_equal(a[k], b[k]), k
 
 
+# ------------------------------------------------------------------------------ input gradient of a strided convolution
 @pytest.mark.parametrize("k,stride,pad,cin,cout,hw,mb", [
     (3, 2, 1, 64, 32, (21, 19), 3),      # classes of unequal size, one K-tile a tap
     (3, 2, 1, 72, 64, (8, 7), 2),        # a ragged channel tile
@@ -743,7 +744,7 @@ def test_direct_bias_gradient_of_wide_layers(dtype, k, cin, cout, hw, mb):
     assert worst <= roundings * 2.0 ** -24
 
 
-# ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
+# ------------------------------------------------------------------------------ 2x2 pools that store and read NCHW
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("relu", [0, 1])
 @pytest.mark.parametrize("c,hw,mb", [
@@ -761,6 +762,7 @@ def test_pool_at_the_end_of_a_stage_in_either_layout(dtype, relu, c, hw, mb):
         assert np.array_equal(a[k], b[k]), k
 
 
+# ------------------------------------------------------------------------------ average pooling: batches of 8, 4 and 1 positions
 @pytest.mark.parametrize("dtype", [C.FP32, C.BF16])
 @pytest.mark.parametrize("k,c,hw", [(1, 8, (3, 4)), (2, 24, (7, 4)), (3, 5, (10, 9)), (5, 16, (5, 11)), (6, 8, (13, 6))])
 def test_avgpool_windows(dtype, k, c, hw):
