@@ -1714,7 +1714,7 @@ hipError_t maxpool2x2_bwd(int dt, const void *dy, const uint8_t *idx, void *dx, 
                           int W, int C, hipStream_t s, bool nchw)
 {
     const size_t outs = (size_t)N * (H / 2) * (W / 2) * C, bytes = (size_t)N * H * W * C * dt_size(dt);
-    if (((H | W) & 1) && !epi.accum && bytes % 4) return hipErrorInvalidValue;
+    if (((H | W) & 1) && !epi.accum && bytes % 4) return hipErrorInvalidValue;      // what the fill below cannot cover, with windows or without
     if (outs == 0) {                     // no window at all
         if (epi.accum || bytes == 0) return hipSuccess;
         hipLaunchKernelGGL(k_fill, dim3(blocks_for(bytes / 4)), dim3(TPB), 0, s, (float *)dx, 0.0f, bytes / 4);
