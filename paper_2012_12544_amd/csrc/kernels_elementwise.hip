@@ -1675,10 +1675,14 @@ static bool pool_vec(int dt, int C, const void *a, const void *b, const void *c,
     return C % (dt == DT_F32 ? 4 : 8) == 0 && aligned16(a) && aligned16(b) && aligned16(c) && (uintptr_t)idx % 8 == 0;
 }
 
-// whether the pool of these sizes and places can take or leave the pooled tensor in NCHW as well
-static bool pool_nchw(int dt, const void *pooled, int N, int C, bool vec)
+// Whether the pool of these sizes and places can take or leave the pooled tensor in NCHW as well, and should.  A block has lanes for 64
+// channels: of fewer than 12 most idle, which is worth the launch that it saves only for few positions (1x1 convolution and pool, two
+// micro-batches, us, conversion by itself -> here: float, 4 / 8 channels, 32768 positions 128 -> 123 and 142 -> 135, 65536 182 -> 183 and
+// 190 -> 189, 131072 272 -> 285 and 293 -> 295; bf16, 8 channels, 16384 83 -> 81, 65536 144 -> 152, 401408 516 -> 568; 12 float and 16 bf16
+// channels are faster here at all of these sizes, 439 -> 433 and 745 -> 736 at the largest).
+static bool pool_nchw(int dt, const void *pooled, int N, int H, int W, int C, bool vec)
 {
-    return vec && N <= 65535 && C <= 64 * 65535 && (uintptr_t)pooled % dt_size(dt) == 0;
+    return vec && N <= 65535 && C <= 64 * 65535 && (uintptr_t)pooled % dt_size(dt) == 0 && (C >= 12 || (size_t)N * (H / 2) * (W / 2) <= 32768);
 }
 
 hipError_t maxpool2x2_fwd(int dt, const void *x, void *y, uint8_t *idx, int N, int H, int W, int C,
@@ -1687,7 +1691,7 @@ hipError_t maxpool2x2_fwd(int dt, const void *x, void *y, uint8_t *idx, int N, i
     size_t outs = (size_t)N * (H / 2) * (W / 2) * C;
     if (outs == 0) return hipSuccess;
     const bool vec = pool_vec(dt, C, x, y, nullptr, idx);
-    if (y_nchw && pool_nchw(dt, y_nchw, N, C, vec)) {
+    if (y_nchw && pool_nchw(dt, y_nchw, N, H, W, C, vec)) {
         *stored = true;
         DISPATCH_T(dt, {
             constexpr int V = vec_width<T>();
@@ -1707,7 +1711,7 @@ hipError_t maxpool2x2_fwd(int dt, const void *x, void *y, uint8_t *idx, int N, i
 
 bool maxpool2x2_bwd_takes_nchw(int dt, const void *dy, const uint8_t *idx, const void *dx, const void *gate, int N, int H, int W, int C)
 {
-    return H >= 2 && W >= 2 && pool_nchw(dt, dy, N, C, pool_vec(dt, C, dx, gate, nullptr, idx));
+    return H >= 2 && W >= 2 && pool_nchw(dt, dy, N, H, W, C, pool_vec(dt, C, dx, gate, nullptr, idx));
 }
 
 hipError_t maxpool2x2_bwd(int dt, const void *dy, const uint8_t *idx, void *dx, GradEpi epi, int N, int H,

@@ -752,6 +752,7 @@ def test_direct_bias_gradient_of_wide_layers(dtype, k, cin, cout, hw, mb):
     (72, (15, 9), 2),        # a second tile of 8 channels, the last row and column in no window
     (8, (2, 3), 1), (136, (33, 2), 2), (16, (32, 32), 4),
     (12, (7, 10), 3),        # bf16: channels that no 16-byte access holds, launches of their own
+    (8, (130, 129), 9),      # more positions than few channels share a launch for
 ])
 def test_pool_at_the_end_of_a_stage_in_either_layout(dtype, relu, c, hw, mb):
     """The pooled tensor leaves, and its gradient comes, in the layout of the boundary."""

@@ -32,6 +32,15 @@ def _gather(lib, case, rec):
     return f(at, at, None, at, ct.c_int(0), _GradEpi(None, case.get("accum", 0), None), ct.byref(_GatherConv(*case["g"])), at, at, None, None, None, None)
 
 
+def _pool(lib, case, rec):
+    """2x2 pool that ends a stage of NCHW neighbours: forward, then the gradient.  Returns whether either takes that layout."""
+    at, dt, shape, stored = ct.c_void_p(SOMEWHERE), ct.c_int(case["dtype"]), [ct.c_int(v) for v in case["shape"]], ct.c_bool(False)
+    assert lib._ZN6bapipe14maxpool2x2_fwdEiPKvPvPhiiiiP12ihipStream_tS2_Pb(dt, at, at, at, *shape, None, at, ct.byref(stored)) == 0
+    takes = lib._ZN6bapipe25maxpool2x2_bwd_takes_nchwEiPKvPKhS1_S1_iiii
+    takes.restype = ct.c_bool
+    return [stored.value, takes(dt, at, at, at, None, *shape)]
+
+
 STREAMS = dict(own=1 << 20, backward=2 << 20, wgrad=3 << 20)
 
 
@@ -185,6 +194,18 @@ def test_an_update_allocates_nothing(record):
                 input=[64, 8, 8], micro_batch=2, n_micro=2, in_flight=2, streams=1)
     got = record([case])[0]
     assert got["rc"] == 0 and got["launches"][-1][0] == "k_sgd_group"
+
+
+# ------------------------------------------------------------------------------ pools that store and read NCHW
+def test_pools_of_few_channels_leave_large_maps_to_the_conversion(record):
+    """Most lanes of the kernel that does both would idle."""
+    shapes = [(C.FP32, n, hw, c) for c in (4, 8, 12, 16) for n, hw in ((4, 64), (32, 64), (33, 64), (32, 224))]
+    shapes += [(C.BF16, n, hw, c) for c in (8, 16, 64) for n, hw in ((1, 2), (32, 64), (33, 65), (32, 224))]
+    cases = [dict(call="pool", dtype=int(dt == C.BF16), shape=[n, hw, hw, c]) for dt, n, hw, c in shapes]
+    for (_, n, hw, c), got in zip(shapes, record(cases)):
+        both = c >= 12 or n * (hw // 2) ** 2 <= 32768
+        assert got["rc"] == [both, both], (n, hw, c)
+        assert [launch[0] for launch in got["launches"]] == ["k_pool_fwd_nchw" if both else "k_pool_fwd"], (got, n, hw, c)
 
 
 # ------------------------------------------------------------------------------ blocks of a kernel that fit a compute unit
