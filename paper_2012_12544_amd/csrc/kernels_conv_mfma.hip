@@ -785,13 +785,16 @@ GatherPlan gather_plan(const GatherConv &g)
     const long long K = (long long)g.R * g.S * g.Ci;
     auto count = [&](int bp, int bc) { return ((npix + bp - 1) / bp) * ((g.Co + bc - 1) / bc); };
     const bool large = 2.0 * g.Co * K > 40e6, k64 = g.Ci % 64 == 0 && g.R * g.S <= 32;
-    // Few rows of a filter of 15 to 20 M weights that is kept in panels: 64 x 64 tiles, and as many blocks share a tile's K as make a block
-    // per unit.  33 / 64 rows, filters that the caches do not hold, us, as one launch of the tiles below -> so: 9216->2048, eight shares
+    // Few rows of a 1x1 filter of 15 to 20 M weights, maps of single pixels: 64 x 64 tiles, and as many blocks share a tile's K as make a block
+    // per unit.  Filters in panels, 33 / 64 rows, that the caches do not hold, us, as one launch of the tiles below -> so: 9216->2048, eight shares
     // and the launch that adds them, 18.6 / 23.0 -> 15.7 / 16.0; 6144->3072, five, 16.1 / 18.0 -> 14.4 / 15.5; 4096->4096, four, which the
     // last of them adds, 14.7 / 14.3 -> 12.8 / 13.6; 3072->5120, three, 13.2 / 14.6 -> 12.3 / 12.9; two: 3072->6144 15.0 / 15.2 -> 13.8 / 14.8,
     // 2560->6144 13.2 / 13.6 -> 12.8 / 14.1, 2048->8192 13.0 / 13.1 -> 12.4 / 13.2.  Of fewer weights a share would be too short
-    // (2048->2048, four of 512, 7.8 -> 11).  Filters in rows keep their one launch.
-    const bool flat = g.wt_panels && g.s_in == 1 && g.Hi == 1 && g.Wi == 1 && g.R * g.S == 1 && !g.by_norm && 2.0 * g.Co * K > 30e6;
+    // (2048->2048, four of 512, 7.8 -> 11).  Of filters in rows a launch adds the shares; mini-batches of four (LSTM: two) micro-batches, either
+    // direction: 1x1 / 2 of 1x1 maps, 33 / 64 rows, 4096->4096 277 / 276 -> 258 / 262, 2048->8192 277 / 285 -> 260 / 268, 9216->2048 313 / 322 ->
+    // 293 / 309; LSTM of 2048, one step, 713 / 744 -> 705 / 711, of 1984, 50 rows, 689 -> 665; its dependent steps the same either way.
+    // A gradient of classes of pixels (s_in > 1, more than one pixel) keeps the kernel that knows them.
+    const bool flat = (g.s_in == 1 || (g.Ho == 1 && g.Wo == 1)) && g.Hi == 1 && g.Wi == 1 && g.R * g.S == 1 && !g.by_norm && 2.0 * g.Co * K > 30e6;
     p.kg = 1;
     if (flat && npix > 32 && npix <= 64 && k64 && count(64, 64) <= 128) {
         p.kg = 2;

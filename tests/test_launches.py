@@ -146,24 +146,22 @@ def _flat(rows, cin, cout, panels):
 BAND = [(2048, 8192), (2560, 6144), (3072, 5120), (4096, 4096), (4608, 4096), (6144, 3072), (9216, 2048)]       # 15 to 20 M weights
 
 
-def test_few_rows_without_panels_are_one_launch(record):
-    """(The input product of an LSTM of one step, strided convolutions of single pixels.)"""
-    cases = [dict(call="gather", g=_flat(rows, cin, cout, 0)) for cin, cout in BAND for rows in (33, 48, 64)]
-    for case, got in zip(cases, record(cases)):
-        assert got["rc"] == 0 and len(got["launches"]) == 1 and got["launches"][0][2][1] == 1, (case, got)
-
-
+@pytest.mark.parametrize("panels", [0, 1])
 @pytest.mark.parametrize("rows,shares", [(32, False), (33, True), (64, True), (65, False)])
-def test_few_rows_of_a_filter_in_panels_share_k(record, rows, shares):
-    """Up to four splits are added by their tile's last block, more by a launch."""
-    cases = [dict(call="gather", g=_flat(rows, cin, cout, 1)) for cin, cout in BAND]
-    for case, (cin, cout), got in zip(cases, BAND, record(cases)):
+def test_few_rows_share_k(record, rows, shares, panels):
+    """Of a filter in panels up to four splits are added by their tile's last block, others by a launch (the input product of an LSTM of one
+    step, strided convolutions of single pixels)."""
+    cases = [dict(call="gather", g=_flat(rows, cin, cout, panels)) for cin, cout in BAND]
+    if not panels:               # the gradient of a 1x1 / 2 convolution of 1x1 maps: one class of pixels
+        cases += [dict(call="gather", g=_strided_gradient(rows, cout, cin, 1, 1, 2)) for cin, cout in BAND]
+    for case, (cin, cout), got in zip(cases, BAND * 2, record(cases)):
         name, args, grid = got["launches"][0][:3]
         assert got["rc"] == 0 and name == "k_gather_mfma", got
         if shares:
-            assert args[KG] == 2 and grid[:2] == [cout // 64, min(256 // (cout // 64), cin // 512)], (case, got)
-            assert [launch[0] for launch in got["launches"][1:]] == (["k_gather_splitk_reduce"] if grid[1] > 4 else []), (case, got)
-        else:
+            assert args[KG] == 2 and grid == [cout // 64, min(256 // (cout // 64), cin // 512), 1], (case, got)
+            adds = not panels or grid[1] > 4
+            assert [launch[0] for launch in got["launches"][1:]] == (["k_gather_splitk_reduce"] if adds else []), (case, got)
+        elif case["g"][10] == 1:
             assert grid[1] == 1 and len(got["launches"]) == 1, (case, got)
 
 
