@@ -53,7 +53,7 @@ template <int BK> __device__ __forceinline__ int swz(int row)
 // PANELS: the filter is kept in panels of 32 columns (GatherConv::wt_panels).  A wave-wide load fetches whole cache lines whatever BK,
 // and what a tile streams is one or two pieces of memory (25088->4096, 64 rows, 50.0 -> 45 us; 4096->4096 16.1 -> 15.1).  A variant of
 // its own: layouts as arguments cost the others up to 0.7 % of a mini-batch.
-template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool PANELS = false, bool TURNS = false>
+template <int BP, int BC, int WP, int WC, int BK, int STAGES, int KG, bool S1, bool TAPS_INNER, bool PHASED = false, bool PANELS = false>
 __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_gather_mfma(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ wt, const float *__restrict__ bias,
     bf16_t *out, const bf16_t *__restrict__ gate, int accum, int relu, int is_grad, GatherGeom g,
@@ -188,22 +188,14 @@ __global__ __launch_bounds__(WP *WC *KG * 64, WP *WC *KG >= 8 ? 1 : 2) void k_ga
         cb = KT ? ti / taps * BK : g.Ci;               // a class without taps reads nothing
     }
 
-    // TURNS: the block starts at a K-tile of its own and goes round.  Blocks that stream a filter in rows of which the caches hold nothing
-    // would otherwise all ask for the same columns of its rows at a time, which lie on few memory channels
-    // (mini-batch of an LSTM of 4096, one step of 64 rows, 2292 -> 2260 us; 1x1 4096->16384 on one 7x7 map, two micro-batches, 648 -> 635).
-    // A variant of its own: the test costs the others 3 % (784 rows, 400 blocks 13.9 -> 14.3).
-    static_assert(!TURNS || (TAPS_INNER && KG == 1 && !PHASED && !PANELS), "of one tap, K not split");
-    const int from = TURNS ? tile_c % (kt1 - kt0) * BK : 0;
     auto issue_tile = [&](int stage) {
         uint16_t *sw = ring + stage * STAGE_ELEMS, *sx = sw + BC * BK;
         if constexpr (FAST) {
             const bool kin = KG > 1 ? ti < kt1 : cb < g.Ci;
             const unsigned bit = kin ? 1u << (kr * Sn + ks) : 0u;
             const int tap = PHASED ? (r0 + sd * kr) * g.S + q0 + sd * ks : kr * g.S + ks;
-            int c0 = cb;
-            if constexpr (TURNS) c0 = cb + from < g.Ci ? cb + from : cb + from - g.Ci;
-            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + c0) * 2u;
-            const unsigned wo = !kin ? OOB : PANELS ? (unsigned)(cb * g.Co) * 2u : (unsigned)(tap * g.Ci + c0) * 2u;
+            const unsigned xo = (unsigned)((kr * g.Wi + ks) * g.Ci + cb) * 2u;
+            const unsigned wo = !kin ? OOB : PANELS ? (unsigned)(cb * g.Co) * 2u : (unsigned)(tap * g.Ci + cb) * 2u;
 #pragma unroll
             for (int i = 0; i < XL; ++i) {
                 unsigned vo = (tapmask[i] & bit) ? xoff[i] + xo : OOB;
@@ -891,8 +883,6 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     const unsigned in_bytes = (unsigned)((size_t)g.N * g.Hi * g.Wi * g.Ci * 2);
     const unsigned wt_bytes = (unsigned)((size_t)g.Co * g.R * g.S * g.Ci * 2);
     float *part = (plan.splits > 1 || raw) ? (float *)workspace : nullptr;      // raw: the fp32 partials are the result
-    // one row of tiles, so that every byte of the filter is read once, and more of them than the L2s hold
-    const bool turned = npix <= 64 && g.R * g.S == 1 && plan.classes == 1 && plan.splits == 1 && wt_bytes > (32u << 20);
     // One block of wave groups, which has its tile in rows, adds up to four sums faster than a launch would start; of eight the launch,
     // whose blocks share them, is the faster way, and so it is where a thread has its sums in pieces of 16 bytes (64 rows, us: 12544<-2048,
     // four splits of 64 x 128, 16.0 and 4.9 by launch, 25.2)
@@ -925,7 +915,6 @@ hipError_t launch_gather(const void *in, const void *wt, const float *bias, void
     } else if constexpr (BK == 64) {
         if constexpr (BP == 64) {
             if (phased) GATHER_LAUNCH(true, true, true);
-            else if (turned) GATHER_LAUNCH(true, true, false, false, true);
             else GATHER_LAUNCH(true, true, false);
         } else GATHER_LAUNCH(true, true, false);                    // one class
     } else if (phased) {

@@ -452,12 +452,6 @@ def test_conv_of_single_pixels(cin, cout, mb, stride):
     compare_minibatch(st, verbose="1x1 / %d of 1x1 maps %d->%d x %d" % (stride, cin, cout, mb))
 
 
-def test_blocks_that_stream_a_filter_in_turns():
-    """Every block starts at a K-tile of its own."""
-    st = single(lambda b: b.conv(1024, 16416, 1, src=-1), 1024, (7, 7), C.BF16, micro_batch=1)
-    compare_minibatch(st, verbose="1x1 1024->16416 on one 7x7 map")
-
-
 @pytest.mark.parametrize("cin,mid,hw,mb", [(512, 64, (7, 7), 3), (512, 72, (10, 9), 2)])
 def test_groups_of_waves_in_a_bottleneck(cin, mid, hw, mb):
     """Every epilogue on tiles of wave groups: statistics, sums of dy and dy*xhat behind a gate, a residual share.  Small

@@ -112,8 +112,8 @@ def record(tmp_path_factory):
 
 
 # ------------------------------------------------------------------------------ gather convolution
-# Template arguments of k_gather_mfma: BP, BC, WP, WC, BK, STAGES, KG, S1, TAPS_INNER, PHASED, PANELS, TURNS
-KG, PHASED, TURNS = 6, 9, 11
+# Template arguments of k_gather_mfma: BP, BC, WP, WC, BK, STAGES, KG, S1, TAPS_INNER, PHASED, PANELS
+KG, PHASED = 6, 9
 
 
 def _strided_gradient(n, c, k, side, r, stride):
@@ -163,17 +163,6 @@ def test_few_rows_share_k(record, rows, shares, panels):
             assert [launch[0] for launch in got["launches"][1:]] == (["k_gather_splitk_reduce"] if adds else []), (case, got)
         elif case["g"][10] == 1:
             assert grid[1] == 1 and len(got["launches"]) == 1, (case, got)
-
-
-def test_a_filter_in_rows_that_is_streamed_is_read_in_turns(record):
-    """The input product of a wide LSTM, 1x1 convolutions of small maps: more than the L2s hold, for one row of tiles."""
-    side7 = lambda cin, cout, n: [n, 7, 7, cin, 7, 7, cout, 1, 1, 1, 1, 0, 0, 0, 0, 0]
-    cases = [(_flat(64, 4096, 16384, 0), 1), (_flat(33, 4096, 16384, 0), 1), (side7(1024, 16416, 1), 1), (side7(4096, 16384, 1), 1),
-             (_flat(64, 4096, 16384, 1), 0), (_flat(65, 4096, 16384, 0), 0), (side7(1024, 16384, 1), 0), (side7(1056, 16416, 1), 0), (side7(1024, 16416, 2), 0)]
-    for (g, turns), got in zip(cases, record([dict(call="gather", g=g) for g, _ in cases])):
-        name, args, grid = got["launches"][0][:3]
-        assert got["rc"] == 0 and name == "k_gather_mfma" and args[TURNS] == turns, (g, got)
-        assert not turns or (grid[1:] == [1, 1] and args[KG] == 1), got
 
 
 @pytest.mark.parametrize("static", [False, True])
