@@ -29,7 +29,7 @@ struct GatherGeom {
 };
 struct GatherConv : GatherGeom {
     // wt is kept in panels of 32 columns, [Ci / 32][Co][32] (1x1 filters, Ci a multiple of 32): neighbouring rows of a K-tile are one
-    // piece of memory.  The shares of K of few rows and the depth of the operand ring depend on it, so the workspace does.
+    // piece of memory.  No tile and no share of K depends on it; who adds the shares and the depth of the operand ring do.
     int wt_panels = 0;
 };
 

@@ -92,7 +92,8 @@ struct Layer {
     // (forward) and the pre-activation gradients (backward) and the cell-gradient carry
     size_t off_gates = 0, off_cells = 0, off_hs = 0, off_pd = 0, off_dcn = 0;
     bool groups = false;                 // its weight gradient may share a launch with others
-    // LINEAR, and a 1x1 convolution of 1x1 maps, on the MFMA kernels: the copies that forward and input gradient read are kept in panels (GatherConv::wt_panels)
+    // LINEAR, a 1x1 convolution of 1x1 maps, and products that stream their filter (streams_filter), on the MFMA kernels: the copies that forward
+    // and input gradient read are kept in panels (GatherConv::wt_panels).  LSTM: of its input block
     bool w_panels = false, wt_panels = false;
     bool permute_in = false;             // LINEAR fed by a flattened (C,H,W) tensor
     int pc = 0, ph = 0, pw = 0;
@@ -288,6 +289,14 @@ GatherConv fwd_geom(const bapipe_stage *st, const Layer &L)
     return g;
 }
 
+// One row of tiles that streams a 1x1 filter of which the caches hold nothing.  In rows of a power of two its blocks would all ask for the same
+// columns at a time, which lie on few memory channels (mini-batches of two, us, in rows -> in panels: two LSTM layers of 4096, one step, 8 / 64 samples, 2253 ->
+// 2177 and 2289 -> 2208; 1x1 4096->16384 on one 7x7 map 648 -> 604, 2048->10240 on two 5x5 maps, whose K is in splits, the same).
+bool streams_filter(const GatherConv &g)
+{
+    return (long long)g.N * g.Ho * g.Wo <= 64 && g.R * g.S == 1 && g.s_in == 1 && g.Ci % 32 == 0 && 2ll * g.Ci * g.Co > (32 << 20);
+}
+
 GatherConv dgrad_geom(const bapipe_stage *st, const Layer &L)
 {
     GatherConv f = fwd_geom(st, L), g;
@@ -402,7 +411,7 @@ hipError_t refresh_transposed(bapipe_stage *st, Layer &L)
     if (L.d.kind == BAPIPE_LSTM) {       // [In][4H] for dx, then [H][4H] for the recurrent gradient
         const int In = L.d.cin, H = L.d.cout, G = 4 * H;
         const size_t es = dt_size(st->dt);
-        hipError_t e = make_dgrad_filter(st->dt, L.w, L.w_t, G, 1, 1, In, st->stream);
+        hipError_t e = make_dgrad_filter(st->dt, L.w, L.w_t, G, 1, 1, In, st->stream, L.wt_panels);
         if (e != hipSuccess) return e;
         return make_dgrad_filter(st->dt, L.w + (size_t)G * In, (char *)L.w_t + (size_t)G * In * es, G, 1, 1, H, st->stream);
     }
@@ -422,7 +431,7 @@ void update_jobs(const bapipe_stage *st, const Layer &L, std::vector<SgdJob> &jo
     if (L.d.kind == BAPIPE_LSTM) {       // the input block [4H][In], then the recurrent block [4H][H]
         const int In = L.d.cin, H = L.d.cout, G = 4 * H;
         const size_t at = (size_t)G * In, es = dt_size(st->dt);
-        jobs.push_back({L.w, L.dw, L.w_work, L.w_t, b, L.db, G, 1, In, false, false});
+        jobs.push_back({L.w, L.dw, L.w_work, L.w_t, b, L.db, G, 1, In, L.w_panels, L.wt_panels});
         jobs.push_back({L.w + at, L.dw + at, (char *)L.w_work + at * es, (char *)L.w_t + at * es, nullptr, nullptr, G, 1, H, false, false});
         return;
     }
@@ -433,7 +442,10 @@ void update_jobs(const bapipe_stage *st, const Layer &L, std::vector<SgdJob> &jo
 hipError_t refresh_work(bapipe_stage *st, Layer &L)
 {
     if (!has_matrix(L.d.kind)) return hipSuccess;
-    hipError_t e = recast(st->dt, L.w, L.w_work, L.w_elems, st->stream, L.w_panels ? L.cin_p : 0);
+    // the part whose copy may be in panels: of an LSTM the input block
+    const size_t part = L.d.kind == BAPIPE_LSTM && L.w_panels ? 4 * (size_t)L.d.cout * L.d.cin : L.w_elems;
+    hipError_t e = recast(st->dt, L.w, L.w_work, part, st->stream, L.w_panels ? L.cin_p : 0);
+    if (e == hipSuccess) e = recast(st->dt, L.w + part, (char *)L.w_work + part * dt_size(st->dt), L.w_elems - part, st->stream);
     if (e != hipSuccess) return e;
     return refresh_transposed(st, L);
 }
@@ -480,7 +492,8 @@ int lstm_forward(bapipe_stage *st, Layer &L, const void *x, void *h, int mbid)
     float *gates = (float *)(slot + L.off_gates), *cells = (float *)(slot + L.off_cells);
     const char *w_hh = (const char *)L.w_work + (size_t)G * In * dt_size(st->dt);
     GradEpi none{nullptr, 0};
-    const GatherConv gx = rows_geom(N, T, In, G);
+    GatherConv gx = rows_geom(N, T, In, G);
+    gx.wt_panels = L.w_panels;
     const bool tp = st->tap_begin(st->dt == DT_BF16 ? BAPIPE_KC_CONV_GATHER_MFMA : BAPIPE_KC_CONV_DIRECT);
     if (st->dt == DT_BF16)
         HIPCHK(conv_gather_mfma(x, L.w_work, L.bias, P, 0, none, gx, st->work, st->tickets, s));
@@ -531,7 +544,8 @@ int lstm_backward(bapipe_stage *st, Layer &L, const void *x, const void *dy, voi
     }
     double flop = 2.0 * N * (T - 1) * (double)G * H;
     if (dx) {
-        const GatherConv gd = rows_geom(N, T, G, In);
+        GatherConv gd = rows_geom(N, T, G, In);
+        gd.wt_panels = L.wt_panels;
         if (mf)
             HIPCHK(conv_gather_mfma(D, wt_x, nullptr, dx, 0, e, gd, st->work, st->tickets, s));
         else
@@ -1307,8 +1321,11 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             const ConvShape cx{N, T, 1, In, T, 1, G, 1, 1, 1, 0}, ch{N, T, 1, H, T, 1, G, 1, 1, 1, 0};
             if (st->dt == DT_BF16) {
                 // the widest request among the whole-sequence products and one step of either recurrence
-                v = conv_gather_mfma_workspace(rows_geom(N, T, In, G)); w = v > w ? v : w;
-                v = conv_gather_mfma_workspace(rows_geom(N, T, G, In)); w = v > w ? v : w;
+                const GatherConv gx = rows_geom(N, T, In, G), gd = rows_geom(N, T, G, In);
+                L.w_panels = streams_filter(gx);
+                L.wt_panels = streams_filter(gd);
+                v = conv_gather_mfma_workspace(gx); w = v > w ? v : w;
+                v = conv_gather_mfma_workspace(gd); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, H, G, 1)); w = v > w ? v : w;
                 v = conv_gather_mfma_raw_workspace(step_geom(N, T, G, H, 1)); w = v > w ? v : w;
                 if (lstm_seq_supported(N, T, H, st->compute_units)) { v = lstm_seq_workspace(N, H); w = v > w ? v : w; }
@@ -1357,9 +1374,11 @@ int bapipe_stage_create(const bapipe_layer_desc_t *layers, int n_layers, int mic
             }
         }
         const bool flat_conv = L.d.kind == BAPIPE_CONV2D && L.d.kh * L.d.kw == 1 && L.d.stride == 1 && A.H * A.W == 1 && L.d.pad == 0;
-        if (L.d.kind == BAPIPE_LINEAR || flat_conv) {
-            L.w_panels = L.cin_p % 32 == 0 && use_mfma_gather(st, fwd_geom(st, L));
-            L.wt_panels = L.d.cout % 32 == 0 && use_mfma_gather(st, dgrad_geom(st, L));
+        if (L.d.kind == BAPIPE_LINEAR || L.d.kind == BAPIPE_CONV2D) {
+            const bool flat = L.d.kind == BAPIPE_LINEAR || flat_conv;
+            const GatherConv fg = fwd_geom(st, L), dg = dgrad_geom(st, L);
+            L.w_panels = (flat ? L.cin_p % 32 == 0 : streams_filter(fg)) && use_mfma_gather(st, fg);
+            L.wt_panels = (flat ? L.d.cout % 32 == 0 : streams_filter(dg)) && use_mfma_gather(st, dg);
         }
         if (L.d.kind == BAPIPE_CONV2D || L.d.kind == BAPIPE_LINEAR) {
             ConvShape cs = conv_shape(st, L);

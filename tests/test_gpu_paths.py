@@ -396,6 +396,10 @@ def test_linear_filters_in_panels(cin, cout, mb):
     b.linear(cin, cout, src=-1)
     st = C._stage("panels", b.layers, C.BF16, (cin, 1, 1), mb, 2, 1, 2, 1, C.BASE_SEED + 79, "kaiming")
     compare_minibatch(st, verbose="linear %d->%d x %d" % (cin, cout, mb))
+    _copies_after_an_update_are_those_of_its_weights(st)
+
+
+def _copies_after_an_update_are_those_of_its_weights(st):
     xs, gs = stage_io(st)
     one = GpuStage(st, gen.all_params(st, perturb=True))
     _mini_batch(one, st, xs, gs)
@@ -405,6 +409,20 @@ def test_linear_filters_in_panels(cin, cout, mb):
         assert np.array_equal(u, v)
     one.close()
     other.close()
+
+
+@pytest.mark.parametrize("layer", ["lstm", "conv"])
+def test_filters_in_panels_that_are_streamed(layer):
+    """The input block of an LSTM, beside a recurrent block in rows; a 1x1 convolution of a map."""
+    b = C._Builder()
+    if layer == "lstm":
+        b.lstm(8224, 512, src=-1)
+        st = C._stage("streamed", b.layers, C.BF16, (8224, 7, 1), 5, 2, 1, 2, 1, C.BASE_SEED + 81, "kaiming")
+    else:
+        b.conv(1024, 16416, 1, src=-1)
+        st = C._stage("streamed", b.layers, C.BF16, (1024, 7, 7), 1, 2, 1, 2, 1, C.BASE_SEED + 82, "kaiming")
+    compare_minibatch(st, verbose="streamed %s" % layer)
+    _copies_after_an_update_are_those_of_its_weights(st)
 
 
 def test_strided_convolutions_to_single_pixels_add_their_gradients():

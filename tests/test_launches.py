@@ -113,7 +113,7 @@ def record(tmp_path_factory):
 
 # ------------------------------------------------------------------------------ gather convolution
 # Template arguments of k_gather_mfma: BP, BC, WP, WC, BK, STAGES, KG, S1, TAPS_INNER, PHASED, PANELS
-KG, PHASED = 6, 9
+KG, PHASED, PANELS = 6, 9, 10
 
 
 def _strided_gradient(n, c, k, side, r, stride):
@@ -163,6 +163,23 @@ def test_few_rows_share_k(record, rows, shares, panels):
             assert [launch[0] for launch in got["launches"][1:]] == (["k_gather_splitk_reduce"] if adds else []), (case, got)
         elif case["g"][10] == 1:
             assert grid[1] == 1 and len(got["launches"]) == 1, (case, got)
+
+
+@pytest.mark.parametrize("layer,input,mb,panels", [
+    (("lstm", [[8224, 512], {}]), (8224, 4, 1), 16, 2),              # 33.7 MB of filter, 64 rows, in either direction
+    (("lstm", [[8224, 512], {}]), (8224, 5, 1), 13, 0),              # 65 rows
+    (("lstm", [[8192, 512], {}]), (8192, 4, 1), 16, 0),              # 32 MiB
+    (("conv", [[1024, 16416, 1], {}]), (1024, 7, 7), 1, 2),
+    (("conv", [[1024, 16416, 1], {}]), (1024, 7, 7), 2, 0),
+    (("conv", [[1024, 16416, 1], dict(stride=2)]), (1024, 14, 14), 1, 1),      # its gradient has classes of pixels
+])
+def test_a_filter_that_is_streamed_is_kept_in_panels(record, layer, input, mb, panels):
+    """The input product of a wide LSTM, 1x1 convolutions of small maps: more than the L2s hold, for one row of tiles."""
+    kind, (args, kw) = layer
+    case = dict(call="mini_batch", layers=[(kind, [args, dict(kw, src=-1)])], input=input, micro_batch=mb, n_micro=1, in_flight=1, streams=1)
+    got = record([case])[0]
+    in_panels = [a[PANELS] for name, a, *_ in got["launches"] if name == "k_gather_mfma"]
+    assert got["rc"] == 0 and len(in_panels) >= 2 and sum(in_panels) == panels, got
 
 
 @pytest.mark.parametrize("static", [False, True])
