@@ -558,9 +558,8 @@ __global__ __launch_bounds__(256, 4) void k_conv3x3_c8(const bf16_t *__restrict_
 // with the reduction, 134 -> 121 us for 64 channels at 224x224, 65.7 -> 61.0 for 64->128 at 112x112 (of that fewer instructions for the
 // addresses of a unit: 135 -> 121, 65.1 -> 61.0); beside convolutions on other streams, whose LDS it shares, VGG stage 1 takes 8825 -> 8520 us a
 // mini-batch.
-// At 256 registers a lane two blocks fit a unit, which launches of more blocks than units need (two micro-batches of a 3x3 layer, us, with 266
-// registers -> so: 768->768 at 32x32, 16 samples, 288 blocks, 1024 -> 878; 1024->1088 at 16x16, 32, 272, 1100 -> 959; with the taps dealt out
-// to the waves, whose blocks hide each other's barriers better, 865 and 942).
+// At 256 registers a lane two blocks fit a unit, which launches of more than a block a unit need (192->192 at 64x64, 32 samples, 261
+// blocks: 117 us, with 266 registers 156; 320->320 at 32x32, 275: 84, 112).
 constexpr int UH = 8, UW = 16, UPIX = UH * UW;                 // unit of 8 x 16 pixels
 constexpr int WH_ROWS = UH + 2, WH_COLS = UW + 2, WH_PIX = WH_ROWS * WH_COLS;      // 10 x 18 halo = 180 pixels
 constexpr int WG_DY_ELEMS = UPIX * 64;                         // 16 KB
@@ -969,11 +968,7 @@ WgHaloPlan wg_halo_plan(const ConvShape &c)
     // sums grows with the block count (at 512 blocks it was a ninth of the first VGG stage's HBM bytes), and a
     // second block per unit made the kernel only 5 % faster on its own; beside kernels of other streams fewer,
     // longer blocks are the better neighbour.
-    // Rounded down, so that no unit is handed a second block, which takes it 1.3 times as long (mini-batch of a 3x3 layer, two micro-batches of
-    // 32 samples, us, 256 blocks rounded up -> down: 192->192 at 64x64, 9 tiles, 261 -> 252 blocks, 572 -> 500; 320->320 at 32x32, 25, 275 -> 250,
-    // 401 -> 358; 16 samples, 576->640, 90, 270 -> 180, 661 -> 633, 704->704, 121, 363 -> 242, 727 -> 700).  Not to one split, where units
-    // would idle for all of a tile's length (768->768, 144 tiles: 878 with 288 blocks, 952 with 144; 960->960, 225: 650 with 450, 678 with 225).
-    int want = p.tiles <= 128 ? 256 / p.tiles : p.tiles < 256 ? 2 : 1;
+    int want = (256 + p.tiles - 1) / p.tiles;
     if (want > U) want = U;
     if (want < 1) want = 1;
     p.units_per_split = (U + want - 1) / want;
