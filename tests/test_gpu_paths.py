@@ -404,22 +404,25 @@ def _copies_after_an_update_are_those_of_its_weights(st):
     one = GpuStage(st, gen.all_params(st, perturb=True))
     _mini_batch(one, st, xs, gs)
     B.bapipe_stage_step(one.h, 0.05)
-    other = GpuStage(st, [one.get_params(0)])
+    other = GpuStage(st, [one.get_params(i) for i in range(len(st["layers"]))])
     for u, v in zip(_mini_batch(one, st, xs, gs), _mini_batch(other, st, xs, gs)):
         assert np.array_equal(u, v)
     one.close()
     other.close()
 
 
-@pytest.mark.parametrize("layer", ["lstm", "conv"])
+@pytest.mark.parametrize("layer", ["lstm", "conv", "norm"])
 def test_filters_in_panels_that_are_streamed(layer):
-    """The input block of an LSTM, beside a recurrent block in rows; a 1x1 convolution of a map."""
+    """The input block of an LSTM, beside a recurrent block in rows; a 1x1 convolution of a map; two around a batch-norm, whose sums they leave."""
     b = C._Builder()
     if layer == "lstm":
         b.lstm(8224, 512, src=-1)
         st = C._stage("streamed", b.layers, C.BF16, (8224, 7, 1), 5, 2, 1, 2, 1, C.BASE_SEED + 81, "kaiming")
     else:
-        b.conv(1024, 16416, 1, src=-1)
+        b.conv(1024, 16416, 1, bias=layer == "conv", src=-1)
+        if layer == "norm":
+            b.bn(16416, relu=1)
+            b.conv(16416, 1024, 1)
         st = C._stage("streamed", b.layers, C.BF16, (1024, 7, 7), 1, 2, 1, 2, 1, C.BASE_SEED + 82, "kaiming")
     compare_minibatch(st, verbose="streamed %s" % layer)
     _copies_after_an_update_are_those_of_its_weights(st)
